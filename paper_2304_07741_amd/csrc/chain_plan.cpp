@@ -184,7 +184,7 @@ class Graph {
         for (size_t i = 0; i < insts.size(); i++) {
             const Inst& U = insts[i];
             if (U.kind != kStencil || dag.nodes[U.node].op != Op::Unfold) continue;
-            if (U.users.size() != 1) return false;
+            if (U.users.size() != 1 || is_output_[U.node]) return false;  // (a reader outside the unit has a gradient of its own to send through the window)
             const Inst& F = insts[U.users[0].first];
             const Node& fn = dag.nodes[F.node];
             if (F.kind != kFoldI || (fn.kind != kSum && fn.kind != kAvg) || !F.users.empty() || !is_output_[F.node] || F.ctx != 0 || U.ctx != 0)
