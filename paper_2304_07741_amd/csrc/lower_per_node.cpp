@@ -4,14 +4,16 @@
 // node joins the chain of one of its operands as long as the grown chain still compiles (a stencil above a
 // reduction, a blend across channel counts, too many taps, registers, instructions or LDS end a chain).  What no
 // chain takes (folds over space or channels, joint softmax, grouped blends ...) is one kernel per node, and so is
-// everything when fusion is switched off.  FC nodes run on the MFMA kernels (bf16 dtype) or the plain ones.
+// everything when fusion is switched off.  FC nodes run on the bf16 MFMA kernels (bf16 dtype) or the fp32 ones.
 // Tensors that cross a unit boundary live in the workspace as fp32 [N, C, T, H, W] together with their gradients;
 // x, y, dy and dx are read and written in place, in their own type, wherever the unit at that end can do so.
 #include "lowering.hpp"
+#include "../../include/canvas_dag.h"
 #include "chain_kernels.hpp"
 #include "chain_plan.hpp"
 #include "gfc_kernels.hpp"
 #include "ref_kernels.hpp"
+#include "sfc_kernels.hpp"
 
 #include <algorithm>
 #include <cstdio>
@@ -21,6 +23,8 @@
 namespace canvas {
 
 namespace {
+
+constexpr int64_t kMaxSfcPartialBytes = 16 << 20;
 
 struct Layout {
     std::vector<int64_t> val, grad, wf;  // byte offsets into the workspace; -1 = not in the workspace
@@ -93,8 +97,9 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         off += align_up((uint64_t)numel * 4);
         return (int64_t)o;
     };
-    // bf16 path: FC nodes run on MFMA and read an Unfold operand implicitly.  An Unfold whose every
-    // consumer is such an FC is never materialised (no value, no gradient, no launch).
+    // FC nodes read an Unfold operand implicitly: an Unfold whose every consumer is such an FC is never materialised
+    // (no value, no gradient, no launch).  The bf16 kernels take windows up to 7 x 7, the fp32 ones those whose rows
+    // fit their operand tile.
     auto bytes_ok = [&](int64_t numel) { return numel * 4 < ((int64_t)1 << 31); };
     bool mfma = bf16 && dag.W >= 4 && (int64_t)dag.N * dag.P() < ((int64_t)1 << 28);
     for (int k = 1; k < n && mfma; k++) {
@@ -106,10 +111,11 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
                bytes_ok((int64_t)f.out * (A.C / f.groups) * A.T);
     }
     std::vector<bool> virt(n, false);
-    if (mfma) {
+    if (mfma || !bf16) {
         for (int k = 1; k < n; k++) {
             const Node& u = dag.nodes[k];
             if (!u.live || u.op != Op::Unfold || u.kh > 7 || u.kw > 7) continue;
+            if (!bf16 && !sfc::window_supported(u.kh, u.kw, dag.H, dag.W)) continue;
             bool only_fc = true;
             for (int j = k + 1; j < n; j++) {
                 const Node& c = dag.nodes[j];
@@ -119,8 +125,8 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             virt[k] = only_fc && dag.out != k;
         }
     }
-    // which fc nodes use the MFMA kernels (32-bit buffer offsets must cover their tensors; a 1 x 1 image has no
-    // 8-pixel units: the plain kernels take it)
+    // which fc nodes use the bf16 MFMA kernels (32-bit buffer offsets must cover their tensors; a 1 x 1 image has no
+    // 8-pixel units: the fp32 kernels take it)
     std::vector<bool> fc_mfma(n, false);
     for (int k = 1; k < n; k++)
         if (dag.nodes[k].live && dag.nodes[k].op == Op::Fc) fc_mfma[k] = mfma && !dag.nodes[k].pooled;
@@ -260,12 +266,13 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         else
             for (int o : U.plan.outputs) mat[o] = true;
     }
-    // who can use the caller's tensors in place: chains (any dtype) and MFMA FC nodes (bf16)
-    auto in_place = [&](int k) { return k > 0 && unit_of[k] >= 0 && (units[unit_of[k]].chain || fc_mfma[k]); };
+    // who can use the caller's tensors in place: chains, and FC nodes whose kernels have the caller's type
+    auto fc_in_place = [&](int k) { return dag.nodes[k].op == Op::Fc && (fc_mfma[k] || !bf16); };
+    auto in_place = [&](int k) { return k > 0 && unit_of[k] >= 0 && (units[unit_of[k]].chain || fc_in_place(k)); };
     // x: read in place by chains and by MFMA FC nodes (also through a virtual Unfold); a widened copy only for the others
     bool need_x32 = dag.out == 0;
     for (int c : consumers[0]) {
-        if (virt[c]) continue;  // (its consumers are MFMA FC nodes)
+        if (virt[c]) continue;  // (its consumers are FC nodes that read x)
         if (!in_place(c)) need_x32 = true;
     }
     // y and dy: in place when the output node is produced by such a unit and nothing else reads it
@@ -277,7 +284,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         std::vector<int> seen;
         for (int c : consumers[0]) {
             if (virt[c]) {
-                for (int f : consumers[c]) x_writers++, x_writer_ok = x_writer_ok && fc_mfma[f];
+                for (int f : consumers[c]) x_writers++, x_writer_ok = x_writer_ok && fc_in_place(f);
                 continue;
             }
             const int u = unit_of[c];
@@ -328,14 +335,26 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         gfc::prepare_wgrad(Q);
         return Q;
     };
+    // the same for fc nodes on the fp32 kernels
+    auto sfc_params = [&](int k) {
+        const Node& f = dag.nodes[k];
+        const bool v = virt[f.a];
+        const Node& U = dag.nodes[f.a];
+        const int srcn = fc_src(k);
+        const Node& S = dag.nodes[srcn];
+        return sfc::shape(dag.N, f.groups, (S.C / f.groups) * S.T, v ? U.kh : 1, v ? U.kw : 1, f.out / f.groups, dag.Hk(srcn), dag.Wk(srcn));
+    };
     lay.wt.assign(dag.n_weights, -1);
     lay.part.assign(dag.n_weights, -1);
+    std::vector<sfc::Params> sgrad(dag.n_weights);  // weight gradients of the fp32 fc nodes
+    int sfc_count = 0;
     for (int i = 0; i < dag.n_weights; i++) {
         const int k = dag.weight_node[i];
         const Node& f = dag.nodes[k];
         if (!f.live) continue;
         if (!fc_mfma[k]) {
             if (bf16) lay.wf[i] = take(wnumel[i]);
+            sfc_count++;
             continue;
         }
         lay.wt[i] = (int64_t)off;
@@ -345,7 +364,17 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         lay.part[i] = (int64_t)off;
         off += align_up((uint64_t)slices * wnumel[i] * 4);
     }
-    low->ws_bytes = off;
+    // Partials of the fp32 weight gradients: at most 16 MB each, and never so much that a plan which fits the library's
+    // static workspace without them no longer does (one slice writes dw itself and needs none).
+    const int64_t room = off < CANVAS_STATIC_WORKSPACE_BYTES ? (int64_t)(CANVAS_STATIC_WORKSPACE_BYTES - off) / std::max(1, sfc_count) - 256 : kMaxSfcPartialBytes;
+    for (int i = 0; i < dag.n_weights; i++) {
+        const int k = dag.weight_node[i];
+        if (!dag.nodes[k].live || fc_mfma[k]) continue;
+        sgrad[i] = sfc_params(k);
+        sfc::prepare_wgrad(sgrad[i], std::min(room, kMaxSfcPartialBytes));
+        if (sgrad[i].slices > 1) lay.part[i] = take(wnumel[i] * sgrad[i].slices);
+    }
+    low->ws_bytes = std::max<uint64_t>(off, 256);  // (a caller always hands over a workspace, also to a plan that needs none)
     const double esz = bf16 ? 2.0 : 4.0;
 
     // pointer resolvers
@@ -427,7 +456,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             };
             break;
         case Op::Fc: {
-            int G = nd.groups, Og = nd.out / G, K = (A.C / G) * A.T;
+            const int K = (A.C / nd.groups) * A.T;
             L.flops = 2.0 * N * dag.Pk(k) * nd.out * K;
             if (fc_mfma[k]) {
                 gfc::Params Q = fc_params(k);
@@ -449,9 +478,19 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
                 };
                 break;
             }
-            L.bytes += 4.0 * wnumel[nd.widx];
-            const int Pn = dag.Pk(k);
-            L.run = [=](const RunArgs& a) { ref::fc_fwd(val(a, nd.a), wptr(a, nd.widx), valw(a, k), N, G, Og, K, Pn, a.stream); };
+            sfc::Params Q = sfc_params(k);
+            sfc::prepare_forward(Q);
+            const int srcn = fc_src(k), widx = nd.widx;
+            const bool to_y = k == dag.out && y_direct;
+            L.name = Q.TV > 1 ? "sfc_fwd_unfold" : "sfc_fwd";
+            L.bytes = 4.0 * (dag.numel(srcn) + dag.numel(k) + wnumel[widx]);
+            L.run = [=](const RunArgs& a) {
+                sfc::Params R = Q;
+                R.src = val(a, srcn);
+                R.w = wptr(a, widx);
+                R.dst = to_y ? (float*)a.y : valw(a, k);
+                sfc::forward(R, a.stream);
+            };
             break;
         }
         case Op::Unary: {
@@ -604,6 +643,46 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             written[srcn] = true;
             continue;
         }
+        if (nd.op == Op::Fc) {
+            const int srcn = fc_src(k), widx = nd.widx;
+            const bool from_dy = k == dag.out && y_direct, to_dx = srcn == 0 && dx_direct;
+            const int acc_s = !to_dx && written[srcn] ? 1 : 0;
+            const int64_t nw = wnumel[widx], poff = lay.part[widx];
+            const double flops = 2.0 * N * dag.Pk(k) * (double)nw;
+            const sfc::Params Q = sgrad[widx];
+            low->bwd.push_back({Q.TV > 1 ? "sfc_wgrad_unfold" : "sfc_wgrad", 4.0 * (dag.numel(srcn) + dag.numel(k) + (double)Q.slices * nw), flops,
+                                [=](const RunArgs& a) {
+                                    sfc::Params R = Q;
+                                    R.src = val(a, srcn);
+                                    R.dy = from_dy ? (const float*)a.dy : grad(a, k);
+                                    R.partial = poff >= 0 ? (float*)(a.ws + poff) : (float*)a.dw[widx];
+                                    sfc::wgrad_partial(R, a.stream);
+                                }});
+            if (poff >= 0) {
+                ReduceJob rj;
+                rj.job.slices = Q.slices;
+                rj.job.kind = 0;
+                rj.job.count = (unsigned)nw;
+                wreduce::plan(rj.job);
+                rj.widx = widx;
+                rj.off = poff;
+                rj.bytes = 4.0 * (Q.slices + 1) * nw;
+                low->rjobs.push_back(rj);
+            }
+            sfc::Params D = sfc::data_gradient_of(Q);
+            D.acc = acc_s;
+            sfc::prepare_forward(D);
+            low->bwd.push_back({D.TV > 1 ? "sfc_dgrad_unfold" : "sfc_dgrad", 4.0 * (dag.numel(k) + dag.numel(srcn) * (1 + acc_s) + nw), flops,
+                                [=](const RunArgs& a) {
+                                    sfc::Params R = D;
+                                    R.src = from_dy ? (const float*)a.dy : grad(a, k);
+                                    R.w = wptr(a, widx);
+                                    R.dst = to_dx ? (float*)a.dx : grad(a, srcn);
+                                    sfc::forward(R, a.stream);
+                                }});
+            written[srcn] = true;
+            continue;
+        }
         const int acc = written[nd.a] ? 1 : 0;
         Launch L;
         L.name = std::string("node_") + op_name(nd.op) + "_bwd";
@@ -617,21 +696,6 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
                 ref::shift(grad(a, k), grad(a, nd.a), N, nd.C, nd.T, dag.H, dag.W, -nd.dh, -nd.dw, nd.c0, nd.c1, acc, a.stream);
             };
             break;
-        case Op::Fc: {
-            int G = nd.groups, Og = nd.out / G, K = (A.C / G) * A.T;
-            Launch D;
-            D.name = "node_fc_dw";
-            const int Pn = dag.Pk(k);
-            D.flops = 2.0 * N * Pn * nd.out * K;
-            D.bytes = 4.0 * (dag.numel(nd.a) + dag.numel(k) + wnumel[nd.widx]);
-            D.run = [=](const RunArgs& a) { ref::fc_dw(grad(a, k), val(a, nd.a), (float*)a.dw[nd.widx], N, G, Og, K, Pn, a.stream); };
-            low->bwd.push_back(std::move(D));
-            L.name = "node_fc_dx";
-            L.flops = 2.0 * N * Pn * nd.out * K;
-            L.bytes += 4.0 * wnumel[nd.widx];
-            L.run = [=](const RunArgs& a) { ref::fc_dx(grad(a, k), wptr(a, nd.widx), grad(a, nd.a), N, G, Og, K, Pn, acc, a.stream); };
-            break;
-        }
         case Op::Unary: {
             int64_t ne = dag.numel(k);
             L.bytes += 4.0 * ne;

@@ -104,64 +104,6 @@ __global__ void k_shift(const float* __restrict__ src, float* __restrict__ dst, 
     dst[i] = acc ? dst[i] + v : v;
 }
 
-// y[n, g*Og+o, p] = sum_i W[(g*Og+o)*K + i] * x[n, g*K + i, p]   (x rows are (c,t) pairs: (g*Cg+c')*T+t = g*K+i)
-__global__ void k_fc_fwd(const float* __restrict__ x, const float* __restrict__ wt, float* __restrict__ y, int64_t total,
-                         int G, int Og, int K, int P) {
-    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= total) return;
-    int p = (int)(i % P);
-    int64_t r = i / P;
-    int go = (int)(r % (G * Og));
-    int64_t n = r / (G * Og);
-    int g = go / Og;
-    const float* xr = x + ((n * G + g) * (int64_t)K) * P + p;
-    const float* wr = wt + (int64_t)go * K;
-    float s = 0.f;
-    for (int k = 0; k < K; k++) s = fmaf(wr[k], xr[(int64_t)k * P], s);
-    y[i] = s;
-}
-
-// gx[n, g*K+i, p] (+)= sum_o W[(g*Og+o)*K+i] * gy[n, g*Og+o, p]
-__global__ void k_fc_dx(const float* __restrict__ gy, const float* __restrict__ wt, float* __restrict__ gx, int64_t total,
-                        int G, int Og, int K, int P, int acc) {
-    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= total) return;
-    int p = (int)(i % P);
-    int64_t r = i / P;
-    int gi = (int)(r % (G * K));
-    int64_t n = r / (G * K);
-    int g = gi / K, k = gi % K;
-    const float* gr = gy + ((n * G + g) * (int64_t)Og) * P + p;
-    const float* wr = wt + ((int64_t)g * Og) * K + k;
-    float s = 0.f;
-    for (int o = 0; o < Og; o++) s = fmaf(wr[(int64_t)o * K], gr[(int64_t)o * P], s);
-    gx[i] = acc ? gx[i] + s : s;
-}
-
-// dW[(g*Og+o)*K+i] = sum_{n,p} gy[n,g*Og+o,p] * x[n,g*K+i,p]; one block per weight, fixed-order tree reduction.
-__global__ void k_fc_dw(const float* __restrict__ gy, const float* __restrict__ x, float* __restrict__ dw, int N, int G,
-                        int Og, int K, int P) {
-    __shared__ float red[kBlock];
-    int64_t widx = blockIdx.x;
-    int k = (int)(widx % K);
-    int go = (int)(widx / K);
-    int g = go / Og;
-    float s = 0.f;
-    int64_t M = (int64_t)N * P;
-    for (int64_t m = threadIdx.x; m < M; m += kBlock) {
-        int64_t n = m / P;
-        int p = (int)(m % P);
-        s = fmaf(gy[(n * G * Og + go) * P + p], x[((n * G + g) * (int64_t)K + k) * P + p], s);
-    }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int st = kBlock / 2; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) dw[widx] = red[0];
-}
-
 __global__ void k_unary_fwd(const float* __restrict__ in, float* __restrict__ out, int64_t n, int kind, float lo, float hi) {
     int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i < n) out[i] = unary_apply(kind, in[i], lo, hi);
@@ -582,18 +524,6 @@ void shift(const float* src, float* dst, int64_t N, int C, int T, int H, int W, 
            hipStream_t s) {
     int64_t total = N * C * T * H * W;
     LAUNCH(k_shift, total, src, dst, total, C, T, H, W, dh, dw, c0, c1, acc);
-}
-void fc_fwd(const float* x, const float* wt, float* y, int64_t N, int G, int Og, int K, int P, hipStream_t s) {
-    int64_t total = N * G * Og * P;
-    LAUNCH(k_fc_fwd, total, x, wt, y, total, G, Og, K, P);
-}
-void fc_dx(const float* gy, const float* wt, float* gx, int64_t N, int G, int Og, int K, int P, int acc, hipStream_t s) {
-    int64_t total = N * G * K * P;
-    LAUNCH(k_fc_dx, total, gy, wt, gx, total, G, Og, K, P, acc);
-}
-void fc_dw(const float* gy, const float* x, float* dw, int64_t N, int G, int Og, int K, int P, hipStream_t s) {
-    int64_t nw = (int64_t)G * Og * K;
-    if (nw > 0) CANVAS_LAUNCH(k_fc_dw, dim3((unsigned)nw), dim3(kBlock), 0, s, gy, x, dw, (int)N, G, Og, K, P);
 }
 void unary_fwd(const float* in, float* out, int64_t n, int kind, float lo, float hi, hipStream_t s) {
     LAUNCH(k_unary_fwd, n, in, out, n, kind, lo, hi);

@@ -16,9 +16,6 @@ void unfold_fwd(const float* in, float* out, int64_t NC, int Tin, int KH, int KW
 void unfold_bwd(const float* gout, float* gin, int64_t NC, int Tin, int KH, int KW, int H, int W, int acc, hipStream_t s);
 void shift(const float* src, float* dst, int64_t N, int C, int T, int H, int W, int dh, int dw, int c0, int c1, int acc,
            hipStream_t s);
-void fc_fwd(const float* x, const float* wt, float* y, int64_t N, int G, int Og, int K, int P, hipStream_t s);
-void fc_dx(const float* gy, const float* wt, float* gx, int64_t N, int G, int Og, int K, int P, int acc, hipStream_t s);
-void fc_dw(const float* gy, const float* x, float* dw, int64_t N, int G, int Og, int K, int P, hipStream_t s);
 void unary_fwd(const float* in, float* out, int64_t n, int kind, float lo, float hi, hipStream_t s);
 void unary_bwd(const float* in, const float* gout, float* gin, int64_t n, int kind, float lo, float hi, int acc, hipStream_t s);
 // P: pixels of the RHS / result, Wd its width; PL: pixels of the LHS; rep: 0 = the LHS has the pixels of the result

@@ -1,0 +1,631 @@
+#include "sfc_kernels.hpp"
+
+#include <algorithm>
+
+#include "launch.hpp"
+
+namespace canvas {
+namespace sfc {
+
+namespace {
+
+using f4 = __attribute__((ext_vector_type(4))) float;
+
+constexpr int kThreads = 256;
+constexpr int kLinearKc = 32;   // channels per chunk without a window
+constexpr int kMaxLds = 64 * 1024;
+
+// Consecutive workgroups go to consecutive XCDs, each with an L2 of its own; this renumbers them so that an XCD works on
+// neighbouring tiles, whose operands overlap (the margin of a window, the other outputs of the same pixels).  The grid is
+// a multiple of eight workgroups; the numbers past the last tile have no work.
+__device__ __forceinline__ unsigned tile_of_block() {
+    const unsigned per = gridDim.x / 8;
+    return (blockIdx.x % 8) * per + blockIdx.x / 8;
+}
+
+// x / d for the small dividends of index arithmetic: exact while x * d < 2^32 (the host checks the image's sizes)
+__device__ __forceinline__ int quotient(int x, int d, uint32_t m) { return d == 1 ? x : (int)__umulhi((uint32_t)x, m); }
+// image of pixel p, counted from an image at whose pixel p0 < P a tile of at most 128 pixels begins
+__device__ __forceinline__ int image_of(const Params& Q, int p) { return Q.P >= 128 ? (p >= Q.P ? 1 : 0) : quotient(p, Q.P, Q.mP); }
+
+// Position j of a window's operand tile whose first pixel is (n0, h0, .) -> element offset of that source pixel in
+// channel 0 of the group, or -1 in the margin.  Rows are numbered through the batch with HP = H + KH - 1 rows per image.
+__device__ __forceinline__ int64_t window_source(const Params& Q, int64_t n0, int h0, int j) {
+    const int s = quotient(j, Q.Wp, Q.mWp), c = j - s * Q.Wp;
+    const int q = h0 + s;
+    const int dn = quotient(q, Q.HP, Q.mHP);
+    const int h = q - dn * Q.HP - Q.KH / 2, w = c - Q.KW / 2;
+    const int64_t n = n0 + dn;
+    if (n >= Q.N || h < 0 || h >= Q.H || w < 0 || w >= Q.W) return -1;
+    return n * Q.G * Q.R * (int64_t)Q.P + (int64_t)h * Q.W + w;
+}
+
+// Forward and data gradient.  A workgroup owns 16*WM outputs of one group and TP = 16*NT*(4/WM) consecutive pixels of the
+// batch, a wavefront 16 outputs and 16*NT pixels; the contraction runs over chunks of KC channels with all their taps.  Bound by the fp32
+// matrix rate (v_mfma_f32_16x16x4_f32: 32 cycles for 2048 flops, 157 TFLOP/s on the chip) and, with the small tiles that
+// fill the chip at these sizes, by the vector instructions beside it.  The operand tile in LDS holds image rows with a
+// zero margin, so a tap is a constant LDS offset and the Unfold costs no memory traffic and no mask; the next chunk's
+// is loaded into registers while this one is multiplied.  The weights go from the caches straight to registers, where
+// a lane finds its channel's taps side by side (36 bytes for 3 x 3, 16 for four channels without a window): staged
+// through LDS they cost more vector instructions than the rest of the loop.
+// Sums: the products of one or two taps (without a window: of 16 channels) are chained in the matrix unit, these parts
+// are added per four channels, these to the result: the rounding errors of the chains stay below those of one sum per
+// tap over all channels, whatever the number of channels (measured against fp64 over 16-128 channels: y 0.8-1.3e-7,
+// dx 0.8-1.3e-7; one thread per element and one chain: 2.0-6.0e-7 and 0.9-2.1e-7).
+// N=32, C=64, 28x28, 3x3 (1.85 GFLOP): 39 us forward, 35 us data gradient, 48-52 TFLOP/s; one thread per output element
+// and a materialised Unfold took 563 + 29 us and 400 + 40 us.  All 16 outputs x 64 pixels of a wavefront on the same
+// outputs (each weight loaded by four wavefronts) 58 and 38 us: a lane's 36 bytes lie a row apart, and the tag lookups
+// of the first-level cache were the limit.
+template <int WM, int NT, int TVT, bool WIN, int NP, int KC, bool TR>
+__global__ __launch_bounds__(kThreads) void k_fwd(Params Q) {
+    extern __shared__ float lds[];
+    float* Bs = lds;  // [KC][CS]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int col = lane & 15, quad = lane >> 4;
+    constexpr int TP = 16 * NT * (4 / WM);
+    const int wm = wave % WM, wn = wave / WM;
+    unsigned b = tile_of_block();
+    if (b >= (unsigned)Q.tiles) return;
+    const int mtile = (int)(b % (unsigned)Q.mtiles);
+    b /= (unsigned)Q.mtiles;
+    const int g = (int)(b % (unsigned)Q.G);
+    const int64_t m0 = (int64_t)(b / (unsigned)Q.G) * TP;
+    const int64_t n0 = m0 / Q.P;
+    const int p0 = (int)(m0 - n0 * Q.P);
+    const int h0 = WIN ? quotient(p0, Q.W, Q.mW) : 0;
+    const int o0 = (mtile * WM + wm) * 16;
+    const int64_t P = Q.P;
+
+    // this thread's positions of the operand tile, in channel 0 of the group (a position of the margin reads the first
+    // element instead and drops it)
+    constexpr int kBRegs = WIN ? NP * KC : KC * TP / kThreads;
+    constexpr int kChStep = kThreads / TP;  // without a window: channels one pass of the workgroup covers
+    const float* src = Q.src + (int64_t)g * Q.R * P;
+    const float* from[NP];
+    bool inside[NP];
+    const int c0 = WIN ? 0 : tid / TP, j0 = WIN ? tid : tid & (TP - 1);
+    if (WIN) {
+#pragma unroll
+        for (int i = 0; i < NP; i++) {
+            const int j = tid + i * kThreads;
+            const int64_t at = j < Q.S ? window_source(Q, n0, h0, j) : -1;
+            inside[i] = at >= 0;
+            from[i] = src + (at >= 0 ? at : 0);
+        }
+    } else {
+        const int p = p0 + j0, dn = image_of(Q, p);
+        inside[0] = m0 + j0 < Q.M;
+        from[0] = src + (inside[0] ? (n0 + dn) * Q.G * Q.R * P + (p - dn * Q.P) : 0);
+    }
+    // the pixels this lane multiplies
+    int lofs[NT];
+    int64_t dofs[NT];
+#pragma unroll
+    for (int t = 0; t < NT; t++) {
+        const int j = (wn * NT + t) * 16 + col;
+        const bool in = m0 + j < Q.M;
+        const int p = in ? p0 + j : p0;
+        const int dn = image_of(Q, p), pp = p - dn * Q.P;
+        if (WIN) {
+            const int h = quotient(pp, Q.W, Q.mW);
+            lofs[t] = (dn * Q.HP + h - h0) * Q.Wp + (pp - h * Q.W);
+        } else {
+            lofs[t] = in ? j : 0;
+        }
+        dofs[t] = in ? (n0 + dn) * Q.G * Q.Og * P + pp : -1;
+    }
+
+    float breg[kBRegs];
+    auto load_b = [&](int r0) {
+        if (WIN) {
+#pragma unroll
+            for (int c = 0; c < KC; c++) {
+                const int64_t ch = min(r0 + c, Q.R - 1) * P;
+#pragma unroll
+                for (int i = 0; i < NP; i++) breg[c * NP + i] = from[i][ch];
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < kBRegs; c++) breg[c] = from[0][min(r0 + c0 + c * kChStep, Q.R - 1) * P];
+        }
+    };
+    auto store_b = [&](int r0) {  // (channels past the last are zero: they meet zero weights)
+        if (WIN) {
+#pragma unroll
+            for (int i = 0; i < NP; i++) {
+                const int j = tid + i * kThreads;
+                if (j < Q.S) {
+#pragma unroll
+                    for (int c = 0; c < KC; c++) Bs[c * Q.CS + j] = inside[i] && r0 + c < Q.R ? breg[c * NP + i] : 0.f;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < kBRegs; c++) {
+                const int ch = c0 + c * kChStep;
+                Bs[ch * Q.CS + j0] = inside[0] && r0 + ch < Q.R ? breg[c] : 0.f;
+            }
+        }
+    };
+    // this lane's weights: output `col` of the wavefront's 16 (the last one again past the end: not stored)
+    const int tv = TVT ? TVT : Q.TV;
+    const int64_t wch = TR ? (int64_t)Q.Og * tv : (TVT ? TVT : tv);  // elements between two channels
+    const float* wrow = Q.w + (int64_t)g * Q.Og * Q.K + min(o0 + col, Q.Og - 1) * (int64_t)(TR ? tv : Q.K);
+    constexpr int NA = TVT == 9 ? 9 : (TVT == 1 ? 4 : 1);  // weights of a step loaded ahead: nine taps of a channel, or four channels
+    // 3 x 3: the taps of channel ch + quad.  No window: channels ch + 4*quad ... + 3.  Channels past the last are zero.
+    auto load_w = [&](int ch, float (&a)[NA]) {
+        if (TVT == 9) {
+            const int c = ch + quad;
+            const float* from = wrow + min(c, Q.R - 1) * wch;
+#pragma unroll
+            for (int t = 0; t < NA; t++) a[TR ? NA - 1 - t : t] = from[t];  // (transposed: the window read backwards)
+            if (ch + 4 > Q.R)
+#pragma unroll
+                for (int t = 0; t < NA; t++) a[t] = c < Q.R ? a[t] : 0.f;
+        } else if (TVT == 1) {
+            const int c = ch + quad * 4;
+            if (ch + 16 <= Q.R) {
+#pragma unroll
+                for (int t = 0; t < NA; t++) a[t] = wrow[(c + t) * wch];
+            } else {
+#pragma unroll
+                for (int t = 0; t < NA; t++) {
+                    a[t] = wrow[min(c + t, Q.R - 1) * wch];
+                    a[t] = c + t < Q.R ? a[t] : 0.f;
+                }
+            }
+        }
+    };
+
+    f4 acc[NT], sum[NT], part[NT];
+    const f4 zero{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < NT; t++) acc[t] = zero;
+    // one matrix step (four products per output and pixel), the first of a part from zero
+    auto mul = [&](bool first, float av, const float* b) {
+        float bv[NT];
+#pragma unroll
+        for (int t = 0; t < NT; t++) bv[t] = b[lofs[t]];
+#pragma unroll
+        for (int t = 0; t < NT; t++) part[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[t], first ? zero : part[t], 0, 0, 0);
+    };
+    auto add = [&](f4 (&to)[NT], const f4 (&v)[NT], bool first) {
+#pragma unroll
+        for (int t = 0; t < NT; t++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) to[t][r] = first ? v[t][r] : to[t][r] + v[t][r];
+    };
+
+    constexpr int kStepCh = TVT == 1 ? 16 : 4, kSteps = KC / kStepCh;  // channels per step, steps per chunk
+    float wreg[2][NA];
+    load_w(0, wreg[0]);
+    load_b(0);
+    for (int r0 = 0; r0 < Q.R; r0 += KC) {
+        store_b(r0);
+        __syncthreads();
+        const int steps = (min(KC, Q.R - r0) + kStepCh - 1) / kStepCh;
+#pragma unroll
+        for (int s = 0; s < kSteps; s++) {
+            if (s >= steps) break;
+            const float (&w)[NA] = wreg[kSteps == 1 ? 0 : s & 1];
+            const int ch = r0 + s * kStepCh;
+            if (kSteps > 1) load_w(min(ch + kStepCh, Q.R - 1), wreg[(s + 1) & 1]);  // (an even number of steps: a chunk begins with the first set)
+            if (s == 0 && r0 + KC < Q.R) load_b(r0 + KC);
+            if (TVT == 1) {
+                const float* b = Bs + (s * 16 + quad * 4) * Q.CS;
+#pragma unroll
+                for (int t = 0; t < 4; t++) mul(t == 0, w[t < NA ? t : 0], b + t * Q.CS);
+                add(acc, part, false);
+            } else if (TVT == 9) {
+                const float* b = Bs + (s * 4 + quad) * Q.CS;
+#pragma unroll
+                for (int tap = 0; tap < 9; tap++) {
+                    mul(tap % 2 == 0, w[tap < NA ? tap : 0], b + tap / 3 * Q.Wp + tap % 3);
+                    if (tap % 2 == 1 || tap == 8) add(sum, part, tap == 1);
+                }
+                add(acc, sum, false);
+            } else {
+                const float* b = Bs + (s * 4 + quad) * Q.CS;
+                const int c = ch + quad;
+                const float* from = wrow + min(c, Q.R - 1) * wch;
+                for (int kh = 0; kh < Q.KH; kh++) {
+                    float row[7];
+#pragma unroll
+                    for (int kw = 0; kw < 7; kw++) {
+                        const int tap = kh * Q.KW + min(kw, Q.KW - 1);
+                        row[kw] = from[TR ? tv - 1 - tap : tap];
+                        row[kw] = c < Q.R ? row[kw] : 0.f;
+                    }
+#pragma unroll
+                    for (int kw = 0; kw < 7; kw++) {
+                        if (kw >= Q.KW) break;
+                        mul(true, row[kw], b + kh * Q.Wp + kw);
+                        add(sum, part, kh + kw == 0);
+                    }
+                }
+                add(acc, sum, false);
+            }
+        }
+        if (kSteps == 1 && r0 + KC < Q.R) load_w(r0 + KC, wreg[0]);
+        __syncthreads();
+    }
+    // lane: pixel `col` of its 16, outputs 4*quad .. 4*quad + 3
+    const int o = o0 + quad * 4, left = Q.Og - o;
+#pragma unroll
+    for (int t = 0; t < NT; t++) {
+        if (dofs[t] < 0) continue;
+        float* d = Q.dst + dofs[t] + ((int64_t)g * Q.Og + o) * P;
+        float old[4] = {0.f, 0.f, 0.f, 0.f};
+        if (Q.acc) {
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+                if (r < left) old[r] = d[r * P];
+        }
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+            if (r < left) d[r * P] = Q.acc ? old[r] + acc[t][r] : acc[t][r];
+    }
+}
+
+constexpr int kPix = 64;        // pixels per step of the weight gradient
+constexpr int kDyStride = 68;   // 4 mod 64: the 16 outputs x 4 pixels of an operand read lie in 64 banks
+
+// Weight gradient: contraction over pixels.  A workgroup owns 16*MT*WM outputs x 16*NT*(4/WM) contraction indices of one
+// group and one slice of the batch's pixels; 64 pixels of dy and of the channels behind those indices (image rows with a
+// zero margin, as above) go through LDS.  A lane's column is one (channel, tap): its LDS base; the pixel's place in the
+// tile comes from a table.  No padding beyond the tile's edges whatever R, Og and the window are.  Bound like k_fwd.
+// Sums: chains of eight pixels in the matrix unit, added as a tree over the 64 pixels of a step, the steps in a row.
+// N=32, C=64, 28x28, 3x3: 46 us (40 TFLOP/s) and 4 us for the sum of the slices; one workgroup per weight took 1259 us.
+template <int MT, int NT, int WM, bool WIN>
+__global__ __launch_bounds__(kThreads) void k_wgrad(Params Q) {
+    constexpr int WN = 4 / WM, BM = 16 * MT * WM, BN = 16 * NT * WN;
+    extern __shared__ float lds[];
+    int64_t* sofs = reinterpret_cast<int64_t*>(lds);   // [2][S]: source of each position, -1 = zero; this step's and the next
+    int* pofs = reinterpret_cast<int*>(sofs + 2 * Q.S);  // [kPix]: place of each pixel in the tile
+    float* Dy = reinterpret_cast<float*>(pofs + kPix);  // [BM][kDyStride]
+    float* Xs = Dy + BM * kDyStride;                   // [nch][CS]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int col = lane & 15, quad = lane >> 4;
+    const int wm = wave % WM, wn = wave / WM;
+    unsigned b = tile_of_block();
+    if (b >= (unsigned)Q.tiles) return;
+    const int mtile = (int)(b % (unsigned)Q.mtiles);
+    b /= (unsigned)Q.mtiles;
+    const int ktile = (int)(b % (unsigned)Q.ktiles);
+    b /= (unsigned)Q.ktiles;
+    const int g = (int)(b % (unsigned)Q.G);
+    const int slice = (int)(b / (unsigned)Q.G);
+    const int o0 = mtile * BM, k0 = ktile * BN;
+    const int r0 = k0 / Q.TV, nch = min(Q.nch, Q.R - r0);
+    const int64_t first = slice * Q.per_slice, last = min(Q.M, first + Q.per_slice);
+
+    int kbase[NT];
+#pragma unroll
+    for (int t = 0; t < NT; t++) {
+        const int k = min(k0 + (wn * NT + t) * 16 + col, Q.K - 1);  // (columns past the last are not stored)
+        const int r = k / Q.TV, tap = k - r * Q.TV, kh = tap / Q.KW;
+        kbase[t] = (r - r0) * Q.CS + kh * Q.Wp + (tap - kh * Q.KW);
+    }
+    f4 acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; i++)
+#pragma unroll
+        for (int t = 0; t < NT; t++) acc[i][t] = f4{0.f, 0.f, 0.f, 0.f};
+
+    const int rows = min(BM, Q.Og - o0);
+    const float* xs = Q.src + ((int64_t)g * Q.R + r0) * Q.P;
+    const float* ds = Q.dy + ((int64_t)g * Q.Og + o0) * Q.P;
+    auto table = [&](int64_t n0, int p0, int count, int64_t* to) {
+        const int h0 = WIN ? quotient(p0, Q.W, Q.mW) : 0;
+        for (int j = tid; j < Q.S; j += kThreads) {
+            if (WIN) {
+                to[j] = window_source(Q, n0, h0, j);
+            } else {
+                const int p = p0 + j, dn = image_of(Q, p);
+                to[j] = j < count ? (n0 + dn) * Q.G * Q.R * (int64_t)Q.P + (p - dn * Q.P) : -1;
+            }
+        }
+    };
+    // What a thread loads of a step in one go: dy of one pixel for BM/4 outputs, and the first kAhead of its x elements (a
+    // wavefront takes every fourth channel, 64 positions at a time: pass k covers channel c = wave + 4*(k / npos)).
+    // (Kept in flight across the multiplication of the step before, they cost a wavefront of occupancy and gained nothing.)
+    constexpr int kRows = BM * kPix / kThreads, kAhead = 16;
+    const int npos = (Q.S + 63) / 64, passes = (nch + 3 - __builtin_amdgcn_readfirstlane(wave)) / 4 * npos;
+    float dreg[kRows], xreg[kAhead];
+    auto load_dy = [&](int64_t n0, int p0, int count) {
+        const int p = p0 + lane, dn = image_of(Q, p);
+        const bool in = lane < count;
+        const float* from = ds + (in ? (n0 + dn) * Q.G * Q.Og * (int64_t)Q.P + (p - dn * Q.P) : 0);
+#pragma unroll
+        for (int i = 0; i < kRows; i++) {
+            const int m = i * 4 + wave;
+            dreg[i] = from[min(m, rows - 1) * (int64_t)Q.P];
+            dreg[i] = in && m < rows ? dreg[i] : 0.f;
+        }
+    };
+    auto load_x = [&](int first_pass, const int64_t* table) {
+        int c = __builtin_amdgcn_readfirstlane(wave) + first_pass / npos * 4, j = first_pass % npos;
+#pragma unroll
+        for (int i = 0; i < kAhead; i++) {
+            const int64_t o = table[min(j * 64 + lane, Q.S - 1)];
+            xreg[i] = xs[(o < 0 ? 0 : o) + (int64_t)min(c, nch - 1) * Q.P];
+            xreg[i] = o < 0 ? 0.f : xreg[i];
+            if (++j == npos) {
+                j = 0;
+                c += 4;
+            }
+        }
+    };
+    auto store_x = [&](int first_pass) {
+        int c = __builtin_amdgcn_readfirstlane(wave) + first_pass / npos * 4, j = first_pass % npos;
+#pragma unroll
+        for (int i = 0; i < kAhead; i++) {
+            if (first_pass + i < passes && j * 64 + lane < Q.S) Xs[c * Q.CS + j * 64 + lane] = xreg[i];
+            if (++j == npos) {
+                j = 0;
+                c += 4;
+            }
+        }
+    };
+    int cur = 0;
+    int64_t n0 = first / Q.P;
+    int p0 = (int)(first - n0 * Q.P), count = (int)min((int64_t)kPix, last - first);
+    table(n0, p0, count, sofs);
+    __syncthreads();
+    for (int64_t m0 = first; m0 < last; m0 += kPix, cur ^= 1) {
+        load_dy(n0, p0, count);
+        load_x(0, sofs + cur * Q.S);
+        if (tid < kPix) {
+            const int h0 = WIN ? quotient(p0, Q.W, Q.mW) : 0;
+            const int p = tid < count ? p0 + tid : p0;
+            const int dn = image_of(Q, p), pp = p - dn * Q.P, h = WIN ? quotient(pp, Q.W, Q.mW) : 0;
+            pofs[tid] = WIN ? (dn * Q.HP + h - h0) * Q.Wp + (pp - h * Q.W) : (tid < count ? tid : 0);
+        }
+#pragma unroll
+        for (int i = 0; i < kRows; i++) Dy[(i * 4 + wave) * kDyStride + lane] = dreg[i];
+        store_x(0);
+        for (int p = kAhead; p < passes; p += kAhead) {
+            load_x(p, sofs + cur * Q.S);
+            store_x(p);
+        }
+        const bool whole = count == kPix, more = m0 + kPix < last;
+        const int here = count;
+        if (more) {
+            const int p = p0 + kPix, dn = image_of(Q, p);
+            n0 += dn;
+            p0 = p - dn * Q.P;
+            count = (int)min((int64_t)kPix, last - m0 - kPix);
+            table(n0, p0, count, sofs + (cur ^ 1) * Q.S);
+        }
+        __syncthreads();
+        const float* a0 = Dy + (wm * 16 * MT + col) * kDyStride + quad;
+        float av[MT][kPix / 4];
+        int po[kPix / 4];
+#pragma unroll
+        for (int i = 0; i < MT; i++)
+#pragma unroll
+            for (int s = 0; s < kPix / 4; s++) av[i][s] = a0[i * 16 * kDyStride + s * 4];
+#pragma unroll
+        for (int s = 0; s < kPix / 4; s++) po[s] = pofs[s * 4 + quad];
+#pragma unroll
+        for (int t = 0; t < NT; t++) {
+            f4 part[kPix / 8][MT];
+#pragma unroll
+            for (int s = 0; s < kPix / 4; s++) {
+                float bv = Xs[kbase[t] + po[s]];
+                if (!whole) bv = s * 4 + quad < here ? bv : 0.f;  // (a pixel past the slice meets dy = 0, and its x must not be an infinity)
+#pragma unroll
+                for (int i = 0; i < MT; i++)
+                    part[s / 2][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i][s], bv, s % 2 ? part[s / 2][i] : f4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                // each finished part joins its neighbours as in a binary counter
+#pragma unroll
+                for (int w = 1; w < kPix / 8; w *= 2)
+                    if (s % 2 == 1 && (s / 2) % (2 * w) == 2 * w - 1)
+#pragma unroll
+                        for (int i = 0; i < MT; i++)
+#pragma unroll
+                            for (int r = 0; r < 4; r++) part[s / 2 - (2 * w - 1)][i][r] += part[s / 2 - (w - 1)][i][r];
+            }
+#pragma unroll
+            for (int i = 0; i < MT; i++)
+#pragma unroll
+                for (int r = 0; r < 4; r++) acc[i][t][r] += part[0][i][r];
+            __builtin_amdgcn_sched_barrier(0);  // (the next column's parts would need another set of registers)
+        }
+        __syncthreads();
+    }
+    float* dw = Q.partial + (int64_t)slice * Q.G * Q.Og * Q.K + (int64_t)g * Q.Og * Q.K;
+#pragma unroll
+    for (int i = 0; i < MT; i++)
+#pragma unroll
+        for (int t = 0; t < NT; t++) {
+            const int k = k0 + (wn * NT + t) * 16 + col;
+            const int o = o0 + (wm * MT + i) * 16 + quad * 4;
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+                if (k < Q.K && o + r < Q.Og) dw[(int64_t)(o + r) * Q.K + k] = acc[i][t][r];
+        }
+}
+
+// Positions a tile of `pixels` consecutive pixels of the batch covers at most, margin included: the image rows it
+// touches, KH - 1 rows for each change of image, and the window's own KH - 1.
+int window_positions(const Params& p, int pixels) {
+    const int rows = (pixels - 1 + p.W - 1) / p.W + 1;
+    const int changes = (rows - 1 + p.H - 1) / p.H;
+    return (rows + (changes + 1) * (p.KH - 1)) * p.Wp;
+}
+
+int up(int v, int mod, int rem) { return v + (rem - v % mod + mod) % mod; }
+
+constexpr int kMaxWindowPositions = 1024;  // what a workgroup's threads keep the offsets of (4 each)
+
+size_t fwd_lds(const Params& p) { return 4 * (size_t)(p.TV == 1 ? kLinearKc : (p.wide ? 4 : 8)) * p.CS; }
+
+size_t wgrad_lds(const Params& p) {
+    return 4 * ((size_t)kPix + 4 * (size_t)p.S + (size_t)16 * p.mt * p.wm * kDyStride + (size_t)p.nch * p.CS);
+}
+
+}  // namespace
+
+bool window_supported(int KH, int KW, int H, int W) {
+    if (KH > 7 || KW > 7 || KH * KW < 2 || W > kMaxWindowPositions) return false;
+    Params p = shape(1, 1, 1, KH, KW, 1, H, W);
+    p.S = window_positions(p, kPix);
+    p.CS = up(p.S, 2, 1);
+    if (p.S > kMaxWindowPositions) return false;
+    if ((int64_t)p.P * W >= (int64_t)1 << 32 || (int64_t)(H + 2 * kMaxWindowPositions) * p.HP >= (int64_t)1 << 32) return false;  // quotient()
+    for (p.wm = 1; p.wm <= 2; p.wm++) {  // the weight gradient's smallest tiles: 32 x 64 and 64 x 32, any number of channels
+        p.mt = 2;
+        p.nch = (16 * (4 / p.wm) + p.TV - 2) / p.TV + 1;
+        if (wgrad_lds(p) > (size_t)kMaxLds) return false;
+    }
+    return true;
+}
+
+Params shape(int64_t N, int G, int R, int KH, int KW, int Og, int H, int W) {
+    Params p;
+    p.N = N;
+    p.G = G;
+    p.R = R;
+    p.KH = KH;
+    p.KW = KW;
+    p.TV = KH * KW;
+    p.K = R * p.TV;
+    p.Og = Og;
+    p.H = H;
+    p.W = W;
+    p.P = H * W;
+    p.M = N * p.P;
+    p.HP = H + KH - 1;
+    p.Wp = W + KW - 1;
+    auto magic = [](uint32_t d) { return (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };
+    p.mP = magic(p.P);
+    p.mW = magic(W);
+    p.mHP = magic(p.HP);
+    p.mWp = magic(p.Wp);
+    return p;
+}
+
+Params data_gradient_of(const Params& f) {
+    Params p = shape(f.N, f.G, f.Og, f.KH, f.KW, f.R, f.H, f.W);
+    p.transposed = 1;
+    return p;
+}
+
+void prepare_forward(Params& p) {
+    const bool win = p.TV > 1;
+    // Up to four wavefronts side by side over the outputs: a weight then reaches the workgroup once, a staged pixel
+    // serves up to 64 outputs.  Half the pixels where the launch would otherwise have less than two workgroups per
+    // compute unit.
+    p.wm = p.Og > 32 ? 4 : (p.Og > 16 ? 2 : 1);
+    p.nt = p.wm == 1 ? 2 : 4;
+    p.mtiles = (p.Og + 16 * p.wm - 1) / (16 * p.wm);
+    auto pixels = [&]() { return 16 * p.nt * (4 / p.wm); };
+    auto tiles = [&]() { return (p.M + pixels() - 1) / pixels() * p.G * p.mtiles; };
+    if (tiles() < 2 * 256) p.nt /= 2;
+    p.wide = 0;
+    if (win) {
+        if (window_positions(p, pixels()) > 2 * kThreads && pixels() > 64) p.nt /= 2;
+        if (window_positions(p, pixels()) > 2 * kThreads) {
+            p.wide = 1;
+            p.nt = p.wm;  // (64 pixels)
+        }
+        p.S = window_positions(p, pixels());
+        p.CS = up(p.S, 64, 16);  // the four channels of an operand read in different banks
+    } else {
+        p.S = pixels();
+        p.CS = up(p.S, 16, 4);  // the same for channels four apart
+    }
+    p.tiles = tiles();
+}
+
+void prepare_wgrad(Params& p, int64_t max_partial_bytes) {
+    const bool win = p.TV > 1;
+    p.S = win ? window_positions(p, kPix) : kPix;
+    p.CS = win ? up(p.S, 2, 1) : up(p.S, 64, 4);
+    // outputs: one or two 16-tiles per wavefront, one or two wavefronts across them
+    p.mt = p.Og > 16 ? 2 : 1;
+    p.wm = p.Og > 32 ? 2 : 1;
+    const int wn = 4 / p.wm;
+    // contraction indices: the widest tile that does not add padding, as far as LDS holds the channels behind it
+    int best = 1;
+    int64_t least = INT64_MAX;
+    for (int nt = 4; nt >= 1; nt--) {
+        p.nt = nt;
+        const int bn = 16 * nt * wn;
+        p.nch = std::min(p.R, win ? (bn + p.TV - 2) / p.TV + 1 : bn);
+        if (wgrad_lds(p) > (size_t)kMaxLds && nt > 1) continue;
+        const int64_t cols = (int64_t)(p.K + bn - 1) / bn * bn;
+        if (cols < least) {
+            least = cols;
+            best = nt;
+        }
+    }
+    p.nt = best;
+    const int bn = 16 * p.nt * wn, bm = 16 * p.mt * p.wm;
+    p.nch = std::min(p.R, win ? (bn + p.TV - 2) / p.TV + 1 : bn);
+    p.ktiles = (p.K + bn - 1) / bn;
+    p.mtiles = (p.Og + bm - 1) / bm;
+    const int64_t tiles = (int64_t)p.ktiles * p.mtiles * p.G;
+    const int64_t steps = (p.M + kPix - 1) / kPix;
+    const int64_t bytes = (int64_t)p.G * p.Og * p.K * 4;
+    int64_t slices = std::max<int64_t>(1, 2 * 256 / tiles);  // (one round: two workgroups of the wide tiles fit a compute unit)
+    slices = std::min(slices, steps);
+    slices = std::min(slices, std::max<int64_t>(1, max_partial_bytes / std::max<int64_t>(1, bytes)));
+    p.per_slice = (steps + slices - 1) / slices * kPix;
+    p.slices = (int)((p.M + p.per_slice - 1) / p.per_slice);
+    p.tiles = p.slices * tiles;
+}
+
+void forward(const Params& p, hipStream_t s) {
+    const dim3 grid((unsigned)((p.tiles + 7) / 8 * 8)), block(kThreads);
+    const size_t lds = fwd_lds(p);
+#define CANVAS_SFC_T(WM, NT, TVT, WIN, NP, KC)                                                                          \
+    do {                                                                                                               \
+        if (p.transposed) CANVAS_LAUNCH((k_fwd<WM, NT, TVT, WIN, NP, KC, true>), grid, block, lds, s, p);              \
+        else CANVAS_LAUNCH((k_fwd<WM, NT, TVT, WIN, NP, KC, false>), grid, block, lds, s, p);                          \
+    } while (0)
+#define CANVAS_SFC(WM, NT)                                                                                             \
+    do {                                                                                                               \
+        if (p.TV == 1) CANVAS_SFC_T(WM, NT, 1, false, 1, kLinearKc);                                                   \
+        else if (p.wide && p.KH == 3 && p.KW == 3) CANVAS_SFC_T(WM, WM, 9, true, 4, 4);                                \
+        else if (p.wide) CANVAS_SFC_T(WM, WM, 0, true, 4, 4);                                                          \
+        else if (p.KH == 3 && p.KW == 3) CANVAS_SFC_T(WM, NT, 9, true, 2, 8);                                          \
+        else CANVAS_SFC_T(WM, NT, 0, true, 2, 8);                                                                      \
+    } while (0)
+    switch (p.wm * 10 + p.nt) {
+    case 11: CANVAS_SFC(1, 1); break;
+    case 12: CANVAS_SFC(1, 2); break;
+    case 22: CANVAS_SFC(2, 2); break;
+    case 24: CANVAS_SFC(2, 4); break;
+    case 42: CANVAS_SFC(4, 2); break;
+    default: CANVAS_SFC(4, 4); break;
+    }
+#undef CANVAS_SFC
+#undef CANVAS_SFC_T
+}
+
+void wgrad_partial(const Params& p, hipStream_t s) {
+    const dim3 grid((unsigned)((p.tiles + 7) / 8 * 8)), block(kThreads);
+    const size_t lds = wgrad_lds(p);
+#define CANVAS_SFC(MT, NT, WM)                                                           \
+    do {                                                                                 \
+        if (p.TV == 1) CANVAS_LAUNCH((k_wgrad<MT, NT, WM, false>), grid, block, lds, s, p); \
+        else CANVAS_LAUNCH((k_wgrad<MT, NT, WM, true>), grid, block, lds, s, p);         \
+    } while (0)
+#define CANVAS_SFC_NT(MT, WM)                    \
+    switch (p.nt) {                              \
+    case 1: CANVAS_SFC(MT, 1, WM); break;        \
+    case 2: CANVAS_SFC(MT, 2, WM); break;        \
+    case 3: CANVAS_SFC(MT, 3, WM); break;        \
+    default: CANVAS_SFC(MT, 4, WM); break;       \
+    }
+    if (p.wm == 2) CANVAS_SFC_NT(2, 2)
+    else if (p.mt == 2) CANVAS_SFC_NT(2, 1)
+    else CANVAS_SFC_NT(1, 1)
+#undef CANVAS_SFC_NT
+#undef CANVAS_SFC
+}
+
+}  // namespace sfc
+}  // namespace canvas

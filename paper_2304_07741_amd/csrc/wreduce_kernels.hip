@@ -12,7 +12,7 @@ namespace {
 // blockIdx.y selects the job.  Threads are numbered in the order of the partials' elements, so the elements
 // of a segment read whole 128-byte lines of each partial; for the packed layout (whose element order differs
 // from dw: the tap is innermost there) the padding is skipped and the small result is written scattered.
-// Order of the sum of one element: the partials of a segment in ascending order, then the segments in
+// Order of the sum of one element: the partials of a segment in ascending blocks of sixteen and four, then the segments in
 // ascending order -- independent of the launch.
 __global__ __launch_bounds__(256) void k_reduce(Jobs jobs) {
     __shared__ float red[256];
@@ -43,19 +43,21 @@ __global__ __launch_bounds__(256) void k_reduce(Jobs jobs) {
         const int end = min(J.slices, (seg + 1) * per);
         const float* src = J.partial + idx;
         int k = seg * per;
-        for (; k + 16 <= end; k += 16) {  // sixteen independent loads in flight (a round trip to memory each), summed in slice order
+        for (; k + 16 <= end; k += 16) {  // sixteen independent loads in flight (a round trip to memory each), added as a tree (a chain's rounding grows with its length)
             float v[16];
 #pragma unroll
             for (int i = 0; i < 16; i++) v[i] = src[(long long)(k + i) * J.count];
 #pragma unroll
-            for (int i = 0; i < 16; i++) sum += v[i];
+            for (int w = 1; w < 16; w *= 2)
+#pragma unroll
+                for (int i = 0; i < 16; i += 2 * w) v[i] += v[i + w];
+            sum += v[0];
         }
         for (; k + 4 <= end; k += 4) {
             float v[4];
 #pragma unroll
             for (int i = 0; i < 4; i++) v[i] = src[(long long)(k + i) * J.count];
-#pragma unroll
-            for (int i = 0; i < 4; i++) sum += v[i];
+            sum += (v[0] + v[1]) + (v[2] + v[3]);
         }
         for (; k < end; k++) sum += src[(long long)k * J.count];
     }
