@@ -20,8 +20,11 @@ constexpr int max_threads_for(int) { return 512; }
 constexpr int min_waves_for(int tm, int vec) { return tm > 1 && tm <= 9 && vec == 2 ? 4 : 1; }
 
 // Channels per trip of the instance with TM lanes and `vec` pixels per thread: 16 lanes in all without taps (so that a
-// thread with few pixels still has 16 independent loads in flight), 2 x 9 lanes up to 9 taps, one channel beyond.
-constexpr int unroll_for(int tm, int vec) { return tm <= 1 ? 16 / vec : (tm <= 9 && vec == 1 ? 2 : 1); }
+// thread with few pixels still has 16 independent loads in flight), one channel with taps: there LDS decides how many
+// lanes a compute unit works on, and more wavefronts with 9 lanes hide each other's dispatch better than fewer with
+// 2 x 9 (backward of unfold 3x3 -> softmax -> product -> gelu -> sum, 16x96 planes of 32x32: 300 us with two channels per
+// trip, 237 us with one).
+constexpr int unroll_for(int tm, int vec) { return tm <= 1 ? 16 / vec : 1; }
 
 // 16-byte pieces of a register of the instance with `tm` lanes and `vec` pixels per thread (all its channels' lanes).
 constexpr int reg_pieces_of(int tm, int vec) { return ((tm <= 1 ? 1 : (tm <= 9 ? 9 : 25)) * vec * unroll_for(tm, vec) + 3) / 4; }

@@ -64,6 +64,25 @@ struct Inst {
     int down = -1;                           // such instances above it (memo)
 };
 
+// Estimated cost of an instruction per pixel and channel, in units of one cheap lane operation.
+double instr_weight(const Instr& I) {
+    double w = 1;
+    switch (I.op) {
+    case OP_LD:
+    case OP_BINLD:
+    case OP_ST: w = 4; break;
+    case OP_XADD: w = 6; break;
+    case OP_UN:
+    case OP_UNBX: w = (I.kind == 0 || I.kind == 1 || I.kind == kUnNeg) ? 1 : 6; break;
+    case OP_SMT:
+    case OP_SMTBX:
+    case OP_SMCSTAT:
+    case OP_SMCAPPLY: w = 6; break;
+    default: break;
+    }
+    return w * I.T;
+}
+
 class Graph {
    public:
     Graph(const Dag& d, const std::vector<bool>& in_unit, const std::vector<bool>& is_output)
@@ -238,8 +257,16 @@ class Emitter {
     int gkey(int v) const { return gidx * (1 << 20) + v; }
 
     void emit(const Instr& I) {
+        if (I.op == OP_MOVA && I.r == a_reg && I.T <= a_lanes) return;  // (A was just written there, or read from there)
         if (pg.n_instr >= kMaxInstr) throw Fail{"too many instructions"};
         pg.ins[pg.n_instr++] = I;
+        weight += instr_weight(I);
+        if (I.op == OP_MOVR || I.op == OP_MOVA) {
+            a_reg = I.r;
+            a_lanes = I.T;
+        } else if (I.op != OP_ST && I.op != OP_PSET && I.op != OP_PADD && I.op != OP_XADD && I.op != OP_SMCSTAT && I.op != OP_SMCDOT) {
+            a_reg = -1;
+        }
     }
     int alloc() {
         for (int r = 0; r < NR; r++)
@@ -313,9 +340,10 @@ class Emitter {
     // ---------------------------------------------------------------- values kept for another use
     // A value (key 2 * instance) or a gradient (key 2 * instance + 1) that `keep` names is stored in a register the
     // first time a pass body computes it and fetched from there afterwards.  `stats` records, per key, how often it was
-    // computed and how many instructions one computation took: what the choice of `keep` is made from.
+    // computed and what one computation cost: what the choice of `keep` is made from.
     struct Stat {
-        int computed = 0, cost = 0;
+        int computed = 0, lanes = 1;
+        double cost = 0;
     };
     void cached(int key0, int lanes, void (Emitter::*raw)(int), int i) {
         const int key = gkey(key0);
@@ -324,11 +352,12 @@ class Emitter {
             emit(simple(OP_MOVA, lanes, it->second));
             return;
         }
-        const int before = pg.n_instr;
+        const double before = weight;
         (this->*raw)(i);
         Stat& st = stats[key];
         st.computed++;
-        st.cost = std::max(st.cost, pg.n_instr - before);
+        st.lanes = lanes;
+        st.cost = std::max(st.cost, weight - before);
         if (keep.count(key)) {
             const int r = alloc();
             emit(simple(OP_MOVR, lanes, r));
@@ -349,8 +378,61 @@ class Emitter {
         for (auto& kv : held) release(kv.second);
         held.clear();
     }
-    void eval(int i) { cached(2 * i, G->insts[i].lanes, &Emitter::eval_raw, i); }
+    // an instance whose value is another one's (a stencil that has nothing to mask)
+    int same_value(int i) const {
+        while (G->insts[i].kind == kIdent || (G->insts[i].kind == kStencil && zero_outside(G->insts[i].opnd[0]))) i = G->insts[i].opnd[0];
+        return i;
+    }
+    void eval(int i) {
+        i = same_value(i);
+        cached(2 * i, G->insts[i].lanes, &Emitter::eval_raw, i);
+    }
     void grad(int i) { cached(2 * i + 1, G->insts[i].lanes, &Emitter::grad_raw, i); }
+    // The register that holds the value (grad_key = 0) or the gradient (1) of instance i already, or -1.
+    int kept(int i, int grad_key) const {
+        if (!grad_key) i = same_value(i);
+        auto it = held.find(gkey(2 * i + grad_key));
+        return it == held.end() ? -1 : it->second;
+    }
+    // The same value in a register, wherever it has to come from; `mine` says that the caller releases it.
+    int to_reg(int i, int grad_key, bool& mine) {
+        mine = false;
+        int r = kept(i, grad_key);
+        if (r >= 0) return r;
+        if (grad_key) grad(i);
+        else eval(i);
+        r = kept(i, grad_key);
+        if (r >= 0) return r;
+        mine = true;
+        r = alloc();
+        emit(simple(OP_MOVR, G->insts[i].lanes, r));
+        return r;
+    }
+    // Whether instance i is zero by itself wherever its position lies outside the image: what it loads is, and what
+    // is done to it keeps zeros (every position below it is its own: no further stencil in between).
+    bool zero_outside(int i) const {
+        const Inst& I = G->insts[i];
+        const Node& nd = G->dag.nodes[I.node];
+        switch (I.kind) {
+        case kExt: return true;
+        case kIdent: return zero_outside(I.opnd[0]);
+        case kUnaryI: return nd.kind != kExpClip && zero_outside(I.opnd[0]);
+        case kBinaryI: return zero_outside(I.opnd[0]) && zero_outside(I.opnd[1]);
+        default: return false;
+        }
+    }
+    // Whether every tensor instance i is made of is read at i's own position: the gradient of a position outside the
+    // image then ends at a read that no pixel receives.
+    bool own_position(int i) const {
+        const Inst& I = G->insts[i];
+        switch (I.kind) {
+        case kExt: return true;
+        case kIdent:
+        case kUnaryI: return own_position(I.opnd[0]);
+        case kBinaryI: return own_position(I.opnd[0]) && own_position(I.opnd[1]);
+        default: return false;
+        }
+    }
 
     // ---------------------------------------------------------------- forward values
     void eval_raw(int i) {
@@ -368,7 +450,7 @@ class Emitter {
         case kStencil: {
             eval(I.opnd[0]);
             const Inst& S = G->insts[I.opnd[0]];
-            if (S.kind != kExt) emit(positional(OP_MASK, S.ctx, I.lanes));  // (a load checks its own position)
+            if (!zero_outside(I.opnd[0])) emit(positional(OP_MASK, S.ctx, I.lanes));  // (a load checks its own position)
             break;
         }
         case kUnaryI: {
@@ -391,12 +473,28 @@ class Emitter {
                 emit(load_and_blend(I.opnd[1], I.lanes, nd.kind, false));
                 break;
             }
-            eval(I.opnd[0]);
-            const int r = alloc();
-            emit(simple(OP_MOVR, tl, r));
+            const bool lhs_scalar = tl == 1 && I.lanes > 1;
+            bool mine;
+            if (kept(I.opnd[0], 0) < 0) {  // (an RHS in a register is taken from there, also when computing the LHS put it there)
+                int rr = kept(I.opnd[1], 0);
+                eval(I.opnd[0]);
+                rr = kept(I.opnd[1], 0);
+                if (rr >= 0) {
+                    emit(simple(OP_BIN, I.lanes, rr, nd.kind | (lhs_scalar ? kBinAccScalar : 0)));
+                    break;
+                }
+                int r = kept(I.opnd[0], 0);
+                mine = r < 0;
+                if (mine) emit(simple(OP_MOVR, tl, r = alloc()));
+                eval(I.opnd[1]);
+                emit(simple(OP_BIN, I.lanes, r, nd.kind | kBinRegIsLhs | (lhs_scalar ? kBinRegScalar : 0)));
+                if (mine) release(r);
+                break;
+            }
+            const int r = to_reg(I.opnd[0], 0, mine);
             eval(I.opnd[1]);
-            emit(simple(OP_BIN, I.lanes, r, nd.kind | kBinRegIsLhs | (tl == 1 && I.lanes > 1 ? kBinRegScalar : 0)));
-            release(r);
+            emit(simple(OP_BIN, I.lanes, r, nd.kind | kBinRegIsLhs | (lhs_scalar ? kBinRegScalar : 0)));
+            if (mine) release(r);
             break;
         }
         case kSmT:
@@ -474,21 +572,22 @@ class Emitter {
             emit(simple(OP_FOLD, wc.kh * wc.kw, 0, un.kind));
             return;
         }
-        grad(u);  // A = gradient of u, U.lanes lanes
+        // (registers and A: a gradient or value that a register keeps is used there, not copied to another one)
+        bool mine = false;
         switch (U.kind) {
-        case kIdent: break;
+        case kIdent: grad(u); break;
         case kStencil:
-            if (I.kind != kExt) emit(positional(OP_MASK, I.ctx, U.lanes));
+            grad(u);
+            if (!own_position(i)) emit(positional(OP_MASK, I.ctx, U.lanes));
             break;
         case kUnaryI: {
-            const int r = alloc();
-            emit(simple(OP_MOVR, U.lanes, r));
-            eval(i);
+            const int r = to_reg(u, 1, mine);
+            eval(un.kind == kRelu && kept(u, 0) >= 0 ? u : i);  // (relu: its result is positive where its argument is)
             Instr b = simple(OP_UNBX, U.lanes, r, un.kind);
             b.f0 = un.lo;
             b.f1 = un.hi;
             emit(b);
-            release(r);
+            if (mine) release(r);
             break;
         }
         case kBinaryI: {
@@ -496,55 +595,61 @@ class Emitter {
             const int tl = G->insts[U.opnd[0]].lanes;
             const bool lhs_scalar = tl == 1 && U.lanes > 1;
             if (un.kind == kAdd || (un.kind == kSub && slot == 0)) {
+                grad(u);
             } else if (un.kind == kSub) {
+                grad(u);
                 emit(simple(OP_UN, U.lanes, 0, kUnNeg));
-            } else if (un.kind == kMul && G->insts[other].kind == kExt) {
+            } else if (un.kind == kMul && kept(other, 0) < 0 && G->insts[other].kind == kExt) {
                 // the gradient in A times the other operand, which comes straight from memory
+                grad(u);
                 emit(load_and_blend(other, U.lanes, kMul, false));
             } else if (un.kind == kMul) {
-                const int r = alloc();
-                emit(simple(OP_MOVR, U.lanes, r));
-                eval(other);
-                // A (the other operand) times the gradient in R[r]; the other operand is a scalar when it is the 1-lane LHS
-                emit(simple(OP_BIN, U.lanes, r, kMul | (slot == 1 && lhs_scalar ? kBinAccScalar : 0)));
-                release(r);
+                // the other operand is a scalar when it is the 1-lane LHS
+                const bool scalar = slot == 1 && lhs_scalar;
+                if (kept(u, 1) < 0) grad(u);
+                const int ro = kept(other, 0), rg = kept(u, 1);
+                if (ro >= 0) {
+                    if (rg >= 0) emit(simple(OP_MOVA, U.lanes, rg));
+                    emit(simple(OP_BIN, U.lanes, ro, kMul | (scalar ? kBinRegScalar : 0)));
+                } else {
+                    const int r = rg >= 0 ? rg : alloc();
+                    if (rg < 0) emit(simple(OP_MOVR, U.lanes, r));
+                    eval(other);
+                    emit(simple(OP_BIN, U.lanes, r, kMul | (scalar ? kBinAccScalar : 0)));
+                    if (rg < 0) release(r);
+                }
             } else {  // min / max: the indicator needs both operands
-                const int rg = alloc();
-                emit(simple(OP_MOVR, U.lanes, rg));
-                eval(U.opnd[0]);
-                const int rl = alloc();
-                emit(simple(OP_MOVR, tl, rl));
+                bool mine_l;
+                const int rg = to_reg(u, 1, mine);
+                const int rl = to_reg(U.opnd[0], 0, mine_l);
                 eval(U.opnd[1]);
                 emit(simple(OP_BING, U.lanes, rl, un.kind | (slot == 1 ? kBingRhsSide : 0) | (lhs_scalar ? kBingLhsScalar : 0)));
                 emit(simple(OP_BIN, U.lanes, rg, kMul));
-                release(rl);
-                release(rg);
+                if (mine_l) release(rl);
+                if (mine) release(rg);
             }
             if (slot == 0 && lhs_scalar) emit(simple(OP_FOLD, U.lanes, 0, kSum));  // the replicated LHS collects all lanes
             break;
         }
         case kSmT: {
-            const int r = alloc();
-            emit(simple(OP_MOVR, U.lanes, r));
+            const int r = to_reg(u, 1, mine);
             eval(u);
             emit(simple(OP_SMTBX, U.lanes, r));
-            release(r);
+            if (mine) release(r);
             break;
         }
         case kSmC: {
-            const int r = alloc();
-            emit(simple(OP_MOVR, U.lanes, r));
+            const int r = to_reg(u, 1, mine);
             eval(u);
             emit(simple(OP_SMCBX, U.lanes, r, 0, dot_slot(u)));
-            release(r);
+            if (mine) release(r);
             break;
         }
         case kFoldI: {
-            const int r = alloc();
-            emit(simple(OP_MOVR, 1, r));
+            const int r = to_reg(u, 1, mine);
             if (un.kind == kMax) eval(i);
             emit(simple(OP_FOLDBX, I.lanes, r, un.kind));
-            release(r);
+            if (mine) release(r);
             break;
         }
         case kBoxAdj: break;  // (handled above)
@@ -553,6 +658,7 @@ class Emitter {
     }
 
     void begin_pass() {
+        a_reg = -1;
         if (pg.n_pass >= kMaxPass) throw Fail{"too many passes"};
         pg.pass[pg.n_pass].pro_begin = (uint16_t)pg.n_instr;
         pg.pass[pg.n_pass].red_begin = pg.pass[pg.n_pass].red_end = (uint16_t)pg.n_red;
@@ -567,7 +673,10 @@ class Emitter {
         pg.red[pg.n_red++] = r;
         pg.pass[pg.n_pass].red_end = (uint16_t)pg.n_red;
     }
-    void begin_body() { pg.pass[pg.n_pass].pro_end = pg.pass[pg.n_pass].body_begin = (uint16_t)pg.n_instr; }
+    void begin_body() {
+        a_reg = -1;
+        pg.pass[pg.n_pass].pro_end = pg.pass[pg.n_pass].body_begin = (uint16_t)pg.n_instr;
+    }
     void end_pass() {
         pg.pass[pg.n_pass++].body_end = (uint16_t)pg.n_instr;
         forget();
@@ -608,6 +717,8 @@ class Emitter {
     std::set<int> keep;
     std::map<int, int> held;
     std::map<int, Stat> stats;
+    double weight = 0;                // of the instructions so far
+    int a_reg = -1, a_lanes = 0;      // the register whose lanes A equals at this point of the program (-1: none)
     std::map<int, int64_t> reach_of;  // per OP_XADD instruction: how far (in pixels) its sources can lie
 };
 
@@ -906,16 +1017,17 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
             E.end_pass();
         };
         // A program is emitted with full recomputation first; then, greedily, the value or gradient whose repeated
-        // computation costs the most instructions is kept in a register, as long as that shortens the program and the
-        // registers last.  Returns the emitter of the shortest program that could be emitted.
+        // computation costs the most is kept in a register, as long as that makes the program cheaper and the registers
+        // last.  Returns the emitter of the cheapest program that could be emitted.
         auto shortest = [&](const std::function<void(Emitter&)>& emit_program) {
             std::set<int> keep;
             auto best = std::make_shared<Emitter>(G, tm);
             emit_program(*best);  // (throws when even the plain program does not fit)
             for (int round = 0; round < regs_for(tm); round++) {
-                int pick = -1, gain = 1;
+                int pick = -1;
+                double gain = 0;
                 for (const auto& kv : best->stats) {
-                    const int g = (kv.second.computed - 1) * (kv.second.cost - 1) - 1;  // (- the store)
+                    const double g = (kv.second.computed - 1) * (kv.second.cost - kv.second.lanes) - kv.second.lanes;  // (fetched instead; - the store)
                     if (!keep.count(kv.first) && g > gain) {
                         gain = g;
                         pick = kv.first;
@@ -927,7 +1039,7 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
                     auto E = std::make_shared<Emitter>(G, tm);
                     E->keep = keep;
                     emit_program(*E);
-                    if (E->pg.n_instr >= best->pg.n_instr) break;
+                    if (E->weight >= best->weight) break;
                     best = E;
                 } catch (const Fail&) {
                     break;
@@ -961,24 +1073,7 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
 double program_cost(const Program& pg) {
     double sum = 0;
     for (int p = 0; p < pg.n_pass; p++)
-        for (int i = pg.pass[p].body_begin; i < pg.pass[p].body_end; i++) {
-            const Instr& I = pg.ins[i];
-            double w = 1;
-            switch (I.op) {
-            case OP_LD:
-            case OP_BINLD:
-            case OP_ST: w = 4; break;
-            case OP_XADD: w = 6; break;
-            case OP_UN:
-            case OP_UNBX: w = (I.kind == 0 || I.kind == 1 || I.kind == kUnNeg) ? 1 : 6; break;
-            case OP_SMT:
-            case OP_SMTBX:
-            case OP_SMCSTAT:
-            case OP_SMCAPPLY: w = 6; break;
-            default: break;
-            }
-            sum += w * I.T;
-        }
+        for (int i = pg.pass[p].body_begin; i < pg.pass[p].body_end; i++) sum += instr_weight(pg.ins[i]);
     // pixels computed per pixel owned (the halo), and the serial walk over the channels where the workgroup's shape leaves
     // a thread more than 16 trips (a program that keeps all channels in one workgroup and has no LDS left for slices)
     const double halo = (double)pg.pix_threads / std::max(1, pg.own_threads + (pg.halo_threads > 0 ? 0 : pg.pix_threads - pg.own_threads));
