@@ -1,8 +1,7 @@
 // v = x (*|+) shift(act(z)) and its adjoint, one thread per 8 consecutive pixels of one channel
 // (16-byte bf16 accesses).  The shift is an address offset plus a zero mask applied AFTER the
 // activation (Shift zero-fills its own output, whatever act(0) is).  Memory-bound: forward reads x, z
-// and writes v; backward reads dv, x, z (dv and x at two positions, the second served by cache) and
-// writes dz and dx1.
+// and writes v; backward reads dv, x, z and writes dz and dx1, each element once.
 #include "ufc_kernels.hpp"
 
 #include <type_traits>
@@ -47,12 +46,13 @@ __device__ __forceinline__ u32x4 load8(rsrc_t r, int e, int bytes) {
     return v;
 }
 
-__device__ __forceinline__ void store8(rsrc_t r, uint16_t* base, int e, const float (&f)[8], int nvalid) {
+__device__ __forceinline__ void store8(rsrc_t r, uint16_t* base, int e, const float (&f)[8], int nvalid, bool nt = true) {
     if (nvalid == 8) {
         u32x4 out;
 #pragma unroll
         for (int k = 0; k < 4; k++) out[k] = pack_bf16(f[2 * k], f[2 * k + 1]);
-        bstore16_nt(r, e * 2, out);
+        if (nt) bstore16_nt(r, e * 2, out);
+        else bstore16(r, e * 2, out);
     } else {
 #pragma unroll
         for (int q = 0; q < 8; q++)
@@ -143,6 +143,31 @@ __global__ __launch_bounds__(256) void k_mid_fwd(MidParams P) {
     store8(rv, P.v, u.plane + u.p, v, u.nvalid);
 }
 
+// act(z) and act'(z)
+template <int ACT>
+__device__ __forceinline__ void act_both(float z, float& t, float& d) {
+    if constexpr (ACT == 2) {
+        float cdf, pdf;
+        normal_parts(z, cdf, pdf);
+        t = z * cdf;
+        d = cdf + z * pdf;
+    } else {
+        t = act_apply<ACT>(z);
+        d = act_grad<ACT>(z);
+    }
+}
+
+// The adjoint, written from the side of p:
+//     dx1(p) = dv(p) * t(p)    with t(p) = act(z(p + d)), zero where p + d leaves the image;  dv(p) for a sum
+//     dz(p + d) = act'(z(p + d)) * dv(p) * x(p)
+// Everything then needs dv and x at p and z at p + d, each once, and act at one point; dz is stored at p + d (an unaligned
+// 16-byte store, as planes that are no multiple of 8 pixels have anyway).  p -> p + d is a bijection of the plane's flat
+// pixel indices except at its two ends: targets outside the plane are dropped, and the thread that owns a pixel without a
+// source writes its zero.  A target that lies in the plane but in another image row receives zero.
+// (Gathered from the side of dz, a shifted channel read dv and z at two points each and evaluated act twice per pixel.
+// With half of the channels shifted, gelu and product: N=128 C=64 56x56 53.7 -> 43.7 us = 5.9 TB/s, C=256 14x14 17.2 -> 14.9,
+// C=512 7x7 11.9 -> 9.4.  As the end of the data gradient that produces dv, without dv in memory, it was slower: 71 us
+// against 44 + 23 at C=64, 36 against 15 + 14 at C=256; the tile's registers leave two or three wavefronts per SIMD.)
 template <int ACT, int BIN>
 __global__ __launch_bounds__(256) void k_mid_bwd(MidParams P) {
     const Unit u = decode(P);
@@ -150,45 +175,39 @@ __global__ __launch_bounds__(256) void k_mid_bwd(MidParams P) {
     const int bytes = P.N * P.C * P.P * 2;
     const rsrc_t rx = make_rsrc(P.x, bytes), rz = make_rsrc(P.z, bytes), rdv = make_rsrc(P.dv, bytes);
     const rsrc_t rdz = make_rsrc(P.dz, bytes), rdx = make_rsrc(P.dx1, bytes);
-    const int off = u.dh * P.W + u.dw;
-    const uint32_t bits_f = shift_bits(P, u.p, u.dh, u.dw);    // t_s(p) reads z(p + d)
-    const uint32_t bits_b = shift_bits(P, u.p, -u.dh, -u.dw);  // dt(p) receives g(p - d)
-    float dv[8], zs[8], z[8], dvb[8], xb[8], dx1[8], dz[8];
-    unpack8(load8(rdv, u.plane + u.p, bytes), dv);
-    unpack8(load8(rz, u.plane + u.p, bytes), z);
-    if (off != 0) {  // (channels that are not shifted read every tensor once)
-        unpack8(load8(rz, u.plane + u.p + off, bytes), zs);
-        unpack8(load8(rdv, u.plane + u.p - off, bytes), dvb);
-    }
-    if (BIN) unpack8(load8(rx, u.plane + u.p - off, bytes), xb);
+    // a shift by the image's size or more: no pixel has a target
+    const bool none = u.dh >= P.H || u.dh <= -P.H || u.dw >= P.W || u.dw <= -P.W;
+    const int off = none ? P.P : u.dh * P.W + u.dw;
+    const int q0 = u.p + off, e = u.plane + u.p;
+    float dv[8], z[8], x[8], dx1[8], dz[8];
+    unpack8(load8(rdv, e, bytes), dv);
+    unpack8(load8(rz, q0 < P.P && q0 + 7 >= 0 ? e + off : kOob / 2, bytes), z);
+    if (BIN) unpack8(load8(rx, e, bytes), x);
+    const uint32_t bits = none ? 0u : ((u.dh | u.dw) != 0 ? shift_bits(P, u.p, u.dh, u.dw) : 0xffu);
 #pragma unroll
     for (int q = 0; q < 8; q++) {
-        const float zq = z[q], zsq = off != 0 ? zs[q] : zq;
         float t, d;
-        if constexpr (ACT == 2) {
-            float cdf, pdf;
-            normal_parts(zq, cdf, pdf);
-            d = cdf + zq * pdf;
-            if (off != 0) {
-                float cdf_s, pdf_s;
-                normal_parts(zsq, cdf_s, pdf_s);
-                t = zsq * cdf_s;
-            } else {
-                t = zq * cdf;
-            }
-        } else {
-            t = act_apply<ACT>(zsq);
-            d = act_grad<ACT>(zq);
-        }
-        t = ((bits_f >> q) & 1u) ? t : 0.f;
-        dx1[q] = BIN ? dv[q] * t : dv[q];
-        const float dvq = off != 0 ? dvb[q] : dv[q];
-        float g = BIN ? dvq * xb[q] : dvq;
-        g = ((bits_b >> q) & 1u) ? g : 0.f;
-        dz[q] = g * d;
+        act_both<ACT>(z[q], t, d);
+        const bool in = (bits >> q) & 1u;
+        dx1[q] = BIN ? dv[q] * (in ? t : 0.f) : dv[q];
+        dz[q] = (in ? (BIN ? dv[q] * x[q] : dv[q]) : 0.f) * d;
     }
-    store8(rdx, P.dx1, u.plane + u.p, dx1, u.nvalid);
-    store8(rdz, P.dz, u.plane + u.p, dz, u.nvalid);
+    store8(rdx, P.dx1, e, dx1, u.nvalid);
+    if (u.nvalid == 8 && q0 >= 0 && q0 + 8 <= P.P) {
+        store8(rdz, P.dz, e + off, dz, 8, off == 0);  // (unaligned stores leave partial lines: kept in the cache until whole)
+    } else {
+#pragma unroll
+        for (int q = 0; q < 8; q++)
+            if (q < u.nvalid && (unsigned)(q0 + q) < (unsigned)P.P) P.dz[e + off + q] = (uint16_t)(pack_bf16(dz[q], 0.f) & 0xffffu);
+    }
+    if (off != 0 && (u.p - off < 0 || u.p + u.nvalid - 1 - off >= P.P)) {
+        for (int q = 0; q < u.nvalid; q++)
+            if ((unsigned)(u.p + q - off) >= (unsigned)P.P) {
+                float t, d;
+                act_both<ACT>(__uint_as_float((uint32_t)P.z[e + q] << 16), t, d);
+                P.dz[e + q] = (uint16_t)(pack_bf16(0.f * d, 0.f) & 0xffffu);
+            }
+    }
 }
 
 template <typename F>
