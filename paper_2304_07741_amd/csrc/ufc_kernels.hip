@@ -110,18 +110,6 @@ __device__ __forceinline__ float act_apply(float z) {
         return unary_apply(ACT, z, 0.f, 0.f);
     }
 }
-template <int ACT>
-__device__ __forceinline__ float act_grad(float z) {
-    if constexpr (ACT == 2) {
-        float cdf, pdf;
-        normal_parts(z, cdf, pdf);
-        return cdf + z * pdf;
-    } else if constexpr (ACT < 0) {
-        return 1.f;
-    } else {
-        return unary_grad(ACT, z, 0.f, 0.f);
-    }
-}
 
 template <int ACT, int BIN>
 __global__ __launch_bounds__(256) void k_mid_fwd(MidParams P) {
@@ -153,7 +141,8 @@ __device__ __forceinline__ void act_both(float z, float& t, float& d) {
         d = cdf + z * pdf;
     } else {
         t = act_apply<ACT>(z);
-        d = act_grad<ACT>(z);
+        if constexpr (ACT < 0) d = 1.f;
+        else d = unary_grad(ACT, z, 0.f, 0.f);
     }
 }
 
