@@ -17,10 +17,10 @@ constexpr int kMaxLds = 64 * 1024;
 
 // Consecutive workgroups go to consecutive XCDs, each with an L2 of its own; this renumbers them so that an XCD works on
 // neighbouring tiles, whose operands overlap (the margin of a window, the other outputs of the same pixels).  The grid is
-// a multiple of eight workgroups; the numbers past the last tile have no work.
+// a multiple of eight workgroups, in rows if it is long (grid_of); the numbers past the last tile have no work.
 __device__ __forceinline__ unsigned tile_of_block() {
     const unsigned per = gridDim.x / 8;
-    return (blockIdx.x % 8) * per + blockIdx.x / 8;
+    return blockIdx.y * gridDim.x + (blockIdx.x % 8) * per + blockIdx.x / 8;
 }
 
 // x / d for the small dividends of index arithmetic: exact while x * d < 2^32 (the host checks the image's sizes)
@@ -577,8 +577,17 @@ void prepare_wgrad(Params& p, int64_t max_partial_bytes) {
     p.tiles = p.slices * tiles;
 }
 
+// A launch has fewer than 2^32 threads along x: one output per group and 128 pixels per workgroup reach that at 2^31
+// elements, 8 GB.  Longer grids get more than one row.
+static dim3 grid_of(int64_t tiles) {
+    constexpr int64_t kMaxX = ((int64_t)1 << 32) / kThreads - 8;
+    const int64_t rows = std::max<int64_t>(1, (tiles + kMaxX - 1) / kMaxX);
+    const int64_t per_row = (tiles + rows - 1) / rows;
+    return dim3((unsigned)((per_row + 7) / 8 * 8), (unsigned)rows);
+}
+
 void forward(const Params& p, hipStream_t s) {
-    const dim3 grid((unsigned)((p.tiles + 7) / 8 * 8)), block(kThreads);
+    const dim3 grid = grid_of(p.tiles), block(kThreads);
     const size_t lds = fwd_lds(p);
 #define CANVAS_SFC_T(WM, NT, TVT, WIN, NP, KC)                                                                          \
     do {                                                                                                               \
@@ -606,7 +615,7 @@ void forward(const Params& p, hipStream_t s) {
 }
 
 void wgrad_partial(const Params& p, hipStream_t s) {
-    const dim3 grid((unsigned)((p.tiles + 7) / 8 * 8)), block(kThreads);
+    const dim3 grid = grid_of(p.tiles), block(kThreads);
     const size_t lds = wgrad_lds(p);
 #define CANVAS_SFC(MT, NT, WM)                                                           \
     do {                                                                                 \
