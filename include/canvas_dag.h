@@ -160,6 +160,10 @@ int canvas_dag_launch_desc(const canvas_dag* dag, int backward, int idx, canvas_
  *   y        [N, C_out, T_out, H, W] dtype dt, written
  *   workspace  workspace_bytes bytes; carries what backward needs, so it must stay
  *            untouched until the matching canvas_dag_backward has run
+ * What a call writes (y; dx, dweights) must not share bytes with the workspace, with the weights or with anything else
+ * the call reads or writes; results are undefined where it does.  One exception: in a plan of one fp32 fc, with or
+ * without an unfold in front, y may overlap x or the weight, and dx may overlap dy or the weight (the call then
+ * passes its result through the workspace).
  * Does not allocate, free or synchronise.  Errors: BAD_ARG,
  * WORKSPACE_TOO_SMALL, HIP_ERROR (launch failure). */
 int canvas_dag_forward(canvas_dag* dag, const void* x, const void* const* weights, void* y, void* workspace,
@@ -174,8 +178,8 @@ int canvas_dag_forward(canvas_dag* dag, const void* x, const void* const* weight
  * needed; no canvas_dag_backward can follow, since that reads the workspace of its forward call.
  * All calls on one GPU, of any plan, share the one array: calls that overlap on a GPU (different streams
  * or host threads) race; calls enqueued on one stream are ordered and safe.
- * Errors: WORKSPACE_TOO_SMALL when the plan's workspace_bytes exceeds CANVAS_STATIC_WORKSPACE_BYTES
- * (nothing is launched), BAD_ARG, HIP_ERROR. */
+ * Errors: WORKSPACE_TOO_SMALL when the plan's workspace_bytes, without the room a single fp32 fc keeps for overlapping
+ * tensors unless they do overlap, exceeds CANVAS_STATIC_WORKSPACE_BYTES (nothing is launched), BAD_ARG, HIP_ERROR. */
 #define CANVAS_STATIC_WORKSPACE_BYTES (64u << 20)
 int canvas_dag_forward_static(canvas_dag* dag, const void* x, const void* const* weights, void* y, void* stream);
 

@@ -206,15 +206,18 @@ int canvas_dag_forward(canvas_dag* dag, const void* x, const void* const* weight
 
 int canvas_dag_forward_static(canvas_dag* dag, const void* x, const void* const* weights, void* y, void* stream) {
     if (!dag) return set_err(CANVAS_BAD_ARG, "null dag handle");
-    if (dag->low->ws_bytes > (uint64_t)CANVAS_STATIC_WORKSPACE_BYTES)
-        return set_err(CANVAS_WORKSPACE_TOO_SMALL, "this plan needs " + std::to_string(dag->low->ws_bytes) +
+    auto too_small = [](uint64_t need) {
+        return set_err(CANVAS_WORKSPACE_TOO_SMALL, "this plan needs " + std::to_string(need) +
                                                        " workspace bytes, the static workspace holds " +
                                                        std::to_string((uint64_t)CANVAS_STATIC_WORKSPACE_BYTES) +
                                                        ": use canvas_dag_forward with a workspace of the caller");
+    };
+    const uint64_t need = dag->low->ws_bytes - dag->low->stage_bytes;
+    if (need > (uint64_t)CANVAS_STATIC_WORKSPACE_BYTES) return too_small(need);
     void* ws = nullptr;
     int rc = static_scratch_of_current_device(&ws);
     if (rc) return rc;
-    rc = check_common(dag, x, weights, ws, (size_t)CANVAS_STATIC_WORKSPACE_BYTES);
+    rc = check_common(dag, x, weights, ws, (size_t)dag->low->ws_bytes);
     if (rc) return rc;
     if (!y || !aligned16(y)) return set_err(CANVAS_BAD_ARG, "y must be a non-null, 16-byte aligned device pointer");
     canvas::RunArgs a;
@@ -223,6 +226,7 @@ int canvas_dag_forward_static(canvas_dag* dag, const void* x, const void* const*
     a.y = y;
     a.ws = (char*)ws;
     a.stream = (hipStream_t)stream;
+    if (dag->low->ws_bytes > (uint64_t)CANVAS_STATIC_WORKSPACE_BYTES && dag->low->fwd_staged(a)) return too_small(dag->low->ws_bytes);
     (void)hipGetLastError();
     // an inference plan keeps its weight-only launches apart: here they run with every call, as the static
     // workspace is shared by all plans and calls on this GPU and keeps nothing between them

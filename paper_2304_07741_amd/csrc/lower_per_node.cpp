@@ -375,6 +375,18 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         if (sgrad[i].slices > 1) lay.part[i] = take(wnumel[i] * sgrad[i].slices);
     }
     low->ws_bytes = std::max<uint64_t>(off, 256);  // (a caller always hands over a workspace, also to a plan that needs none)
+    // An fp32 FC that is the whole DAG reads x and writes y, reads dy and writes dx in one launch each.  A call that passes
+    // overlapping buffers for them (in place, say) writes to this end of the workspace first and copies.
+    auto fc_alone = [&](int k) { return !bf16 && k == dag.out && y_direct && fc_src(k) == 0; };
+    int64_t stage = -1;
+    if (dag.out > 0 && dag.nodes[dag.out].op == Op::Fc && fc_alone(dag.out)) {
+        const int64_t nx = dag.numel(0) * 4, ny = dag.numel(dag.out) * 4, nw = wnumel[dag.nodes[dag.out].widx] * 4;
+        const int widx = dag.nodes[dag.out].widx;
+        stage = (int64_t)low->ws_bytes;
+        low->stage_bytes = align_up((uint64_t)std::max(nx, ny));
+        low->ws_bytes += low->stage_bytes;
+        low->fwd_staged = [=](const RunArgs& a) { return overlap(a.y, ny, a.x, nx) || overlap(a.y, ny, a.w[widx], nw); };
+    }
     const double esz = bf16 ? 2.0 : 4.0;
 
     // pointer resolvers
@@ -482,6 +494,8 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             sfc::prepare_forward(Q);
             const int srcn = fc_src(k), widx = nd.widx;
             const bool to_y = k == dag.out && y_direct;
+            const int64_t ny = dag.numel(k);
+            const auto overlaps = stage >= 0 ? low->fwd_staged : [](const RunArgs&) { return false; };
             L.name = Q.TV > 1 ? "sfc_fwd_unfold" : "sfc_fwd";
             L.bytes = 4.0 * (dag.numel(srcn) + dag.numel(k) + wnumel[widx]);
             L.run = [=](const RunArgs& a) {
@@ -489,7 +503,10 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
                 R.src = val(a, srcn);
                 R.w = wptr(a, widx);
                 R.dst = to_y ? (float*)a.y : valw(a, k);
+                const bool staged = overlaps(a);
+                if (staged) R.dst = (float*)(a.ws + stage);
                 sfc::forward(R, a.stream);
+                if (staged) ref::copy_f32(R.dst, (float*)a.y, ny, a.stream);
             };
             break;
         }
@@ -672,13 +689,17 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             sfc::Params D = sfc::data_gradient_of(Q);
             D.acc = acc_s;
             sfc::prepare_forward(D);
+            const int64_t nx = dag.numel(0), ny = dag.numel(k);
             low->bwd.push_back({D.TV > 1 ? "sfc_dgrad_unfold" : "sfc_dgrad", 4.0 * (dag.numel(k) + dag.numel(srcn) * (1 + acc_s) + nw), flops,
                                 [=](const RunArgs& a) {
                                     sfc::Params R = D;
                                     R.src = from_dy ? (const float*)a.dy : grad(a, k);
                                     R.w = wptr(a, widx);
                                     R.dst = to_dx ? (float*)a.dx : grad(a, srcn);
+                                    const bool staged = stage >= 0 && (overlap(a.dx, nx * 4, a.dy, ny * 4) || overlap(a.dx, nx * 4, a.w[widx], nw * 4));
+                                    if (staged) R.dst = (float*)(a.ws + stage);
                                     sfc::forward(R, a.stream);
+                                    if (staged) ref::copy_f32(R.dst, (float*)a.dx, nx, a.stream);
                                 }});
             written[srcn] = true;
             continue;

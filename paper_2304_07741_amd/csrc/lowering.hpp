@@ -58,6 +58,8 @@ struct Lowering {
     int chain_units = 0;           // fused chains in the forward list (each is one kernel forward, one backward)
     int chain_nodes = 0;           // nodes inside them
     uint64_t ws_bytes = 0;
+    uint64_t stage_bytes = 0;      // the end of the workspace, used only by calls whose tensors overlap
+    std::function<bool(const RunArgs&)> fwd_staged;  // with stage_bytes: whether a forward call is one
     std::vector<Launch> fwd, bwd;
     std::vector<WeightJob> wjobs;  // collected while lowering; batch_weight_jobs turns them into launches
     std::vector<ReduceJob> rjobs;  // likewise; batch_reduce_jobs
@@ -74,6 +76,11 @@ void batch_reduce_jobs(Lowering& low);
 
 // Turns a lowering into a forward-only plan: weight-only launches move to `prep`, the backward list is dropped.
 void make_inference_plan(Lowering& low);
+
+// Whether two device ranges of a call share bytes: a launch that reads one and writes the other cannot work in place.
+inline bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes) {
+    return (const char*)a < (const char*)b + b_bytes && (const char*)b < (const char*)a + a_bytes;
+}
 
 inline uint64_t align_up(uint64_t v, uint64_t a = 256) { return (v + a - 1) / a * a; }
 
