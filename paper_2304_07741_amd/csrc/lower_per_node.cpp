@@ -26,6 +26,8 @@ namespace {
 
 constexpr int64_t kMaxSfcPartialBytes = 16 << 20;
 
+std::string sfc_name(const char* what, const sfc::Params& q) { return std::string(what) + (q.TV > 1 ? "_unfold" : "") + (q.narrow ? "_narrow" : ""); }
+
 struct Layout {
     std::vector<int64_t> val, grad, wf;  // byte offsets into the workspace; -1 = not in the workspace
     std::vector<int64_t> wt, part;       // per fc (bf16 path): transposed weights, weight-gradient partials
@@ -269,7 +271,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
     // who can use the caller's tensors in place: chains, and FC nodes whose kernels have the caller's type
     auto fc_in_place = [&](int k) { return dag.nodes[k].op == Op::Fc && (fc_mfma[k] || !bf16); };
     auto in_place = [&](int k) { return k > 0 && unit_of[k] >= 0 && (units[unit_of[k]].chain || fc_in_place(k)); };
-    // x: read in place by chains and by MFMA FC nodes (also through a virtual Unfold); a widened copy only for the others
+    // x: read in place by such units (FC nodes also through a virtual Unfold); a widened copy only for the others
     bool need_x32 = dag.out == 0;
     for (int c : consumers[0]) {
         if (virt[c]) continue;  // (its consumers are FC nodes that read x)
@@ -496,7 +498,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             const bool to_y = k == dag.out && y_direct;
             const int64_t ny = dag.numel(k);
             const auto overlaps = stage >= 0 ? low->fwd_staged : [](const RunArgs&) { return false; };
-            L.name = Q.TV > 1 ? "sfc_fwd_unfold" : "sfc_fwd";
+            L.name = sfc_name("sfc_fwd", Q);
             L.bytes = 4.0 * (dag.numel(srcn) + dag.numel(k) + wnumel[widx]);
             L.run = [=](const RunArgs& a) {
                 sfc::Params R = Q;
@@ -667,7 +669,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             const int64_t nw = wnumel[widx], poff = lay.part[widx];
             const double flops = 2.0 * N * dag.Pk(k) * (double)nw;
             const sfc::Params Q = sgrad[widx];
-            low->bwd.push_back({Q.TV > 1 ? "sfc_wgrad_unfold" : "sfc_wgrad", 4.0 * (dag.numel(srcn) + dag.numel(k) + (double)Q.slices * nw), flops,
+            low->bwd.push_back({sfc_name("sfc_wgrad", Q), 4.0 * (dag.numel(srcn) + dag.numel(k) + (double)Q.slices * nw), flops,
                                 [=](const RunArgs& a) {
                                     sfc::Params R = Q;
                                     R.src = val(a, srcn);
@@ -690,7 +692,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             D.acc = acc_s;
             sfc::prepare_forward(D);
             const int64_t nx = dag.numel(0), ny = dag.numel(k);
-            low->bwd.push_back({D.TV > 1 ? "sfc_dgrad_unfold" : "sfc_dgrad", 4.0 * (dag.numel(k) + dag.numel(srcn) * (1 + acc_s) + nw), flops,
+            low->bwd.push_back({sfc_name("sfc_dgrad", D), 4.0 * (dag.numel(k) + dag.numel(srcn) * (1 + acc_s) + nw), flops,
                                 [=](const RunArgs& a) {
                                     sfc::Params R = D;
                                     R.src = from_dy ? (const float*)a.dy : grad(a, k);

@@ -10,6 +10,7 @@ namespace sfc {
 namespace {
 
 using f4 = __attribute__((ext_vector_type(4))) float;
+using f4u = __attribute__((ext_vector_type(4), aligned(4))) float;  // in memory, at any element
 
 constexpr int kThreads = 256;
 constexpr int kLinearKc = 32;   // channels per chunk without a window
@@ -267,6 +268,7 @@ __global__ __launch_bounds__(kThreads) void k_fwd(Params Q) {
     }
 }
 
+constexpr int kNarrowPix = 4 * kThreads;  // pixels per step of the narrow weight gradient
 constexpr int kPix = 64;        // pixels per step of the weight gradient
 constexpr int kDyStride = 68;   // 4 mod 64: the 16 outputs x 4 pixels of an operand read lie in 64 banks
 
@@ -447,6 +449,225 @@ __global__ __launch_bounds__(kThreads) void k_wgrad(Params Q) {
         }
 }
 
+// Few rows and outputs per group (a depthwise or nearly depthwise contraction): a matrix tile would consist of padding, 16
+// outputs and 4 to 32 channels of which one to four are there.  One thread per V pixels of a group and OT outputs on the
+// vector unit, numbered through [N, G, P], so that a wavefront reads and writes whole lines also of planes smaller than
+// itself; a window's taps are loads of their own, mostly from the first-level cache.  Bound by memory without a window, by
+// the loads of the taps with one.
+// Sums: chains of a window row's taps (without a window: of four channels), these parts added per channel, these to the result.
+// N=64, 56x56, 64 channels, one per group: 23 us without a window (4.4 TB/s), 107 us with 3 x 3, 278 us with 5 x 5; k_fwd
+// takes 328, 415 and 970 us there.  Errors against fp64 are those of k_fwd or smaller (1 x 1 2.5-5.7e-8, 3 x 3 5.0-6.4e-8
+// against 5.5-6.9e-8).
+template <int OT, int V, int TVT, bool TR>
+__global__ __launch_bounds__(kThreads) void k_fwd_narrow(Params Q) {
+    unsigned b = tile_of_block();
+    if (b >= (unsigned)Q.tiles) return;
+    const int o0 = (int)(b % (unsigned)Q.mtiles) * OT;
+    const int64_t base = (int64_t)(b / (unsigned)Q.mtiles) * (kThreads * V);  // V divides P: a thread's pixels lie in one plane
+    const int64_t P = Q.P, ng0 = base / P;
+    int p = (int)(base - ng0 * P) + (int)threadIdx.x * V;
+    const int dn = Q.P >= kThreads * V ? (p >= Q.P ? 1 : 0) : quotient(p, Q.P, Q.mP);
+    p -= dn * Q.P;
+    const int64_t ng = ng0 + dn;
+    if (ng >= Q.N * Q.G) return;
+    const int g = (int)(((uint32_t)(ng0 % Q.G) + (uint32_t)dn) % (uint32_t)Q.G);
+    const float* src = Q.src + ng * Q.R * P;
+    const int tv = TVT ? TVT : Q.TV;
+    // element (output o0 + o, row r, tap t) of the weights; an output past the last reads the last one's and is not stored
+    const float* w = Q.w + (int64_t)g * Q.Og * Q.K;
+    int64_t wo[OT];
+#pragma unroll
+    for (int o = 0; o < OT; o++) wo[o] = (int64_t)min(o0 + o, Q.Og - 1) * (TR ? tv : Q.K);
+    const int64_t wr = TR ? (int64_t)Q.Og * tv : tv;
+    float acc[OT][V];
+#pragma unroll
+    for (int o = 0; o < OT; o++)
+#pragma unroll
+        for (int v = 0; v < V; v++) acc[o][v] = 0.f;
+    if (TVT == 1) {
+        for (int r0 = 0; r0 < Q.R; r0 += 4) {
+            float part[OT][V];
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const int r = r0 + k;
+                if (k > 0 && r >= Q.R) break;
+                float x[V];
+                if (V == 4) {
+                    const f4u d = *reinterpret_cast<const f4u*>(src + r * P + p);
+#pragma unroll
+                    for (int v = 0; v < V; v++) x[v] = d[v];
+                } else {
+                    x[0] = src[r * P + p];
+                }
+#pragma unroll
+                for (int o = 0; o < OT; o++) {
+                    const float a = w[wo[o] + r * wr];
+#pragma unroll
+                    for (int v = 0; v < V; v++) part[o][v] = k == 0 ? a * x[v] : fmaf(a, x[v], part[o][v]);
+                }
+            }
+#pragma unroll
+            for (int o = 0; o < OT; o++)
+#pragma unroll
+                for (int v = 0; v < V; v++) acc[o][v] += part[o][v];
+        }
+    } else {
+        int h[V], c[V];
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            h[v] = quotient(p + v, Q.W, Q.mW);
+            c[v] = p + v - h[v] * Q.W;
+        }
+        constexpr int KW = TVT == 9 ? 3 : 7;
+        const int kh_n = TVT == 9 ? 3 : Q.KH, kw_n = TVT == 9 ? 3 : Q.KW;
+        for (int r = 0; r < Q.R; r++) {
+            float sum[OT][V];
+#pragma unroll TVT == 9 ? 3 : 1
+            for (int kh = 0; kh < kh_n; kh++) {
+                float x[KW][V], part[OT][V];
+#pragma unroll
+                for (int kw = 0; kw < KW; kw++) {
+                    if (kw >= kw_n) break;
+#pragma unroll
+                    for (int v = 0; v < V; v++) {
+                        const int hh = h[v] + kh - kh_n / 2, cc = c[v] + kw - kw_n / 2;
+                        const bool in = (unsigned)hh < (unsigned)Q.H && (unsigned)cc < (unsigned)Q.W;
+                        x[kw][v] = src[r * P + (in ? hh * Q.W + cc : p)];
+                        x[kw][v] = in ? x[kw][v] : 0.f;
+                    }
+                }
+#pragma unroll
+                for (int o = 0; o < OT; o++) {
+#pragma unroll
+                    for (int kw = 0; kw < KW; kw++) {
+                        if (kw >= kw_n) break;
+                        const int tap = kh * kw_n + kw;
+                        const float a = w[wo[o] + r * wr + (TR ? tv - 1 - tap : tap)];  // (transposed: the window read backwards)
+#pragma unroll
+                        for (int v = 0; v < V; v++) part[o][v] = kw == 0 ? a * x[kw][v] : fmaf(a, x[kw][v], part[o][v]);
+                    }
+#pragma unroll
+                    for (int v = 0; v < V; v++) sum[o][v] = kh == 0 ? part[o][v] : sum[o][v] + part[o][v];
+                }
+            }
+#pragma unroll
+            for (int o = 0; o < OT; o++)
+#pragma unroll
+                for (int v = 0; v < V; v++) acc[o][v] += sum[o][v];
+        }
+    }
+    float* dst = Q.dst + (ng * Q.Og + o0) * P + p;
+#pragma unroll
+    for (int o = 0; o < OT; o++) {
+        if (o0 + o >= Q.Og) break;
+        float* d = dst + o * P;
+        if (V == 4) {
+            f4u out;
+            if (Q.acc) out = *reinterpret_cast<const f4u*>(d);
+#pragma unroll
+            for (int v = 0; v < V; v++) out[v] = Q.acc ? out[v] + acc[o][v] : acc[o][v];
+            *reinterpret_cast<f4u*>(d) = out;
+        } else {
+            *d = Q.acc ? *d + acc[o][0] : acc[o][0];
+        }
+    }
+}
+
+// Weight gradient of such a contraction.  A workgroup owns OT outputs and one row of a group, with all taps of a 3 x 3
+// window or one window row of another, and a slice of the batch's pixels; a thread takes every 256th pixel.
+// Sums: chains of four pixels, these per thread, the threads as a tree.
+// The same tensors: 21, 45 and 158 us; k_wgrad takes 1070, 1285 and 1371 us.  Errors as k_wgrad's (1.0-1.2e-7).
+template <int OT, int TVT>
+__global__ __launch_bounds__(kThreads) void k_wgrad_narrow(Params Q) {
+    constexpr int NT = TVT == 1 ? 1 : (TVT == 9 ? 9 : 7), U = 4;
+    __shared__ float red[kThreads / 64][OT * NT];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    unsigned b = tile_of_block();
+    if (b >= (unsigned)Q.tiles) return;
+    const int o0 = (int)(b % (unsigned)Q.mtiles) * OT;
+    b /= (unsigned)Q.mtiles;
+    const int kt = (int)(b % (unsigned)Q.ktiles);
+    b /= (unsigned)Q.ktiles;
+    const int g = (int)(b % (unsigned)Q.G);
+    const int slice = (int)(b / (unsigned)Q.G);
+    const int r = TVT ? kt : kt / Q.KH, kh0 = TVT ? 0 : kt - r * Q.KH;
+    const int64_t P = Q.P, first = slice * Q.per_slice, last = min(Q.M, first + Q.per_slice);
+    // every 256th pixel: the image and the place in it advance by a fixed step and a carry
+    const int step_n = kThreads / Q.P, step_p = kThreads - step_n * Q.P;
+    const int64_t m_first = first + tid;
+    int64_t n = m_first / P;
+    int p = (int)(m_first - n * P);
+    const float* xs = Q.src + ((int64_t)g * Q.R + r) * P;
+    const float* ds = Q.dy + ((int64_t)g * Q.Og + o0) * P;
+    const int64_t xn = (int64_t)Q.G * Q.R * P, dn = (int64_t)Q.G * Q.Og * P;
+    float acc[OT][NT];
+#pragma unroll
+    for (int o = 0; o < OT; o++)
+#pragma unroll
+        for (int t = 0; t < NT; t++) acc[o][t] = 0.f;
+    for (int64_t m = m_first; m < last; m += U * kThreads) {
+        float x[U][NT], dy[U][OT];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const bool in = m + u * kThreads < last;
+            const float* xp = xs + (in ? n * xn : 0);  // (a pixel past the slice reads the first image and counts as zero)
+            const int q = in ? p : 0;
+#pragma unroll
+            for (int o = 0; o < OT; o++) {
+                dy[u][o] = ds[(in ? n * dn : 0) + min(o, Q.Og - 1 - o0) * P + q];
+                dy[u][o] = in ? dy[u][o] : 0.f;
+            }
+            if (TVT == 1) {
+                x[u][0] = xp[q];
+                x[u][0] = in ? x[u][0] : 0.f;
+            } else {
+                const int h = quotient(q, Q.W, Q.mW), c = q - h * Q.W;
+#pragma unroll
+                for (int t = 0; t < NT; t++) {
+                    x[u][t] = 0.f;
+                    if (TVT != 9 && t >= Q.KW) continue;
+                    const int hh = h + (TVT == 9 ? t / 3 - 1 : kh0 - Q.KH / 2), cc = c + (TVT == 9 ? t % 3 - 1 : t - Q.KW / 2);
+                    const bool inside = in && (unsigned)hh < (unsigned)Q.H && (unsigned)cc < (unsigned)Q.W;
+                    x[u][t] = xp[inside ? hh * Q.W + cc : q];
+                    x[u][t] = inside ? x[u][t] : 0.f;
+                }
+            }
+            n += step_n;
+            p += step_p;
+            if (p >= Q.P) {
+                p -= Q.P;
+                n++;
+            }
+        }
+#pragma unroll
+        for (int o = 0; o < OT; o++)
+#pragma unroll
+            for (int t = 0; t < NT; t++) {
+                float part = dy[0][o] * x[0][t];
+#pragma unroll
+                for (int u = 1; u < U; u++) part = fmaf(dy[u][o], x[u][t], part);
+                acc[o][t] += part;
+            }
+    }
+#pragma unroll
+    for (int o = 0; o < OT; o++)
+#pragma unroll
+        for (int t = 0; t < NT; t++) {
+            float v = acc[o][t];
+#pragma unroll
+            for (int d = 32; d >= 1; d /= 2) v += __shfl_xor(v, d);
+            if (lane == 0) red[wave][o * NT + t] = v;
+        }
+    __syncthreads();
+    const int taps = TVT ? TVT : Q.KW;
+    if (tid < OT * NT) {
+        const int o = tid / NT, t = tid - o * NT;
+        if (o0 + o < Q.Og && t < taps)
+            Q.partial[(int64_t)slice * Q.G * Q.Og * Q.K + ((int64_t)g * Q.Og + o0 + o) * Q.K + (int64_t)r * Q.TV + kh0 * Q.KW + t] =
+                (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+    }
+}
+
 // Positions a tile of `pixels` consecutive pixels of the batch covers at most, margin included: the image rows it
 // touches, KH - 1 rows for each change of image, and the window's own KH - 1.
 int window_positions(const Params& p, int pixels) {
@@ -482,6 +703,32 @@ bool window_supported(int KH, int KW, int H, int W) {
     return true;
 }
 
+// Where the vector unit is faster than padded matrix tiles (both measured at N=32, 28x28, about 64 channels, 1-16 rows and
+// outputs per group; us matrix / narrow).  Without a window up to eight rows, since each costs a load: R=8, Og=1 9.0 / 4.2,
+// Og=16 8.6 / 5.5; R=16 5.8 / 4.4 at one output, but transposed 6.3 / 6.6 at four.  3 x 3: R=1, Og=8 12.3 / 9.2, Og=16
+// 8.0 / 9.2; R=2, Og=4 20.0 / 13.8, Og=6 13.5 / 13.9; R=3 20.9 / 21.7.  Other windows (5 x 5): R=1, Og=4 37.8 / 27.1, Og=6
+// 25.4 / 27.4; R=2, Og=2 63.9 / 72.6.  A window on few pixels is a chain of loads on an empty chip: 8 images of 15x15 in four
+// groups, 5 x 5 6.4 / 7.3, 50 176 pixels and groups 5.4 / 5.0.
+constexpr int64_t kNarrowWindowPixels = 32768;
+
+static int narrow_forward(const Params& p) {
+    if (p.TV == 1) return p.R <= 8 ? p.Og <= 16 : p.R <= 16 && p.Og <= 2;
+    if (p.M * p.G < kNarrowWindowPixels) return 0;
+    if (p.KH == 3 && p.KW == 3) return p.R == 1 ? p.Og <= 8 : p.R == 2 && p.Og <= 4;
+    return p.R == 1 && p.Og <= 4;
+}
+
+// The same for the weight gradient, whose cost is that of its R * Og products per pixel and tap.  Without a window: R=8, Og=8
+// 28.9 / 14.4 (N=64, 56x56: 147 / 41), R=64, Og=1 21.1 / 14.9, 16 x 16 20.2 / 18.8.  3 x 3: 4 x 4 50.2 / 31.0, R=4, Og=6
+// 34.4 / 34.6, R=16, Og=1 29.4 / 14.8.  5 x 5: R=1, Og=8 32.3 / 28.0, R=2, Og=6 36.6 / 39.6.  Few pixels, 3 x 3: 12 544
+// 10.9 / 14.8, 50 176 14.8 / 5.2.
+static int narrow_wgrad(const Params& p) {
+    const int64_t products = (int64_t)p.R * p.Og;
+    if (p.TV == 1) return products <= 64;
+    if (p.M * p.G < kNarrowWindowPixels) return 0;
+    return products <= (p.KH == 3 && p.KW == 3 ? 16 : 8);
+}
+
 Params shape(int64_t N, int G, int R, int KH, int KW, int Og, int H, int W) {
     Params p;
     p.N = N;
@@ -514,6 +761,14 @@ Params data_gradient_of(const Params& f) {
 
 void prepare_forward(Params& p) {
     const bool win = p.TV > 1;
+    p.narrow = narrow_forward(p);
+    if (p.narrow) {
+        p.ot = p.Og > 2 ? 4 : p.Og;
+        p.vec = p.P % 4 == 0 ? 4 : 1;
+        p.mtiles = (p.Og + p.ot - 1) / p.ot;
+        p.tiles = (p.M * p.G + kThreads * p.vec - 1) / (kThreads * p.vec) * p.mtiles;
+        return;
+    }
     // Up to four wavefronts side by side over the outputs: a weight then reaches the workgroup once, a staged pixel
     // serves up to 64 outputs.  Half the pixels where the launch would otherwise have less than two workgroups per
     // compute unit.
@@ -539,8 +794,29 @@ void prepare_forward(Params& p) {
     p.tiles = tiles();
 }
 
+// Slices of whole steps, for about `workgroups` of them.
+static void split(Params& p, int workgroups, int step, int64_t max_partial_bytes) {
+    const int64_t tiles = (int64_t)p.ktiles * p.mtiles * p.G;
+    const int64_t steps = (p.M + step - 1) / step;
+    const int64_t bytes = (int64_t)p.G * p.Og * p.K * 4;
+    int64_t slices = std::max<int64_t>(1, workgroups / tiles);
+    slices = std::min(slices, steps);
+    slices = std::min(slices, std::max<int64_t>(1, max_partial_bytes / std::max<int64_t>(1, bytes)));
+    p.per_slice = (steps + slices - 1) / slices * step;
+    p.slices = (int)((p.M + p.per_slice - 1) / p.per_slice);
+    p.tiles = p.slices * tiles;
+}
+
 void prepare_wgrad(Params& p, int64_t max_partial_bytes) {
     const bool win = p.TV > 1;
+    p.narrow = narrow_wgrad(p);
+    if (p.narrow) {
+        p.ot = p.Og > 2 ? 4 : p.Og;
+        p.mtiles = (p.Og + p.ot - 1) / p.ot;
+        p.ktiles = p.R * (p.TV == 1 || (p.KH == 3 && p.KW == 3) ? 1 : p.KH);
+        split(p, 4096, kNarrowPix, max_partial_bytes);
+        return;
+    }
     p.S = win ? window_positions(p, kPix) : kPix;
     p.CS = win ? up(p.S, 2, 1) : up(p.S, 64, 4);
     // outputs: one or two 16-tiles per wavefront, one or two wavefronts across them
@@ -566,15 +842,7 @@ void prepare_wgrad(Params& p, int64_t max_partial_bytes) {
     p.nch = std::min(p.R, win ? (bn + p.TV - 2) / p.TV + 1 : bn);
     p.ktiles = (p.K + bn - 1) / bn;
     p.mtiles = (p.Og + bm - 1) / bm;
-    const int64_t tiles = (int64_t)p.ktiles * p.mtiles * p.G;
-    const int64_t steps = (p.M + kPix - 1) / kPix;
-    const int64_t bytes = (int64_t)p.G * p.Og * p.K * 4;
-    int64_t slices = std::max<int64_t>(1, 2 * 256 / tiles);  // (one round: two workgroups of the wide tiles fit a compute unit)
-    slices = std::min(slices, steps);
-    slices = std::min(slices, std::max<int64_t>(1, max_partial_bytes / std::max<int64_t>(1, bytes)));
-    p.per_slice = (steps + slices - 1) / slices * kPix;
-    p.slices = (int)((p.M + p.per_slice - 1) / p.per_slice);
-    p.tiles = p.slices * tiles;
+    split(p, 2 * 256, kPix, max_partial_bytes);  // (one round: two workgroups of the wide tiles fit a compute unit)
 }
 
 // A launch has fewer than 2^32 threads along x: one output per group and 128 pixels per workgroup reach that at 2^31
@@ -588,6 +856,30 @@ static dim3 grid_of(int64_t tiles) {
 
 void forward(const Params& p, hipStream_t s) {
     const dim3 grid = grid_of(p.tiles), block(kThreads);
+    if (p.narrow) {
+#define CANVAS_SFC_T(OT, V, TVT)                                                                                       \
+    do {                                                                                                               \
+        if (p.transposed) CANVAS_LAUNCH((k_fwd_narrow<OT, V, TVT, true>), grid, block, 0, s, p);                       \
+        else CANVAS_LAUNCH((k_fwd_narrow<OT, V, TVT, false>), grid, block, 0, s, p);                                   \
+    } while (0)
+#define CANVAS_SFC(OT, V)                                               \
+    do {                                                                \
+        if (p.TV == 1) CANVAS_SFC_T(OT, V, 1);                          \
+        else if (p.KH == 3 && p.KW == 3) CANVAS_SFC_T(OT, V, 9);        \
+        else CANVAS_SFC_T(OT, V, 0);                                    \
+    } while (0)
+        switch (p.ot * 10 + p.vec) {
+        case 11: CANVAS_SFC(1, 1); break;
+        case 14: CANVAS_SFC(1, 4); break;
+        case 21: CANVAS_SFC(2, 1); break;
+        case 24: CANVAS_SFC(2, 4); break;
+        case 41: CANVAS_SFC(4, 1); break;
+        default: CANVAS_SFC(4, 4); break;
+        }
+#undef CANVAS_SFC
+#undef CANVAS_SFC_T
+        return;
+    }
     const size_t lds = fwd_lds(p);
 #define CANVAS_SFC_T(WM, NT, TVT, WIN, NP, KC)                                                                          \
     do {                                                                                                               \
@@ -616,6 +908,21 @@ void forward(const Params& p, hipStream_t s) {
 
 void wgrad_partial(const Params& p, hipStream_t s) {
     const dim3 grid = grid_of(p.tiles), block(kThreads);
+    if (p.narrow) {
+#define CANVAS_SFC(OT)                                                                                       \
+    do {                                                                                                     \
+        if (p.TV == 1) CANVAS_LAUNCH((k_wgrad_narrow<OT, 1>), grid, block, 0, s, p);                         \
+        else if (p.KH == 3 && p.KW == 3) CANVAS_LAUNCH((k_wgrad_narrow<OT, 9>), grid, block, 0, s, p);       \
+        else CANVAS_LAUNCH((k_wgrad_narrow<OT, 0>), grid, block, 0, s, p);                                   \
+    } while (0)
+        switch (p.ot) {
+        case 1: CANVAS_SFC(1); break;
+        case 2: CANVAS_SFC(2); break;
+        default: CANVAS_SFC(4); break;
+        }
+#undef CANVAS_SFC
+        return;
+    }
     const size_t lds = wgrad_lds(p);
 #define CANVAS_SFC(MT, NT, WM)                                                           \
     do {                                                                                 \

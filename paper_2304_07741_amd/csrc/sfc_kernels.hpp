@@ -26,6 +26,8 @@ struct Params {
     // forward tile: 16*wm outputs x 16*nt*(4/wm) pixels; weight gradient: 16*mt*wm outputs x 16*nt*(4/wm) contraction indices
     int wm = 1, mt = 1, nt = 1, wide = 0;  // wide: an operand tile of more than 512 positions
     int ktiles = 1, mtiles = 1, nch = 0, slices = 1;
+    // narrow: few rows and outputs per group, one thread per pixel on the vector unit; ot outputs, vec pixels per thread
+    int narrow = 0, ot = 1, vec = 1;
     int64_t per_slice = 0;                             // pixels per slice
     int64_t tiles = 0;                                 // workgroups with work
 };

@@ -56,11 +56,41 @@ CASES = [
     ("3x3_128_pixels_o16_small_planes", "in_lds", WIN.format(kh=3, kw=3, g=8, o=128), (100, 40, 9, 11)),
     ("3x3_128_pixels_o20_planes_of_130", "in_lds", WIN.format(kh=3, kw=3, g=8, o=160), (70, 40, 10, 13)),
     ("5x5_128_pixels_o3", "in_lds", WIN.format(kh=5, kw=5, g=8, o=24), (9, 16, 31, 33)),
+    # few rows and outputs per group: one thread per pixel (four where the plane is a multiple of four pixels); groups that end
+    # inside a workgroup, planes below and above a workgroup's pixels, one to four outputs per thread and a remainder
+    ("narrow_1x1_1_1", "-", FC.format(g=7, o=7), (5, 7, 6, 9)),
+    ("narrow_1x1_1_1_one_pixel", "-", FC.format(g=300, o=300), (3, 300, 1, 1)),
+    ("narrow_1x1_2_5", "-", FC.format(g=9, o=45), (3, 18, 7, 7)),
+    ("narrow_1x1_8_16", "-", FC.format(g=3, o=48), (2, 24, 20, 60)),
+    ("narrow_1x1_16_2", "-", FC.format(g=2, o=4), (3, 32, 33, 31)),
+    ("narrow_1x1_17_1_beside_tiles", "-", FC.format(g=2, o=2), (3, 34, 9, 8)),
+    ("narrow_3x3_1_1", "in_lds", WIN.format(kh=3, kw=3, g=70, o=70), (10, 70, 7, 7)),
+    ("narrow_3x3_1_8", "in_lds", WIN.format(kh=3, kw=3, g=9, o=72), (4, 9, 31, 33)),
+    ("narrow_3x3_2_3", "in_lds", WIN.format(kh=3, kw=3, g=21, o=63), (4, 42, 20, 22)),
+    ("narrow_3x3_one_column", "in_lds", WIN.format(kh=3, kw=3, g=64, o=64), (70, 64, 9, 1)),
+    ("narrow_5x5_1_3", "in_lds", WIN.format(kh=5, kw=5, g=33, o=99), (2, 33, 24, 22)),
+    ("narrow_7x7_1_1", "in_lds", WIN.format(kh=7, kw=7, g=37, o=37), (3, 37, 17, 19)),
+    ("narrow_1x3_1_1", "in_lds", WIN.format(kh=1, kw=3, g=64, o=64), (5, 64, 11, 10)),
+    ("narrow_3x1_1_4", "in_lds", WIN.format(kh=3, kw=1, g=32, o=128), (5, 32, 15, 16)),
+    ("narrow_9x1_stored", "stored", WIN.format(kh=9, kw=1, g=12, o=12), (3, 12, 18, 9)),
+    ("narrow_fan_out", "in_lds", FAN.format(g=8, o=8), (70, 8, 21, 24)),
 ]
+# cases whose launches (forward, weight gradient, data gradient) are expected on the vector unit; one letter each
+NARROW = {"one_element": "fwd", "pooled_size": "fwd", "1x1_groups": "w", "5x5_128_pixels_o3": "w",
+          "narrow_1x1_1_1": "fwd", "narrow_1x1_1_1_one_pixel": "fwd", "narrow_1x1_2_5": "fwd",
+          "narrow_1x1_8_16": "f", "narrow_1x1_16_2": "fwd", "narrow_1x1_17_1_beside_tiles": "w", "narrow_3x3_1_1": "fwd",
+          "narrow_3x3_1_8": "fw", "narrow_3x3_2_3": "fw", "narrow_3x3_one_column": "fwd", "narrow_5x5_1_3": "fw",
+          "narrow_7x7_1_1": "fwd", "narrow_1x3_1_1": "fwd", "narrow_3x1_1_4": "fw", "narrow_9x1_stored": "fwd", "narrow_fan_out": None}
 
 
-def check_path(path, blob, shape, fwd, bwd):
+def check_path(name, path, blob, shape, fwd, bwd):
     """The launch lists (names) fit the path that a case is written for."""
+    if NARROW.get(name, "") is not None:
+        narrow = "".join(l for l, names, what in [("f", fwd, "sfc_fwd"), ("w", bwd, "sfc_wgrad"), ("d", bwd, "sfc_dgrad")]
+                         if any(n.startswith(what) and n.endswith("_narrow") for n in names))
+        assert narrow == NARROW.get(name, ""), narrow
+    slices_wanted = shape[0] * shape[2] * shape[3] > (1024 if any("wgrad" in n and "narrow" in n for n in bwd) else 64)
+    fwd, bwd = ([n.replace("_narrow", "") for n in names] for names in (fwd, bwd))
     fans = blob.count("= fc ")
     sfc = lambda names, what: [n for n in names if n.startswith("sfc_" + what)]
     if path == "in_lds":
@@ -72,8 +102,9 @@ def check_path(path, blob, shape, fwd, bwd):
     else:
         assert sfc(fwd, "") == ["sfc_fwd"] * fans and sorted(sfc(bwd, "")) == ["sfc_dgrad"] * fans + ["sfc_wgrad"] * fans, (fwd, bwd)
         assert any("node_unfold" in n or n.startswith("chain") for n in fwd) == (path == "stored"), fwd
-    # the weight gradient of more than one step of 64 pixels is split into slices, as long as they fit the partials' budget
-    assert ("wgrad_reduce" in bwd) == (shape[0] * shape[2] * shape[3] > 64), bwd
+    # the weight gradient of more than one step (64 pixels, on the vector unit 1024) is split into slices, as long as they fit
+    # the partials' budget
+    assert ("wgrad_reduce" in bwd) == slices_wanted, bwd
 
 
 @pytest.mark.parametrize("name,path,blob,shape", CASES, ids=[c[0] for c in CASES])
@@ -88,7 +119,7 @@ def test_fp32_fc(name, path, blob, shape):
     f = lambda *s: rng.standard_normal(s).astype(np.float32)
     case = {"blob": blob, "shape": shape, "dtype": "f32", "x": f(*shape), "weights": [f(*s) / np.sqrt(s[2]) for s in wsh], "seed": 1}
     res, r, dy = harness.run_case(case)
-    check_path(path, blob, shape, *[[d["name"] for d in r.launches(b)] for b in (0, 1)])
+    check_path(name, path, blob, shape, *[[d["name"] for d in r.launches(b)] for b in (0, 1)])
     ref = canvas_oracle.run(blob, case["x"], case["weights"], dy)
     # A sum of K fp32 terms in any order is off by at most about K * 2^-24 of the sum of their magnitudes, in practice by
     # sqrt(K) * 2^-24: below 1e-5 of the largest element up to K = 2.8e4 (the longest here, 7e4 pixels, in slices).
