@@ -455,8 +455,8 @@ __global__ __launch_bounds__(kThreads) void k_wgrad(Params Q) {
 // itself; a window's taps are loads of their own, mostly from the first-level cache.  Bound by memory without a window, by
 // the loads of the taps with one.
 // Sums: chains of a window row's taps (without a window: of four channels), these parts added per channel, these to the result.
-// N=64, 56x56, 64 channels, one per group: 23 us without a window (4.4 TB/s), 107 us with 3 x 3, 278 us with 5 x 5; k_fwd
-// takes 328, 415 and 970 us there.  Errors against fp64 are those of k_fwd or smaller (1 x 1 2.5-5.7e-8, 3 x 3 5.0-6.4e-8
+// N=64, 56x56, 64 channels, one per group: 17 us without a window (6.2 TB/s, x partly in the last-level cache), 102 us with
+// 3 x 3, 275 us with 5 x 5; k_fwd takes 328, 415 and 970 us there.  Errors against fp64 are those of k_fwd or smaller (1 x 1 2.5-5.7e-8, 3 x 3 5.0-6.4e-8
 // against 5.5-6.9e-8).
 template <int OT, int V, int TVT, bool TR>
 __global__ __launch_bounds__(kThreads) void k_fwd_narrow(Params Q) {
@@ -561,14 +561,18 @@ __global__ __launch_bounds__(kThreads) void k_fwd_narrow(Params Q) {
     for (int o = 0; o < OT; o++) {
         if (o0 + o >= Q.Og) break;
         float* d = dst + o * P;
+        if (Q.acc) {
+            asm volatile("");  // (keeps the compiler from reading dst also where nothing is added: +51 MB at the size above)
+#pragma unroll
+            for (int v = 0; v < V; v++) acc[o][v] += d[v];
+        }
         if (V == 4) {
             f4u out;
-            if (Q.acc) out = *reinterpret_cast<const f4u*>(d);
 #pragma unroll
-            for (int v = 0; v < V; v++) out[v] = Q.acc ? out[v] + acc[o][v] : acc[o][v];
+            for (int v = 0; v < V; v++) out[v] = acc[o][v];
             *reinterpret_cast<f4u*>(d) = out;
         } else {
-            *d = Q.acc ? *d + acc[o][0] : acc[o][0];
+            *d = acc[o][0];
         }
     }
 }
