@@ -476,9 +476,8 @@ class Emitter {
             const bool lhs_scalar = tl == 1 && I.lanes > 1;
             bool mine;
             if (kept(I.opnd[0], 0) < 0) {  // (an RHS in a register is taken from there, also when computing the LHS put it there)
-                int rr = kept(I.opnd[1], 0);
                 eval(I.opnd[0]);
-                rr = kept(I.opnd[1], 0);
+                const int rr = kept(I.opnd[1], 0);
                 if (rr >= 0) {
                     emit(simple(OP_BIN, I.lanes, rr, nd.kind | (lhs_scalar ? kBinAccScalar : 0)));
                     break;

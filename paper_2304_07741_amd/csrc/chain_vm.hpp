@@ -1123,8 +1123,8 @@ CHAIN_HD void vm_exec_lanes(const Program& pg, const Geo& g, const Instr& I, con
 }
 
 // An instruction over all TM lanes of the instance (the common case of a program with taps) runs the copy of the
-// dispatch whose tap loops are straight-line code.  (Not the one-pixel instances: the second copy cost them 16-18
-// registers and with those a wavefront per SIMD.)
+// dispatch whose tap loops are straight-line code, in the one-pixel instances as well: with one channel per trip the second
+// copy fits them (9 lanes: 99 registers, four wavefronts per SIMD; 25 lanes: 201, two, as geometry_for() counts).
 template <int TM, int V, int U>
 CHAIN_HD void vm_exec(const Program& pg, const Geo& g, const Instr& I, const Env& ev, const Thread& th, State<TM, V, U>& st, float* Pm, float* Rm) {
     constexpr int TC = TM > 1 ? TM : 0;
