@@ -42,9 +42,10 @@ __device__ __forceinline__ int64_t window_source(const Params& Q, int64_t n0, in
 }
 
 // Forward and data gradient.  A workgroup owns 16*WM outputs of one group and TP = 16*NT*(4/WM) consecutive pixels of the
-// batch, a wavefront 16 outputs and 16*NT pixels; the contraction runs over chunks of KC channels with all their taps.  Bound by the fp32
-// matrix rate (v_mfma_f32_16x16x4_f32: 32 cycles for 2048 flops, 157 TFLOP/s on the chip) and, with the small tiles that
-// fill the chip at these sizes, by the vector instructions beside it.  The operand tile in LDS holds image rows with a
+// batch, a wavefront 16 outputs and 16*NT pixels; the contraction runs over chunks of KC channels with all their taps.  With the small tiles
+// that fill the chip at these sizes it is bound by the latency of its steps: the matrix pipes (v_mfma_f32_16x16x4_f32: 32
+// cycles for 2048 flops, 157 TFLOP/s on the chip) are busy a third of the time, three wavefronts per SIMD wait for data in
+// a third of their cycles and for their turn to issue in two fifths (SQ counters at the size below).  The operand tile in LDS holds image rows with a
 // zero margin, so a tap is a constant LDS offset and the Unfold costs no memory traffic and no mask; the next chunk's
 // is loaded into registers while this one is multiplied.  The weights go from the caches straight to registers, where
 // a lane finds its channel's taps side by side (36 bytes for 3 x 3, 16 for four channels without a window): staged
@@ -275,7 +276,8 @@ constexpr int kDyStride = 68;   // 4 mod 64: the 16 outputs x 4 pixels of an ope
 // Weight gradient: contraction over pixels.  A workgroup owns 16*MT*WM outputs x 16*NT*(4/WM) contraction indices of one
 // group and one slice of the batch's pixels; 64 pixels of dy and of the channels behind those indices (image rows with a
 // zero margin, as above) go through LDS.  A lane's column is one (channel, tap): its LDS base; the pixel's place in the
-// tile comes from a table.  No padding beyond the tile's edges whatever R, Og and the window are.  Bound like k_fwd.
+// tile comes from a table.  No padding beyond the tile's edges whatever R, Og and the window are.  Bound like k_fwd: the
+// matrix pipes are busy a quarter of the time, two wavefronts per SIMD.
 // Sums: chains of eight pixels in the matrix unit, added as a tree over the 64 pixels of a step, the steps in a row.
 // N=32, C=64, 28x28, 3x3: 46 us (40 TFLOP/s) and 4 us for the sum of the slices; one workgroup per weight took 1259 us.
 template <int MT, int NT, int WM, bool WIN>
@@ -456,8 +458,8 @@ __global__ __launch_bounds__(kThreads) void k_wgrad(Params Q) {
 // the loads of the taps with one.
 // Sums: chains of a window row's taps (without a window: of four channels), these parts added per channel, these to the result.
 // N=64, 56x56, 64 channels, one per group: 17 us without a window (6.2 TB/s, x partly in the last-level cache), 102 us with
-// 3 x 3, 275 us with 5 x 5; k_fwd takes 328, 415 and 970 us there.  Errors against fp64 are those of k_fwd or smaller (1 x 1 2.5-5.7e-8, 3 x 3 5.0-6.4e-8
-// against 5.5-6.9e-8).
+// 3 x 3, 275 us with 5 x 5; k_fwd takes 328, 415 and 970 us there.  Errors against fp64 are those of k_fwd or smaller
+// (1 x 1 2.5-5.7e-8, 3 x 3 5.0-6.4e-8 against 5.5-6.9e-8).
 template <int OT, int V, int TVT, bool TR>
 __global__ __launch_bounds__(kThreads) void k_fwd_narrow(Params Q) {
     unsigned b = tile_of_block();
