@@ -30,7 +30,7 @@ __device__ __forceinline__ const Program& stage_program(unsigned char* sprog) {
     return *(const Program*)sprog;
 }
 
-template <int TM, int V, int U>
+template <int TM, int V, int U, bool F32W>
 __global__ __launch_bounds__(max_threads_for(TM), min_waves_for(TM, V)) void k_chain(const Program) {
     __shared__ __align__(16) unsigned char sprog[sizeof(Program)];
     const Program& pg = stage_program(sprog);
@@ -55,6 +55,7 @@ __global__ __launch_bounds__(max_threads_for(TM), min_waves_for(TM, V)) void k_c
     Env ev;
     ev.np = vm_u(pg.n_persist);
     ev.fast = vm_u(pg.fast_math) != 0;
+    ev.f32_windows = F32W;
     ev.pstride = threads;
     ev.rstride = rstride;
     // The workgroup stays and walks over its share of the work items (image, tile, channel range): the program is staged
@@ -160,14 +161,26 @@ inline unsigned grid_for(const Program& pg) {
     return (unsigned)((items + per - 1) / per);
 }
 
-template <int TM, int V>
+// Whether a program loads a window of an fp32 tensor.  The instance with 9 lanes x 2 pixels exists with and without the code
+// for that: at its 128 registers the code costs programs that never run it 3-4 % (3x3 box of bf16 tensors, N=128, C=64,
+// 56x56: 172-175 us without, 179.3 with), and gives those that do 25-30 % (3x3 avg of fp32 tensors, 32x64 planes of 56x56:
+// 75 us without, 51 with).
+bool f32_windows(const Program& pg) {
+    for (int i = 0; i < pg.n_instr; i++) {
+        const Instr& I = pg.ins[i];
+        if ((I.op == OP_LD || I.op == OP_BINLD) && (I.kind & kWin) && !pg.ext[I.a].bf16) return true;
+    }
+    return false;
+}
+
+template <int TM, int V, bool F32W = true>
 void launch(const Program& pg, hipStream_t stream) {
     constexpr int U = unroll_for(TM, V);
     // (more than 64 KB of dynamic LDS must be asked for, once per kernel)
-    static const hipError_t lds_ok = hipFuncSetAttribute((const void*)k_chain<TM, V, U>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLdsBytes);
+    static const hipError_t lds_ok = hipFuncSetAttribute((const void*)k_chain<TM, V, U, F32W>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLdsBytes);
     (void)lds_ok;
     const dim3 grid(grid_for(pg));
-    CANVAS_LAUNCH((k_chain<TM, V, U>), grid, dim3((unsigned)pg.threads), lds_bytes(pg), stream, pg);
+    CANVAS_LAUNCH((k_chain<TM, V, U, F32W>), grid, dim3((unsigned)pg.threads), lds_bytes(pg), stream, pg);
 }
 
 }  // namespace
@@ -182,7 +195,8 @@ void run(const Program& pg, hipStream_t stream) {
         else launch<1, 1>(pg, stream);
     } else if (pg.tm <= 9) {
         if (v == 4) launch<9, 4>(pg, stream);
-        else if (v == 2) launch<9, 2>(pg, stream);
+        else if (v == 2 && f32_windows(pg)) launch<9, 2>(pg, stream);
+        else if (v == 2) launch<9, 2, false>(pg, stream);
         else launch<9, 1>(pg, stream);
     } else {
         launch<25, 1>(pg, stream);

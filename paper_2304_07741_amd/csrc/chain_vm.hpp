@@ -657,6 +657,7 @@ struct Env {
     int h = 0;        // channels of the trip that exist (0 .. U)
     bool pro = false; // the prologue of a pass (once per workgroup item, not per channel)
     bool fast = false; // Program::fast_math
+    bool f32_windows = true;  // window loads of fp32 tensors by vm_ld_window_f32, not by the general loads
     int np = 0;       // persistent floats per pixel and channel
     int pstride = 0;  // floats between consecutive persistent floats of a thread (the workgroup's size)
     int rstride = 0;  // floats between consecutive register pieces of a thread
@@ -685,7 +686,7 @@ CHAIN_HD void vm_ld(const Program& pg, const Geo& g, const Instr& I, const Env& 
                     else vm_ld_window_bf16<TM, V, 0, 0>(e, g, th, chan, dh, dw, KH, KW, T, out);
                     continue;
                 }
-                if (V == 4 || V == 2 || V == 1) {
+                if ((V == 4 || V == 2 || V == 1) && ev.f32_windows) {
                     float* out = dst + u * TV;
                     if (TM >= 9 && KH == 3 && KW == 3 && T == 9) vm_ld_window_f32<TM, V, (TM >= 9 ? 3 : 0), (TM >= 9 ? 3 : 0)>(e, g, th, chan, dh, dw, 3, 3, 9, out);
                     else if (TM >= 25 && KH == 5 && KW == 5 && T == 25) vm_ld_window_f32<TM, V, (TM >= 25 ? 5 : 0), (TM >= 25 ? 5 : 0)>(e, g, th, chan, dh, dw, 5, 5, 25, out);
