@@ -35,20 +35,20 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # plain copy of 25 088 KiB reads FETCH_SIZE 12 557 -> units of 1.998 KiB, and WRITE_SIZE 25 088 -> KiB; the dispatches of
 # a run are attributed to the launches of a step by position; commands and tables in profiles/).  The figures are valid
 # only for the kernel sources they were taken on (one hash over the library's source folder), otherwise `traffic` is null.
-TRAFFIC_SHA256 = "ec1265c4444f106f035e35af331360bea8b740119e3314958fd250b8083d8362"
+TRAFFIC_SHA256 = "d5e2bb9adbce51796bd4cfe9af52c5244da8a5e8f29b3d18642b646c9ed2f077"
 TRAFFIC_KIB = {  # workload -> launch (phase:name) -> (KiB fetched, KiB written) per launch
-    'shift_residual': {'fwd:sgfc_fwd': (28777.3, 25090.5), 'bwd:sgfc_bwd': (52695.3, 25888.5), 'bwd:sgfc_dw_reduce': (3226.8, 4.0)},
-    'involution': {'fwd:weight_prep': (326.0, 40.0), 'fwd:dyn_fc1_softmax': (6732.5, 882.0), 'fwd:dyn_apply': (7266.5, 6272.0), 'fwd:dyn_fc2': (6991.1, 6272.0), 'bwd:dyn_fc2_wgrad': (15872.3, 6656.0), 'bwd:dyn_fc2_dgrad': (6991.0, 6272.0), 'bwd:dyn_apply_dx_da': (20214.1, 7154.2), 'bwd:dyn_softmax_bwd': (2075.0, 1323.0), 'bwd:dyn_fc1_wgrad': (10052.0, 900.0), 'bwd:dyn_fc1_dgrad': (7235.3, 6272.0), 'bwd:wgrad_reduce': (7617.4, 68.5)},
-    'sampled_c64_h56': {'fwd:weight_prep': (169.0, 44.0), 'fwd:ufc_fc1_unfold': (50565.3, 50176.0), 'fwd:ufc_mid_fwd': (101107.9, 50185.0), 'fwd:ufc_fc2': (50608.4, 50176.0), 'bwd:ufc_fc2_wgrad': (100522.6, 6272.0), 'bwd:ufc_fc2_dgrad': (50608.4, 50176.0), 'bwd:ufc_mid_bwd': (151267.3, 100579.5), 'bwd:ufc_fc1_wgrad_unfold': (105583.8, 4608.0), 'bwd:ufc_fc1_dgrad_unfold': (100795.2, 50176.0), 'bwd:wgrad_reduce': (10938.1, 104.0)},
-    'sampled_c128_h28': {'fwd:weight_prep': (531.7, 104.0), 'fwd:ufc_fc1_unfold': (25632.5, 25098.1), 'fwd:ufc_mid_fwd': (50598.4, 25093.2), 'fwd:ufc_fc2': (26280.8, 25095.7), 'bwd:ufc_fc2_wgrad': (65520.4, 6656.0), 'bwd:ufc_fc2_dgrad': (26280.8, 25088.0), 'bwd:ufc_mid_bwd': (75694.0, 50297.3), 'bwd:ufc_fc1_wgrad_unfold': (60953.9, 4608.0), 'bwd:ufc_fc1_dgrad_unfold': (50700.8, 25135.4), 'bwd:wgrad_reduce': (11321.7, 416.0)},
-    'sampled_c256_h14': {'fwd:weight_prep': (2214.2, 416.0), 'fwd:ufc_fc1_unfold': (13282.5, 12564.1), 'fwd:ufc_mid_fwd': (25905.9, 12866.0), 'fwd:ufc_fc2': (14592.4, 12592.0), 'bwd:ufc_fc2_wgrad': (25351.3, 8192.0), 'bwd:ufc_fc2_dgrad': (14592.3, 12592.0), 'bwd:ufc_mid_bwd': (38867.5, 27813.4), 'bwd:ufc_fc1_wgrad_unfold': (61716.1, 6624.0), 'bwd:ufc_fc1_dgrad_unfold': (26117.5, 12617.3), 'bwd:wgrad_reduce': (14870.2, 1104.0)},
-    'sampled_c512_h7': {'fwd:weight_prep': (6709.9, 1664.0), 'fwd:ufc_fc1_unfold': (7412.9, 6273.1), 'fwd:ufc_mid_fwd': (13052.8, 6322.3), 'fwd:ufc_fc2': (10617.3, 6272.0), 'bwd:ufc_fc2_wgrad': (12805.1, 8192.0), 'bwd:ufc_fc2_dgrad': (10617.2, 6272.0), 'bwd:ufc_mid_bwd': (19565.4, 16655.6), 'bwd:ufc_fc1_wgrad_unfold': (19712.4, 4608.0), 'bwd:ufc_fc1_dgrad_unfold': (13693.1, 6273.3), 'bwd:wgrad_reduce': (12856.2, 6656.0)},
-    'chain_relu': {'fwd:chain_fwd': (50496.5, 56814.8), 'bwd:chain_bwd': (100768.6, 56001.4)},
-    'chain_gate': {'fwd:chain_fwd': (50655.6, 57640.4), 'bwd:chain_bwd': (101088.3, 58140.6)},
-    'chain_shift_residual': {'fwd:chain_fwd': (50652.9, 59747.0), 'bwd:chain_bwd': (100836.5, 57022.4)},
-    'chain_box3': {'fwd:chain_fwd': (55439.4, 51561.2), 'bwd:chain_bwd': (55443.5, 51553.1)},
-    'chain_softmax_c': {'fwd:chain_fwd': (100596.1, 55538.5), 'bwd:chain_bwd': (251278.3, 53593.4)},
-    'fuzz': {'all:chain': (64907.5, 45035.6)},
+    'shift_residual': {'fwd:sgfc_fwd': (28776.8, 25089.6), 'bwd:sgfc_bwd': (52695.3, 25888.3), 'bwd:sgfc_dw_reduce': (3226.8, 4.0)},
+    'involution': {'fwd:weight_prep': (326.0, 40.0), 'fwd:dyn_fc1_softmax': (6732.5, 882.0), 'fwd:dyn_apply': (7266.5, 6272.0), 'fwd:dyn_fc2': (6991.1, 6272.0), 'bwd:dyn_fc2_wgrad': (15872.3, 6656.0), 'bwd:dyn_fc2_dgrad': (6991.0, 6272.0), 'bwd:dyn_apply_dx_da': (20214.1, 7154.1), 'bwd:dyn_softmax_bwd': (2075.0, 1323.0), 'bwd:dyn_fc1_wgrad': (10052.0, 900.0), 'bwd:dyn_fc1_dgrad': (7235.3, 6272.0), 'bwd:wgrad_reduce': (7617.4, 68.5)},
+    'sampled_c64_h56': {'fwd:weight_prep': (169.0, 44.0), 'fwd:ufc_fc1_unfold': (50565.3, 50176.0), 'fwd:ufc_mid_fwd': (101107.9, 50187.0), 'fwd:ufc_fc2': (50608.4, 50176.0), 'bwd:ufc_fc2_wgrad': (100522.6, 6272.0), 'bwd:ufc_fc2_dgrad': (50608.4, 50176.0), 'bwd:ufc_mid_bwd': (151267.5, 100584.2), 'bwd:ufc_fc1_wgrad_unfold': (105583.9, 4608.0), 'bwd:ufc_fc1_dgrad_unfold': (100704.1, 50176.0), 'bwd:wgrad_reduce': (10938.1, 104.0)},
+    'sampled_c128_h28': {'fwd:weight_prep': (531.6, 104.0), 'fwd:ufc_fc1_unfold': (25632.7, 25100.0), 'fwd:ufc_mid_fwd': (50598.4, 25094.9), 'fwd:ufc_fc2': (26280.8, 25093.4), 'bwd:ufc_fc2_wgrad': (65534.7, 6656.0), 'bwd:ufc_fc2_dgrad': (26280.8, 25088.0), 'bwd:ufc_mid_bwd': (75694.1, 50297.3), 'bwd:ufc_fc1_wgrad_unfold': (60951.4, 4608.0), 'bwd:ufc_fc1_dgrad_unfold': (50701.3, 25138.8), 'bwd:wgrad_reduce': (11321.7, 416.0)},
+    'sampled_c256_h14': {'fwd:weight_prep': (2214.2, 416.0), 'fwd:ufc_fc1_unfold': (13282.5, 12565.2), 'fwd:ufc_mid_fwd': (25905.9, 12870.0), 'fwd:ufc_fc2': (14592.4, 12592.0), 'bwd:ufc_fc2_wgrad': (25351.3, 8192.0), 'bwd:ufc_fc2_dgrad': (14592.3, 12592.0), 'bwd:ufc_mid_bwd': (38864.4, 27812.1), 'bwd:ufc_fc1_wgrad_unfold': (61715.0, 6624.0), 'bwd:ufc_fc1_dgrad_unfold': (26115.6, 12605.5), 'bwd:wgrad_reduce': (14870.2, 1104.0)},
+    'sampled_c512_h7': {'fwd:weight_prep': (6709.8, 1664.0), 'fwd:ufc_fc1_unfold': (7412.9, 6275.2), 'fwd:ufc_mid_fwd': (13052.8, 6322.6), 'fwd:ufc_fc2': (10617.3, 6272.0), 'bwd:ufc_fc2_wgrad': (12805.0, 8192.0), 'bwd:ufc_fc2_dgrad': (10617.2, 6272.0), 'bwd:ufc_mid_bwd': (19566.8, 16658.9), 'bwd:ufc_fc1_wgrad_unfold': (19712.4, 4608.0), 'bwd:ufc_fc1_dgrad_unfold': (13692.8, 6273.5), 'bwd:wgrad_reduce': (12856.2, 6656.0)},
+    'chain_relu': {'fwd:chain_fwd': (50453.2, 57238.8), 'bwd:chain_bwd': (100732.2, 56265.6)},
+    'chain_gate': {'fwd:chain_fwd': (50613.3, 57512.5), 'bwd:chain_bwd': (101067.9, 57423.0)},
+    'chain_shift_residual': {'fwd:chain_fwd': (50613.0, 59975.3), 'bwd:chain_bwd': (100811.4, 56804.8)},
+    'chain_box3': {'fwd:chain_fwd': (55417.6, 51562.9), 'bwd:chain_bwd': (55418.5, 51554.1)},
+    'chain_softmax_c': {'fwd:chain_fwd': (100540.3, 54772.2), 'bwd:chain_bwd': (251247.9, 53669.1)},
+    'fuzz': {'all:chain': (64846.6, 45039.1)},
 }
 
 
