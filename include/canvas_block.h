@@ -11,9 +11,10 @@
  *   C_in  = m * C_out (reduce)  instance j reads channels [j * C, (j + 1) * C) of x; y is the sum of the instances'
  *                               outputs.  dx of instance j is channels [j * C, (j + 1) * C) of dx.
  *
- * The instances run one after the other through the plan of canvas_dag.h compiled for [N, C, H, W]; channel slices
- * are regrouped into dense tensors and back by one launch of the library's own kernels per direction, the instances'
- * results are added in fp32 in instance order and rounded to the element type once.  (The normalisation that the paper's code generator inserts, Section 7, is a layer
+ * The instances run through the plan of canvas_dag.h compiled for [N, C, H, W], one after the other or, where the plan's
+ * kernels can, all in one launch; channel slices are read in place or regrouped into dense tensors and back by one launch of
+ * the library's own kernels per direction, the instances' results are added in fp32 in instance order and rounded to the
+ * element type once.  (The normalisation that the paper's code generator inserts, Section 7, is a layer
  * of the surrounding network and not part of a block.)
  *
  * Pointers: device pointers unless stated, owned by the caller, 16-byte aligned, contiguous NCHW.  All functions

@@ -307,6 +307,49 @@ int plan_backward(canvas_dag* dag, const void* x, const void* const* weights, co
     return finish_launches();
 }
 
+int plan_max_instances(const canvas_dag* dag) { return dag ? dag->low->max_instances : 0; }
+
+int plan_block_forward(canvas_dag* dag, int m, bool expand, const void* x, const void* const* weights, void* y, void* workspace, size_t ws_stride,
+                       void* stream) {
+    for (int j = 0; j < m; j++) {
+        const int rc = check_common(dag, x, weights ? weights + j : nullptr, workspace, ws_stride);
+        if (rc) return rc;
+    }
+    BlockArgs b;
+    b.m = m;
+    b.expand = expand;
+    b.ws_stride = ws_stride;
+    b.args.x = x;
+    b.args.w = weights;
+    b.args.y = y;
+    b.args.ws = (char*)workspace;
+    b.args.stream = (hipStream_t)stream;
+    dag->low->block_fwd(b);
+    return finish_launches();
+}
+
+int plan_block_backward(canvas_dag* dag, int m, bool expand, const void* x, const void* const* weights, const void* dy, void* dx,
+                        void* const* dweights, void* workspace, size_t ws_stride, void* stream) {
+    for (int j = 0; j < m; j++) {
+        const int rc = check_common(dag, x, weights ? weights + j : nullptr, workspace, ws_stride);
+        if (rc) return rc;
+        if (!dweights[j] || !aligned16(dweights[j])) return set_err(CANVAS_BAD_ARG, "a dweights pointer is null or misaligned");
+    }
+    BlockArgs b;
+    b.m = m;
+    b.expand = expand;
+    b.ws_stride = ws_stride;
+    b.args.x = x;
+    b.args.w = weights;
+    b.args.dy = dy;
+    b.args.dx = dx;
+    b.args.dw = dweights;
+    b.args.ws = (char*)workspace;
+    b.args.stream = (hipStream_t)stream;
+    dag->low->block_bwd(b);
+    return finish_launches();
+}
+
 }  // namespace canvas
 
 extern "C" {

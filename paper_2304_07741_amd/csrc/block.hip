@@ -2,9 +2,10 @@
 // m = max(C_in, C_out) / min(C_in, C_out) instances of the template's plan at [N, C, H, W], C = min(C_in, C_out).
 // Expand (C_out = m C): every instance reads x, instance j writes channel slice j of y, dx is the sum of the instances'
 // dx.  Reduce (C_in = m C): instance j reads channel slice j of x, y is the sum, instance j writes slice j of dx.
-// A channel slice of an NCHW batch is strided over the images.  Plans whose kernels address their input and output through
-// an image stride (the fused shift / grouped FC / unary / residual family) read and write the slices in place; the other
-// plans take dense tensors: ONE launch
+// A channel slice of an NCHW batch is strided over the images.  Plans whose kernels walk over the instances themselves (the
+// fused shift / grouped FC / unary / residual family with groups of 16 channels, up to eight instances) take the block's own
+// tensors: one launch for all instances, their sum included.  Those whose kernels address their input and output through an
+// image stride (the rest of that family) read and write the slices in place; the other plans take dense tensors: ONE launch
 // regroups [N, m, C P] into m dense tensors [N, C P] or back (16-byte accesses), ONE launch adds the m dense results of
 // the instances (in fp32 registers, in instance order, rounded once).
 #include <hip/hip_runtime.h>
@@ -16,6 +17,7 @@
 
 #include "../../include/canvas_block.h"
 #include "launch.hpp"
+#include "lowering.hpp"
 #include "plan_calls.hpp"
 #include "tile_util.hpp"
 
@@ -30,6 +32,8 @@ struct canvas_block {
     int m = 1;
     bool expand = true, bf16 = false;
     bool direct = false;  // the plan's kernels take channel slices of the wide tensors as they are (image strides): no regrouping
+    bool joint = false;   // the plan's kernels walk over the instances themselves: one launch for all of them, and their sum inside it
+    uint64_t weight_bytes = 0;  // of one instance's weight (joint)
     uint64_t plan_ws = 0, dense = 0, off_a = 0, off_b = 0;  // workspace: m plan workspaces | m dense inputs | m dense results
 };
 
@@ -40,7 +44,6 @@ namespace {
 using canvas::tile::u32x4;
 
 int set_err(int code, const std::string& msg) { return canvas::set_last_error(code, msg); }
-uint64_t align_up(uint64_t v) { return (v + 255) / 256 * 256; }
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // sliced [N][m][unit] <-> dense [m][N][unit] (instance j's dense tensor starts at j * dense_stride bytes); a unit is one
@@ -132,6 +135,17 @@ int check(const canvas_block* b, const void* x, const void* const* weights, cons
     return CANVAS_OK;
 }
 
+// Whether the output of a call (out_slices channel slices) shares bytes with one of its inputs.  The instances in one launch
+// write while others still read; one after the other with their sum at the end, they take such calls as far as they ever did.
+bool overlaps_any(const canvas_block* b, const void* out, int out_slices, const void* x, int x_slices, const void* dy, int dy_slices,
+                  const void* const* weights) {
+    const int64_t slice = b->N * b->C * b->P * (b->bf16 ? 2 : 4), bytes = out_slices * slice;
+    if (canvas::overlap(out, bytes, x, x_slices * slice) || (dy && canvas::overlap(out, bytes, dy, dy_slices * slice))) return true;
+    for (int j = 0; j < b->m; j++)
+        if (weights[j] && canvas::overlap(out, bytes, weights[j], (int64_t)b->weight_bytes)) return true;
+    return false;
+}
+
 int finish() {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_err(CANVAS_HIP_ERROR, std::string("kernel launch failed: ") + hipGetErrorString(e));
@@ -176,12 +190,14 @@ int canvas_block_compile(const void* blob, size_t blob_len, const int64_t in_sha
     b->N = in_shape[0];
     b->P = in_shape[2] * in_shape[3];
     b->bf16 = dt == CANVAS_BF16;
-    b->dense = align_up((uint64_t)(b->N * b->C * b->P) * (b->bf16 ? 2 : 4));
-    b->plan_ws = align_up(pi.workspace_bytes);
+    b->dense = canvas::align_up((uint64_t)(b->N * b->C * b->P) * (b->bf16 ? 2 : 4));
+    b->plan_ws = canvas::align_up(pi.workspace_bytes);
     b->off_a = b->plan_ws * (uint64_t)b->m;
     b->off_b = b->off_a + b->dense * (uint64_t)b->m;
     // (in place: 32-bit byte offsets over the wide tensors)
     b->direct = b->m > 1 && canvas::plan_takes_strided_io(b->plan) && b->N * b->C * b->m * b->P * (b->bf16 ? 2 : 4) < ((int64_t)1 << 31);
+    b->joint = b->direct && b->m <= canvas::plan_max_instances(b->plan);
+    if (b->joint) b->weight_bytes = (uint64_t)(pi.weight_shape[0][0] * pi.weight_shape[0][1] * pi.weight_shape[0][2]) * 2;
     b->info.instances = b->m;
     b->info.expand = b->expand ? 1 : 0;
     b->info.template_channels = b->C;
@@ -211,6 +227,8 @@ int canvas_block_forward(canvas_block* b, const void* x, const void* const* weig
     (void)hipGetLastError();
     const int64_t slice = b->C * b->P, wide = slice * b->m;      // elements of one image's slice / of one wide image
     const int64_t sbytes = slice * (b->bf16 ? 2 : 4);
+    if (b->joint && !overlaps_any(b, y, b->expand ? b->m : 1, x, b->expand ? 1 : b->m, nullptr, 0, weights))
+        return canvas::plan_block_forward(b->plan, b->m, b->expand, x, weights, y, ws, b->plan_ws, stream);
     if (!b->expand && !b->direct) regroup(b, x, A, true, s);
     for (int j = 0; j < b->m; j++) {
         void* pws = ws + (uint64_t)j * b->plan_ws;
@@ -243,6 +261,8 @@ int canvas_block_backward(canvas_block* b, const void* x, const void* const* wei
     (void)hipGetLastError();
     const int64_t slice = b->C * b->P, wide = slice * b->m;
     const int64_t sbytes = slice * (b->bf16 ? 2 : 4);
+    if (b->joint && !overlaps_any(b, dx, b->expand ? 1 : b->m, x, b->expand ? 1 : b->m, dy, b->expand ? b->m : 1, weights))
+        return canvas::plan_block_backward(b->plan, b->m, b->expand, x, weights, dy, dx, dweights, ws, b->plan_ws, stream);
     if (b->expand && b->m > 1 && !b->direct) regroup(b, dy, A, true, s);  // (expand: the slices of dy; reduce: A still holds the slices of x)
     for (int j = 0; j < b->m; j++) {
         void* pws = ws + (uint64_t)j * b->plan_ws;

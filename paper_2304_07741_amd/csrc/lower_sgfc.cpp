@@ -119,8 +119,46 @@ std::unique_ptr<Lowering> lower_sgfc(const Dag& dag, bool bf16) {
                         }});
     const int wpg = P.wgs_per_group;
     low->bwd.push_back({"sgfc_dw_reduce", 4.0 * G * elems * (wpg + 1), 0, [=](const RunArgs& a) {
-                            sgfc::dw_reduce((const float*)a.ws, (float*)a.dw[widx], G, wpg, elems, a.stream);
+                            sgfc::Instances I;
+                            I.dw[0] = (float*)a.dw[widx];
+                            sgfc::dw_reduce((const float*)a.ws, I, G, wpg, elems, a.stream);
                         }});
+    // Blocks: the instances of one tile in one wavefront.  Groups of 16 channels and an output as wide as the input; up to
+    // eight instances, whose dW accumulators (4 KB of LDS each per workgroup) leave two workgroups a compute unit.  One
+    // instance's workspace holds its partials and nothing else, so the instances' partials lie a workspace apart.
+    if (KC == 1 && MO == 1 && fc.out == C) {
+        low->max_instances = sgfc::kMaxInstances;
+        auto fill = [=](const BlockArgs& b, sgfc::Params& Q, sgfc::Instances& I) {
+            Q = P;
+            I.m = b.m;
+            I.slice = xs_dense;
+            I.part_stride = (long long)(b.ws_stride / 4);
+            Q.xs = b.expand ? xs_dense : b.m * xs_dense;
+            Q.ys = b.expand ? b.m * ys_dense : ys_dense;
+            Q.x = (const uint16_t*)b.args.x;
+            Q.y = (uint16_t*)b.args.y;
+            Q.dy = (const uint16_t*)b.args.dy;
+            Q.dx = (uint16_t*)b.args.dx;
+            Q.partial = (float*)b.args.ws;
+            for (int j = 0; j < b.m; j++) {
+                I.w[j] = (const uint16_t*)b.args.w[j];
+                if (b.args.dw) I.dw[j] = (float*)b.args.dw[j];
+            }
+        };
+        low->block_fwd = [=](const BlockArgs& b) {
+            sgfc::Params Q;
+            sgfc::Instances I;
+            fill(b, Q, I);
+            sgfc::forward_multi(Q, I, b.expand, b.args.stream);
+        };
+        low->block_bwd = [=](const BlockArgs& b) {
+            sgfc::Params Q;
+            sgfc::Instances I;
+            fill(b, Q, I);
+            sgfc::backward_multi(Q, I, b.expand, b.args.stream);
+            sgfc::dw_reduce(Q.partial, I, G, wpg, elems, b.args.stream);
+        };
+    }
     return low;
 }
 

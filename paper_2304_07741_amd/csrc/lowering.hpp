@@ -28,6 +28,15 @@ struct RunArgs {
     int64_t x_stride = 0, y_stride = 0;
 };
 
+// A call of a block: m instances of a plan with one weight each (args.w, args.dw: one per instance), whose x or dx
+// (reduce) or y or dy (expand) are the channel slices of one wide tensor.
+struct BlockArgs {
+    RunArgs args;
+    int m = 1;
+    bool expand = true;
+    uint64_t ws_stride = 0;  // bytes between the instances' workspaces
+};
+
 struct Launch {
     std::string name;
     double bytes = 0;  // algorithmic bytes: every operand of the launch once
@@ -55,6 +64,8 @@ struct ReduceJob {
 struct Lowering {
     bool fused = false;            // one of the whole-DAG kernel families
     bool strided_io = false;       // honours RunArgs::x_stride / y_stride
+    int max_instances = 0;         // up to so many instances of a block run in the launches of block_fwd / block_bwd
+    std::function<void(const BlockArgs&)> block_fwd, block_bwd;
     int chain_units = 0;           // fused chains in the forward list (each is one kernel forward, one backward)
     int chain_nodes = 0;           // nodes inside them
     uint64_t ws_bytes = 0;

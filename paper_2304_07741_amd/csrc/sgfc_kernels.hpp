@@ -30,11 +30,25 @@ struct Params {
     int dh[kMaxGroups] = {0}, dw[kMaxGroups] = {0};  // shift of each FC group's channels
 };
 
+// The instances of a block (one plan, weights of their own) that one launch works on.
+constexpr int kMaxInstances = 8;
+struct Instances {
+    const uint16_t* w[kMaxInstances] = {nullptr};
+    float* dw[kMaxInstances] = {nullptr};
+    int m = 1;
+    int slice = 0;                 // elements between the channel slices of an image of the wide tensor
+    long long part_stride = 0;     // floats between the instances' partials
+};
+
 // KC = CG/16, MO = OG/16
 bool supported(int KC, int MO);
 void forward(const Params& P, int KC, int MO, hipStream_t s);
 void backward(const Params& P, int KC, int MO, hipStream_t s);
-void dw_reduce(const float* partial, float* dw, int G, int n_partials, int elems, hipStream_t s);
+// All instances of a block whose groups have 16 channels: Params::xs, ys are the image strides of the narrow and the wide
+// tensor, `w` and the partials of the instances are in I.
+void forward_multi(const Params& P, const Instances& I, bool expand, hipStream_t s);
+void backward_multi(const Params& P, const Instances& I, bool expand, hipStream_t s);
+void dw_reduce(const float* partial, const Instances& I, int G, int n_partials, int elems, hipStream_t s);
 
 }  // namespace sgfc
 }  // namespace canvas
