@@ -366,6 +366,39 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         lay.part[i] = (int64_t)off;
         off += align_up((uint64_t)slices * wnumel[i] * 4);
     }
+    // fp32 contractions on the bf16 matrix units read their weights cut into parts, forward and transposed, from the workspace;
+    // a plan that fits the library's static workspace without them keeps to the fp32 units if it would not with them.
+    std::vector<sfc::Params> sfwd(dag.n_weights), sdata(dag.n_weights);
+    std::vector<std::pair<int, int64_t>> wsplit[2];  // (weight, offset) of the split weights, forward and transposed
+    for (int i = 0; i < dag.n_weights; i++) {
+        const int k = dag.weight_node[i];
+        if (!dag.nodes[k].live || fc_mfma[k]) continue;
+        sfwd[i] = sfc_params(k);
+        sdata[i] = sfc::data_gradient_of(sfwd[i]);
+        // (both directions or neither: one launch cuts the weights for both, and costs what one direction gains at the least)
+        sfc::prepare_forward(sfwd[i], !bf16);
+        sfc::prepare_forward(sdata[i], !bf16);
+        uint64_t bytes[2] = {0, 0};
+        const bool both = sfwd[i].split && sdata[i].split;
+        if (both)
+            for (int d = 0; d < 2; d++) bytes[d] = align_up((uint64_t)48 * sfc::split_job(d ? sdata[i] : sfwd[i]).items);
+        if (!both || (off <= CANVAS_STATIC_WORKSPACE_BYTES && off + bytes[0] + bytes[1] > CANVAS_STATIC_WORKSPACE_BYTES)) {
+            sfwd[i] = sfc_params(k);
+            sdata[i] = sfc::data_gradient_of(sfwd[i]);
+            sfc::prepare_forward(sfwd[i]);
+            sfc::prepare_forward(sdata[i]);
+            continue;
+        }
+        for (int d = 0; d < 2; d++) {
+            wsplit[d].push_back({i, (int64_t)off});
+            off += bytes[d];
+        }
+    }
+    auto split_at = [&](int d, int widx) {
+        for (const auto& s : wsplit[d])
+            if (s.first == widx) return s.second;
+        return (int64_t)-1;
+    };
     // Partials of the fp32 weight gradients: at most 16 MB each, and never so much that a plan which fits the library's
     // static workspace without them no longer does (one slice writes dw itself and needs none).
     const int64_t room = off < CANVAS_STATIC_WORKSPACE_BYTES ? (int64_t)(CANVAS_STATIC_WORKSPACE_BYTES - off) / std::max(1, sfc_count) - 256 : kMaxSfcPartialBytes;
@@ -410,6 +443,29 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             int64_t nw = wnumel[i];
             int64_t o = lay.wf[i];
             low->fwd.push_back({"widen_w", nw * 6.0, 0, [=](const RunArgs& a) { ref::widen_bf16(a.w[i], (float*)(a.ws + o), nw, a.stream); }, true});
+        }
+    }
+    // the split weights of forward and backward, several per launch (backward runs on the weights and the workspace of the
+    // preceding forward)
+    {
+        std::vector<std::pair<sfc::SplitJob, std::pair<int, int64_t>>> all;
+        for (int d = 0; d < 2; d++)
+            for (const auto& s : wsplit[d]) all.push_back({sfc::split_job(d ? sdata[s.first] : sfwd[s.first]), s});
+        for (size_t first = 0; first < all.size(); first += sfc::kMaxSplitJobs) {
+            const auto part = std::vector<std::pair<sfc::SplitJob, std::pair<int, int64_t>>>(
+                all.begin() + first, all.begin() + std::min(all.size(), first + (size_t)sfc::kMaxSplitJobs));
+            double bytes = 0;
+            for (const auto& j : part) bytes += 48.0 * j.first.items + 4.0 * wnumel[j.second.first];
+            low->fwd.push_back({"weight_prep", bytes, 0, [part](const RunArgs& a) {
+                                    sfc::SplitJobs J;
+                                    for (const auto& j : part) {
+                                        sfc::SplitJob& d = J.j[J.n++];
+                                        d = j.first;
+                                        d.w = (const float*)a.w[j.second.first];
+                                        d.out = a.ws + j.second.second;
+                                    }
+                                    sfc::split_weights(J, a.stream);
+                                }, true});
         }
     }
     // where an external tensor of a chain program lives
@@ -492,9 +548,9 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
                 };
                 break;
             }
-            sfc::Params Q = sfc_params(k);
-            sfc::prepare_forward(Q);
             const int srcn = fc_src(k), widx = nd.widx;
+            const sfc::Params Q = sfwd[widx];
+            const int64_t woff = split_at(0, widx);
             const bool to_y = k == dag.out && y_direct;
             const int64_t ny = dag.numel(k);
             const auto overlaps = stage >= 0 ? low->fwd_staged : [](const RunArgs&) { return false; };
@@ -504,6 +560,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
                 sfc::Params R = Q;
                 R.src = val(a, srcn);
                 R.w = wptr(a, widx);
+                R.wsplit = a.ws + woff;
                 R.dst = to_y ? (float*)a.y : valw(a, k);
                 const bool staged = overlaps(a);
                 if (staged) R.dst = (float*)(a.ws + stage);
@@ -688,15 +745,16 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
                 rj.bytes = 4.0 * (Q.slices + 1) * nw;
                 low->rjobs.push_back(rj);
             }
-            sfc::Params D = sfc::data_gradient_of(Q);
+            sfc::Params D = sdata[widx];
             D.acc = acc_s;
-            sfc::prepare_forward(D);
+            const int64_t woff = split_at(1, widx);
             const int64_t nx = dag.numel(0), ny = dag.numel(k);
             low->bwd.push_back({sfc_name("sfc_dgrad", D), 4.0 * (dag.numel(k) + dag.numel(srcn) * (1 + acc_s) + nw), flops,
                                 [=](const RunArgs& a) {
                                     sfc::Params R = D;
                                     R.src = from_dy ? (const float*)a.dy : grad(a, k);
                                     R.w = wptr(a, widx);
+                                    R.wsplit = a.ws + woff;
                                     R.dst = to_dx ? (float*)a.dx : grad(a, srcn);
                                     const bool staged = stage >= 0 && (overlap(a.dx, nx * 4, a.dy, ny * 4) || overlap(a.dx, nx * 4, a.w[widx], nw * 4));
                                     if (staged) R.dst = (float*)(a.ws + stage);

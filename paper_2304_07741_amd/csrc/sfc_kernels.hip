@@ -3,6 +3,7 @@
 #include <algorithm>
 
 #include "launch.hpp"
+#include "sfc_device.hpp"
 
 namespace canvas {
 namespace sfc {
@@ -15,31 +16,6 @@ using f4u = __attribute__((ext_vector_type(4), aligned(4))) float;  // in memory
 constexpr int kThreads = 256;
 constexpr int kLinearKc = 32;   // channels per chunk without a window
 constexpr int kMaxLds = 64 * 1024;
-
-// Consecutive workgroups go to consecutive XCDs, each with an L2 of its own; this renumbers them so that an XCD works on
-// neighbouring tiles, whose operands overlap (the margin of a window, the other outputs of the same pixels).  The grid is
-// a multiple of eight workgroups, in rows if it is long (grid_of); the numbers past the last tile have no work.
-__device__ __forceinline__ unsigned tile_of_block() {
-    const unsigned per = gridDim.x / 8;
-    return blockIdx.y * gridDim.x + (blockIdx.x % 8) * per + blockIdx.x / 8;
-}
-
-// x / d for the small dividends of index arithmetic: exact while x * d < 2^32 (the host checks the image's sizes)
-__device__ __forceinline__ int quotient(int x, int d, uint32_t m) { return d == 1 ? x : (int)__umulhi((uint32_t)x, m); }
-// image of pixel p, counted from an image at whose pixel p0 < P a tile of at most 128 pixels begins
-__device__ __forceinline__ int image_of(const Params& Q, int p) { return Q.P >= 128 ? (p >= Q.P ? 1 : 0) : quotient(p, Q.P, Q.mP); }
-
-// Position j of a window's operand tile whose first pixel is (n0, h0, .) -> element offset of that source pixel in
-// channel 0 of the group, or -1 in the margin.  Rows are numbered through the batch with HP = H + KH - 1 rows per image.
-__device__ __forceinline__ int64_t window_source(const Params& Q, int64_t n0, int h0, int j) {
-    const int s = quotient(j, Q.Wp, Q.mWp), c = j - s * Q.Wp;
-    const int q = h0 + s;
-    const int dn = quotient(q, Q.HP, Q.mHP);
-    const int h = q - dn * Q.HP - Q.KH / 2, w = c - Q.KW / 2;
-    const int64_t n = n0 + dn;
-    if (n >= Q.N || h < 0 || h >= Q.H || w < 0 || w >= Q.W) return -1;
-    return n * Q.G * Q.R * (int64_t)Q.P + (int64_t)h * Q.W + w;
-}
 
 // Forward and data gradient.  A workgroup owns 16*WM outputs of one group and TP = 16*NT*(4/WM) consecutive pixels of the
 // batch, a wavefront 16 outputs and 16*NT pixels; the contraction runs over chunks of KC channels with all their taps.  With the small tiles
@@ -765,7 +741,34 @@ Params data_gradient_of(const Params& f) {
     return p;
 }
 
-void prepare_forward(Params& p) {
+// Where the bf16 matrix units are faster, the cutting of the weights included (fp32 units / here, us; 4.2 for the launch that
+// cuts the weights of both directions).  3 x 3, forward + data gradient: 64 channels 32x28x28 38.6 + 36.4 / 21.0 + 21.2, 8x40x40
+// 22.4 + 22.1 / 15.0 + 15.2, 1x28x28 15.8 + 16.0 / 12.4 + 12.4; 96 channels 8x40x40 52.0 + 49.5 / 30.7 + 30.7; 128 channels
+// 32x14x14 40.8 + 39.7 / 21.4 + 21.4; eight groups of 32 32x14x14 22.8 + 21.0 / 14.2 + 14.2, of 64 16x7x7 16.7 + 17.4 / 13.4 + 13.4
+// (6.0 for the weights); 32 channels 32x28x28 13.9 + 13.0 / 10.6 + 10.7; but 48 channels 32x14x14 (98 workgroups) 12.7 + 13.0 /
+// 11.1 + 11.2.  Without a window: 128 channels 32x28x28 24.8 + 23.5 / 18.4 + 18.2, 512 channels 32x14x14 69.6 + 68.3 / 41.1 + 41.0;
+// but 64 channels 32x28x28 9.2 + 8.9 / 8.1 + 8.2, 512 channels 16x7x7 (104 workgroups) 19.1 + 18.2 / 17.7 + 16.8.
+static bool split_forward(Params& p) {
+    const bool win = p.KH == 3 && p.KW == 3;
+    if (!win && p.TV != 1) return false;
+    Params q = p;
+    q.split = 1;
+    q.wm = p.Og > 32 ? 2 : 1;
+    const int pixels = 32 * (4 / q.wm);
+    q.mtiles = (q.Og + 32 * q.wm - 1) / (32 * q.wm);
+    q.tiles = (q.M + pixels - 1) / pixels * q.G * q.mtiles;
+    if (win ? p.Og < 32 || p.R < 32 || (p.R < 64 && q.tiles < 192) : p.Og <= 32 || p.R < 128 || q.tiles < 384) return false;
+    q.S = win ? window_positions(q, pixels) : pixels;
+    if (q.S > 512) return false;  // (four items of the operand tile per thread)
+    // 32-bit byte offsets within the images of a tile and within a group's weights, and 3 GB of cut weights
+    const int64_t images = (pixels + q.P - 1) / q.P + 1;
+    if (images * q.G * q.R * q.P >= (int64_t)1 << 29 || (int64_t)q.Og * q.K >= (int64_t)1 << 29) return false;
+    if ((int64_t)q.G * q.mtiles * q.wm * ((q.R + 15) / 16) * q.TV * 64 >= (int64_t)1 << 26) return false;
+    p = q;
+    return true;
+}
+
+void prepare_forward(Params& p, bool may_split) {
     const bool win = p.TV > 1;
     p.narrow = narrow_forward(p);
     if (p.narrow) {
@@ -775,6 +778,7 @@ void prepare_forward(Params& p) {
         p.tiles = (p.M * p.G + kThreads * p.vec - 1) / (kThreads * p.vec) * p.mtiles;
         return;
     }
+    if (may_split && split_forward(p)) return;
     // Up to four wavefronts side by side over the outputs: a weight then reaches the workgroup once, a staged pixel
     // serves up to 64 outputs.  Half the pixels where the launch would otherwise have less than two workgroups per
     // compute unit.
@@ -884,6 +888,10 @@ void forward(const Params& p, hipStream_t s) {
         }
 #undef CANVAS_SFC
 #undef CANVAS_SFC_T
+        return;
+    }
+    if (p.split) {
+        forward_split(p, grid, s);
         return;
     }
     const size_t lds = fwd_lds(p);

@@ -14,6 +14,7 @@ namespace sfc {
 struct Params {
     const float* src = nullptr;  // row tensor
     const float* w = nullptr;    // [G][Og][R][TV]; transposed: [G][R][Og][TV], taps flipped
+    const void* wsplit = nullptr;  // split: the same as k_split_weights leaves them
     float* dst = nullptr;        // forward: [N, G*Og, P]
     const float* dy = nullptr;   // weight gradient: [N, G*Og, P]
     float* partial = nullptr;    // weight gradient: [slices][G*Og*K] (one slice: dw itself)
@@ -28,6 +29,7 @@ struct Params {
     int ktiles = 1, mtiles = 1, nch = 0, slices = 1;
     // narrow: few rows and outputs per group, one thread per pixel on the vector unit; ot outputs, vec pixels per thread
     int narrow = 0, ot = 1, vec = 1;
+    int split = 0;  // forward: operands cut into three bf16 parts; 32*wm outputs x 32*(4/wm) pixels
     int64_t per_slice = 0;                             // pixels per slice
     int64_t tiles = 0;                                 // workgroups with work
 };
@@ -39,9 +41,29 @@ bool window_supported(int KH, int KW, int H, int W);
 Params shape(int64_t N, int G, int R, int KH, int KW, int Og, int H, int W);
 // The data gradient of a contraction: rows and outputs swapped, transposed weights, the window read backwards.
 Params data_gradient_of(const Params& fwd);
-void prepare_forward(Params& p);
+// may_split: whether the caller keeps the split weights (split_job) that the plan then asks for.
+void prepare_forward(Params& p, bool may_split = false);
 // Splits the pixels over slices, at most max_partial_bytes of partials (0: one slice, written straight to dw).
 void prepare_wgrad(Params& p, int64_t max_partial_bytes);
+
+// The kernels of sfc_split_kernels.hip: forward with Params::split, and the LDS it takes (at most kMaxSplitLds).
+constexpr int kMaxSplitLds = 128 * 1024;
+void forward_split(const Params& p, dim3 grid, hipStream_t s);
+size_t split_lds(const Params& p);
+
+// The weights that a split contraction reads (Params::wsplit): 48 * items bytes at `out`, from w as Params::w.
+struct SplitJob {
+    const float* w = nullptr;
+    void* out = nullptr;
+    int G = 0, R = 0, Og = 0, TV = 1, transposed = 0, mt32 = 0, items = 0;
+};
+constexpr int kMaxSplitJobs = 8;
+struct SplitJobs {
+    SplitJob j[kMaxSplitJobs];
+    int n = 0;
+};
+SplitJob split_job(const Params& p);
+void split_weights(const SplitJobs& jobs, hipStream_t s);
 
 // dst[n, g*Og+o, p] (+)= sum_k w[g][o][k] * src_row(n, g, k)[p + off(k)]
 void forward(const Params& p, hipStream_t s);

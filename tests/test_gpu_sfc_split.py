@@ -1,0 +1,115 @@
+"""fp32 FCs on the bf16 matrix units (operands cut into three parts) at the edges of their tiles: remainders in channels,
+outputs, pixels and images, groups, wide images, accumulated gradients, results that overlap an input, and values that the
+parts cannot hold."""
+import numpy as np
+import pytest
+
+from oracle import canvas_oracle
+from paper_2304_07741_amd import binding as B
+from paper_2304_07741_amd import harness
+
+pytestmark = pytest.mark.gpu
+
+FC = "canvas-dag 1\n%1 = fc %0 groups={g} out={o}\noutput %1\n"
+WIN = "canvas-dag 1\n%1 = unfold %0 kh=3 kw=3\n%2 = fc %1 groups={g} out={o}\noutput %2\n"
+FAN = ("canvas-dag 1\n%1 = unfold %0 kh=3 kw=3\n%2 = fc %1 groups=1 out={o}\n%3 = fc %1 groups=1 out={o}\n"
+       "%4 = binary %2 %3 op=mul\noutput %4\n")
+
+CASES = [
+    ("3x3_four_pixels", WIN.format(g=1, o=64), (1, 64, 2, 2)),
+    ("3x3_few_pixels", WIN.format(g=1, o=65), (3, 64, 2, 3)),
+    ("3x3_ragged_channels", WIN.format(g=1, o=71), (2, 69, 9, 7)),
+    ("3x3_images_per_tile", WIN.format(g=1, o=64), (23, 66, 3, 5)),
+    ("3x3_groups_of_32", WIN.format(g=4, o=128), (9, 128, 28, 25)),
+    ("3x3_two_rows_of_outputs", WIN.format(g=1, o=129), (2, 65, 11, 13)),
+    ("3x3_three_items", WIN.format(g=1, o=64), (2, 64, 10, 50)),
+    ("3x3_four_items", WIN.format(g=1, o=64), (2, 64, 10, 60)),
+    ("3x3_one_column", WIN.format(g=1, o=64), (2, 64, 70, 1)),
+    ("1x1_ragged", FC.format(g=1, o=131), (70, 133, 11, 13)),
+    ("1x1_groups", FC.format(g=2, o=260), (35, 256, 14, 15)),
+    ("fan_out", FAN.format(o=64), (3, 64, 9, 14)),
+]
+
+
+def _case(name, blob, shape):
+    h = B.canvas_dag_compile(blob, shape, B.CANVAS_F32)
+    info = B.canvas_dag_query(h)
+    names = [B.canvas_dag_launch_desc(h, 0, i)["name"] for i in range(info.n_launches_fwd)]
+    wsh = [tuple(int(v) for v in info.weight_shape[k]) for k in range(info.n_weights)]
+    B.canvas_dag_destroy(h)
+    assert names[0] == "weight_prep", names
+    rng = np.random.default_rng(len(name))
+    f = lambda *s: rng.standard_normal(s).astype(np.float32)
+    return {"blob": blob, "shape": shape, "dtype": "f32", "x": f(*shape), "weights": [f(*s) / np.sqrt(s[2]) for s in wsh], "seed": 1}
+
+
+def _check(case, res, dy):
+    # (K terms in any order: about sqrt(K) * 2^-24 of the largest element, K up to 2.8e4 here)
+    ref = canvas_oracle.run(case["blob"], case["x"], case["weights"], dy)
+    for n, a, b in [("y", res["y"], ref["y"]), ("dx", res["dx"], ref["dx"])] + [(f"dw{k}", a, b) for k, (a, b) in enumerate(zip(res["dw"], ref["dw"]))]:
+        err = np.abs(a.reshape(b.shape) - b).max() / max(np.abs(b).max(), 1e-30)
+        assert np.isfinite(a).all() and err <= 1e-5, (n, err)
+
+
+@pytest.mark.parametrize("name,blob,shape", CASES, ids=[c[0] for c in CASES])
+def test_split_fc(name, blob, shape):
+    case = _case(name, blob, shape)
+    res, r, dy = harness.run_case(case)
+    r.ws.fill_(0xFF)  # (a second pass on a workspace of NaN: nothing is read before it is written)
+    r.poison_outputs()
+    r.forward()
+    r.backward()
+    again = r.results()
+    r.close()
+    for a, b in zip([res["y"], res["dx"], *res["dw"]], [again["y"], again["dx"], *again["dw"]]):
+        assert np.array_equal(a, b)
+    _check(case, res, dy)
+
+
+def test_values_that_the_parts_cannot_hold():
+    """Infinities, NaN and magnitudes that round to an infinity in bf16 give what fp32 gives, in their windows and nowhere else."""
+    case = _case("3x3_values", WIN.format(g=1, o=64), (2, 64, 9, 11))
+    x, w = case["x"], case["weights"][0]
+    x[0, 3, 4, 5], x[0, 9, 0, 0], x[1, 63, 8, 10], x[1, 7, 4, 1] = np.inf, -np.inf, np.nan, 3.4e38
+    x[1, 30, 4, 6] = -3.39e38
+    w.reshape(64, 64, 9)[:, 7] *= 1e-3
+    w.reshape(64, 64, 9)[:, 30] *= 1e-3
+    res, r, dy = harness.run_case(case)
+    r.close()
+    xp = np.pad(x.astype(np.float64), ((0, 0), (0, 0), (1, 1), (1, 1)))
+    with np.errstate(invalid="ignore"):
+        ref = sum(np.einsum("oc,nchw->nohw", w.reshape(64, 64, 3, 3)[:, :, i, j].astype(np.float64), xp[:, :, i:i + 9, j:j + 11], optimize=False)
+                  for i in range(3) for j in range(3))
+    got = res["y"].reshape(ref.shape)
+    # (einsum multiplies an infinity into every output of its pixel; elsewhere in a window it meets real weights too)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref)) and np.array_equal(np.isneginf(got), np.isneginf(ref))
+    ok = np.isfinite(ref)
+    small = ok & (np.abs(ref) < 1e6)
+    assert small.sum() > 0.5 * ref.size and np.abs(got[small] - ref[small]).max() <= 1e-5 * np.abs(ref[small]).max()
+    big = ok & (np.abs(ref) > 1e30)
+    assert big.any() and (np.abs(got[big] - ref[big]) <= 1e-5 * np.abs(ref[big])).all()
+
+
+@pytest.mark.parametrize("what", ["x", "w"])
+def test_result_on_top_of_an_input(what):
+    import torch
+
+    case = _case("3x3_overlap", WIN.format(g=1, o=64), (2, 64, 12, 12))
+    r = harness.DagRunner(case["blob"], case["shape"], "f32")
+    dy = np.random.default_rng(3).standard_normal(r.out_shape).astype(np.float32)
+    r.load(case["x"], case["weights"], dy)
+    n = r.y.numel()
+    if what == "x":
+        y = r.x.view(-1).view(r.y.shape)
+        B.canvas_dag_forward(r.handle, r.x, r.w, y, r.ws)
+    else:
+        buf = torch.empty(max(n, r.w[0].numel()), dtype=torch.float32, device="cuda")
+        w = buf[:r.w[0].numel()].view(r.w[0].shape)
+        w.copy_(r.w[0])
+        y = buf[:n].view(r.y.shape)
+        B.canvas_dag_forward(r.handle, r.x, [w], y, r.ws)
+    torch.cuda.synchronize()
+    got = y.cpu().numpy()
+    r.close()
+    ref = canvas_oracle.run(case["blob"], case["x"], case["weights"], dy.reshape(2, 64, 12, 12))["y"]
+    assert np.abs(got.reshape(ref.shape) - ref).max() <= 1e-5 * np.abs(ref).max()
