@@ -656,6 +656,207 @@ class Emitter {
         }
     }
 
+    // ---------------------------------------------------------------- gradients through a window, fetched by the source pixel
+    // The gradient of a tensor read through a window is, for its pixel p, the sum over the taps t of what lane t of the
+    // consumer at p - offset(t) hands back.  Where that depends on nothing but the consumer's own values (lanes equal) and on
+    // the source pixel's, p evaluates it itself: whatever the consumer reads at its own position is read through the window
+    // (which is symmetric: the lanes come in the opposite order, for all of them alike), whatever it reads through the window
+    // is p's own.  Lanes and positions change places; a value that the consumer computes from all of its taps (a fold's
+    // result, a softmax over the taps, the first maximum) cannot be had this way and the leaf keeps its hand-over (Fail).
+    // mlanes: lanes of instance i in that view; meval: its value; mgrad: its gradient, mlanes(i) lanes.  The factor 1/T of
+    // an avg fold on the way is applied where the lanes are added (`avg`; everything in between is linear).
+    int mwin = -1;  // the window's context
+    int mtaps() const { return G->ctxs[mwin].kh * G->ctxs[mwin].kw; }
+    int mlanes(int i) const {
+        const Inst& I = G->insts[i];
+        if (I.ctx != 0 && I.ctx != mwin) throw Fail{"mirror: another position"};
+        switch (I.kind) {
+        case kExt:
+            if (G->dag.nodes[I.node].T != 1) throw Fail{"mirror: a tensor with taps"};
+            return I.ctx == mwin ? 1 : mtaps();
+        case kIdent:
+        case kUnaryI: return mlanes(I.opnd[0]);
+        case kStencil:
+            if (G->dag.nodes[I.node].op != Op::Unfold || G->insts[I.opnd[0]].ctx != mwin) throw Fail{"mirror: a shift"};
+            return mlanes(I.opnd[0]);
+        case kBinaryI: return std::max(mlanes(I.opnd[0]), mlanes(I.opnd[1]));
+        default: throw Fail{"mirror: a value of all taps"};
+        }
+    }
+    int mctx(int i) const { return G->insts[i].ctx == mwin ? 0 : mwin; }  // (of a leaf)
+    // A (lanes) blended with the leaf i in its place: OP_BINLD as load_and_blend
+    void mblend(int i, int lanes, int blend, bool loaded_is_lhs) {
+        Instr I = positional(OP_BINLD, mctx(i), lanes);
+        I.a = (uint16_t)ext_slot(G->insts[i].node, kValueIn);
+        I.kind |= (uint8_t)(blend << kBinLdKindShift);
+        if (loaded_is_lhs) I.kind |= kBinLdLoadedIsLhs;
+        if (mlanes(i) == 1 && lanes > 1) {
+            I.kind = (uint8_t)((I.kind & ~kWin) | kBinLdLoadedScalar);
+            I.r = 0;
+        }
+        emit(I);
+    }
+    void meval(int i) {
+        const Inst& I = G->insts[i];
+        const Node& nd = G->dag.nodes[I.node];
+        const int lanes = mlanes(i);
+        switch (I.kind) {
+        case kExt: {
+            Instr ld = positional(OP_LD, mctx(i), lanes);
+            ld.a = (uint16_t)ext_slot(I.node, kValueIn);
+            emit(ld);
+            break;
+        }
+        case kUnaryI: {
+            meval(I.opnd[0]);
+            Instr u = simple(OP_UN, lanes, 0, nd.kind);
+            u.f0 = nd.lo;
+            u.f1 = nd.hi;
+            emit(u);
+            break;
+        }
+        case kBinaryI: {
+            const int a = I.opnd[0], b = I.opnd[1];
+            if (G->insts[a].kind == kExt && mlanes(b) == lanes) {
+                meval(b);
+                mblend(a, lanes, nd.kind, true);
+                break;
+            }
+            if (G->insts[b].kind == kExt && mlanes(a) == lanes) {
+                meval(a);
+                mblend(b, lanes, nd.kind, false);
+                break;
+            }
+            meval(a);
+            const int r = alloc();
+            emit(simple(OP_MOVR, mlanes(a), r));
+            meval(b);
+            emit(simple(OP_BIN, lanes, r, nd.kind | kBinRegIsLhs | (mlanes(a) < lanes ? kBinRegScalar : 0) | (mlanes(b) < lanes ? kBinAccScalar : 0)));
+            release(r);
+            break;
+        }
+        default: meval(I.opnd[0]);  // (a view: the values outside the image belong to pixels that do not exist)
+        }
+    }
+    void mgrad(int i, bool& avg) {
+        const Inst& I = G->insts[i];
+        const int lanes = mlanes(i);
+        bool first = true;
+        int sum = -1;
+        auto begin_term = [&]() {
+            if (!first) emit(simple(OP_MOVR, lanes, sum = alloc()));
+        };
+        auto end_term = [&](bool a) {
+            if (!first) {
+                if (a != avg) throw Fail{"mirror: terms with and without the factor of an avg fold"};
+                emit(simple(OP_BIN, lanes, sum, kAdd | kBinRegIsLhs));
+                release(sum);
+            }
+            avg = a;
+            first = false;
+        };
+        if (I.kind != kExt && I.ctx == 0 && G->is_output_[I.node] && I.lanes == G->dag.nodes[I.node].T) {
+            if (I.lanes != 1) throw Fail{"mirror: an output with taps"};
+            begin_term();
+            Instr ld = positional(OP_LD, mwin, mtaps());
+            ld.a = (uint16_t)ext_slot(I.node, kGradIn);
+            emit(ld);
+            end_term(false);
+        }
+        for (const auto& u : I.users) {
+            begin_term();
+            bool a = false;
+            mcontribution(u.first, u.second, i, a);
+            end_term(a);
+        }
+        if (first) throw Fail{"internal: an instance without users"};
+    }
+    // lanes of the user's gradient in this view (a fold's result is a value of the consumer: one per tap of the window)
+    int mglanes(int u) const {
+        if (G->insts[u].kind == kFoldI && G->insts[u].ctx == 0) return mtaps();
+        return mlanes(u);
+    }
+    void mgrad_of_user(int u, bool& avg) {
+        const Inst& U = G->insts[u];
+        if (U.kind != kFoldI) {
+            mgrad(u, avg);
+            return;
+        }
+        if (U.ctx != 0 || G->dag.nodes[U.node].kind == kMax || G->insts[U.opnd[0]].lanes != mtaps()) throw Fail{"mirror: a fold of other lanes"};
+        // the fold's own gradient: only the one that comes from memory (a consumer of its result inside the unit would go on here)
+        if (!U.users.empty() || !G->is_output_[U.node]) throw Fail{"mirror: a fold whose result is used inside the unit"};
+        Instr ld = positional(OP_LD, mwin, mtaps());
+        ld.a = (uint16_t)ext_slot(U.node, kGradIn);
+        emit(ld);
+        avg = G->dag.nodes[U.node].kind == kAvg;
+    }
+    void mcontribution(int u, int slot, int i, bool& avg) {
+        const Inst& U = G->insts[u];
+        const Node& un = G->dag.nodes[U.node];
+        const int lanes = mglanes(u), mine = mlanes(i);
+        switch (U.kind) {
+        case kIdent:
+        case kStencil:
+        case kFoldI: mgrad_of_user(u, avg); break;
+        case kUnaryI: {
+            mgrad(u, avg);
+            const int r = alloc();
+            emit(simple(OP_MOVR, lanes, r));
+            meval(i);
+            Instr b = simple(OP_UNBX, lanes, r, un.kind);
+            b.f0 = un.lo;
+            b.f1 = un.hi;
+            emit(b);
+            release(r);
+            break;
+        }
+        case kBinaryI: {
+            const int other = U.opnd[1 - slot];
+            mgrad(u, avg);
+            if (un.kind == kAdd || (un.kind == kSub && slot == 0)) break;
+            if (un.kind == kSub) {
+                emit(simple(OP_UN, lanes, 0, kUnNeg));
+                break;
+            }
+            if (un.kind == kMul && G->insts[other].kind == kExt) {
+                mblend(other, lanes, kMul, false);
+                break;
+            }
+            const int rg = alloc();
+            emit(simple(OP_MOVR, lanes, rg));
+            if (un.kind == kMul) {
+                meval(other);
+                emit(simple(OP_BIN, lanes, rg, kMul | (mlanes(other) < lanes ? kBinAccScalar : 0)));
+            } else {
+                const int ll = mlanes(U.opnd[0]), lr = mlanes(U.opnd[1]);
+                meval(U.opnd[0]);
+                const int rl = alloc();
+                emit(simple(OP_MOVR, ll, rl));
+                meval(U.opnd[1]);
+                emit(simple(OP_BING, lanes, rl, un.kind | (slot == 1 ? kBingRhsSide : 0) | (ll < lanes ? kBingLhsScalar : 0) | (lr < lanes ? kBingRhsScalar : 0)));
+                emit(simple(OP_BIN, lanes, rg, kMul));
+                release(rl);
+            }
+            release(rg);
+            break;
+        }
+        default: throw Fail{"mirror: a gradient of all taps"};
+        }
+        if (mine < lanes) {
+            emit(simple(OP_FOLD, lanes, 0, avg ? kAvg : kSum));
+            avg = false;
+        }
+    }
+    // the whole of it: d loss / d (the tensor leaf i reads through its window), one lane, in A
+    void mirror(int i) {
+        mwin = G->insts[i].ctx;
+        const Ctx& c = G->ctxs[mwin];
+        if (!c.terms.empty() || mlanes(i) != 1) throw Fail{"mirror: a window behind a shift"};
+        bool avg = false;
+        mgrad(i, avg);
+        if (avg) throw Fail{"mirror: lanes that were never added"};
+    }
+
     void begin_pass() {
         a_reg = -1;
         if (pg.n_pass >= kMaxPass) throw Fail{"too many passes"};
@@ -678,7 +879,7 @@ class Emitter {
     }
     void end_pass() {
         pg.pass[pg.n_pass++].body_end = (uint16_t)pg.n_instr;
-        forget();
+        if (!one_trip) forget();
     }
 
     // the passes that collect the statistics of every softmax over channels, lowest first
@@ -707,6 +908,10 @@ class Emitter {
 
     Graph* G;
     int gidx = 0;
+    // The threads make one trip through every body (the workgroup has a thread for every channel): what one pass kept is
+    // there in the next, for the same channels.  A value or gradient that a pass computes rests on statistics that are
+    // complete by then, so it is the same in every later pass.
+    bool one_trip = false;
     Program pg;
     std::vector<ExtRef> ext;
     int NR;
@@ -725,10 +930,11 @@ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Workgroup shape for V pixels per thread and `pt` threads per slice: tile and halo, channel range and slices.
 // Returns the estimated cost of the launch (arbitrary units, see set_geometry) or a negative number when it does not fit.
-double geometry_for(Program& pg, const Dag& dag, int C, int64_t reach_px, bool all_channels, int V, int pt, int trips) {
+double geometry_for(Program& pg, const Dag& dag, int C, int64_t reach_px, bool all_channels, bool one_trip, bool one_copy, int V, int pt, int trips) {
     const int HW = dag.H * dag.W;
     pg.vec = V;
     pg.unroll = unroll_for(pg.tm, V);
+    pg.persist_copies = one_copy ? 1 : pg.unroll;
     const int PP = HW / V;                                   // pixel threads of a plane
     const int64_t HT = (reach_px + V - 1) / V;               // halo, in pixel threads
     const int per_thread = std::max<int>(1, (int)lds_bytes_per_thread(pg));
@@ -758,6 +964,7 @@ double geometry_for(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
         pg.chunks = ceil_div(C, pg.chunk);
         pg.slices = std::min(S, ceil_div(pg.chunk, pg.unroll));
     }
+    if (one_trip && pg.slices * pg.unroll < pg.chunk) return -1;
     pg.threads = pg.slices * pg.pix_threads;
     if (lds_bytes(pg) > kMaxLdsBytes || (int64_t)dag.N * pg.tiles * pg.chunks >= ((int64_t)1 << 31)) return -1;
     // cost: trips of a thread x what a trip costs (a fixed part for fetching and dispatching the instructions, worth
@@ -776,7 +983,8 @@ double geometry_for(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
 }
 
 // Pixels per thread, threads per slice and trips per thread: whatever the estimate likes best.
-void set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool all_channels) {
+// Returns the estimate.
+double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool all_channels, bool one_trip) {
     pg.N = dag.N;
     pg.C = C;
     pg.H = dag.H;
@@ -785,23 +993,32 @@ void set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool all
     for (int i = 0; i < pg.n_instr; i++)
         if (pg.ins[i].op == OP_XADD) pg.xadd_lanes = std::max<int>(pg.xadd_lanes, pg.ins[i].T);
     const int HW = dag.H * dag.W;
-    Program best;
+    // (a program that makes one trip keeps its registers' LDS: floats that no channel has for itself exist once.  The other
+    // programs' workgroups were weighed with a copy per channel of the trip, and the estimate errs without them: softmax over
+    // channels, 128x64 planes of 56x56 backward 177 us with the workgroup it chooses so, 250 otherwise.)
+    bool one_copy = one_trip;
+    for (int p = 0; p < pg.n_pass; p++)
+        for (int i = pg.pass[p].body_begin; i < pg.pass[p].body_end; i++)
+            if (pg.ins[i].op == OP_PSET || pg.ins[i].op == OP_PADD || pg.ins[i].op == OP_PLD || pg.ins[i].op == OP_XADD) one_copy = false;
+    int best[3] = {0, 0, 0};
     double best_cost = -1;
     for (int V = max_vec_for(pg.tm); V >= 1; V /= 2) {
         if (HW % V != 0 || dag.W < V) continue;
         for (int pt = 64; pt <= max_threads_for(pg.tm); pt += 64)
             for (int trips = 1; trips <= (all_channels ? 1 : 8); trips *= 2) {
-                Program q = pg;
-                const double cost = geometry_for(q, dag, C, reach_px, all_channels, V, pt, trips);
+                const double cost = geometry_for(pg, dag, C, reach_px, all_channels, one_trip, one_copy, V, pt, trips);
                 if (cost < 0) continue;
                 if (best_cost < 0 || cost < best_cost * 0.999) {  // (ties: the wider vector, the smaller workgroup, fewer trips)
                     best_cost = cost;
-                    best = q;
+                    best[0] = V;
+                    best[1] = pt;
+                    best[2] = trips;
                 }
             }
     }
     if (best_cost < 0) throw Fail{"tile, halo and persistent state do not fit one workgroup"};
-    pg = best;
+    (void)geometry_for(pg, dag, C, reach_px, all_channels, one_trip, one_copy, best[0], best[1], best[2]);
+    return best_cost;
 }
 
 }  // namespace
@@ -920,6 +1137,18 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
             }
             E.end_pass();
         };
+        // Leaves read through a window whose gradient the source pixel fetches (Emitter::mirror), found by trying.
+        std::set<int> mirrored;
+        for (int i : leaves) {
+            if (!G.ctxs[G.insts[i].ctx].win) continue;
+            try {
+                Emitter trial(G, tm);
+                trial.mirror(i);
+                mirrored.insert(i);
+            } catch (const Fail&) {
+            }
+        }
+        bool use_mirrors = false;
         auto emit_bwd = [&](Emitter& E) {
             E.stat_passes(smc);
             int deepest = 0;
@@ -934,12 +1163,11 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
                 E.begin_body();
                 for (int i : smc)
                     if (G.down(i) == d) {
-                        E.grad(i);
-                        const int r = E.alloc();
-                        E.emit(Emitter::simple(OP_MOVR, G.insts[i].lanes, r));
+                        bool mine;
+                        const int r = E.to_reg(i, 1, mine);
                         E.eval(i);
                         E.emit(Emitter::simple(OP_SMCDOT, G.insts[i].lanes, r, 0, E.dot_slot(i)));
-                        E.release(r);
+                        if (mine) E.release(r);
                     }
                 E.end_pass();
             }
@@ -955,7 +1183,7 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
                 // no hand-over among the leaves: their contributions are summed in a register instead of LDS floats
                 bool local = !direct;
                 for (int i : mine)
-                    if (G.insts[i].lanes != Te || (G.insts[i].ctx != 0 && !pulls.count(i))) local = false;
+                    if (!(use_mirrors && mirrored.count(i)) && (G.insts[i].lanes != Te || (G.insts[i].ctx != 0 && !pulls.count(i)))) local = false;
                 int acc = -1, racc = -1;
                 if (!direct && !local) {
                     acc = E.persist(Te);
@@ -982,6 +1210,11 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
                     if (local && !first_term) {  // (the sum so far waits in a register while the next term is computed)
                         racc = E.alloc();
                         E.emit(Emitter::simple(OP_MOVR, Te, racc));
+                    }
+                    if (use_mirrors && mirrored.count(i)) {
+                        E.mirror(i);
+                        add_term(1);
+                        continue;
                     }
                     auto pl = pulls.find(i);
                     if (pl != pulls.end()) {  // fetched from the displaced copy of the unit
@@ -1018,11 +1251,12 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
         // A program is emitted with full recomputation first; then, greedily, the value or gradient whose repeated
         // computation costs the most is kept in a register, as long as that makes the program cheaper and the registers
         // last.  Returns the emitter of the cheapest program that could be emitted.
-        auto shortest = [&](const std::function<void(Emitter&)>& emit_program) {
+        auto shortest = [&](const std::function<void(Emitter&)>& emit_program, bool one_trip, int most_kept) {
             std::set<int> keep;
             auto best = std::make_shared<Emitter>(G, tm);
+            best->one_trip = one_trip;
             emit_program(*best);  // (throws when even the plain program does not fit)
-            for (int round = 0; round < regs_for(tm); round++) {
+            for (int round = 0; round < most_kept; round++) {
                 int pick = -1;
                 double gain = 0;
                 for (const auto& kv : best->stats) {
@@ -1037,6 +1271,7 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
                 try {
                     auto E = std::make_shared<Emitter>(G, tm);
                     E->keep = keep;
+                    E->one_trip = one_trip;
                     emit_program(*E);
                     if (E->weight >= best->weight) break;
                     best = E;
@@ -1046,22 +1281,45 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
             }
             return best;
         };
-        {
-            auto E = shortest(emit_fwd);
-            set_geometry(E->pg, dag, C, 0, !smc.empty());
-            out.fwd = E->pg;
-            out.fwd_ext = E->ext;
-        }
-        {
-            auto E = shortest(emit_bwd);
-            int64_t halo = 0;
-            for (int i = 0; i < E->pg.n_instr; i++)  // (the reach of the hand-overs of the program that was chosen)
-                if (E->pg.ins[i].op == OP_XADD) halo = std::max(halo, E->reach_of[i]);
-            set_geometry(E->pg, dag, C, halo, !smc.empty());
-            out.bwd = E->pg;
-            out.bwd_ext = E->ext;
-            out.cost = program_cost(out.fwd) + program_cost(out.bwd);
-        }
+        // The variants of a program: backward also with the gradients of windows fetched by the source pixel, if that is
+        // cheaper by instructions x halo (bit 1; a 5x5 window under a product and an avg fold, 16x96 planes of 32x32: 368 -> 200 us); with softmaxes over channels also with values kept across the passes
+        // (bit 0), where the workgroup that suits the plain program has a thread for every channel anyway: 16x96 planes of
+        // 32x32 forward + backward 19.9 + 38.7 -> 16.9 + 26.5 us; a workgroup chosen for it lost more than the passes gained
+        // (128x64 planes of 56x56 backward 177 -> 252 us, 128x40 of 28x28 48.5 -> 75.4).  Where a chain is cut goes by the plain
+        // programs.  Returns the plain program's cost.
+        auto best_of = [&](const std::function<void(Emitter&)>& emit_program, bool backward, Program& pg, std::vector<ExtRef>& refs) {
+            double plain = -1, best = -1, best_geometry = 0;
+            for (int v = 0; v < 4; v++) {
+                const bool one_trip = v & 1, mirrors = v & 2;
+                if ((one_trip && smc.empty()) || (mirrors && (!backward || mirrored.empty()))) continue;
+                use_mirrors = mirrors;
+                // (fewer kept values where their registers leave no room for the threads that one trip takes)
+                for (int most_kept = regs_for(tm); most_kept >= (one_trip ? 1 : regs_for(tm)); most_kept--) {
+                    try {
+                        auto E = shortest(emit_program, one_trip, most_kept);
+                        most_kept = std::min(most_kept, (int)E->keep.size());
+                        int64_t halo = 0;
+                        for (int i = 0; i < E->pg.n_instr; i++)  // (the reach of the hand-overs of the program that was chosen)
+                            if (E->pg.ins[i].op == OP_XADD) halo = std::max(halo, E->reach_of[i]);
+                        const double geometry = set_geometry(E->pg, dag, C, halo, !smc.empty(), one_trip);
+                        const double cost = program_cost(E->pg);
+                        if (v == 0) plain = cost;
+                        if (v == 0 || (cost < best && (!one_trip || (geometry <= best_geometry * 1.001 && E->pg.vec == pg.vec)))) {
+                            best = cost;
+                            best_geometry = geometry;
+                            pg = E->pg;
+                            refs = E->ext;
+                        }
+                        break;
+                    } catch (const Fail&) {
+                        if (v == 0) throw;
+                    }
+                }
+            }
+            return plain;
+        };
+        out.cost = best_of(emit_fwd, false, out.fwd, out.fwd_ext);
+        out.cost += best_of(emit_bwd, true, out.bwd, out.bwd_ext);
         return true;
     } catch (const Fail& f) {
         why = f.why;
