@@ -1078,18 +1078,31 @@ Params shape(int N, int G, int R, int KH, int KW, int Og, int H, int W) {
     Q.Rp = (Q.gm * R + 15) / 16 * 16;
     const int Om = Q.gm * Og;
     Q.mo = Om <= 16 ? 1 : (Om <= 32 || KW > 1 ? 2 : 4);  // windows: the buffers of two groups leave room for 32 outputs
+    const int64_t tiles16 = ((int64_t)N * Q.upi + 15) / 16 * Q.Gm;
+    const int nrc = Q.Rp / 16;
+    const int most_split = nrc >= 4 ? 4 : (nrc >= 2 ? 2 : 1);
+    auto waves_of = [&](int mo) { return tiles16 * ((Om + 16 * mo - 1) / (16 * mo)); };
     if (Q.mo == 4) {
         // 64 outputs per wavefront need ~200 registers (two wavefronts per SIMD, 2 048 at once), 32 outputs ~124 (four,
         // 4 096): where the launch with 64 needs a second round of wavefronts and the one with 32 fits at once, 32 are
         // faster although the source is read once more
-        const int64_t tiles16 = ((int64_t)N * Q.upi + 15) / 16 * Q.Gm;
-        const int64_t w4 = tiles16 * ((Om + 63) / 64), w2 = tiles16 * ((Om + 31) / 32);
-        if (w4 > 2048 && w2 <= 4096) Q.mo = 2;
+        if (waves_of(4) > 2048 && waves_of(2) <= 4096) Q.mo = 2;
+    }
+    // Few pixels: the launch is as long as one wavefront's chain of loads, weight tile and split-K sum, and a tile of fewer
+    // outputs makes each of them shorter while the wavefronts still find room.  Without a window (us with 64 / 32 / 16
+    // outputs per tile): 1x256x14x14 7.5 / 6.1 / 5.4, 8x512x7x7 9.9 / 7.9 / 7.3, 8x256x14x14 7.9 / 6.2 / 5.9, 20x80x27x29 7.5 / 6.3 /
+    // 6.2; but 8x128x28x28 5.8 / 4.9 / 5.4, 32x128x28x28 7.9 / 6.9 / 7.9 (data gradient of 128 -> 9 outputs, one chunk: 8.6 / 6.5 /
+    // 5.3), and 128x256x14x14 14.7 / 17.7 / 26.6, 128x512x7x7 14.2 / 17.5 / 28.4.  With one, 32 / 16 outputs, forward and data
+    // gradient: 1x256x14x14 7.9 / 6.8, 16x256x14x14 8.2 + 10.3 / 7.1 + 8.0, 128x512x7x7 14.4 + 16.2 / 17.8 + 19.6.
+    if (KW == 1) {
+        if (Q.mo == 4 && (waves_of(2) * most_split <= 2048 || (nrc <= 8 && waves_of(2) * std::min(most_split, 2) <= 2048))) Q.mo = 2;
+        if (Q.mo == 2 && Om > 16 && (waves_of(1) * most_split <= 1024 || (nrc == 1 && waves_of(1) <= 2048))) Q.mo = 1;
+    } else if (Q.mo == 2 && Om > 16 && waves_of(1) * most_split <= 1024) {
+        Q.mo = 1;
     }
     Q.otiles = (Om + 16 * Q.mo - 1) / (16 * Q.mo);
     // few tiles with a long K loop: split the row chunks of a tile over 2 or 4 wavefronts
-    const int64_t waves = (((int64_t)N * Q.upi + 15) / 16) * Q.Gm * Q.otiles;
-    const int nrc = Q.Rp / 16;
+    const int64_t waves = waves_of(Q.mo);
     Q.ksplit = 1;
     // (only while all wavefronts are resident at once, two per SIMD: a second round of wavefronts costs more than the
     // longer K loop; C=128, 28x28, N=128, 64 outputs per tile: 1 568 wavefronts unsplit 13.8 us, 3 136 split by two 17.1 us,
