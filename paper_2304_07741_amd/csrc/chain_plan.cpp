@@ -928,28 +928,13 @@ class Emitter {
 
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
-// Workgroup shape for V pixels per thread and `pt` threads per slice: tile and halo, channel range and slices.
+// Workgroup shape for the pixels per thread already set and `pt` threads per slice (at most `cap`): tile and halo (`own`
+// threads of the tile store, HT more on either side), channel range and slices.
 // Returns the estimated cost of the launch (arbitrary units, see set_geometry) or a negative number when it does not fit.
-double geometry_for(Program& pg, const Dag& dag, int C, int64_t reach_px, bool all_channels, bool one_trip, bool one_copy, int V, int pt, int trips) {
-    const int HW = dag.H * dag.W;
-    pg.vec = V;
-    pg.unroll = unroll_for(pg.tm, V);
-    pg.persist_copies = one_copy ? 1 : pg.unroll;
-    const int PP = HW / V;                                   // pixel threads of a plane
-    const int64_t HT = (reach_px + V - 1) / V;               // halo, in pixel threads
-    const int per_thread = std::max<int>(1, (int)lds_bytes_per_thread(pg));
-    const int cap = (int)(std::min<int64_t>(max_threads_for(pg.tm), (int64_t)kMaxLdsBytes / per_thread) / 64 * 64);
-    if (cap < 64 || pt > cap || 2 * HT >= pt) return -1;
-    int own = pt - 2 * (int)HT;
-    if (own >= PP) {  // the whole plane in one tile
-        if (ceil_div(PP + 2 * (int)HT, 64) * 64 != pt) return -1;  // (counted once, at its own size)
-        own = PP;
-    } else {
-        own = ceil_div(PP, ceil_div(PP, own));  // tiles evened out over the plane
-    }
+double geometry_for(Program& pg, const Dag& dag, int C, bool all_channels, bool one_trip, int PP, int HT, int cap, int own, int pt, int trips) {
     pg.pix_threads = pt;
     pg.own_threads = own;
-    pg.halo_threads = (int)HT;
+    pg.halo_threads = HT;
     pg.tiles = ceil_div(PP, own);
     // channel slices: the loads of different channels are independent, so threads are worth more than trips
     const int max_slices = std::max(1, cap / pt);
@@ -974,12 +959,12 @@ double geometry_for(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
     const double threads_total = (double)dag.N * pg.tiles * pg.chunks * pg.threads;
     // (the instances with 9 lanes x 4 pixels and with 25 lanes hold more than 128 vector registers: two wavefronts per
     // SIMD, not four)
-    const double resident_threads = (pg.tm > 9 || (pg.tm > 1 && V >= 4)) ? 512.0 : 1024.0;
+    const double resident_threads = (pg.tm > 9 || (pg.tm > 1 && pg.vec >= 4)) ? 512.0 : 1024.0;
     const double wgs_per_cu = std::max(1.0, std::min(resident_threads / pg.threads, std::floor(160.0 * 1024.0 / (double)(lds_bytes(pg) + 4352))));
     // (whole rounds: a round that a few left-over workgroups make takes as long as a full one)
     const double rounds = std::max(1.0, std::ceil(threads_total / (256.0 * wgs_per_cu * pg.threads) - 0.05));
     // (a work item also costs its set-up: the thread's position, the pass headers; worth about 6 of these units)
-    return (6.0 + trips_per_thread * (8.0 + (V + 4.0) * pg.unroll)) * rounds;
+    return (6.0 + trips_per_thread * (8.0 + (pg.vec + 4.0) * pg.unroll)) * rounds;
 }
 
 // Pixels per thread, threads per slice and trips per thread: whatever the estimate likes best.
@@ -1000,24 +985,38 @@ double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
     for (int p = 0; p < pg.n_pass; p++)
         for (int i = pg.pass[p].body_begin; i < pg.pass[p].body_end; i++)
             if (pg.ins[i].op == OP_PSET || pg.ins[i].op == OP_PADD || pg.ins[i].op == OP_PLD || pg.ins[i].op == OP_XADD) one_copy = false;
-    int best[3] = {0, 0, 0};
+    Program best_shape = pg;
     double best_cost = -1;
     for (int V = max_vec_for(pg.tm); V >= 1; V /= 2) {
         if (HW % V != 0 || dag.W < V) continue;
-        for (int pt = 64; pt <= max_threads_for(pg.tm); pt += 64)
-            for (int trips = 1; trips <= (all_channels ? 1 : 8); trips *= 2) {
-                const double cost = geometry_for(pg, dag, C, reach_px, all_channels, one_trip, one_copy, V, pt, trips);
-                if (cost < 0) continue;
-                if (best_cost < 0 || cost < best_cost * 0.999) {  // (ties: the wider vector, the smaller workgroup, fewer trips)
-                    best_cost = cost;
-                    best[0] = V;
-                    best[1] = pt;
-                    best[2] = trips;
-                }
+        pg.vec = V;
+        pg.unroll = unroll_for(pg.tm, V);
+        pg.persist_copies = one_copy ? 1 : pg.unroll;
+        const int PP = HW / V;                                   // pixel threads of a plane
+        const int64_t HT = (reach_px + V - 1) / V;               // halo, in pixel threads
+        const int per_thread = std::max<int>(1, (int)lds_bytes_per_thread(pg));
+        const int cap = (int)(std::min<int64_t>(max_threads_for(pg.tm), (int64_t)kMaxLdsBytes / per_thread) / 64 * 64);
+        for (int pt = 64; pt <= cap; pt += 64) {
+            if (2 * HT >= pt) continue;
+            int own = pt - 2 * (int)HT;
+            if (own >= PP) {  // the whole plane in one tile
+                if (ceil_div(PP + 2 * (int)HT, 64) * 64 != pt) break;  // (counted once, at its own size)
+                own = PP;
+            } else {
+                own = ceil_div(PP, ceil_div(PP, own));  // tiles evened out over the plane
             }
+            for (int trips = 1; trips <= (all_channels ? 1 : 8); trips *= 2) {
+                const double cost = geometry_for(pg, dag, C, all_channels, one_trip, PP, (int)HT, cap, own, pt, trips);
+                if (cost >= 0 && (best_cost < 0 || cost < best_cost * 0.999)) {  // (ties: the wider vector, the smaller workgroup, fewer trips)
+                    best_cost = cost;
+                    best_shape = pg;
+                }
+                if (pg.chunks == 1) break;  // (more trips give the same shape)
+            }
+        }
     }
     if (best_cost < 0) throw Fail{"tile, halo and persistent state do not fit one workgroup"};
-    (void)geometry_for(pg, dag, C, reach_px, all_channels, one_trip, one_copy, best[0], best[1], best[2]);
+    pg = best_shape;
     return best_cost;
 }
 
@@ -1045,7 +1044,7 @@ bool chain_candidate(const Dag& dag, int k) {
     }
 }
 
-bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vector<bool>& is_output, UnitPlan& out, std::string& why) {
+bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vector<bool>& is_output, bool variants, UnitPlan& out, std::string& why) {
     try {
         if (nodes.empty()) throw Fail{"empty unit"};
         std::vector<bool> in_unit(dag.nodes.size(), false);
@@ -1140,7 +1139,7 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
         // Leaves read through a window whose gradient the source pixel fetches (Emitter::mirror), found by trying.
         std::set<int> mirrored;
         for (int i : leaves) {
-            if (!G.ctxs[G.insts[i].ctx].win) continue;
+            if (!variants || !G.ctxs[G.insts[i].ctx].win) continue;
             try {
                 Emitter trial(G, tm);
                 trial.mirror(i);
@@ -1291,7 +1290,7 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
             double plain = -1, best = -1, best_geometry = 0;
             for (int v = 0; v < 4; v++) {
                 const bool one_trip = v & 1, mirrors = v & 2;
-                if ((one_trip && smc.empty()) || (mirrors && (!backward || mirrored.empty()))) continue;
+                if ((one_trip && (!variants || smc.empty())) || (mirrors && (!backward || mirrored.empty()))) continue;
                 use_mirrors = mirrors;
                 // (fewer kept values where their registers leave no room for the threads that one trip takes)
                 for (int most_kept = regs_for(tm); most_kept >= (one_trip ? 1 : regs_for(tm)); most_kept--) {

@@ -39,7 +39,10 @@ bool chain_candidate(const Dag& dag, int k);
 // Compiles the unit `nodes` (ascending node ids, all chain candidates).  `is_output(k)`: node k of the unit must be
 // stored (it is the DAG's output or something outside the unit reads it).  Returns false (and says why) when the
 // unit does not fit the machine: a stencil above a reduction, too many instructions, registers, passes, LDS ...
-bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vector<bool>& is_output, UnitPlan& out, std::string& why);
+// `variants` false: only the plain programs, for the search over the chains, which asks for nothing but the answer and the
+// cost (both the same without them); eight random micro-DAGs take 1.7 ms to plan so, 4.0 with them in every attempt and every
+// attempt made again.
+bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vector<bool>& is_output, bool variants, UnitPlan& out, std::string& why);
 
 // Estimated work of a program per pixel and channel of the unit, in units of one cheap lane operation: a lane of a
 // tensor access counts 4, of a gradient hand-over 6, of a transcendental function 6; the whole is scaled by the pixels a

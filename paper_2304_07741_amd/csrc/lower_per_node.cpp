@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
+#include <map>
 #include <stdexcept>
 
 namespace canvas {
@@ -154,6 +155,16 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         return outp;
     };
     const bool log = std::getenv("CANVAS_LOG") != nullptr;
+    // What a chain of these nodes costs by its plain programs, negative where there is none (the search asks for some chains
+    // several times).
+    std::map<std::vector<int>, double> known_cost;
+    std::string why;
+    auto chain_cost = [&](const std::vector<int>& nodes) {
+        auto it = known_cost.find(nodes);
+        if (it != known_cost.end()) return it->second;
+        chain::UnitPlan plan;
+        return known_cost[nodes] = chain::compile_unit(dag, nodes, outputs_of(nodes), false, plan, why) ? plan.cost : -1.0;
+    };
     for (int k = 1; k < n; k++) {
         const Node& nd = dag.nodes[k];
         if (!nd.live || virt[k]) continue;
@@ -172,11 +183,8 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
                 if (!ok) continue;
                 std::vector<int> grown = units[u].nodes;
                 grown.push_back(k);
-                chain::UnitPlan plan;
-                std::string why;
-                if (chain::compile_unit(dag, grown, outputs_of(grown), plan, why)) {
+                if (chain_cost(grown) >= 0) {
                     units[u].nodes = grown;
-                    units[u].plan = plan;
                     unit_of[k] = u;
                     placed = true;
                     break;
@@ -184,14 +192,11 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
                 if (log) std::fprintf(stderr, "canvas: node %d does not join chain %d: %s\n", k, u, why.c_str());
             }
             if (!placed) {
-                chain::UnitPlan plan;
-                std::string why;
                 std::vector<int> alone{k};
-                if (chain::compile_unit(dag, alone, outputs_of(alone), plan, why)) {
+                if (chain_cost(alone) >= 0) {
                     Unit U;
                     U.chain = true;
                     U.nodes = alone;
-                    U.plan = plan;
                     units.push_back(U);
                     unit_of[k] = (int)units.size() - 1;
                     placed = true;
@@ -215,11 +220,9 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
     // softmax over channels of an unfolded tensor, whose passes each recompute the whole window.
     for (size_t u = 0; u < units.size(); u++) {
         if (!units[u].chain || units[u].nodes.size() < 2) continue;
-        std::string why;
-        chain::UnitPlan whole;
-        if (!chain::compile_unit(dag, units[u].nodes, outputs_of(units[u].nodes), whole, why)) continue;
         const std::vector<int> nodes = units[u].nodes;
-        double best = whole.cost;
+        const double whole = chain_cost(nodes);
+        double best = whole;
         size_t cut = 0;
         for (size_t i = 1; i < nodes.size(); i++) {
             const std::vector<int> A(nodes.begin(), nodes.begin() + i), Bn(nodes.begin() + i, nodes.end());
@@ -227,16 +230,16 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             for (int k : Bn)
                 for (int o : {dag.nodes[k].a, dag.nodes[k].b})
                     if (o > 0 && std::find(A.begin(), A.end(), o) != A.end() && dag.nodes[o].T != 1) taps = true;
-            chain::UnitPlan pa, pb;
-            if (!chain::compile_unit(dag, A, outputs_of(A), pa, why) || !chain::compile_unit(dag, Bn, outputs_of(Bn), pb, why)) continue;
-            const double apart = (pa.cost + pb.cost) / (taps ? 0.4 : 0.8);  // (as if the whole had to be that much dearer)
+            const double ca = chain_cost(A), cb = ca < 0 ? -1 : chain_cost(Bn);
+            if (cb < 0) continue;
+            const double apart = (ca + cb) / (taps ? 0.4 : 0.8);  // (as if the whole had to be that much dearer)
             if (apart < best) {
                 best = apart;
                 cut = i;
             }
         }
         if (cut == 0) continue;
-        if (log) std::fprintf(stderr, "canvas: chain %zu cut after %zu of %zu nodes: weighted cost %.0f apart, %.0f whole\n", u, cut, nodes.size(), best, whole.cost);
+        if (log) std::fprintf(stderr, "canvas: chain %zu cut after %zu of %zu nodes: weighted cost %.0f apart, %.0f whole\n", u, cut, nodes.size(), best, whole);
         Unit B;
         B.chain = true;
         B.nodes.assign(nodes.begin() + cut, nodes.end());
@@ -250,8 +253,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
     // other units, which never removes an output, but a later joiner of THIS unit may have: compile the final sets
     for (Unit& U : units)
         if (U.chain) {
-            std::string why;
-            if (!chain::compile_unit(dag, U.nodes, outputs_of(U.nodes), U.plan, why)) throw std::runtime_error("chain unit no longer compiles: " + why);
+            if (!chain::compile_unit(dag, U.nodes, outputs_of(U.nodes), true, U.plan, why)) throw std::runtime_error("chain unit no longer compiles: " + why);
             low->chain_units++;
             low->chain_nodes += (int)U.nodes.size();
             if (log) {
