@@ -806,15 +806,39 @@ void prepare_forward(Params& p, bool may_split) {
 
 // Slices of whole steps, for about `workgroups` of them.
 static void split(Params& p, int workgroups, int step, int64_t max_partial_bytes) {
-    const int64_t tiles = (int64_t)p.ktiles * p.mtiles * p.G;
-    const int64_t steps = (p.M + step - 1) / step;
+    const int64_t tiles = (int64_t)p.ktiles * p.mtiles * p.G * (p.split ? p.KH : 1);
+    const int64_t places = p.split ? p.N * p.HP * p.Wp : p.M;
+    const int64_t steps = (places + step - 1) / step;
     const int64_t bytes = (int64_t)p.G * p.Og * p.K * 4;
     int64_t slices = std::max<int64_t>(1, workgroups / tiles);
+    if (p.split && steps <= 4) slices = 1;  // (a step takes 1.2 us, the launch that sums two slices 4.1)
     slices = std::min(slices, steps);
     slices = std::min(slices, std::max<int64_t>(1, max_partial_bytes / std::max<int64_t>(1, bytes)));
     p.per_slice = (steps + slices - 1) / slices * step;
-    p.slices = (int)((p.M + p.per_slice - 1) / p.per_slice);
+    p.slices = (int)((places + p.per_slice - 1) / p.per_slice);
     p.tiles = p.slices * tiles;
+}
+
+// Weight gradient on the bf16 matrix units, behind a 3 x 3 window where a tile of 32 x 32 is filled (fp32 units / here, us): 64
+// channels 32x28x28 46.5 / 28.0, 1x28x28 10.3 / 7.9, 32x7x7 11.2 / 9.0; 128 channels 32x14x14 45.4 / 30.5, 16x56x20 95 / 62;
+// eight groups of 32 32x14x14 43.6 / 21.5, of 64 16x7x7 22.0 / 15.2; 48 channels 6x23x17 11.4 / 8.7; 32 channels 32x28x28
+// 22.7 / 14.7, 4x28x28 7.7 / 7.5; 64 channels 1x8x8 9.8 / 9.7.
+static bool split_wgrad(Params& p, int64_t max_partial_bytes) {
+    if (p.KH != 3 || p.KW != 3 || p.Og < 32 || p.R < 32) return false;
+    Params q = p;
+    q.split = 1;
+    q.wm = q.Og > 32 ? 2 : 1;
+    q.mtiles = (q.Og + 32 * q.wm - 1) / (32 * q.wm);
+    q.ktiles = (q.R + 31) / 32;
+    q.HP = q.H + 1;
+    q.Wp = q.W + 1;
+    q.mWp = (uint32_t)((((uint64_t)1 << 32) + q.Wp - 1) / q.Wp);
+    // 32-bit byte offsets within the tensors, exact quotients
+    if (q.N * q.G * std::max(q.R, q.Og) * (int64_t)q.P >= (int64_t)1 << 30 || (int64_t)q.HP * q.Wp * q.Wp >= (int64_t)1 << 31 || q.N * q.HP * q.Wp >= (int64_t)1 << 31)
+        return false;
+    split(q, 2 * 256, kPix, max_partial_bytes);
+    p = q;
+    return true;
 }
 
 void prepare_wgrad(Params& p, int64_t max_partial_bytes) {
@@ -827,6 +851,7 @@ void prepare_wgrad(Params& p, int64_t max_partial_bytes) {
         split(p, 4096, kNarrowPix, max_partial_bytes);
         return;
     }
+    if (split_wgrad(p, max_partial_bytes)) return;
     p.S = win ? window_positions(p, kPix) : kPix;
     p.CS = win ? up(p.S, 2, 1) : up(p.S, 64, 4);
     // outputs: one or two 16-tiles per wavefront, one or two wavefronts across them
@@ -935,6 +960,10 @@ void wgrad_partial(const Params& p, hipStream_t s) {
         default: CANVAS_SFC(4); break;
         }
 #undef CANVAS_SFC
+        return;
+    }
+    if (p.split) {
+        wgrad_split(p, grid, s);
         return;
     }
     const size_t lds = wgrad_lds(p);

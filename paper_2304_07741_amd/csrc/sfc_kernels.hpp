@@ -29,8 +29,10 @@ struct Params {
     int ktiles = 1, mtiles = 1, nch = 0, slices = 1;
     // narrow: few rows and outputs per group, one thread per pixel on the vector unit; ot outputs, vec pixels per thread
     int narrow = 0, ot = 1, vec = 1;
-    int split = 0;  // forward: operands cut into three bf16 parts; 32*wm outputs x 32*(4/wm) pixels
-    int64_t per_slice = 0;                             // pixels per slice
+    // operands cut into three bf16 parts; forward: 32*wm outputs x 32*(4/wm) pixels; weight gradient: 32*wm outputs x 32 rows x
+    // one window row, with HP = H + 1 and Wp = W + 1
+    int split = 0;
+    int64_t per_slice = 0;                             // pixels per slice; split: positions
     int64_t tiles = 0;                                 // workgroups with work
 };
 
@@ -46,9 +48,10 @@ void prepare_forward(Params& p, bool may_split = false);
 // Splits the pixels over slices, at most max_partial_bytes of partials (0: one slice, written straight to dw).
 void prepare_wgrad(Params& p, int64_t max_partial_bytes);
 
-// The kernels of sfc_split_kernels.hip: forward with Params::split, and the LDS it takes (at most kMaxSplitLds).
+// The kernels of sfc_split_kernels.hip: forward and weight gradient with Params::split, and the LDS forward takes (at most kMaxSplitLds).
 constexpr int kMaxSplitLds = 128 * 1024;
 void forward_split(const Params& p, dim3 grid, hipStream_t s);
+void wgrad_split(const Params& p, dim3 grid, hipStream_t s);
 size_t split_lds(const Params& p);
 
 // The weights that a split contraction reads (Params::wsplit): 48 * items bytes at `out`, from w as Params::w.

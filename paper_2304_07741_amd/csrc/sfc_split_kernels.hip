@@ -4,6 +4,7 @@
 // each exact in the matrix unit.  v_mfma_f32_32x32x16_bf16 does 16 times the work of the fp32 instruction, six of them 2.7
 // times.
 #include <algorithm>
+#include <type_traits>
 
 #include "launch.hpp"
 #include "sfc_device.hpp"
@@ -248,6 +249,271 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     }
 }
 
+constexpr int kXRow = 36;  // dwords of a channel's row of the operand tile: 34 pairs of positions, 16-byte pieces in different banks
+
+// Weight gradient behind a 3 x 3 window, with the same parts and products.  A workgroup owns 32*WM outputs x 32 channels x the
+// three taps of one window row and one slice of the batch's positions; a wavefront 32 outputs x 32 channels x three taps of
+// every (4/WM)th part of a step, the depth of a matrix instruction being sixteen positions.  Positions are those of the image
+// with one zero column behind each row and one zero row behind each image, so that a tap is a constant distance and needs no
+// mask: dy is zero in the margin, x too.  64 positions of dy and 68 of x, from two before the window row's first, go cut into
+// LDS, [part][row][position], where a lane finds eight positions of its output or channel in one 16-byte read; the taps to the
+// left and right are the same dwords moved by one position.
+// Sums: per step the five small products first, then the leading ones, in one chain; the steps in a row in fp32, the
+// wavefronts' sums at the end.  The matrix unit cuts off what its sums cannot hold, always downwards: over the thousands of steps
+// of a batch that adds up (3.6e-7 of the result at 32 channels, 32x28x28), so every other step multiplies -dy.  Results that are not finite are summed again in fp32, in the slice they occurred in.
+// Bound by the vector instructions that cut and stage the operands, about 510 per wavefront and step (half of a wavefront's life at
+// two per SIMD; its 36 matrix instructions a quarter).  N=32, C=64, 28x28: 28 us (66 TFLOP/s), k_wgrad 46.5; 128 channels 32x14x14
+// 30.5 / 45.4, 384 in eight groups 51 / 73.  Errors against fp64: 1.04e-7 and 9.1e-8, k_wgrad's 1.15 and 1.02e-7.
+template <int WM>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad_split(Params Q) {
+    constexpr int WS = 4 / WM, NS = 4 / WS;               // wavefronts that share a tile's steps, matrix steps of each
+    constexpr int AR = 32 * WM;                           // rows of dy
+    constexpr int APART = AR * 32, XPART = 32 * kXRow;    // dwords of a part
+    constexpr int BUF = 3 * (APART + XPART);
+    extern __shared__ u32x4 lds_split[];  // [2][BUF] dwords
+    uint32_t* const lds = reinterpret_cast<uint32_t*>(lds_split);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, half = lane >> 5;
+    const int wm = wave % WM, ws = wave / WM;
+    unsigned b = tile_of_block();
+    if (b >= (unsigned)Q.tiles) return;
+    const int kh = (int)(b % 3u);  // (neighbours in the launch: they read the same rows, and write the same lines)
+    b /= 3u;
+    const int mtile = (int)(b % (unsigned)Q.mtiles);
+    b /= (unsigned)Q.mtiles;
+    const int ctile = (int)(b % (unsigned)Q.ktiles);
+    b /= (unsigned)Q.ktiles;
+    const int g = (int)(b % (unsigned)Q.G);
+    const int slice = (int)(b / (unsigned)Q.G);
+    const int o0 = mtile * AR, r0 = ctile * 32;
+    const int rows = min(AR, Q.Og - o0), chans = min(32, Q.R - r0);
+    const int HPW = Q.HP * Q.Wp;
+    const int64_t end = Q.N * HPW;
+    const int64_t first = slice * Q.per_slice, last = min(end, first + Q.per_slice);
+
+    const float* const ds = Q.dy + ((int64_t)g * Q.Og + o0) * Q.P;
+    const float* const xs = Q.src + ((int64_t)g * Q.R + r0) * Q.P;
+    // Two neighbouring positions: image and place in it of the first; what they hold comes from an element offset or is zero.
+    struct Pair {
+        int n, rem;
+    };
+    auto place = [&](int64_t q) {
+        Pair at;
+        if (q < 0) {  // (before the first image)
+            at.n = -1;
+            at.rem = (int)q + HPW;  // (a row and two positions at most, and an image has two rows of two)
+        } else {
+            at.n = (int)(q / HPW);
+            at.rem = (int)(q - (int64_t)at.n * HPW);
+        }
+        return at;
+    };
+    auto advance = [&](Pair& at) {
+        at.rem += 64;
+        while (at.rem >= HPW) {
+            at.rem -= HPW;
+            at.n++;
+        }
+    };
+    auto offsets = [&](const Pair& at, int rowlen, uint32_t (&off)[2], bool (&in)[2]) {
+        int n = at.n, h = quotient(at.rem, Q.Wp, Q.mWp), w = at.rem - h * Q.Wp;
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+            in[e] = (unsigned)n < (unsigned)Q.N && h < Q.H && w < Q.W;
+            off[e] = in[e] ? (uint32_t)(n * rowlen + h * Q.W + w) : 0u;
+            if (++w == Q.Wp) {
+                w = 0;
+                if (++h == Q.HP) {
+                    h = 0;
+                    n++;
+                }
+            }
+        }
+    };
+    const int pair = tid & 31, rr = tid >> 5;  // this thread's positions of the step and its first row (of every eighth)
+    const int64_t xfirst = first + (int64_t)(kh - 1) * Q.Wp - 2;
+    Pair da = place(first + 2 * pair), xa = place(xfirst + 2 * pair), xe = place(xfirst + 64 + 2 * (tid & 1));
+    const int dlen = Q.G * Q.Og * Q.P, xlen = Q.G * Q.R * Q.P;
+    constexpr int DN = AR / 8;
+    float dreg[DN][2], xreg[4][2], ereg[2];
+    bool din[2], xin[2], ein[2];
+    // `n` pairs of every eighth row from this thread's first on; byte offsets from uniform addresses where the tile is whole
+    auto at = [](const float* base, uint32_t elem) { return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + elem * 4u); };
+    auto load_rows = [&](const float* from, const uint32_t (&off)[2], int have, auto& to, auto count) {
+        constexpr int n = decltype(count)::value;
+        if (have == n * 8) {
+            const uint32_t ro = (uint32_t)(rr * Q.P);
+#pragma unroll
+            for (int i = 0; i < n; i++)
+#pragma unroll
+                for (int e = 0; e < 2; e++) to[i][e] = at(from + (int64_t)i * 8 * Q.P, off[e] + ro);
+        } else {
+#pragma unroll
+            for (int i = 0; i < n; i++)
+#pragma unroll
+                for (int e = 0; e < 2; e++) to[i][e] = at(from, off[e] + (uint32_t)(min(i * 8 + rr, have - 1) * Q.P));
+        }
+    };
+    auto load = [&]() {
+        uint32_t off[2];
+        offsets(da, dlen, off, din);
+        load_rows(ds, off, rows, dreg, std::integral_constant<int, DN>());
+        advance(da);
+        offsets(xa, xlen, off, xin);
+        load_rows(xs, off, chans, xreg, std::integral_constant<int, 4>());
+        advance(xa);
+        if (wave == 0) {  // the last two pairs of the 32 rows
+            offsets(xe, xlen, off, ein);
+#pragma unroll
+            for (int e = 0; e < 2; e++) ereg[e] = at(xs, off[e] + (uint32_t)(min(tid >> 1, chans - 1) * Q.P));
+            advance(xe);
+        }
+    };
+    auto put = [&](uint32_t* to, int part, const float (&v)[2]) {
+        const uint32_t h = tile::pack_bf16(v[0], v[1]);
+        const float m0 = v[0] - tile::lo_f32(h), m1 = v[1] - tile::hi_f32(h);
+        const uint32_t m = tile::pack_bf16(m0, m1);
+        to[0] = h;
+        to[part] = m;
+        to[2 * part] = tile::pack_bf16(m0 - tile::lo_f32(m), m1 - tile::hi_f32(m));
+    };
+    auto store = [&](uint32_t* to, float sign) {  // (zero in the margin and past the last row)
+#pragma unroll
+        for (int i = 0; i < DN; i++) {  // (the 16-byte pieces of a row change places with its number: reads of 32 rows in different banks)
+            const int row = i * 8 + rr;
+            float v[2];
+#pragma unroll
+            for (int e = 0; e < 2; e++) v[e] = din[e] && row < rows ? dreg[i][e] * sign : 0.f;
+            put(to + row * 32 + (((pair >> 2) ^ (row & 7)) << 2) + (pair & 3), APART, v);
+        }
+        uint32_t* const x = to + 3 * APART;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int row = i * 8 + rr;
+            float v[2];
+#pragma unroll
+            for (int e = 0; e < 2; e++) v[e] = xin[e] && row < chans ? xreg[i][e] : 0.f;
+            put(x + row * kXRow + pair, XPART, v);
+        }
+        if (wave == 0) {
+            float v[2];
+#pragma unroll
+            for (int e = 0; e < 2; e++) v[e] = ein[e] && (tid >> 1) < chans ? ereg[e] : 0.f;
+            put(x + (tid >> 1) * kXRow + 32 + (tid & 1), XPART, v);
+        }
+    };
+    f16v total[3];
+#pragma unroll
+    for (int t = 0; t < 3; t++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) total[t][r] = 0.f;
+    uint32_t *cur = lds, *next = lds + BUF;
+    // (sign of dy in the step that begins at q)
+    auto sign_of = [](int64_t q) { return (q >> 6) & 1 ? -1.f : 1.f; };
+    load();
+    store(cur, sign_of(first));
+    for (int64_t q = first; q < last; q += 64) {
+        __syncthreads();  // (this step is written, and the other buffer has been read)
+        const bool more = q + 64 < last;
+        if (more) load();
+        f16v sum[3];
+#pragma unroll
+        for (int t = 0; t < 3; t++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) sum[t][r] = 0.f;
+        u32x4 lead_a[NS], lead_b[NS][3];
+#pragma unroll
+        for (int s = 0; s < NS; s++) {
+            const int piece = (ws * NS + s) * 2 + half;  // this lane's eight positions
+            const int arow = wm * 32 + col;
+            u32x4 a[3], x[3][3];
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                a[k] = *reinterpret_cast<const u32x4*>(cur + k * APART + arow * 32 + ((piece ^ (arow & 7)) << 2));
+                const uint32_t* const from = cur + 3 * APART + k * XPART + col * kXRow + piece * 4;
+                const u32x4 lo = *reinterpret_cast<const u32x4*>(from);
+                const uint2 hi = *reinterpret_cast<const uint2*>(from + 4);
+                const uint32_t d[6] = {lo[0], lo[1], lo[2], lo[3], hi.x, hi.y};
+#pragma unroll
+                for (int v = 0; v < 4; v++) {
+                    x[0][k][v] = __builtin_amdgcn_alignbit(d[v + 1], d[v], 16);
+                    x[1][k][v] = d[v + 1];
+                    x[2][k][v] = __builtin_amdgcn_alignbit(d[v + 2], d[v + 1], 16);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 3; t++) sum[t] = mfma(a[2], x[t][0], sum[t]);
+#pragma unroll
+            for (int t = 0; t < 3; t++) sum[t] = mfma(a[0], x[t][2], sum[t]);
+#pragma unroll
+            for (int t = 0; t < 3; t++) sum[t] = mfma(a[1], x[t][1], sum[t]);
+#pragma unroll
+            for (int t = 0; t < 3; t++) sum[t] = mfma(a[1], x[t][0], sum[t]);
+#pragma unroll
+            for (int t = 0; t < 3; t++) sum[t] = mfma(a[0], x[t][1], sum[t]);
+            lead_a[s] = a[0];
+#pragma unroll
+            for (int t = 0; t < 3; t++) lead_b[s][t] = x[t][0];
+        }
+#pragma unroll
+        for (int s = 0; s < NS; s++)
+#pragma unroll
+            for (int t = 0; t < 3; t++) sum[t] = mfma(lead_a[s], lead_b[s][t], sum[t]);
+#pragma unroll
+        for (int t = 0; t < 3; t++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) total[t][r] = fmaf(sum[t][r], sign_of(q), total[t][r]);
+        if (more) store(next, sign_of(q + 64));
+        uint32_t* const t = cur;
+        cur = next;
+        next = t;
+    }
+    // the sums of the wavefronts that shared the tile
+    __syncthreads();
+    float* const share = reinterpret_cast<float*>(lds_split);  // [WS - 1][WM][3 * 16][64]
+    if (ws > 0) {
+#pragma unroll
+        for (int t = 0; t < 3; t++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) share[(((ws - 1) * WM + wm) * 48 + t * 16 + r) * 64 + lane] = total[t][r];
+    }
+    __syncthreads();
+    if (ws > 0) return;
+#pragma unroll
+    for (int k = 0; k < WS - 1; k++)
+#pragma unroll
+        for (int t = 0; t < 3; t++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) total[t][r] += share[((k * WM + wm) * 48 + t * 16 + r) * 64 + lane];
+    // lane: channel `col`, outputs r % 4 + 8 * (r / 4) + 4 * half
+    if (col >= chans) return;
+    const int ob = wm * 32 + 4 * half;
+    float* const dw = Q.partial + (((int64_t)slice * Q.G + g) * Q.Og + o0) * Q.K + (int64_t)(r0 + col) * 9 + kh * 3;
+    uint64_t again = 0;
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+        const int o = ob + r % 4 + 8 * (r / 4);
+        if (o >= rows) continue;
+#pragma unroll
+        for (int t = 0; t < 3; t++) {
+            dw[(int64_t)o * Q.K + t] = total[t][r];
+            if (!(fabsf(total[t][r]) <= 3.4e38f)) again |= (uint64_t)1 << (r * 3 + t);
+        }
+    }
+    while (again) {
+        const int k = __ffsll((unsigned long long)again) - 1, r = k / 3, t = k - r * 3, o = ob + r % 4 + 8 * (r / 4);
+        again &= again - 1;
+        float sum = 0.f;
+        for (int64_t q = first; q < last; q++) {
+            const int n = (int)(q / HPW), rem = (int)(q - (int64_t)n * HPW), h = rem / Q.Wp, w = rem - h * Q.Wp;
+            const int y = h + kh - 1, x = w + t - 1;
+            if (h >= Q.H || w >= Q.W || (unsigned)y >= (unsigned)Q.H || (unsigned)x >= (unsigned)Q.W) continue;
+            sum = fmaf(ds[(int64_t)n * dlen + (int64_t)o * Q.P + h * Q.W + w], xs[(int64_t)n * xlen + (int64_t)col * Q.P + y * Q.W + x], sum);
+        }
+        dw[(int64_t)o * Q.K + t] = sum;
+    }
+}
+
 // The weights of a contraction in the order in which k_fwd_split reads them: [group][32 outputs][step][part][lane], a lane's
 // output lane % 32 and its eight channels from 8 * (lane / 32) of the step's sixteen; zero past the last output and channel.
 __global__ __launch_bounds__(kThreads) void k_split_weights(SplitJobs jobs) {
@@ -319,6 +585,21 @@ void forward_split(const Params& p, dim3 grid, hipStream_t s) {
         if (items <= 2) launch_one<1, 9, 2>(p, grid, s);
         else if (items == 3) launch_one<1, 9, 3>(p, grid, s);
         else launch_one<1, 9, 4>(p, grid, s);
+    }
+}
+
+static size_t wgrad_split_lds(const Params& p) { return (size_t)4 * 2 * 3 * (32 * p.wm * 32 + 32 * kXRow); }
+
+void wgrad_split(const Params& p, dim3 grid, hipStream_t s) {
+    const dim3 block(kThreads);
+    const size_t lds = wgrad_split_lds(p);
+    auto allow = [](const void* f) { return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxSplitLds); };
+    if (p.wm == 2) {
+        static const hipError_t ok = allow((const void*)k_wgrad_split<2>);
+        (void)ok;
+        CANVAS_LAUNCH((k_wgrad_split<2>), grid, block, lds, s, p);
+    } else {
+        CANVAS_LAUNCH((k_wgrad_split<1>), grid, block, lds, s, p);
     }
 }
 

@@ -113,3 +113,49 @@ def test_result_on_top_of_an_input(what):
     r.close()
     ref = canvas_oracle.run(case["blob"], case["x"], case["weights"], dy.reshape(2, 64, 12, 12))["y"]
     assert np.abs(got.reshape(ref.shape) - ref).max() <= 1e-5 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("shape,o,groups", [((1, 32, 1, 9), 33, 1), ((3, 40, 7, 7), 32, 1), ((40, 64, 13, 17), 97, 1), ((9, 192, 11, 6), 192, 4)])
+def test_weight_gradient(shape, o, groups):
+    """Weight gradients of one slice and of many, ragged tiles of outputs and channels; an infinity, a NaN and a value whose bf16 is
+    infinite reach exactly the weights whose products meet them."""
+    import torch
+
+    N, C, H, W = shape
+    r = harness.DagRunner(WIN.format(g=groups, o=o), shape, "f32")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    for t in [r.x, r.dy, *r.w]:
+        t.copy_(torch.randn(t.shape, generator=g, device="cuda"))
+    for extreme in [False, True]:
+        if extreme:
+            r.x[0, 3, 0, 0], r.x[N - 1, C - 1, H - 1, W - 1], r.x[0, 20, 0, W // 2] = float("inf"), float("nan"), 3.4e38
+            r.dy.view(N, o, H, W)[0, 1, 0, 1] = -float("inf")
+            r.dy.mul_(0.25)  # (3.4e38 times dy is finite)
+        r.poison_outputs()
+        r.ws.fill_(0xFF)
+        r.forward()
+        r.backward()
+        got = r.dw[0].cpu().double().reshape(o, C // groups, 3, 3)
+        xp = torch.nn.functional.pad(r.x.cpu().double(), (1, 1, 1, 1))
+        dy = r.dy.cpu().double().view(N, o, H, W)
+        og, cg = o // groups, C // groups
+        ref = torch.empty_like(got)
+        for k in range(groups):
+            d = dy[:, k * og:(k + 1) * og].transpose(0, 1).reshape(og, -1)
+            for i in range(3):
+                for j in range(3):
+                    v = xp[:, k * cg:(k + 1) * cg, i:i + H, j:j + W]
+                    # (pixels whose x lies in the margin take no part, whatever dy is there)
+                    inside = torch.nn.functional.pad(torch.ones(H, W), (1, 1, 1, 1))[i:i + H, j:j + W].bool().expand(N, H, W).reshape(-1)
+                    ref[k * og:(k + 1) * og, :, i, j] = d[:, inside] @ v.transpose(0, 1).reshape(cg, -1)[:, inside].T
+        if not extreme:
+            # (N*H*W terms of unit variance: some 2^-24 of the sum's root mean square per hundred of them, in any order)
+            assert (got - ref).norm() <= 1e-6 * ref.norm()
+            continue
+        finite = torch.isfinite(ref) & (ref.abs() < 3e38)
+        assert torch.equal(torch.isnan(got), torch.isnan(ref)) and not torch.isfinite(got[torch.isinf(ref)]).any()
+        err = (got - ref).abs()[finite]
+        assert (err <= 1e-5 * ref.abs()[finite].clamp_min(float(N * H * W) ** 0.5)).all()
+        assert torch.isfinite(got).any() and not torch.isfinite(got).all()
+    r.close()
