@@ -117,7 +117,7 @@ typedef struct canvas_dag_info {
     int32_t out_node;
     int32_t n_weights;                        /* number of fc nodes */
     int32_t n_launches_fwd, n_launches_bwd;   /* kernels enqueued per call */
-    int32_t fused;                            /* 1 when one of the whole-DAG kernel families was chosen, else 0 (lowering by units) */
+    int32_t fused;                            /* 1 when one of the whole-DAG kernel families was chosen, else 0 (lowering by units; also the shift / FC family on planes that are no multiple of 8 pixels or narrower) */
     int32_t n_launches_prepare;               /* inference plans: kernels canvas_dag_prepare enqueues, else 0 */
     int32_t n_fused_chains;                   /* lowering by units: chains of memory-bound nodes fused into one kernel each */
     int64_t out_shape[5];                     /* N, C, T, H, W */

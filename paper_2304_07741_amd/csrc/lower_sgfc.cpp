@@ -59,7 +59,7 @@ std::unique_ptr<Lowering> lower_sgfc(const Dag& dag, bool bf16) {
         P.dw[g] = sdw[g * CG];
     }
     const int Pn = dag.P();
-    if (Pn % 8 || dag.W < 8 || (int64_t)Pn * dag.W >= ((int64_t)1 << 31)) return nullptr;
+    if (dag.W < 2 || (int64_t)Pn * dag.W >= ((int64_t)1 << 31)) return nullptr;
     // tensors are addressed with 32-bit byte offsets through buffer descriptors
     if ((int64_t)dag.N * std::max(C, fc.out) * Pn * 2 >= ((int64_t)1 << 31) || dag.N > 65535) return nullptr;
     if ((int64_t)dag.N * ((Pn + 127) / 128) * ((Pn + 127) / 128) >= ((int64_t)1 << 31)) return nullptr;
@@ -87,7 +87,7 @@ std::unique_ptr<Lowering> lower_sgfc(const Dag& dag, bool bf16) {
     P.wgs_per_group = (tiles_per_group + 4 * tpw - 1) / (4 * tpw);
 
     auto low = std::make_unique<Lowering>();
-    low->fused = true;
+    low->fused = Pn % 8 == 0 && dag.W >= 8;  // (what the query has always reported: planes of whole 8-pixel units)
     low->strided_io = true;
     const int elems = OG * CG;
     low->ws_bytes = align_up((uint64_t)G * P.wgs_per_group * elems * 4);

@@ -90,8 +90,26 @@ __device__ __forceinline__ float act_dz(const Params& P, float z, float dy) {
     return dy * unary_grad(ACT, z, P.ulo, P.uhi);
 }
 
+// Planes that are no multiple of eight pixels (RAG): a plane's last unit is `left` < 8 pixels of its own, then the next plane's.
+// Those are cleared where a sum over pixels would take them in and never stored, rows begin at any element, and an unshifted
+// access too can cross the tensor's end.  (The lowering by units, which such planes used to take: a step of N=6, 64 channels, 20x41 71.7 us, here
+// 19.3; N=64, 27x29 231, here 19.6; 64 => 128 channels N=5, 21x11 289, here 19.0.)
+template <bool RAG>
+__device__ __forceinline__ void store_unit(rsrc_t r, int off, const u32x4& v, int left) {
+    if (!RAG) {
+        bstore16_nt(r, off, v);
+    } else if (left >= 8) {
+        bstore16(r, off, v);  // (unaligned: kept in the cache until its lines are whole)
+    } else {
+#pragma unroll
+        for (int q = 0; q < 8; q++)
+            if (q < left) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(v[q >> 1] >> (16 * (q & 1))), r, off + 2 * q, 0, 0);
+    }
+}
+__device__ __forceinline__ u32x4 own_pixels(int left) { return mask_of(left >= 8 ? 0xffu : (left > 0 ? (1u << left) - 1u : 0u)); }
+
 // ------------------------------------------------------------------------------------------ forward
-template <int KC, int MO, int ACT, bool RES>
+template <int KC, int MO, int ACT, bool RES, bool RAG>
 __global__ __launch_bounds__(64 * kWaves) void k_fwd(Params P) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -141,6 +159,12 @@ __global__ __launch_bounds__(64 * kWaves) void k_fwd(Params P) {
                 xr[mo][j] = bload16_nt(rx, live ? xo + ((mo * 16 + 4 * r + j) * P.P + p) * 2 : kOob);
                 pin(xr[mo][j]);
             }
+        if (RAG && tile_near_ends(xo / 2, xo / 2 + (OG - 1) * P.P, p0, 0, xelems)) {
+#pragma unroll
+            for (int mo = 0; mo < MO; mo++)
+#pragma unroll
+                for (int j = 0; j < 4; j++) reload_if_partial(xr[mo][j], rx, live ? xo + ((mo * 16 + 4 * r + j) * P.P + p) * 2 : kOob, xelems * 2);
+        }
     }
 
     float4_t acc[MO][8];
@@ -177,7 +201,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_fwd(Params P) {
             u32x4 out;
 #pragma unroll
             for (int k = 0; k < 4; k++) out[k] = pack_bf16(v[2 * k], v[2 * k + 1]);
-            bstore16_nt(ry, live ? yo + ((mo * 16 + 4 * r + j) * P.P + p) * 2 : kOob, out);
+            store_unit<RAG>(ry, live ? yo + ((mo * 16 + 4 * r + j) * P.P + p) * 2 : kOob, out, P.P - p);
         }
 }
 
@@ -191,7 +215,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_fwd(Params P) {
 // wave-private LDS tile ([16 channels][128 pixels], rows padded to 272 bytes) to change distribution.
 constexpr int kLdsRow = 17;  // u32x4 per LDS row: 16 units + 1 pad
 
-template <int KC, int MO, int ACT, bool RES>
+template <int KC, int MO, int ACT, bool RES, bool RAG>
 __device__ __forceinline__ void bwd_tile(const Params& P, rsrc_t rx, rsrc_t rdy, rsrc_t rdx, u32x4* lds_x, u32x4* lds_dz, int n, int g,
                                          int p0, int lane, const short4_t (&wa)[MO][KC], const short4_t (&wt)[KC][MO],
                                          float4_t (&dwacc)[MO][KC]) {
@@ -212,6 +236,13 @@ __device__ __forceinline__ void bwd_tile(const Params& P, rsrc_t rx, rsrc_t rdy,
     for (int kc = 0; kc < KC; kc++)
 #pragma unroll
         for (int j = 0; j < 4; j++) xa[kc][j] = bload16_nt(rx, liveA ? xg + ((kc * 16 + 4 * r + j) * P.P + pA) * 2 : kOob);
+    const int xelems = extent(P.N, P.xs, P.C, P.P);
+    if (RAG && tile_near_ends(xg / 2, xg / 2 + (CG - 1) * P.P, p0, 0, xelems)) {
+#pragma unroll
+        for (int kc = 0; kc < KC; kc++)
+#pragma unroll
+            for (int j = 0; j < 4; j++) reload_if_partial(xa[kc][j], rx, liveA ? xg + ((kc * 16 + 4 * r + j) * P.P + pA) * 2 : kOob, xelems * 2);
+    }
 #pragma unroll
     for (int mo = 0; mo < MO; mo++)
 #pragma unroll
@@ -224,6 +255,13 @@ __device__ __forceinline__ void bwd_tile(const Params& P, rsrc_t rx, rsrc_t rdy,
             for (int j = 0; j < 4; j++)
                 reload_if_partial(dya[mo][j], rdy, liveA ? dyg + ((mo * 16 + 4 * r + j) * P.P + pA - off) * 2 : kOob, dyelems * 2);
     }
+    auto reload_residual = [&](int kc, u32x4 (&v)[4]) {
+        const int dyelems = extent(P.N, P.ys, Cout, P.P);
+        if (RAG && tile_near_ends(dyg / 2, dyg / 2 + (OG - 1) * P.P, p0, 0, dyelems)) {
+#pragma unroll
+            for (int j = 0; j < 4; j++) reload_if_partial(v[j], rdy, liveA ? dyg + ((kc * 16 + 4 * r + j) * P.P + pA) * 2 : kOob, dyelems * 2);
+        }
+    };
     // (the unshifted dy of the residual: with one 16-channel block per group it is fetched with everything else; with
     // more the registers are short, and each block's rows are fetched just ahead of its dx)
     if (RES && KC == 1) {
@@ -232,6 +270,14 @@ __device__ __forceinline__ void bwd_tile(const Params& P, rsrc_t rx, rsrc_t rdy,
             dyu[0][j] = bload16_nt(rdy, liveA ? dyg + ((4 * r + j) * P.P + pA) * 2 : kOob);
             pin(dyu[0][j]);
         }
+        reload_residual(0, dyu[0]);
+    }
+    if (RAG) {
+        const u32x4 own = own_pixels(P.P - pA);
+#pragma unroll
+        for (int kc = 0; kc < KC; kc++)
+#pragma unroll
+            for (int j = 0; j < 4; j++) xa[kc][j] = xa[kc][j] & own;
     }
     // x -> LDS rows (channel 4r+j, unit s) and -> MFMA operands
     short4_t xq[KC][8];
@@ -283,6 +329,7 @@ __device__ __forceinline__ void bwd_tile(const Params& P, rsrc_t rx, rsrc_t rdy,
             asm volatile("" ::: "memory");  // (not earlier: the registers are needed until here)
 #pragma unroll
             for (int j = 0; j < 4; j++) dyu[kc][j] = bload16_nt(rdy, liveA ? dyg + ((kc * 16 + 4 * r + j) * P.P + pA) * 2 : kOob);
+            reload_residual(kc, dyu[kc]);
         }
         float4_t dxs[8];
 #pragma unroll
@@ -306,7 +353,7 @@ __device__ __forceinline__ void bwd_tile(const Params& P, rsrc_t rx, rsrc_t rdy,
             u32x4 out;
 #pragma unroll
             for (int k = 0; k < 4; k++) out[k] = pack_bf16(v[2 * k], v[2 * k + 1]);
-            bstore16_nt(rdx, liveA ? xg + ((kc * 16 + 4 * r + j) * P.P + pA) * 2 : kOob, out);
+            store_unit<RAG>(rdx, liveA ? xg + ((kc * 16 + 4 * r + j) * P.P + pA) * 2 : kOob, out, P.P - pA);
         }
     }
     // dW += dz x^T over the tile's pixels: lane reads channel s, unit 4m+r (8 consecutive pixels) of both tiles;
@@ -324,7 +371,7 @@ __device__ __forceinline__ void bwd_tile(const Params& P, rsrc_t rx, rsrc_t rdy,
         }
 }
 
-template <int KC, int MO, int ACT, bool RES>
+template <int KC, int MO, int ACT, bool RES, bool RAG>
 __device__ __forceinline__ void bwd_body(const Params& P) {
     __shared__ u32x4 lds[kWaves][(KC + MO) * 16 * kLdsRow];
     const int lane = threadIdx.x & 63;
@@ -361,7 +408,7 @@ __device__ __forceinline__ void bwd_body(const Params& P) {
         const int t = (wg * kWaves + wave) * P.tiles_per_wave + it;
         if (t >= tiles_per_group) break;
         const int n = P.chunks == 1 ? t : (int)__umulhi((uint32_t)t, P.magicChunks), chunk = t - n * P.chunks;  // magic overflows for 1
-        bwd_tile<KC, MO, ACT, RES>(P, rx, rdy, rdx, lds_x, lds_dz, n, g, chunk * kTilePx, lane, wa, wt, dwacc);
+        bwd_tile<KC, MO, ACT, RES, RAG>(P, rx, rdy, rdx, lds_x, lds_dz, n, g, chunk * kTilePx, lane, wa, wt, dwacc);
     }
     // the workgroup's four wavefronts are summed in a fixed order through LDS: one partial per workgroup;
     // the reduction kernel then sums the partials in a fixed order
@@ -383,19 +430,19 @@ __device__ __forceinline__ void bwd_body(const Params& P) {
     }
 }
 
-// Cheap activations fit 128 registers (4 wavefronts per SIMD); gelu and clipped exp need more.
+// Cheap activations fit 128 registers (4 wavefronts per SIMD); gelu, clipped exp and planes with a ragged end need more.
 template <int KC, int MO, int ACT, bool RES>
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_bwd(Params P) {
-    bwd_body<KC, MO, ACT, RES>(P);
+    bwd_body<KC, MO, ACT, RES, false>(P);
 }
-template <int KC, int MO, int ACT, bool RES>
+template <int KC, int MO, int ACT, bool RES, bool RAG>
 __global__ __launch_bounds__(64 * kWaves) void k_bwd_wide(Params P) {
-    bwd_body<KC, MO, ACT, RES>(P);
+    bwd_body<KC, MO, ACT, RES, RAG>(P);
 }
 // Groups of 32 channels: two wavefronts per SIMD is what the tile's registers allow.
-template <int KC, int MO, int ACT, bool RES>
+template <int KC, int MO, int ACT, bool RES, bool RAG>
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_bwd_two(Params P) {
-    bwd_body<KC, MO, ACT, RES>(P);
+    bwd_body<KC, MO, ACT, RES, RAG>(P);
 }
 
 // ----------------------------------------------------------------------- m instances on one tile (blocks)
@@ -414,11 +461,11 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
 constexpr int kDead = -0x7fffffff - 1;  // plus any offset inside a tensor: still outside
 // Wavefronts per SIMD that the registers of the backward kernel leave room for (expand with relu and residual: 173 registers;
 // held to three wavefronts it spills four and takes 28.1 instead of 26.3 us, 64 => 128).
-constexpr int multi_waves(int act, bool res, bool expand) { return act == 2 || (res && expand) ? 2 : 3; }
+constexpr int multi_waves(int act, bool res, bool expand, bool rag) { return act == 2 || rag || (res && expand) ? 2 : 3; }
 constexpr int lds_pieces_multi(int KC, int m) { return kWaves * (2 * KC * 16 * 16 + m * KC * KC * 64); }
 __device__ __forceinline__ int swz(int row, int unit) { return row * 16 + (unit ^ (row & 15)); }
 
-template <int KC, int ACT, bool RES, bool EXPAND>
+template <int KC, int ACT, bool RES, bool EXPAND, bool RAG>
 __global__ __launch_bounds__(64 * kWaves) void k_fwd_multi(Params P, Instances I) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -471,6 +518,12 @@ __global__ __launch_bounds__(64 * kWaves) void k_fwd_multi(Params P, Instances I
                 xr[mo][k] = bload16_nt(rx, px + (xj + (mo * 16 + k) * P.P * 2));
                 pin(xr[mo][k]);
             }
+        if (RAG && tile_near_ends(xj / 2, xj / 2 + (CG - 1) * P.P, p0, 0, xelems)) {
+#pragma unroll
+            for (int mo = 0; mo < KC; mo++)
+#pragma unroll
+                for (int k = 0; k < 4; k++) reload_if_partial(xr[mo][k], rx, px + (xj + (mo * 16 + k) * P.P * 2), xelems * 2);
+        }
     };
     auto gather_x = [&]() {
 #pragma unroll
@@ -531,13 +584,13 @@ __global__ __launch_bounds__(64 * kWaves) void k_fwd_multi(Params P, Instances I
                     u32x4 out;
 #pragma unroll
                     for (int e = 0; e < 4; e++) out[e] = pack_bf16(v[2 * e], v[2 * e + 1]);
-                    bstore16_nt(ry, px + (yg + ((EXPAND ? j * I.slice : 0) + (mo * 16 + k) * P.P) * 2), out);
+                    store_unit<RAG>(ry, px + (yg + ((EXPAND ? j * I.slice : 0) + (mo * 16 + k) * P.P) * 2), out, P.P - p);
                 }
             }
     }
 }
 
-template <int KC, int ACT, bool RES, bool EXPAND>
+template <int KC, int ACT, bool RES, bool EXPAND, bool RAG>
 __device__ __forceinline__ void bwd_multi_body(const Params& P, const Instances& I, u32x4* lds) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -587,6 +640,13 @@ __device__ __forceinline__ void bwd_multi_body(const Params& P, const Instances&
             for (int kc = 0; kc < KC; kc++)
 #pragma unroll
                 for (int k = 0; k < 4; k++) xa[kc][k] = bload16_nt(rx, px + (xj + (kc * 16 + k) * P.P * 2));
+            const int xelems = P.N * P.xs;
+            if (RAG && tile_near_ends(xj / 2, xj / 2 + (CG - 1) * P.P, p0, 0, xelems)) {
+#pragma unroll
+                for (int kc = 0; kc < KC; kc++)
+#pragma unroll
+                    for (int k = 0; k < 4; k++) reload_if_partial(xa[kc][k], rx, px + (xj + (kc * 16 + k) * P.P * 2), xelems * 2);
+            }
         };
         auto load_dy = [&](int j) {
             const int dyj = dyg + j * I.slice * 2;
@@ -611,6 +671,12 @@ __device__ __forceinline__ void bwd_multi_body(const Params& P, const Instances&
                     dyu[kc][k] = bload16_nt(rdy, px + (dyj + (kc * 16 + k) * P.P * 2));
                     pin(dyu[kc][k]);
                 }
+            if (RAG && tile_near_ends(dyj / 2, dyj / 2 + (CG - 1) * P.P, p0, 0, dyelems)) {
+#pragma unroll
+                for (int kc = 0; kc < KC; kc++)
+#pragma unroll
+                    for (int k = 0; k < 4; k++) reload_if_partial(dyu[kc][k], rdy, px + (dyj + (kc * 16 + k) * P.P * 2), dyelems * 2);
+            }
         };
         auto mask_dy = [&]() {
 #pragma unroll
@@ -619,6 +685,13 @@ __device__ __forceinline__ void bwd_multi_body(const Params& P, const Instances&
                 for (int k = 0; k < 4; k++) dya[mo][k] = dya[mo][k] & msk;
         };
         auto take_x = [&]() {  // x -> LDS rows (channel 4r+k, unit s) and -> MFMA operands
+            if (RAG) {
+                const u32x4 own = own_pixels(P.P - pA);
+#pragma unroll
+                for (int kc = 0; kc < KC; kc++)
+#pragma unroll
+                    for (int k = 0; k < 4; k++) xa[kc][k] = xa[kc][k] & own;
+            }
 #pragma unroll
             for (int kc = 0; kc < KC; kc++) {
 #pragma unroll
@@ -705,7 +778,7 @@ __device__ __forceinline__ void bwd_multi_body(const Params& P, const Instances&
                         u32x4 out;
 #pragma unroll
                         for (int e = 0; e < 4; e++) out[e] = pack_bf16(dxs[kc][2 * e][k], dxs[kc][2 * e + 1][k]);
-                        bstore16_nt(rdx, px + (xg + ((EXPAND ? 0 : j * I.slice) + (kc * 16 + k) * P.P) * 2), out);
+                        store_unit<RAG>(rdx, px + (xg + ((EXPAND ? 0 : j * I.slice) + (kc * 16 + k) * P.P) * 2), out, P.P - pA);
                     }
             }
             // dW_j += dz x^T over the tile's pixels (the operand layout of bwd_tile)
@@ -742,10 +815,10 @@ __device__ __forceinline__ void bwd_multi_body(const Params& P, const Instances&
     }
 }
 
-template <int KC, int ACT, bool RES, bool EXPAND>
-__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(multi_waves(ACT, RES, EXPAND), multi_waves(ACT, RES, EXPAND)))) void k_bwd_multi(Params P, Instances I) {
+template <int KC, int ACT, bool RES, bool EXPAND, bool RAG>
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(multi_waves(ACT, RES, EXPAND, RAG), multi_waves(ACT, RES, EXPAND, RAG)))) void k_bwd_multi(Params P, Instances I) {
     extern __shared__ __align__(16) u32x4 lds_multi[];
-    bwd_multi_body<KC, ACT, RES, EXPAND>(P, I, lds_multi);
+    bwd_multi_body<KC, ACT, RES, EXPAND, RAG>(P, I, lds_multi);
 }
 
 // dW[g][e] = sum over the group's partials in a fixed order (grid.z: the instances of a block).  Bound by the launch itself: a
@@ -793,18 +866,24 @@ bool supported(int KC, int MO) { return KC == MO && (KC == 1 || KC == 2); }
 
 template <int ACT, bool RES>
 static void launch_fwd(const Params& P, int W, hipStream_t s) {
-    const dim3 grid((unsigned)((P.chunks + kWaves - 1) / kWaves), (unsigned)P.G, (unsigned)P.N);
+    const dim3 grid((unsigned)((P.chunks + kWaves - 1) / kWaves), (unsigned)P.G, (unsigned)P.N), block(64 * kWaves);
     if (!P.total_tiles) return;
-    if (W == 2) CANVAS_LAUNCH((k_fwd<2, 2, ACT, RES>), grid, dim3(64 * kWaves), 0, s, P);
-    else CANVAS_LAUNCH((k_fwd<1, 1, ACT, RES>), grid, dim3(64 * kWaves), 0, s, P);
+    if (P.P % 8) {
+        if (W == 2) CANVAS_LAUNCH((k_fwd<2, 2, ACT, RES, true>), grid, block, 0, s, P);
+        else CANVAS_LAUNCH((k_fwd<1, 1, ACT, RES, true>), grid, block, 0, s, P);
+    } else if (W == 2) CANVAS_LAUNCH((k_fwd<2, 2, ACT, RES, false>), grid, block, 0, s, P);
+    else CANVAS_LAUNCH((k_fwd<1, 1, ACT, RES, false>), grid, block, 0, s, P);
 }
 template <int ACT, bool RES>
 static void launch_bwd(const Params& P, int W, hipStream_t s) {
-    const dim3 grid((unsigned)P.wgs_per_group, (unsigned)P.G);
+    const dim3 grid((unsigned)P.wgs_per_group, (unsigned)P.G), block(64 * kWaves);
     if (!P.total_tiles) return;
-    if (W == 2) CANVAS_LAUNCH((k_bwd_two<2, 2, ACT, RES>), grid, dim3(64 * kWaves), 0, s, P);
-    else if (ACT == 2 || ACT == 3) CANVAS_LAUNCH((k_bwd_wide<1, 1, ACT, RES>), grid, dim3(64 * kWaves), 0, s, P);
-    else CANVAS_LAUNCH((k_bwd<1, 1, ACT, RES>), grid, dim3(64 * kWaves), 0, s, P);
+    if (P.P % 8) {
+        if (W == 2) CANVAS_LAUNCH((k_bwd_two<2, 2, ACT, RES, true>), grid, block, 0, s, P);
+        else CANVAS_LAUNCH((k_bwd_wide<1, 1, ACT, RES, true>), grid, block, 0, s, P);
+    } else if (W == 2) CANVAS_LAUNCH((k_bwd_two<2, 2, ACT, RES, false>), grid, block, 0, s, P);
+    else if (ACT == 2 || ACT == 3) CANVAS_LAUNCH((k_bwd_wide<1, 1, ACT, RES, false>), grid, block, 0, s, P);
+    else CANVAS_LAUNCH((k_bwd<1, 1, ACT, RES>), grid, block, 0, s, P);
 }
 
 #define SGFC_DISPATCH(fn)                                                        \
@@ -826,20 +905,29 @@ void backward(const Params& P, int KC, int MO, hipStream_t s) {
     SGFC_DISPATCH(launch_bwd)
 }
 
-template <int ACT, bool RES>
-static void launch_fwd_multi(const Params& P, const Instances& I, bool expand, hipStream_t s) {
+template <int ACT, bool RES, bool RAG>
+static void launch_fwd_of(const Params& P, const Instances& I, bool expand, hipStream_t s) {
     const dim3 grid((unsigned)((P.chunks + kWaves - 1) / kWaves), (unsigned)P.G, (unsigned)P.N);
     if (!P.total_tiles) return;
-    if (expand) CANVAS_LAUNCH((k_fwd_multi<1, ACT, RES, true>), grid, dim3(64 * kWaves), 0, s, P, I);
-    else CANVAS_LAUNCH((k_fwd_multi<1, ACT, RES, false>), grid, dim3(64 * kWaves), 0, s, P, I);
+    if (expand) CANVAS_LAUNCH((k_fwd_multi<1, ACT, RES, true, RAG>), grid, dim3(64 * kWaves), 0, s, P, I);
+    else CANVAS_LAUNCH((k_fwd_multi<1, ACT, RES, false, RAG>), grid, dim3(64 * kWaves), 0, s, P, I);
 }
-template <int ACT, bool RES>
-static void launch_bwd_multi(const Params& P, const Instances& I, bool expand, hipStream_t s) {
+template <int ACT, bool RES, bool RAG>
+static void launch_bwd_of(const Params& P, const Instances& I, bool expand, hipStream_t s) {
     const dim3 grid((unsigned)P.wgs_per_group, (unsigned)P.G);
     if (!P.total_tiles) return;
     const size_t lds = (size_t)lds_pieces_multi(1, I.m) * 16;
-    if (expand) CANVAS_LAUNCH((k_bwd_multi<1, ACT, RES, true>), grid, dim3(64 * kWaves), lds, s, P, I);
-    else CANVAS_LAUNCH((k_bwd_multi<1, ACT, RES, false>), grid, dim3(64 * kWaves), lds, s, P, I);
+    if (expand) CANVAS_LAUNCH((k_bwd_multi<1, ACT, RES, true, RAG>), grid, dim3(64 * kWaves), lds, s, P, I);
+    else CANVAS_LAUNCH((k_bwd_multi<1, ACT, RES, false, RAG>), grid, dim3(64 * kWaves), lds, s, P, I);
+}
+
+template <int ACT, bool RES>
+static void launch_fwd_multi(const Params& P, const Instances& I, bool expand, hipStream_t s) {
+    P.P % 8 ? launch_fwd_of<ACT, RES, true>(P, I, expand, s) : launch_fwd_of<ACT, RES, false>(P, I, expand, s);
+}
+template <int ACT, bool RES>
+static void launch_bwd_multi(const Params& P, const Instances& I, bool expand, hipStream_t s) {
+    P.P % 8 ? launch_bwd_of<ACT, RES, true>(P, I, expand, s) : launch_bwd_of<ACT, RES, false>(P, I, expand, s);
 }
 
 #define SGFC_DISPATCH_MULTI(fn)                                                  \

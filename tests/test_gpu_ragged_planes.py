@@ -1,0 +1,94 @@
+"""The shift / grouped FC / unary / residual kernels on planes that are no multiple of eight pixels: odd and even planes, narrower than a
+unit, one pixel more or less than a tile of 128, groups of 16 and 32 channels, blocks that widen and narrow; what lies behind a
+plane's last pixel takes no part in its sums."""
+import numpy as np
+import pytest
+
+from helpers import TOL, assert_close, has_kinks
+from paper_2304_07741_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _blob(C, groups, act, res):
+    n = C // groups
+    lines = [f"%1 = shift %0 dh=1 dw=-1 c0=0 c1={n}", f"%2 = shift %1 dh=0 dw=1 c0={C - n} c1={C}", f"%3 = fc %2 groups={groups} out={C}"]
+    if act:
+        lines.append(f"%4 = unary %3 op={act}")
+    if res:
+        lines.append(f"%{len(lines) + 1} = binary %{len(lines)} %0 op=add")
+    return wl.HEADER + "\n".join(lines) + f"\noutput %{len(lines)}\n"
+
+
+# (channels, groups, N, H, W, activation, residual)
+DAGS = [(32, 2, 3, 13, 13, "relu", True), (64, 4, 2, 14, 14, "gelu", True), (32, 2, 1, 1, 2, "relu", True), (32, 2, 2, 3, 43, "abs", True),
+        (32, 2, 2, 127, 1 + 1, None, False), (64, 2, 3, 7, 7, "relu", True), (64, 2, 2, 11, 12, "expclip lo=-1 hi=1", True), (64, 2, 1, 129, 3, "gelu", False)]
+
+
+@pytest.mark.parametrize("C,groups,N,H,W,act,res", DAGS)
+def test_dag(C, groups, N, H, W, act, res):
+    from oracle import canvas_oracle
+    from paper_2304_07741_amd import harness
+
+    blob = _blob(C, groups, act, res)
+    case = wl.block_case("ragged", blob, (N, C, H, W), C, "bf16", 900 + H, [(groups, C // groups, C // groups)], [0.25])
+    case["weights"] = case["weights"][0]
+    got, r, dy = harness.run_case(case, dy=case["dy"])
+    assert [d["name"] for d in r.launches(1)] == ["sgfc_bwd", "sgfc_dw_reduce"]
+    r.close()
+    ref = canvas_oracle.run(blob, case["x"], case["weights"], dy)
+    alt = {}
+
+    def of(mg, v):
+        if (mg, v) not in alt:
+            alt[(mg, v)] = canvas_oracle.run(blob, case["x"], case["weights"], dy, tie_margin=v[0] * mg, tie_rule=v[1])
+        return alt[(mg, v)]
+
+    kinks, floor = has_kinks(blob), 1e-5 * float(np.abs(dy).max())
+    assert_close(got["y"], ref["y"], TOL["bf16"], "y")
+    assert_close(got["dx"], ref["dx"], TOL["bf16"], "dx", (lambda mg, v: of(mg, v)["dx"]) if kinks else None, floor)
+    assert_close(got["dw"][0], ref["dw"][0], TOL["bf16"], "dw", (lambda mg, v: of(mg, v)["dw"][0]) if kinks else None, floor)
+
+
+@pytest.mark.parametrize("c_in,c_out,N,H,W", [(32, 64, 5, 13, 11), (64, 32, 5, 13, 11), (16, 64, 3, 14, 14), (64, 16, 3, 14, 14), (16, 144, 2, 9, 7), (144, 16, 2, 9, 7)])
+def test_block(c_in, c_out, N, H, W):
+    from oracle import block_oracle
+    from paper_2304_07741_amd import harness
+
+    C = min(c_in, c_out)
+    blob = _blob(C, C // 16, None, True)
+    case = wl.block_case("raggedblock", blob, (N, c_in, H, W), c_out, "bf16", 950 + c_in, [(C // 16, 16, 16)], [0.25])
+    r = harness.BlockRunner(blob, (N, c_in, H, W), c_out, "bf16")
+    r.load(case["x"], case["weights"], case["dy"])
+    got, again = r.run(), r.run()
+    r.close()
+    ref = block_oracle.run_block(blob, case["x"], case["weights"], c_out, case["dy"])
+    assert np.array_equal(got["y"], again["y"]) and np.array_equal(got["dx"], again["dx"])
+    assert_close(got["y"], ref["y"], TOL["bf16"], "y")
+    assert_close(got["dx"], ref["dx"], TOL["bf16"], "dx")
+    for a, b in zip(got["dw"], ref["dw"]):
+        assert_close(a[0], b[0], TOL["bf16"], "dw")
+
+
+@pytest.mark.parametrize("C,groups", [(32, 2), (64, 2)])
+def test_what_lies_behind_a_plane(C, groups):
+    """Infinities in every second channel: the weight gradients of the others stay finite, also where the next plane's first
+    pixels are loaded with a plane's last ones."""
+    import torch
+
+    from paper_2304_07741_amd import harness
+
+    r = harness.DagRunner(_blob(C, groups, "relu", True), (2, C, 5, 7), "bf16")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    for t in [r.x, r.dy, *r.w]:
+        t.copy_(torch.randn(t.shape, generator=g, device="cuda"))
+    r.x[:, 1::2, 0, :] = float("inf")
+    r.w[0].abs_()
+    r.poison_outputs()
+    r.forward()
+    r.backward()
+    torch.cuda.synchronize()
+    assert torch.isfinite(r.dw[0][:, :, 0::2]).all() and not torch.isfinite(r.dw[0][:, :, 1::2]).all()
+    assert torch.isfinite(r.dx).all()
+    r.close()
