@@ -111,7 +111,7 @@ struct Red {
 };
 
 struct Program {
-    // geometry.  A thread owns `vec` consecutive pixels of one image plane (H * W is a multiple of vec, vec <= W); the
+    // geometry.  A thread owns `vec` consecutive pixels of one image plane (vec <= W; of the last ones fewer may exist); the
     // plane is dealt out in tiles of `own_threads` such threads, and a workgroup computes `halo_threads` more on either
     // side of its tile (backward programs: the gradient hand-over of OP_XADD reads what neighbouring pixels computed).
     int32_t N = 0, C = 0, H = 0, W = 0;

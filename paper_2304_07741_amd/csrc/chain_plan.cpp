@@ -988,11 +988,15 @@ double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
     Program best_shape = pg;
     double best_cost = -1;
     for (int V = max_vec_for(pg.tm); V >= 1; V /= 2) {
-        if (HW % V != 0 || dag.W < V) continue;
+        // (planes that V does not divide have a last thread with fewer pixels: gate, 64x120 planes of 27x23, 40 + 101 us with one
+        // pixel per thread, 18 + 37 with sixteen.  Not where four divide them: 64x64 planes of 14x14 8.9 + 19.3 with four, 9.6 + 18.8
+        // with eight.  Nor where a workgroup holds all channels: there the estimate errs, one program over 9x96 planes of 23x17
+        // took 126 us with two pixels, 38 with one)
+        if (dag.W < V || (HW % V != 0 && (all_channels || HW % 4 == 0))) continue;
         pg.vec = V;
         pg.unroll = unroll_for(pg.tm, V);
         pg.persist_copies = one_copy ? 1 : pg.unroll;
-        const int PP = HW / V;                                   // pixel threads of a plane
+        const int PP = ceil_div(HW, V);                          // pixel threads of a plane
         const int64_t HT = (reach_px + V - 1) / V;               // halo, in pixel threads
         const int per_thread = std::max<int>(1, (int)lds_bytes_per_thread(pg));
         const int cap = (int)(std::min<int64_t>(max_threads_for(pg.tm), (int64_t)kMaxLdsBytes / per_thread) / 64 * 64);

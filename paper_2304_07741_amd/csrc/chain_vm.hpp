@@ -49,6 +49,9 @@ struct Geo {
     int H = 0, W = 0, C = 0, HW = 0, N = 0;
     int npx = 0;  // pixels a slice of the workgroup computes = pix_threads * V
     bool whole_rows = false;  // W is a multiple of V: the V pixels of a thread never straddle two image rows
+    // HW is no multiple of V: planes begin at any element, and the last thread of a plane has pixels behind it, which it computes
+    // on what the next plane holds there and never stores (nothing but a store or a hand-over leaves a pixel's own lanes)
+    bool ragged = false;
 };
 
 // Each case of the dispatch begins with an empty volatile asm statement: the cases are small, and without it the
@@ -223,9 +226,22 @@ __device__ __forceinline__ void vm_load(const Tensor& e, int elem, float* out) {
     }
 }
 
-// V elements to element `elem` (always inside the tensor and a multiple of V: only owned pixels are stored).
+// `left` (V in all, a multiple of V, unless planes are ragged) elements to element `elem`: only owned pixels are stored.
 template <int V>
-__device__ __forceinline__ void vm_store(const Tensor& e, int elem, const float* in, bool add) {
+__device__ __forceinline__ void vm_store(const Tensor& e, int elem, const float* in, bool add, bool ragged, int left) {
+    if (ragged && left < V) {
+#pragma unroll
+        for (int v = 0; v < V; v++)
+            if (v < left) {
+                if (e.bf16) {
+                    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(tile::pack_bf16(in[v], 0.f) & 0xffffu), e.rs, (elem + v) * 2, 0, 0);
+                } else {
+                    const float old = add ? __uint_as_float(tile::elem_b32(e.rs, (elem + v) * 4, e.bytes)) : 0.f;
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(add ? old + in[v] : in[v]), e.rs, (elem + v) * 4, 0, 0);
+                }
+            }
+        return;
+    }
     if (e.bf16) {
         const int o = elem * 2;
         if (V % 8 == 0) {
@@ -234,7 +250,8 @@ __device__ __forceinline__ void vm_store(const Tensor& e, int elem, const float*
                 tile::u32x4 d;
 #pragma unroll
                 for (int k = 0; k < 4; k++) d[k] = tile::pack_bf16(in[8 * q + 2 * k], in[8 * q + 2 * k + 1]);
-                tile::bstore16_nt(e.rs, o + 16 * q, d);
+                if (ragged) tile::bstore16(e.rs, o + 16 * q, d);  // (unaligned: kept in the cache until its lines are whole)
+                else tile::bstore16_nt(e.rs, o + 16 * q, d);
             }
         } else if (V == 4) {
             vm_u32x2 d;
@@ -263,7 +280,8 @@ __device__ __forceinline__ void vm_store(const Tensor& e, int elem, const float*
                 tile::u32x4 d;
 #pragma unroll
                 for (int k = 0; k < 4; k++) d[k] = __float_as_uint(v[4 * q + k]);
-                tile::bstore16_nt(e.rs, o + 16 * q, d);
+                if (ragged) tile::bstore16(e.rs, o + 16 * q, d);
+                else tile::bstore16_nt(e.rs, o + 16 * q, d);
             }
         } else {
 #pragma unroll
@@ -290,13 +308,14 @@ inline void vm_load(const Tensor& e, int elem, float* out) {
     }
 }
 template <int V>
-inline void vm_store(const Tensor& e, int elem, const float* in, bool add) {
+inline void vm_store(const Tensor& e, int elem, const float* in, bool add, bool ragged, int left) {
     const int64_t n = e.bytes / (e.bf16 ? 2 : 4);
-    if (elem < 0 || (int64_t)elem + V > n || elem % V) {
+    if (!ragged || left > V) left = V;
+    if (elem < 0 || (int64_t)elem + left > n || (!ragged && elem % V)) {
         std::fprintf(stderr, "chain vm: store of %d elements at %d outside a tensor of %lld\n", V, elem, (long long)n);
         std::abort();
     }
-    for (int v = 0; v < V; v++) {
+    for (int v = 0; v < left; v++) {
         if (e.bf16) ((uint16_t*)e.ptr)[elem + v] = vm_f32_to_bf16(in[v]);
         else if (add) ((float*)e.ptr)[elem + v] += in[v];
         else ((float*)e.ptr)[elem + v] = in[v];
@@ -466,7 +485,8 @@ CHAIN_HD uint32_t vm_valid(const Geo& g, const Thread& th, int oh, int ow) {
 template <int V>
 CHAIN_HD void vm_load_at(const Tensor& e, const Geo& g, const Thread& th, int plane, int oh, int ow, float* out) {
     if (oh == 0 && ow == 0) {
-        vm_load<V, true>(e, plane * g.HW + th.p0, out);
+        if (g.ragged) vm_load<V, false>(e, plane * g.HW + th.p0, out);
+        else vm_load<V, true>(e, plane * g.HW + th.p0, out);
     } else {
         float raw[V];
         vm_load<V, false>(e, plane * g.HW + th.p0 + oh * g.W + ow, raw);
@@ -907,7 +927,7 @@ CHAIN_HD void vm_exec_lanes(const Program& pg, const Geo& g, const Instr& I, con
                 const int chan = (th.n * g.C + ev.c + u) * e.T;
 #pragma unroll
                 for (int t = 0; t < TM; t++)
-                    if (t < T) vm_store<V>(e, (chan + t) * g.HW + th.p0, A + u * TV + t * V, (I.kind & kStAdd) != 0);
+                    if (t < T) vm_store<V>(e, (chan + t) * g.HW + th.p0, A + u * TV + t * V, (I.kind & kStAdd) != 0, g.ragged, g.HW - th.p0);
             }
         break;
     }
