@@ -981,44 +981,50 @@ double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
     // (a program that makes one trip keeps its registers' LDS: floats that no channel has for itself exist once.  The other
     // programs' workgroups were weighed with a copy per channel of the trip, and the estimate errs without them: softmax over
     // channels, 128x64 planes of 56x56 backward 177 us with the workgroup it chooses so, 250 otherwise.)
-    bool one_copy = one_trip;
+    // Except where the launch then still has a compute unit for every workgroup: more slices of the channels are all that
+    // helps there (two softmaxes over 192 channels, 7 planes of 16x28, backward: 280 us with three slices, 153 with eight).
+    bool one_copy = all_channels;
     for (int p = 0; p < pg.n_pass; p++)
         for (int i = pg.pass[p].body_begin; i < pg.pass[p].body_end; i++)
             if (pg.ins[i].op == OP_PSET || pg.ins[i].op == OP_PADD || pg.ins[i].op == OP_PLD || pg.ins[i].op == OP_XADD) one_copy = false;
     Program best_shape = pg;
     double best_cost = -1;
-    for (int V = max_vec_for(pg.tm); V >= 1; V /= 2) {
-        // (planes that V does not divide have a last thread with fewer pixels: gate, 64x120 planes of 27x23, 40 + 101 us with one
-        // pixel per thread, 18 + 37 with sixteen.  Not where four divide them: 64x64 planes of 14x14 8.9 + 19.3 with four, 9.6 + 18.8
-        // with eight.  Nor where a workgroup holds all channels: there the estimate errs, one program over 9x96 planes of 23x17
-        // took 126 us with two pixels, 38 with one)
-        if (dag.W < V || (HW % V != 0 && (all_channels || HW % 4 == 0))) continue;
-        pg.vec = V;
-        pg.unroll = unroll_for(pg.tm, V);
-        pg.persist_copies = one_copy ? 1 : pg.unroll;
-        const int PP = ceil_div(HW, V);                          // pixel threads of a plane
-        const int64_t HT = (reach_px + V - 1) / V;               // halo, in pixel threads
-        const int per_thread = std::max<int>(1, (int)lds_bytes_per_thread(pg));
-        const int cap = (int)(std::min<int64_t>(max_threads_for(pg.tm), (int64_t)kMaxLdsBytes / per_thread) / 64 * 64);
-        for (int pt = 64; pt <= cap; pt += 64) {
-            if (2 * HT >= pt) continue;
-            int own = pt - 2 * (int)HT;
-            if (own >= PP) {  // the whole plane in one tile
-                if (ceil_div(PP + 2 * (int)HT, 64) * 64 != pt) break;  // (counted once, at its own size)
-                own = PP;
-            } else {
-                own = ceil_div(PP, ceil_div(PP, own));  // tiles evened out over the plane
-            }
-            for (int trips = 1; trips <= (all_channels ? 1 : 8); trips *= 2) {
-                const double cost = geometry_for(pg, dag, C, all_channels, one_trip, PP, (int)HT, cap, own, pt, trips);
-                if (cost >= 0 && (best_cost < 0 || cost < best_cost * 0.999)) {  // (ties: the wider vector, the smaller workgroup, fewer trips)
-                    best_cost = cost;
-                    best_shape = pg;
+    auto look = [&](bool one_copy, int widest, int narrowest, int64_t most_workgroups) {
+        for (int V = widest; V >= narrowest; V /= 2) {
+            // (planes that V does not divide have a last thread with fewer pixels: gate, 64x120 planes of 27x23, 40 + 101 us with one
+            // pixel per thread, 18 + 37 with sixteen.  Not where four divide them: 64x64 planes of 14x14 8.9 + 19.3 with four, 9.6 + 18.8
+            // with eight.  Nor where a workgroup holds all channels: there the estimate errs, one program over 9x96 planes of 23x17
+            // took 126 us with two pixels, 38 with one)
+            if (dag.W < V || (HW % V != 0 && (all_channels || HW % 4 == 0))) continue;
+            pg.vec = V;
+            pg.unroll = unroll_for(pg.tm, V);
+            pg.persist_copies = one_copy ? 1 : pg.unroll;
+            const int PP = ceil_div(HW, V);                          // pixel threads of a plane
+            const int64_t HT = (reach_px + V - 1) / V;               // halo, in pixel threads
+            const int per_thread = std::max<int>(1, (int)lds_bytes_per_thread(pg));
+            const int cap = (int)(std::min<int64_t>(max_threads_for(pg.tm), (int64_t)kMaxLdsBytes / per_thread) / 64 * 64);
+            for (int pt = 64; pt <= cap; pt += 64) {
+                if (2 * HT >= pt) continue;
+                int own = pt - 2 * (int)HT;
+                if (own >= PP) {  // the whole plane in one tile
+                    if (ceil_div(PP + 2 * (int)HT, 64) * 64 != pt) break;  // (counted once, at its own size)
+                    own = PP;
+                } else {
+                    own = ceil_div(PP, ceil_div(PP, own));  // tiles evened out over the plane
                 }
-                if (pg.chunks == 1) break;  // (more trips give the same shape)
+                for (int trips = 1; trips <= (all_channels ? 1 : 8); trips *= 2) {
+                    const double cost = geometry_for(pg, dag, C, all_channels, one_trip, PP, (int)HT, cap, own, pt, trips);
+                    if (cost >= 0 && (int64_t)dag.N * pg.tiles * pg.chunks <= most_workgroups && (best_cost < 0 || cost < best_cost * 0.999)) {  // (ties: the wider vector, the smaller workgroup, fewer trips)
+                        best_cost = cost;
+                        best_shape = pg;
+                    }
+                    if (pg.chunks == 1) break;  // (more trips give the same shape)
+                }
             }
         }
-    }
+    };
+    look(one_trip && one_copy, max_vec_for(pg.tm), 1, INT64_MAX);
+    if (!one_trip && one_copy && best_cost >= 0) look(true, best_shape.vec, best_shape.vec, 256);
     if (best_cost < 0) throw Fail{"tile, halo and persistent state do not fit one workgroup"};
     pg = best_shape;
     return best_cost;
