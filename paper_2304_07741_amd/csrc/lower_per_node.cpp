@@ -11,7 +11,9 @@
 #include "../../include/canvas_dag.h"
 #include "chain_kernels.hpp"
 #include "chain_plan.hpp"
+#include "fc_emit.hpp"
 #include "gfc_kernels.hpp"
+#include "gfc_tm_kernels.hpp"
 #include "ref_kernels.hpp"
 #include "sfc_kernels.hpp"
 
@@ -348,6 +350,44 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         const Node& S = dag.nodes[srcn];
         return sfc::shape(dag.N, f.groups, (S.C / f.groups) * S.T, v ? U.kh : 1, v ? U.kw : 1, f.out / f.groups, dag.Hk(srcn), dag.Wk(srcn));
     };
+    // Contractions whose operand is the caller's bf16 tensor take the tap-major kernels: forward where the FC reads x, the data
+    // gradient where it reads dy (generic / tap-major kernels, us, forward + data gradient: 3x3, 2x48
+    // planes of 40x40 36.0 + 40.6 / 8.3 + 8.2, 7x32 of 14x14 21.7 + 22.5 / 7 + 7, 32x128 of 14x14 93.6 + 94.9 / 10.8 + 10.7).  Not the
+    // weight gradient: those kernels multiply what lies behind a plane's last pixel by zero, so that an infinity there spreads.
+    enum { kTmFwd = 1, kTmData = 2 };
+    std::vector<int> tm(dag.n_weights, 0);
+    uint64_t plain_bytes = 0, tm_bytes = 0;  // weight copies and partials without and with them
+    for (int i = 0; i < dag.n_weights; i++) {
+        const int k = dag.weight_node[i];
+        if (!dag.nodes[k].live || !fc_mfma[k]) continue;
+        const bool from_x = fc_src(k) == 0, from_dy = k == dag.out && y_direct;
+        const gfc::Params Q = fc_params(k), Wg = wgrad_params(k);
+        const uint64_t wt = align_up((uint64_t)wnumel[i] * 2), part = align_up((uint64_t)gfc::wgrad_partials(Wg) * wnumel[i] * 4);
+        plain_bytes += wt + part;
+        // (groups that share a tile meet each other's infinities as 0 * inf: those keep the generic kernels)
+        auto covers = [&](int R, int Og) {
+            return gfctm::supported(Q.N, Q.G, R, Q.KH, Q.KW, Og, Q.H, Q.W) && gfctm::shape(Q.N, Q.G, R, Q.KH, Q.KW, Og, Q.H, Q.W).gm == 1;
+        };
+        // (forward without a window only where the weights are read as they are: packing them is one more launch)
+        const bool as_they_are = Q.TV == 1 && Q.R % 16 == 0 && covers(Q.R, Q.Og) && gfctm::shape(Q.N, Q.G, Q.R, 1, 1, Q.Og, Q.H, Q.W).Omp == Q.Og;
+        if (from_x && covers(Q.R, Q.Og) && (Q.TV > 1 || as_they_are)) {
+            tm[i] |= kTmFwd;
+            tm_bytes += align_up((uint64_t)gfctm::packed_elems(gfctm::shape(Q.N, Q.G, Q.R, Q.KH, Q.KW, Q.Og, Q.H, Q.W)) * 2);
+        }
+        if (from_dy && covers(Q.Og, Q.R)) {
+            tm[i] |= kTmData;
+            tm_bytes += align_up((uint64_t)gfctm::packed_elems(gfctm::shape(Q.N, Q.G, Q.Og, Q.KH, Q.KW, Q.R, Q.H, Q.W)) * 2);
+        }
+        tm_bytes += part;
+        if (!(tm[i] & kTmData)) tm_bytes += wt;
+    }
+    // (a plan that fits the library's static workspace keeps fitting it)
+    if (off + plain_bytes <= CANVAS_STATIC_WORKSPACE_BYTES && off + tm_bytes > CANVAS_STATIC_WORKSPACE_BYTES) tm.assign(dag.n_weights, 0);
+    const TakeFn take_bytes = [&off](uint64_t bytes) {
+        const uint64_t o = off;
+        off += align_up(bytes);
+        return (int64_t)o;
+    };
     lay.wt.assign(dag.n_weights, -1);
     lay.part.assign(dag.n_weights, -1);
     std::vector<sfc::Params> sgrad(dag.n_weights);  // weight gradients of the fp32 fc nodes
@@ -361,12 +401,10 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             sfc_count++;
             continue;
         }
-        lay.wt[i] = (int64_t)off;
-        off += align_up((uint64_t)wnumel[i] * 2);
+        if (!(tm[i] & kTmData)) lay.wt[i] = take_bytes((uint64_t)wnumel[i] * 2);
         const gfc::Params Q = wgrad_params(k);
         const int64_t slices = gfc::wgrad_partials(Q);
-        lay.part[i] = (int64_t)off;
-        off += align_up((uint64_t)slices * wnumel[i] * 4);
+        lay.part[i] = take_bytes((uint64_t)slices * wnumel[i] * 4);
     }
     // fp32 contractions on the bf16 matrix units read their weights cut into parts, forward and transposed, from the workspace;
     // a plan that fits the library's static workspace without them keeps to the fp32 units if it would not with them.
@@ -535,6 +573,13 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
                 const int srcn = fc_src(k);
                 const bool src_x = srcn == 0;  // the caller's bf16 input is read directly
                 const bool to_y = k == dag.out && y_direct;  // the output node: written as bf16 where the caller wants it
+                if (tm[nd.widx] & kTmFwd) {
+                    emit_fc(*low, false, dag, take_bytes, Q.TV > 1 ? "gfc_fwd_unfold" : "gfc_fwd", Q.G, Q.R, Q.KH, Q.KW, Q.Og, false, nd.widx,
+                            FcOperand{[](const RunArgs& a) { return a.x; }, false},
+                            [=](const RunArgs& a) { return to_y ? (const void*)a.y : (const void*)valw(a, k); }, false,
+                            2.0 * dag.numel(srcn) + (to_y ? 2.0 : 4.0) * dag.numel(k) + 2.0 * wnumel[nd.widx], L.flops, !to_y);
+                    continue;
+                }
                 Q.src_f32 = src_x ? 0 : 1;
                 Q.dst_f32 = to_y ? 0 : 1;
                 gfc::prepare_forward(Q);
@@ -679,8 +724,8 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             const double flops = 2.0 * N * P * nd.out * (double)(wnumel[widx] / nd.out);
             // weight gradient: partial sums over slices of the (image, pixel) range, then a fixed-order sum
             const gfc::Params Q = wgrad_params(k);
-            const int64_t poff = lay.part[widx], toff = lay.wt[widx];
             const int64_t nw = wnumel[widx];
+            const int64_t poff = lay.part[widx];
             const int slices = gfc::wgrad_partials(Q);
             low->bwd.push_back({Q.TV > 1 ? "gfc_wgrad_unfold" : "gfc_wgrad", (src_x ? 2.0 : 4.0) * dag.numel(srcn) + 4.0 * dag.numel(k) + 4.0 * slices * nw, flops,
                                 [=](const RunArgs& a) {
@@ -707,10 +752,30 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             D.dst_f32 = to_dx ? 0 : 1;
             D.acc = to_dx ? 0 : acc_s;
             const int G = nd.groups, TV = D.TV;
+            const double dgrad_bytes = (from_dy ? 2.0 : 4.0) * dag.numel(k) + (to_dx ? 2.0 : 4.0 * (1 + acc_s)) * dag.numel(srcn) + 2.0 * nw;
+            if (tm[widx] & kTmData) {  // (the output's gradient is the first of the backward pass: there is nothing to add to yet)
+                if (D.acc) throw std::runtime_error("internal: a gradient before the output's");
+                emit_fc(*low, true, dag, take_bytes, TV > 1 ? "gfc_dgrad_unfold" : "gfc_dgrad", G, Og, Q.KH, Q.KW, Rrows, true, widx,
+                        FcOperand{[](const RunArgs& a) { return a.dy; }, false},
+                        [=](const RunArgs& a) { return to_dx ? (const void*)a.dx : (const void*)grad(a, srcn); }, false, dgrad_bytes, flops, !to_dx);
+                const WeightJob job = low->wjobs.back();  // (packed in the backward pass, where they are needed)
+                low->wjobs.pop_back();
+                low->bwd.insert(low->bwd.end() - 1, {"gfc_transpose_w", job.bytes, 0, [=](const RunArgs& a) {
+                                                         wprep::Jobs J;
+                                                         J.n = 1;
+                                                         J.j[0] = job.job;
+                                                         J.j[0].w = (const uint16_t*)a.w[widx];
+                                                         J.j[0].out = (uint16_t*)(a.ws + job.off);
+                                                         wprep::run(J, a.stream);
+                                                     }});
+                written[srcn] = true;
+                continue;
+            }
+            const int64_t toff = lay.wt[widx];
             low->bwd.push_back({"gfc_transpose_w", 4.0 * nw, 0, [=](const RunArgs& a) {
                                     gfc::transpose_weights((const uint16_t*)a.w[widx], (uint16_t*)(a.ws + toff), G, Og, Rrows, TV, a.stream);
                                 }});
-            low->bwd.push_back({TV > 1 ? "gfc_dgrad_unfold" : "gfc_dgrad", 4.0 * dag.numel(k) + 4.0 * dag.numel(srcn) * (1 + acc_s) + 2.0 * nw, flops,
+            low->bwd.push_back({TV > 1 ? "gfc_dgrad_unfold" : "gfc_dgrad", dgrad_bytes, flops,
                                 [=](const RunArgs& a) {
                                     gfc::Params R = D;
                                     R.src = from_dy ? a.dy : (const void*)grad(a, k);
@@ -867,6 +932,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         else low->bwd.push_back({"copy_dx", ne * 8.0, 0, [=](const RunArgs& a) { ref::copy_f32(grad(a, 0), (float*)a.dx, ne, a.stream); }});
     }
     (void)esz;
+    if (bf16) low->ws_bytes = std::max<uint64_t>(off, 256);
     return low;
 }
 

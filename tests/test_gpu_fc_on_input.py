@@ -1,0 +1,71 @@
+"""bf16 FCs on the caller's own tensors (x forward, dy backward) in the lowering by units: tap-major kernels, alone, behind a window,
+with fp32 intermediates on the other side, ragged channels and planes; an infinity reaches what its products reach and nothing else."""
+import numpy as np
+import pytest
+
+from helpers import check_against_oracle
+from paper_2304_07741_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+FC = "%1 = fc %0 groups={g} out={o}\noutput %1\n"
+WIN = "%1 = unfold %0 kh={k} kw={k}\n%2 = fc %1 groups={g} out={o}\noutput %2\n"
+MID = "%1 = unfold %0 kh=3 kw=3\n%2 = fc %1 groups={g} out={o}\n%3 = unary %2 op=gelu\n%4 = shift %3 dh=1 dw=-1 c0=0 c1=9\n%5 = fc %4 groups={g} out={o}\noutput %5\n"
+FAN = "%1 = fc %0 groups=1 out={o}\n%2 = unary %0 op=gelu\n%3 = binary %1 %2 op=mul\n%4 = fc %3 groups=1 out={o}\noutput %4\n"
+
+CASES = [
+    (WIN.format(k=3, g=1, o=24), [(1, 24, 216)], (2, 24, 7, 9)),
+    (WIN.format(k=3, g=1, o=33), [(1, 33, 153)], (1, 17, 8, 4)),
+    (WIN.format(k=5, g=2, o=40), [(2, 20, 500)], (3, 40, 11, 13)),
+    (WIN.format(k=3, g=2, o=128), [(2, 64, 576)], (5, 128, 14, 14)),
+    (WIN.format(k=3, g=4, o=16), [(4, 4, 36)], (2, 16, 6, 11)),
+    (FC.format(g=1, o=40), [(1, 40, 72)], (3, 72, 5, 7)),
+    (FC.format(g=3, o=66), [(3, 22, 32)], (2, 96, 9, 10)),
+    (MID.format(g=1, o=20), [(1, 20, 180), (1, 20, 20)], (2, 20, 9, 11)),
+    (MID.format(g=2, o=48), [(2, 24, 216), (2, 24, 24)], (3, 48, 7, 7)),
+    (FAN.format(o=32), [(1, 32, 32), (1, 32, 32)], (2, 32, 6, 9)),
+]
+
+
+@pytest.mark.parametrize("no_fusion", [False, True])
+@pytest.mark.parametrize("idx", range(len(CASES)))
+def test_fc_on_input(oracle, idx, no_fusion):
+    from paper_2304_07741_amd import binding as B
+    from paper_2304_07741_amd import harness
+
+    body, wshapes, shape = CASES[idx]
+    case = wl._case(f"fc_on_input{idx}", wl.HEADER + body, shape, "bf16", 60 + idx, wshapes, [1.0 / s[2] ** 0.5 for s in wshapes])
+    res, r, dy = harness.run_case(case, B.CANVAS_OPT_NO_FUSION if no_fusion else 0)
+    r.ws.fill_(0xFF)
+    r.poison_outputs()
+    r.forward()
+    r.backward()
+    again = r.results()
+    r.close()
+    assert np.array_equal(res["y"], again["y"]) and np.array_equal(res["dx"], again["dx"]) and all(np.array_equal(a, b) for a, b in zip(res["dw"], again["dw"]))
+    check_against_oracle(oracle, case, res, dy)
+
+
+@pytest.mark.parametrize("k", [1, 3])
+def test_infinities_stay_where_they_are(k):
+    import torch
+
+    from paper_2304_07741_amd import harness
+
+    r = harness.DagRunner(wl.HEADER + (WIN.format(k=3, g=2, o=64) if k == 3 else FC.format(g=2, o=64)), (2, 64, 5, 7), "bf16")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    for t in [r.x, r.dy, *r.w]:
+        t.copy_(torch.randn(t.shape, generator=g, device="cuda"))
+    r.x[:, 1:32:2, 0, :2] = float("inf")     # (the pixels behind the planes of the even channels)
+    r.dy.view(2, 64, 5, 7)[:, 1:32:2, 0, :2] = float("inf")
+    r.poison_outputs()
+    r.forward()
+    r.backward()
+    torch.cuda.synchronize()
+    y, dx = r.y.view(2, 64, 5, 7), r.dx
+    for t in (y, dx):
+        assert torch.isfinite(t[:, 32:]).all() and torch.isfinite(t[:, :32, 3:]).all() and not torch.isfinite(t[:, :32, 0, :2]).any()
+    dw = r.dw[0].view(2, 32, 32, -1)
+    assert torch.isfinite(dw[1]).all() and torch.isfinite(dw[0, 0::2, 0::2]).all() and not torch.isfinite(dw[0, 1::2, 1::2]).all()
+    r.close()
