@@ -80,7 +80,11 @@ std::unique_ptr<Lowering> lower_sgfc(const Dag& dag, bool bf16) {
     P.chunks = (Pn + 127) / 128;
     P.magicChunks = (uint32_t)((((uint64_t)1 << 32) + P.chunks - 1) / P.chunks);
     P.total_tiles = (long long)dag.N * G * P.chunks;
-    int tpw = 2;  // two tiles per wavefront measured best at the ResNet-18 stage-1 shape
+    // Tiles per wavefront of the backward kernels: two share a wavefront's weights and its partial, but one after the other, so only
+    // where the launch is more than one round of wavefronts (four per SIMD: 4096).  Backward with one / two tiles, us: 840 tiles
+    // (30x128 planes of 28x28) 8.2 / 11.3, 5200 (100x128 of 40x40) 25.0 / 27.3, block 256 => 64 30x28x28 10.7 / 16.7, 64 => 128 11x32x32 7.3 / 10.5,
+    // 128 => 64 60x40x40 (3120) 13.7 / 15.1; 6400 (64x64 planes of 56x56) 16.6 / 16.8, block 64 => 128 there 26.7 / 26.2.
+    int tpw = P.total_tiles > 6144 ? 2 : 1;
     if (const char* e = std::getenv("CANVAS_SGFC_TPW")) tpw = std::max(1, std::atoi(e));
     P.tiles_per_wave = tpw;
     const int tiles_per_group = dag.N * P.chunks;
