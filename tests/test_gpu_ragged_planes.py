@@ -1,5 +1,5 @@
 """The shift / grouped FC / unary / residual kernels on planes that are no multiple of eight pixels: odd and even planes, narrower than a
-unit, one pixel more or less than a tile of 128, groups of 16 and 32 channels, blocks that widen and narrow; what lies behind a
+unit, whole units but narrow, one pixel more or less than a tile of 128, one and two tiles per wavefront, groups of 16 and 32 channels, blocks that widen and narrow; what lies behind a
 plane's last pixel takes no part in its sums."""
 import numpy as np
 import pytest
@@ -22,7 +22,8 @@ def _blob(C, groups, act, res):
 
 # (channels, groups, N, H, W, activation, residual)
 DAGS = [(32, 2, 3, 13, 13, "relu", True), (64, 4, 2, 14, 14, "gelu", True), (32, 2, 1, 1, 2, "relu", True), (32, 2, 2, 3, 43, "abs", True),
-        (32, 2, 2, 127, 1 + 1, None, False), (64, 2, 3, 7, 7, "relu", True), (64, 2, 2, 11, 12, "expclip lo=-1 hi=1", True), (64, 2, 1, 129, 3, "gelu", False)]
+        (32, 2, 2, 127, 1 + 1, None, False), (64, 2, 3, 7, 7, "relu", True), (64, 2, 2, 11, 12, "expclip lo=-1 hi=1", True), (64, 2, 1, 129, 3, "gelu", False),
+        (32, 2, 3, 4, 4, "relu", True), (32, 2, 2, 16, 7, "gelu", True), (64, 2, 2, 8, 3, "abs", True), (32, 2, 41, 9, 15, "relu", True)]
 
 
 @pytest.mark.parametrize("C,groups,N,H,W,act,res", DAGS)
@@ -50,7 +51,7 @@ def test_dag(C, groups, N, H, W, act, res):
     assert_close(got["dw"][0], ref["dw"][0], TOL["bf16"], "dw", (lambda mg, v: of(mg, v)["dw"][0]) if kinks else None, floor)
 
 
-@pytest.mark.parametrize("c_in,c_out,N,H,W", [(32, 64, 5, 13, 11), (64, 32, 5, 13, 11), (16, 64, 3, 14, 14), (64, 16, 3, 14, 14), (16, 144, 2, 9, 7), (144, 16, 2, 9, 7)])
+@pytest.mark.parametrize("c_in,c_out,N,H,W", [(32, 64, 5, 13, 11), (64, 32, 5, 13, 11), (32, 64, 2, 8, 5), (64, 32, 2, 8, 5), (32, 128, 70, 31, 29), (16, 64, 3, 14, 14), (64, 16, 3, 14, 14), (16, 144, 2, 9, 7), (144, 16, 2, 9, 7)])
 def test_block(c_in, c_out, N, H, W):
     from oracle import block_oracle
     from paper_2304_07741_amd import harness
