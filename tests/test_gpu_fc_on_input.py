@@ -12,6 +12,8 @@ FC = "%1 = fc %0 groups={g} out={o}\noutput %1\n"
 WIN = "%1 = unfold %0 kh={k} kw={k}\n%2 = fc %1 groups={g} out={o}\noutput %2\n"
 MID = "%1 = unfold %0 kh=3 kw=3\n%2 = fc %1 groups={g} out={o}\n%3 = unary %2 op=gelu\n%4 = shift %3 dh=1 dw=-1 c0=0 c1=9\n%5 = fc %4 groups={g} out={o}\noutput %5\n"
 FAN = "%1 = fc %0 groups=1 out={o}\n%2 = unary %0 op=gelu\n%3 = binary %1 %2 op=mul\n%4 = fc %3 groups=1 out={o}\noutput %4\n"
+LONG = "%1 = unary %0 op=gelu\n%2 = unfold %1 kh={k} kw={k}\n%3 = fc %2 groups=1 out={o}\noutput %3\n"
+TAPS = "%1 = unfold %0 kh=5 kw=5\n%2 = unary %1 op=gelu\n%3 = fc %2 groups=1 out=24\noutput %3\n"
 
 CASES = [
     (WIN.format(k=3, g=1, o=24), [(1, 24, 216)], (2, 24, 7, 9)),
@@ -24,6 +26,9 @@ CASES = [
     (MID.format(g=1, o=20), [(1, 20, 180), (1, 20, 20)], (2, 20, 9, 11)),
     (MID.format(g=2, o=48), [(2, 24, 216), (2, 24, 24)], (3, 48, 7, 7)),
     (FAN.format(o=32), [(1, 32, 32), (1, 32, 32)], (2, 32, 6, 9)),
+    (LONG.format(o=40, k=3), [(1, 40, 576)], (2, 64, 7, 9)),       # an fp32 tensor copied to bf16 first
+    (LONG.format(o=17, k=5), [(1, 17, 575)], (3, 23, 6, 11)),
+    (TAPS, [(1, 24, 600)], (2, 24, 9, 5)),
 ]
 
 
