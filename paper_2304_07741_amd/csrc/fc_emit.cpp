@@ -9,15 +9,17 @@ void emit_fc(Lowering& low, bool backward, const Dag& dag, const TakeFn& take, c
              bool transposed, int widx, FcOperand src, PtrFn dst, bool addend_is_dst, double bytes, double flops, bool dst_f32, bool softmax) {
     std::vector<Launch>& list = backward ? low.bwd : low.fwd;
     const int64_t nw = (int64_t)G * Og * R * kh * kw;
-    if (!src.f32 && gfctm::supported(dag.N, G, R, kh, kw, Og, dag.H, dag.W)) {
-        const gfctm::Params T = gfctm::shape(dag.N, G, R, kh, kw, Og, dag.H, dag.W);
-        const bool identity = !transposed && T.TV == 1 && T.gm == 1 && T.Rp == R && T.Omp == Og;
+    const int rows = src.pairs ? 2 * R : R;
+    if (!src.f32 && gfctm::supported(dag.N, G, rows, kh, kw, Og, dag.H, dag.W)) {
+        const gfctm::Params T = gfctm::shape(dag.N, G, rows, kh, kw, Og, dag.H, dag.W);
+        const bool identity = !src.pairs && !transposed && T.TV == 1 && T.gm == 1 && T.Rp == R && T.Omp == Og;
         const int64_t opk = identity ? -1 : take((uint64_t)gfctm::packed_elems(T) * 2);
         if (!identity) {
             WeightJob j;
             j.job.kind = 0;
             j.job.G = T.G;
             j.job.R = T.R;
+            j.job.Rw = R;
             j.job.Og = T.Og;
             j.job.TV = T.TV;
             j.job.gm = T.gm;

@@ -16,6 +16,7 @@ using PtrFn = std::function<const void*(const RunArgs&)>;
 struct FcOperand {
     PtrFn ptr;
     bool f32 = false;  // fp32 tensor (else bf16)
+    bool pairs = false;  // fp32 values as two bf16 rows each, [N, G, 2, R, P] (ref::split_bf16; the tap-major kernels cover 2 R rows)
 };
 
 // y = FC(src) (forward), or, with `transposed`, the data gradient src = dy -> dst = d(source of the FC):

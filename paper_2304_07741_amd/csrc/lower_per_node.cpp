@@ -354,13 +354,16 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
     // gradient where it reads dy (generic / tap-major kernels, us, forward + data gradient: 3x3, 2x48
     // planes of 40x40 36.0 + 40.6 / 8.3 + 8.2, 7x32 of 14x14 21.7 + 22.5 / 7 + 7, 32x128 of 14x14 93.6 + 94.9 / 10.8 + 10.7).  Not the
     // weight gradient: those kernels multiply what lies behind a plane's last pixel by zero, so that an infinity there spreads.
-    // An fp32 tensor between units is copied to bf16 first (the generic kernels round it the same way as they read it) where the
-    // contraction is long: K = 864 behind a window, eight launches of a micro-DAG around it, 16x96 planes of 32x32 604 us / 388, 4x96 of
-    // 22x17 499 / 280; K = 2400 of a tensor with 25 taps, 4x96 of 22x17 476 / 301.  Without a window not where the copy is long
-    // too: 39 M elements, two groups of 96 outputs 654 / 667.
-    enum { kTmFwd = 1, kTmData = 2, kTmFwdCopy = 4 };
+    // An fp32 tensor between units is cut into bf16 pairs first, hi = bf16(x) and lo = bf16(x - hi), and contracted as twice the rows
+    // against the same weights: the values and products are those of the generic kernels, which cut every element again for every
+    // output tile.  Where the contraction is long (us, generic kernels / cutting, packing the weights and contracting): 3x3, 96 -> 96
+    // channels (K = 864) 16x96 planes of 32x32 91 / 32, 4x96 of 22x17 95 / 21, 96 -> 8 16x96 of 32x32 73 / 22; without a window, tensors of
+    // nine taps (K = 864) 4x96 planes of 22x17 70 / 27, 16x96 of 32x32 (14 M elements) 64 / 46, of 25 taps (K = 2400) 4x96 of 22x17 201 / 55.
+    // Not where what is cut without a window is longer: 39 M elements are 315 MB to move, and the whole contraction of two groups
+    // of 96 outputs takes 90.
+    enum { kTmFwd = 1, kTmData = 2, kTmFwdPairs = 4 };
     constexpr int kLongContraction = 512;
-    constexpr int64_t kLongCopy = (int64_t)16 << 20;
+    constexpr int64_t kLongPairs = (int64_t)16 << 20;
     std::vector<int> tm(dag.n_weights, 0);
     uint64_t plain_bytes = 0, tm_bytes = 0;  // weight copies and partials without and with them
     for (int i = 0; i < dag.n_weights; i++) {
@@ -384,9 +387,9 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             tm[i] |= kTmData;
             tm_bytes += align_up((uint64_t)gfctm::packed_elems(gfctm::shape(Q.N, Q.G, Q.Og, Q.KH, Q.KW, Q.R, Q.H, Q.W)) * 2);
         }
-        if (!from_x && Q.K >= kLongContraction && (Q.TV > 1 || dag.numel(fc_src(k)) <= kLongCopy) && covers(Q.R, Q.Og)) {
-            tm[i] |= kTmFwd | kTmFwdCopy;
-            tm_bytes += align_up((uint64_t)gfctm::packed_elems(gfctm::shape(Q.N, Q.G, Q.R, Q.KH, Q.KW, Q.Og, Q.H, Q.W)) * 2) + align_up((uint64_t)dag.numel(fc_src(k)) * 2);
+        if (!from_x && Q.K >= kLongContraction && (Q.TV > 1 || dag.numel(fc_src(k)) <= kLongPairs) && covers(2 * Q.R, Q.Og)) {
+            tm[i] |= kTmFwd | kTmFwdPairs;
+            tm_bytes += align_up((uint64_t)gfctm::packed_elems(gfctm::shape(Q.N, Q.G, 2 * Q.R, Q.KH, Q.KW, Q.Og, Q.H, Q.W)) * 2) + align_up((uint64_t)dag.numel(fc_src(k)) * 4);
         }
         tm_bytes += part;
         if (!(tm[i] & kTmData)) tm_bytes += wt;
@@ -584,15 +587,15 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
                 const bool src_x = srcn == 0;  // the caller's bf16 input is read directly
                 const bool to_y = k == dag.out && y_direct;  // the output node: written as bf16 where the caller wants it
                 if (tm[nd.widx] & kTmFwd) {
-                    const int64_t copy = tm[nd.widx] & kTmFwdCopy ? take_bytes((uint64_t)dag.numel(srcn) * 2) : -1;
-                    if (copy >= 0) {
-                        const int64_t ne = dag.numel(srcn);
-                        low->fwd.push_back({"gfc_narrow", 6.0 * ne, 0, [=](const RunArgs& a) { ref::narrow_bf16(val(a, srcn), a.ws + copy, ne, a.stream); }});
+                    const int64_t pairs = tm[nd.widx] & kTmFwdPairs ? take_bytes((uint64_t)dag.numel(srcn) * 4) : -1;
+                    if (pairs >= 0) {
+                        const int64_t ne = dag.numel(srcn), block = (int64_t)Q.R * Q.P;
+                        low->fwd.push_back({"gfc_split", 8.0 * ne, 0, [=](const RunArgs& a) { ref::split_bf16(val(a, srcn), a.ws + pairs, ne, block, a.stream); }});
                     }
                     emit_fc(*low, false, dag, take_bytes, Q.TV > 1 ? "gfc_fwd_unfold" : "gfc_fwd", Q.G, Q.R, Q.KH, Q.KW, Q.Og, false, nd.widx,
-                            FcOperand{[=](const RunArgs& a) { return copy >= 0 ? (const void*)(a.ws + copy) : a.x; }, false},
+                            FcOperand{[=](const RunArgs& a) { return pairs >= 0 ? (const void*)(a.ws + pairs) : a.x; }, false, pairs >= 0},
                             [=](const RunArgs& a) { return to_y ? (const void*)a.y : (const void*)valw(a, k); }, false,
-                            2.0 * dag.numel(srcn) + (to_y ? 2.0 : 4.0) * dag.numel(k) + 2.0 * wnumel[nd.widx], L.flops, !to_y);
+                            (pairs >= 0 ? 4.0 : 2.0) * dag.numel(srcn) + (to_y ? 2.0 : 4.0) * dag.numel(k) + 2.0 * wnumel[nd.widx], L.flops, !to_y);
                     continue;
                 }
                 Q.src_f32 = src_x ? 0 : 1;

@@ -29,6 +29,24 @@ __global__ void k_f32_to_bf16(const float* __restrict__ in, uint16_t* __restrict
     if (i < n) out[i] = f32_to_bf16(in[i]);
 }
 
+// V elements per thread.  hi = bf16(x), lo = bf16(x - hi), which keep 16 bits of x; the blocks of `block` elements become [2][block].
+template <int V>
+__global__ void k_split_bf16(const float* __restrict__ in, uint16_t* __restrict__ out, uint32_t n, uint32_t block) {
+    const uint32_t i = (blockIdx.x * (uint32_t)kBlock + threadIdx.x) * V;
+    if (i >= n) return;
+    float x[V];
+    uint16_t hi[V], lo[V];
+    __builtin_memcpy(x, in + i, 4 * V);
+#pragma unroll
+    for (int k = 0; k < V; k++) {
+        hi[k] = f32_to_bf16(x[k]);
+        lo[k] = f32_to_bf16(x[k] - bf16_to_f32(hi[k]));
+    }
+    uint16_t* const o = out + i + (size_t)(i / block) * block;
+    __builtin_memcpy(o, hi, 2 * V);
+    __builtin_memcpy(o + block, lo, 2 * V);
+}
+
 __global__ void k_fill_f32(float* __restrict__ out, float v, int64_t n) {
     int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i < n) out[i] = v;
@@ -410,6 +428,10 @@ __global__ void k_fold_bwd(const float* __restrict__ in, const float* __restrict
 
 void widen_bf16(const void* in, float* out, int64_t n, hipStream_t s) { LAUNCH(k_bf16_to_f32, n, (const uint16_t*)in, out, n); }
 void narrow_bf16(const float* in, void* out, int64_t n, hipStream_t s) { LAUNCH(k_f32_to_bf16, n, in, (uint16_t*)out, n); }
+void split_bf16(const float* in, void* out, int64_t n, int64_t block, hipStream_t s) {
+    if (block % 4 == 0) LAUNCH(k_split_bf16<4>, n / 4, in, (uint16_t*)out, (uint32_t)n, (uint32_t)block);
+    else LAUNCH(k_split_bf16<1>, n, in, (uint16_t*)out, (uint32_t)n, (uint32_t)block);
+}
 void fill_f32(float* out, float v, int64_t n, hipStream_t s) { LAUNCH(k_fill_f32, n, out, v, n); }
 void copy_f32(const float* in, float* out, int64_t n, hipStream_t s) { LAUNCH(k_copy_f32, n, in, out, n); }
 

@@ -10,6 +10,8 @@ namespace ref {
 
 void widen_bf16(const void* in, float* out, int64_t n, hipStream_t s);
 void narrow_bf16(const float* in, void* out, int64_t n, hipStream_t s);
+// bf16 pairs of fp32 values: hi = bf16(x), lo = bf16(x - hi); every `block` elements of `in` become block high parts, then block low parts
+void split_bf16(const float* in, void* out, int64_t n, int64_t block, hipStream_t s);
 void fill_f32(float* out, float v, int64_t n, hipStream_t s);
 void copy_f32(const float* in, float* out, int64_t n, hipStream_t s);
 void unfold_fwd(const float* in, float* out, int64_t NC, int Tin, int KH, int KW, int H, int W, hipStream_t s);

@@ -21,12 +21,12 @@ __device__ __forceinline__ void write_element(const Job& J, IDX i) {
         t /= (IDX)J.TV;
         const int op = (int)(t % (IDX)J.Omp), gmi = (int)(t / (IDX)J.Omp);
         const int sub = op / J.Og, o = op - sub * J.Og;
-        const int subr = rp / J.R, row = rp - subr * J.R;
+        const int subr = rp / J.R, r = rp - subr * J.R, row = r < J.Rw ? r : r - J.Rw;
         const int g = gmi * J.gm + sub;
         uint16_t v = 0;
         if (sub < J.gm && subr == sub && g < J.G)
-            v = J.transposed ? J.w[(((long long)g * J.R + row) * J.Og + o) * J.TV + (J.TV - 1 - tap)]
-                             : J.w[(((long long)g * J.Og + o) * J.R + row) * J.TV + tap];
+            v = J.transposed ? J.w[(((long long)g * J.Rw + row) * J.Og + o) * J.TV + (J.TV - 1 - tap)]
+                             : J.w[(((long long)g * J.Og + o) * J.Rw + row) * J.TV + tap];
         J.out[i] = v;
     } else {
         const int tv = (int)(i % (IDX)J.TV);

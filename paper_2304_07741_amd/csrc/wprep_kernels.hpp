@@ -14,6 +14,7 @@ struct Job {
     uint16_t* out = nullptr;
     int kind = 0;                 // 0: tap-major pack [Gm][Omp][TV][Rp]; 1: plain transpose [G][R][Og][TV] -> [G][Og][R][TV flipped]
     int G = 0, R = 0, Og = 0, TV = 1;
+    int Rw = 0;                           // kind 0: rows of the weights; 2 Rw = R: the contraction reads every row twice, as a high and a low part
     int gm = 1, Gm = 0, Rp = 0, Omp = 0;  // kind 0 only
     int transposed = 0;           // kind 0 only
     long long total = 0;          // elements written

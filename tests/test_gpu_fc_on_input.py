@@ -74,3 +74,32 @@ def test_infinities_stay_where_they_are(k):
     dw = r.dw[0].view(2, 32, 32, -1)
     assert torch.isfinite(dw[1]).all() and torch.isfinite(dw[0, 0::2, 0::2]).all() and not torch.isfinite(dw[0, 1::2, 1::2]).all()
     r.close()
+
+
+SQUARE = "%1 = binary %0 %0 op=mul\n%2 = unfold %1 kh={k} kw={k}\n%3 = fc %2 groups={g} out={o}\noutput %3\n"
+SQUARED_TAPS = "%1 = unfold %0 kh=5 kw=5\n%2 = binary %1 %1 op=mul\n%3 = fc %2 groups={g} out={o}\noutput %3\n"
+SQUARES = [
+    (SQUARE.format(k=3, g=1, o=40), [(1, 40, 576)], (2, 64, 7, 9)),
+    (SQUARE.format(k=3, g=2, o=34), [(2, 17, 576)], (3, 128, 8, 5)),
+    (SQUARE.format(k=5, g=1, o=17), [(1, 17, 575)], (3, 23, 6, 11)),
+    (SQUARE.format(k=3, g=1, o=24), [(1, 24, 504)], (2, 56, 9, 7)),     # a short contraction: the generic kernels, as a yardstick
+    (SQUARED_TAPS.format(g=1, o=24), [(1, 24, 600)], (2, 24, 9, 5)),
+    (SQUARED_TAPS.format(g=2, o=96), [(2, 48, 575)], (1, 46, 5, 6)),
+]
+
+
+@pytest.mark.parametrize("idx", range(len(SQUARES)))
+def test_fp32_operands_keep_sixteen_bits(oracle, idx):
+    """The square of a bf16 value has 16 bits: as a high and a low bf16 part it enters the contraction exactly, so y is the exact
+    sum rounded to bf16, but for the sums so close to a tie that fp32 rounding decides (1e-6 of the terms against a spacing of
+    2^-8 of the sum: under one in a hundred).  With the high part alone a third of y is off."""
+    from paper_2304_07741_amd import harness
+
+    body, wshapes, shape = SQUARES[idx]
+    case = wl._case(f"squares{idx}", wl.HEADER + body, shape, "bf16", 80 + idx, wshapes, [1.0 / s[2] ** 0.5 for s in wshapes])
+    res, r, dy = harness.run_case(case)
+    r.close()
+    want = wl.round_to_bf16(oracle.run(case["blob"], case["x"], case["weights"], dy)["y"])
+    off = float(np.mean(res["y"] != want.reshape(res["y"].shape)))
+    print(f"[squares {idx}] share of y that is not the rounded exact sum: {off:.4f}")
+    assert off <= 0.02
