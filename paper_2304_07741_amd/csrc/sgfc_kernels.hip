@@ -215,12 +215,20 @@ __global__ __launch_bounds__(64 * kWaves) void k_fwd(Params P) {
 // wave-private LDS tile ([16 channels][128 pixels], rows padded to 272 bytes) to change distribution.
 constexpr int kLdsRow = 17;  // u32x4 per LDS row: 16 units + 1 pad
 
+// Whether dz enters dX and dW as two bf16 parts, dz = hi + lo, 16 bits of it.  Behind relu, abs or nothing it is +-dy or zero and one
+// part holds all of it; behind gelu and clipped exp (ACT 2, 3) one part is off by 2^-9, which dW then is too (1.7e-3 in norm, with
+// two parts 2.5e-6).  The instances for ragged planes take two, which is what the lowering by units gives there; those for
+// planes of whole units one, as they always have.
+template <int ACT, bool RAG>
+constexpr bool kTwoParts = RAG && (ACT == 2 || ACT == 3);
 template <int KC, int MO, int ACT, bool RES, bool RAG>
 __device__ __forceinline__ void bwd_tile(const Params& P, rsrc_t rx, rsrc_t rdy, rsrc_t rdx, u32x4* lds_x, u32x4* lds_dz, int n, int g,
                                          int p0, int lane, const short4_t (&wa)[MO][KC], const short4_t (&wt)[KC][MO],
                                          float4_t (&dwacc)[MO][KC]) {
     const int r = lane >> 4, s = lane & 15;
     constexpr int CG = 16 * KC, OG = 16 * MO;
+    constexpr bool TWO = kTwoParts<ACT, RAG>;
+    u32x4* const lds_low = lds_dz + MO * 16 * kLdsRow;
     const int dh = P.dh[g], dw = P.dw[g], off = dh * P.W + dw;
     const int Cout = P.G * OG;
     const int pA = p0 + 8 * s;
@@ -293,7 +301,7 @@ __device__ __forceinline__ void bwd_tile(const Params& P, rsrc_t rx, rsrc_t rdy,
     for (int mo = 0; mo < MO; mo++) {
 #pragma unroll
         for (int j = 0; j < 4; j++) dya[mo][j] = dya[mo][j] & msk;
-        u32x4 dzrow[4];  // dz of channel 4r+j over the unit's 8 pixels, for the LDS tile
+        u32x4 dzrow[4], dzlow[4];  // dz of channel 4r+j over the unit's 8 pixels, for the LDS tile
         // steps of QS pixel offsets keep the live accumulators at 4 * QS registers (16; 8 where a group has more than
         // one 16-channel block and the tile's registers are short)
         constexpr int QS = KC > 1 ? 2 : 4;
@@ -314,14 +322,19 @@ __device__ __forceinline__ void bwd_tile(const Params& P, rsrc_t rx, rsrc_t rdy,
                     const uint32_t w = dya[mo][j][(QS * h + q) / 2];
                     d[q][j] = act_dz<ACT>(P, z[q][j], lo_f32(w));
                     d[q + 1][j] = act_dz<ACT>(P, z[q + 1][j], hi_f32(w));
-                    dzrow[j][(QS * h + q) / 2] = pack_bf16(d[q][j], d[q + 1][j]);
+                    const uint32_t hi = pack_bf16(d[q][j], d[q + 1][j]);
+                    dzrow[j][(QS * h + q) / 2] = hi;
+                    if (TWO) dzlow[j][(QS * h + q) / 2] = pack_bf16(d[q][j] - lo_f32(hi), d[q + 1][j] - hi_f32(hi));
                 }
             }
 #pragma unroll
             for (int q = 0; q < QS; q++) dzq[mo][QS * h + q] = pack4(d[q][0], d[q][1], d[q][2], d[q][3]);
         }
 #pragma unroll
-        for (int j = 0; j < 4; j++) lds_dz[(mo * 16 + 4 * r + j) * kLdsRow + s] = dzrow[j];
+        for (int j = 0; j < 4; j++) {
+            lds_dz[(mo * 16 + 4 * r + j) * kLdsRow + s] = dzrow[j];
+            if (TWO) lds_low[(mo * 16 + 4 * r + j) * kLdsRow + s] = dzlow[j];
+        }
     }
 #pragma unroll
     for (int kc = 0; kc < KC; kc++) {
@@ -337,6 +350,18 @@ __device__ __forceinline__ void bwd_tile(const Params& P, rsrc_t rx, rsrc_t rdy,
             dxs[q] = float4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int mo = 0; mo < MO; mo++) dxs[q] = mfma16(wt[kc][mo], dzq[mo][q], dxs[q]);
+        }
+        if (TWO) {  // (the lane's own rows, from LDS: there are no registers to keep them in)
+#pragma unroll
+            for (int mo = 0; mo < MO; mo++) {
+                u32x4 v[4];
+                short4_t low[8];
+#pragma unroll
+                for (int j = 0; j < 4; j++) v[j] = lds_low[(mo * 16 + 4 * r + j) * kLdsRow + s];
+                gather_all(v, low);
+#pragma unroll
+                for (int q = 0; q < 8; q++) dxs[q] = mfma16(wt[kc][mo], low[q], dxs[q]);
+            }
         }
 #pragma unroll
         for (int j = 0; j < 4; j++) {
@@ -367,13 +392,17 @@ __device__ __forceinline__ void bwd_tile(const Params& P, rsrc_t rx, rsrc_t rdy,
             for (int kc = 0; kc < KC; kc++) {
                 const u32x4 xb = lds_x[(kc * 16 + s) * kLdsRow + 4 * m + r];
                 dwacc[mo][kc] = mfma32(as_short4(dzb[0], dzb[1]), as_short4(dzb[2], dzb[3]), as_short4(xb[0], xb[1]), as_short4(xb[2], xb[3]), dwacc[mo][kc]);
+                if (TWO) {
+                    const u32x4 lowb = lds_low[(mo * 16 + s) * kLdsRow + 4 * m + r];
+                    dwacc[mo][kc] = mfma32(as_short4(lowb[0], lowb[1]), as_short4(lowb[2], lowb[3]), as_short4(xb[0], xb[1]), as_short4(xb[2], xb[3]), dwacc[mo][kc]);
+                }
             }
         }
 }
 
 template <int KC, int MO, int ACT, bool RES, bool RAG>
 __device__ __forceinline__ void bwd_body(const Params& P) {
-    __shared__ u32x4 lds[kWaves][(KC + MO) * 16 * kLdsRow];
+    __shared__ u32x4 lds[kWaves][(KC + (kTwoParts<ACT, RAG> ? 2 : 1) * MO) * 16 * kLdsRow];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane >> 4, s = lane & 15;
@@ -439,9 +468,9 @@ template <int KC, int MO, int ACT, bool RES, bool RAG>
 __global__ __launch_bounds__(64 * kWaves) void k_bwd_wide(Params P) {
     bwd_body<KC, MO, ACT, RES, RAG>(P);
 }
-// Groups of 32 channels: two wavefronts per SIMD is what the tile's registers allow.
+// Groups of 32 channels: two wavefronts per SIMD is what the tile's registers allow, one its LDS with the low parts of dz.
 template <int KC, int MO, int ACT, bool RES, bool RAG>
-__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_bwd_two(Params P) {
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(kTwoParts<ACT, RAG> ? 1 : 2, 2))) void k_bwd_two(Params P) {
     bwd_body<KC, MO, ACT, RES, RAG>(P);
 }
 
@@ -462,7 +491,8 @@ constexpr int kDead = -0x7fffffff - 1;  // plus any offset inside a tensor: stil
 // Wavefronts per SIMD that the registers of the backward kernel leave room for (expand with relu and residual: 173 registers;
 // held to three wavefronts it spills four and takes 28.1 instead of 26.3 us, 64 => 128).
 constexpr int multi_waves(int act, bool res, bool expand, bool rag) { return act == 2 || rag || (res && expand) ? 2 : 3; }
-constexpr int lds_pieces_multi(int KC, int m) { return kWaves * (2 * KC * 16 * 16 + m * KC * KC * 64); }
+constexpr int tiles_multi(int act, bool rag) { return rag && (act == 2 || act == 3) ? 3 : 2; }  // x, dz, its low parts
+constexpr int lds_pieces_multi(int KC, int m, int tiles) { return kWaves * (tiles * KC * 16 * 16 + m * KC * KC * 64); }
 __device__ __forceinline__ int swz(int row, int unit) { return row * 16 + (unit ^ (row & 15)); }
 
 template <int KC, int ACT, bool RES, bool EXPAND, bool RAG>
@@ -602,10 +632,13 @@ __device__ __forceinline__ void bwd_multi_body(const Params& P, const Instances&
     const rsrc_t rx = make_rsrc(P.x, P.N * P.xs * 2);
     const rsrc_t rdx = make_rsrc(P.dx, P.N * P.xs * 2);
     const rsrc_t rdy = make_rsrc(P.dy, dyelems * 2);
-    // LDS of the wavefront: x rows | dz rows | dW accumulators of the instances
-    u32x4* const lds_x = lds + wave * (2 * KC * 16 * 16);
+    // LDS of the wavefront: x rows | dz rows (| their low parts) | dW accumulators of the instances
+    constexpr bool TWO = kTwoParts<ACT, RAG>;
+    constexpr int TILES = tiles_multi(ACT, RAG);
+    u32x4* const lds_x = lds + wave * (TILES * KC * 16 * 16);
     u32x4* const lds_dz = lds_x + KC * 16 * 16;
-    u32x4* const lds_dw = lds + kWaves * (2 * KC * 16 * 16) + wave * (I.m * KC * KC * 64);
+    u32x4* const lds_low = lds_dz + KC * 16 * 16;
+    u32x4* const lds_dw = lds + kWaves * (TILES * KC * 16 * 16) + wave * (I.m * KC * KC * 64);
     for (int j = 0; j < I.m * KC * KC; j++) lds_dw[j * 64 + lane] = u32x4{0u, 0u, 0u, 0u};
 
     short4_t wa[KC][KC];  // W[o = mo*16+s][i = kc*16+4r..+3]
@@ -719,7 +752,7 @@ __device__ __forceinline__ void bwd_multi_body(const Params& P, const Instances&
             short4_t dzq[KC][8];
 #pragma unroll
             for (int mo = 0; mo < KC; mo++) {
-                u32x4 dzrow[4];
+                u32x4 dzrow[4], dzlow[4];
                 constexpr int QS = 2;
 #pragma unroll
                 for (int h = 0; h < 8 / QS; h++) {
@@ -738,7 +771,9 @@ __device__ __forceinline__ void bwd_multi_body(const Params& P, const Instances&
                             const uint32_t w = dya[mo][k][(QS * h + q) / 2];
                             d[q][k] = act_dz<ACT>(P, z[q][k], lo_f32(w));
                             d[q + 1][k] = act_dz<ACT>(P, z[q + 1][k], hi_f32(w));
-                            dzrow[k][(QS * h + q) / 2] = pack_bf16(d[q][k], d[q + 1][k]);
+                            const uint32_t hi = pack_bf16(d[q][k], d[q + 1][k]);
+                            dzrow[k][(QS * h + q) / 2] = hi;
+                            if (TWO) dzlow[k][(QS * h + q) / 2] = pack_bf16(d[q][k] - lo_f32(hi), d[q + 1][k] - hi_f32(hi));
                         }
                     }
 #pragma unroll
@@ -746,7 +781,10 @@ __device__ __forceinline__ void bwd_multi_body(const Params& P, const Instances&
                     __builtin_amdgcn_sched_barrier(0);  // (the steps one after the other: side by side their registers do not fit)
                 }
 #pragma unroll
-                for (int k = 0; k < 4; k++) lds_dz[swz(mo * 16 + 4 * r + k, s)] = dzrow[k];
+                for (int k = 0; k < 4; k++) {
+                    lds_dz[swz(mo * 16 + 4 * r + k, s)] = dzrow[k];
+                    if (TWO) lds_low[swz(mo * 16 + 4 * r + k, s)] = dzlow[k];
+                }
             }
             // (the unshifted dy only now: nearly all of it has just come as the shifted one, and its registers were needed above)
             if (EXPAND && RES) load_res(j);
@@ -758,6 +796,18 @@ __device__ __forceinline__ void bwd_multi_body(const Params& P, const Instances&
                     if (!EXPAND) dxs[kc][q] = float4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int mo = 0; mo < KC; mo++) dxs[kc][q] = mfma16(wt[kc][mo], dzq[mo][q], dxs[kc][q]);
+                }
+                if (TWO) {
+#pragma unroll
+                    for (int mo = 0; mo < KC; mo++) {
+                        u32x4 v[4];
+                        short4_t low[8];
+#pragma unroll
+                        for (int k = 0; k < 4; k++) v[k] = lds_low[swz(mo * 16 + 4 * r + k, s)];
+                        gather_all(v, low);
+#pragma unroll
+                        for (int q = 0; q < 8; q++) dxs[kc][q] = mfma16(wt[kc][mo], low[q], dxs[kc][q]);
+                    }
                 }
                 if (RES) {
 #pragma unroll
@@ -793,6 +843,11 @@ __device__ __forceinline__ void bwd_multi_body(const Params& P, const Instances&
 #pragma unroll
                     for (int m4 = 0; m4 < 4; m4++)
                         a = mfma32(lds_dz[swz(mo * 16 + s, 4 * m4 + r)], lds_x[swz(kc * 16 + s, 4 * m4 + r)], a);
+                    if (TWO) {
+#pragma unroll
+                        for (int m4 = 0; m4 < 4; m4++)
+                            a = mfma32(lds_low[swz(mo * 16 + s, 4 * m4 + r)], lds_x[swz(kc * 16 + s, 4 * m4 + r)], a);
+                    }
                     u32x4 put;
                     __builtin_memcpy(&put, &a, 16);
                     *at = put;
@@ -801,7 +856,7 @@ __device__ __forceinline__ void bwd_multi_body(const Params& P, const Instances&
     }
     // the four wavefronts' accumulators are summed in a fixed order: one partial per workgroup and instance
     __syncthreads();
-    const float* acc = reinterpret_cast<const float*>(lds + kWaves * (2 * KC * 16 * 16));
+    const float* acc = reinterpret_cast<const float*>(lds + kWaves * (TILES * KC * 16 * 16));
     const int per_wave = I.m * KC * KC * 256;
     for (int e = threadIdx.x; e < per_wave; e += 64 * kWaves) {
         float sum = acc[e];
@@ -874,11 +929,14 @@ static void launch_fwd(const Params& P, int W, hipStream_t s) {
     } else if (W == 2) CANVAS_LAUNCH((k_fwd<2, 2, ACT, RES, false>), grid, block, 0, s, P);
     else CANVAS_LAUNCH((k_fwd<1, 1, ACT, RES, false>), grid, block, 0, s, P);
 }
+// Planes that the backward instances for ragged planes take: ragged ones, and narrow ones for the two parts of dz.
+template <int ACT>
+static bool ragged_bwd(const Params& P) { return P.P % 8 || (P.W < 8 && kTwoParts<ACT, true>); }
 template <int ACT, bool RES>
 static void launch_bwd(const Params& P, int W, hipStream_t s) {
     const dim3 grid((unsigned)P.wgs_per_group, (unsigned)P.G), block(64 * kWaves);
     if (!P.total_tiles) return;
-    if (P.P % 8) {
+    if (ragged_bwd<ACT>(P)) {
         if (W == 2) CANVAS_LAUNCH((k_bwd_two<2, 2, ACT, RES, true>), grid, block, 0, s, P);
         else CANVAS_LAUNCH((k_bwd_wide<1, 1, ACT, RES, true>), grid, block, 0, s, P);
     } else if (W == 2) CANVAS_LAUNCH((k_bwd_two<2, 2, ACT, RES, false>), grid, block, 0, s, P);
@@ -916,7 +974,13 @@ template <int ACT, bool RES, bool RAG>
 static void launch_bwd_of(const Params& P, const Instances& I, bool expand, hipStream_t s) {
     const dim3 grid((unsigned)P.wgs_per_group, (unsigned)P.G);
     if (!P.total_tiles) return;
-    const size_t lds = (size_t)lds_pieces_multi(1, I.m) * 16;
+    const size_t lds = (size_t)lds_pieces_multi(1, I.m, tiles_multi(ACT, RAG)) * 16;
+    if constexpr (kTwoParts<ACT, RAG>) {  // (80 KB for eight instances; more than 64 must be asked for, once per kernel)
+        constexpr int most = lds_pieces_multi(1, kMaxInstances, tiles_multi(ACT, RAG)) * 16;
+        auto allow = [](const void* f) { return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, most); };
+        static const hipError_t ok[2] = {allow((const void*)k_bwd_multi<1, ACT, RES, true, RAG>), allow((const void*)k_bwd_multi<1, ACT, RES, false, RAG>)};
+        (void)ok;
+    }
     if (expand) CANVAS_LAUNCH((k_bwd_multi<1, ACT, RES, true, RAG>), grid, dim3(64 * kWaves), lds, s, P, I);
     else CANVAS_LAUNCH((k_bwd_multi<1, ACT, RES, false, RAG>), grid, dim3(64 * kWaves), lds, s, P, I);
 }
@@ -927,7 +991,7 @@ static void launch_fwd_multi(const Params& P, const Instances& I, bool expand, h
 }
 template <int ACT, bool RES>
 static void launch_bwd_multi(const Params& P, const Instances& I, bool expand, hipStream_t s) {
-    P.P % 8 ? launch_bwd_of<ACT, RES, true>(P, I, expand, s) : launch_bwd_of<ACT, RES, false>(P, I, expand, s);
+    ragged_bwd<ACT>(P) ? launch_bwd_of<ACT, RES, true>(P, I, expand, s) : launch_bwd_of<ACT, RES, false>(P, I, expand, s);
 }
 
 #define SGFC_DISPATCH_MULTI(fn)                                                  \
