@@ -242,8 +242,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         for (int c = 0; c < Q.R; c++)
             for (int k = 0; k < TVT; k++) {
                 const int y = hh + k / 3 - 1, x = pp - hh * Q.W + k % 3 - 1;
-                if (WIN && ((unsigned)y >= (unsigned)Q.H || (unsigned)x >= (unsigned)Q.W)) continue;
-                sum = fmaf(w[c * wch + (tr ? TVT - 1 - k : k)], xs[c * P + (WIN ? y * Q.W + x : pp)], sum);
+                const bool in = !WIN || ((unsigned)y < (unsigned)Q.H && (unsigned)x < (unsigned)Q.W);
+                sum = fmaf(w[c * wch + (tr ? TVT - 1 - k : k)], in ? xs[c * P + (WIN ? y * Q.W + x : pp)] : 0.f, sum);
             }
         d[o * P] = Q.acc ? d[o * P] + sum : sum;
     }
@@ -507,8 +507,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         for (int64_t q = first; q < last; q++) {
             const int n = (int)(q / HPW), rem = (int)(q - (int64_t)n * HPW), h = rem / Q.Wp, w = rem - h * Q.Wp;
             const int y = h + kh - 1, x = w + t - 1;
-            if (h >= Q.H || w >= Q.W || (unsigned)y >= (unsigned)Q.H || (unsigned)x >= (unsigned)Q.W) continue;
-            sum = fmaf(ds[(int64_t)n * dlen + (int64_t)o * Q.P + h * Q.W + w], xs[(int64_t)n * xlen + (int64_t)col * Q.P + y * Q.W + x], sum);
+            if (h >= Q.H || w >= Q.W) continue;
+            const bool in = (unsigned)y < (unsigned)Q.H && (unsigned)x < (unsigned)Q.W;  // (else in the margin: the zero is multiplied)
+            sum = fmaf(ds[(int64_t)n * dlen + (int64_t)o * Q.P + h * Q.W + w], in ? xs[(int64_t)n * xlen + (int64_t)col * Q.P + y * Q.W + x] : 0.f, sum);
         }
         dw[(int64_t)o * Q.K + t] = sum;
     }

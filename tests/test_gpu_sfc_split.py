@@ -146,9 +146,7 @@ def test_weight_gradient(shape, o, groups):
             for i in range(3):
                 for j in range(3):
                     v = xp[:, k * cg:(k + 1) * cg, i:i + H, j:j + W]
-                    # (pixels whose x lies in the margin take no part, whatever dy is there)
-                    inside = torch.nn.functional.pad(torch.ones(H, W), (1, 1, 1, 1))[i:i + H, j:j + W].bool().expand(N, H, W).reshape(-1)
-                    ref[k * og:(k + 1) * og, :, i, j] = d[:, inside] @ v.transpose(0, 1).reshape(cg, -1)[:, inside].T
+                    ref[k * og:(k + 1) * og, :, i, j] = d @ v.transpose(0, 1).reshape(cg, -1).T  # (the margin's zeros are multiplied)
         if not extreme:
             # (N*H*W terms of unit variance: some 2^-24 of the sum's root mean square per hundred of them, in any order)
             assert (got - ref).norm() <= 1e-6 * ref.norm()
@@ -159,3 +157,40 @@ def test_weight_gradient(shape, o, groups):
         assert (err <= 1e-5 * ref.abs()[finite].clamp_min(float(N * H * W) ** 0.5)).all()
         assert torch.isfinite(got).any() and not torch.isfinite(got).all()
     r.close()
+
+
+@pytest.mark.parametrize("shape,o,groups", [((2, 64, 7, 9), 96, 1), ((3, 128, 5, 6), 128, 2)])
+def test_infinite_weights_and_gradients_at_the_border(shape, o, groups):
+    """The margin's zeros are multiplied, as in every fp32 FC kernel here: an infinite weight makes NaN of the pixels whose tap lies
+    there and infinities of the others (forward; and, on dy, the data gradient), an infinite dy NaN of the taps that leave the image."""
+    case = _case("3x3_border", WIN.format(g=groups, o=o), shape)
+    N, C, H, W = shape
+    og, cg = o // groups, C // groups
+    w = case["weights"][0].reshape(o, cg, 3, 3)
+    w[5, 2, 0, 0] = np.inf
+    dy = np.random.default_rng(11).standard_normal((N, o, H, W)).astype(np.float32)
+    dy[0, 1, 0, 1], dy[N - 1, o - 1, H - 1, W - 1] = np.inf, -np.inf
+    res, r, _ = harness.run_case(case, dy=dy)
+    r.close()
+
+    def windows(t):  # [N, channels, 9, H, W]
+        p = np.pad(t.astype(np.float64), ((0, 0), (0, 0), (1, 1), (1, 1)))
+        return np.stack([p[:, :, i:i + H, j:j + W] for i in range(3) for j in range(3)], 2)
+
+    ref = {"y": np.empty((N, o, H, W)), "dx": np.empty(shape), "dw": np.empty((o, cg, 3, 3))}
+    with np.errstate(invalid="ignore"):
+        for k in range(groups):
+            so, sc = slice(k * og, (k + 1) * og), slice(k * cg, (k + 1) * cg)
+            xw, dw, wk = windows(case["x"][:, sc]), windows(dy[:, so]), w[so].astype(np.float64).reshape(og, cg, 9)
+            for n in range(N):
+                ref["y"][n, so] = (wk.reshape(og, -1) @ xw[n].reshape(cg * 9, -1)).reshape(og, H, W)
+                ref["dx"][n, sc] = (wk[:, :, ::-1].transpose(1, 0, 2).reshape(cg, -1) @ dw[n].reshape(og * 9, -1)).reshape(cg, H, W)
+            d = dy[:, so].astype(np.float64).transpose(1, 0, 2, 3).reshape(og, -1)
+            ref["dw"][so] = (d @ xw.transpose(0, 3, 4, 1, 2).reshape(-1, cg * 9)).reshape(og, cg, 3, 3)
+    for name, got in [("y", res["y"]), ("dx", res["dx"]), ("dw", res["dw"][0])]:
+        want = ref[name]
+        got = got.reshape(want.shape)
+        assert np.array_equal(np.isnan(got), np.isnan(want)) and np.isnan(want).any(), name
+        inf, ok = np.isinf(want), np.isfinite(want)
+        assert np.array_equal(got[inf], want[inf]) and inf.any(), name
+        assert np.abs(got[ok] - want[ok]).max() <= 1e-5 * np.abs(want[ok]).max(), name
