@@ -29,6 +29,9 @@ __device__ __forceinline__ f16v mfma(const u32x4& a, const u32x4& b, f16v c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, c, 0, 0, 0);
 }
 
+// The fp32 instruction with the same tile, for what the parts cannot hold: 32 x 32 results, two of the contraction's elements (lane / 32)
+__device__ __forceinline__ f16v mfma_f32(float a, float b, f16v c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+
 // Eight floats -> their three bf16 parts.  A value that is infinite, NaN or rounds to an infinity makes the second part NaN:
 // every result that it reaches is NaN then, and is computed again in fp32.
 __device__ __forceinline__ void split8(const float (&v)[8], u32x4& h, u32x4& m, u32x4& l) {
@@ -210,42 +213,65 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     }
     // lane: pixel `col` of the wavefront's 32, outputs r % 4 + 8 * (r / 4) + 4 * half
     const int ob = o0 + 4 * half;
-    const bool tr = Q.transposed;
-    const float* const wbase = Q.w + (int64_t)g * Q.Og * Q.K;
-    const int64_t wch = tr ? (int64_t)Q.Og * TVT : TVT;
-    if (m0 + j >= Q.M) return;
-    float* const d = Q.dst + ((n0 + dn) * Q.G + g) * Q.Og * P + ob * P + pp;
-    float old[16];
+    const bool live = m0 + j < Q.M;
     unsigned again = 0;
 #pragma unroll
     for (int r = 0; r < 16; r++) {
-        const int o = r % 4 + 8 * (r / 4);
         total[r] += small[0][r] + small[1][r];
-        old[r] = 0.f;
-        if (ob + o < Q.Og) {
-            if (!(fabsf(total[r]) <= 3.4e38f)) again |= 1u << r;
-            if (Q.acc) old[r] = d[o * P];
+        if (live && ob + r % 4 + 8 * (r / 4) < Q.Og && !(fabsf(total[r]) <= 3.4e38f)) again |= 1u << r;
+    }
+    // Results that an infinity, a NaN or a value beyond the range of bf16 reached: once more, in fp32.  All of the wavefront's tile at
+    // the rate of the fp32 units, whatever the values are: operands straight from memory, the margin's zeros among them.
+    if (__builtin_expect(__ballot(again != 0) != 0, 0)) {
+        f16v exact;
+#pragma unroll
+        for (int r = 0; r < 16; r++) exact[r] = 0.f;
+        const bool tr = Q.transposed;
+        const int o = min(o0 + col, Q.Og - 1);
+        const float* const wo = Q.w + (int64_t)g * Q.Og * Q.K + (tr ? (int64_t)o * TVT : (int64_t)o * Q.K);
+        const int64_t wch = tr ? (int64_t)Q.Og * TVT : TVT;
+        const float* const xs = src + (int64_t)dn * Q.G * Q.R * P;
+        const int ww = pp - hh * Q.W;
+        int from[TVT];  // of the taps in a channel's plane, -1: in the margin
+#pragma unroll
+        for (int k = 0; k < TVT; k++) {
+            const int y = hh + k / 3 - 1, x = ww + k % 3 - 1;
+            from[k] = !WIN ? pp : ((unsigned)y < (unsigned)Q.H && (unsigned)x < (unsigned)Q.W ? y * Q.W + x : -1);
         }
+        constexpr int PAIRS = WIN ? 1 : 8;  // of channels whose loads are in flight together
+        for (int c0 = 0; c0 < Q.R; c0 += 2 * PAIRS) {
+            float wk[PAIRS][TVT], xk[PAIRS][TVT];
+#pragma unroll
+            for (int u = 0; u < PAIRS; u++) {
+                const int c = c0 + 2 * u + half, cc = min(c, Q.R - 1);
+#pragma unroll
+                for (int k = 0; k < TVT; k++) {
+                    wk[u][k] = wo[cc * wch + (tr ? TVT - 1 - k : k)];
+                    xk[u][k] = xs[cc * P + max(from[k], 0)];
+                    if (c >= Q.R) wk[u][k] = 0.f;
+                    if (c >= Q.R || from[k] < 0) xk[u][k] = 0.f;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < PAIRS; u++)
+#pragma unroll
+                for (int k = 0; k < TVT; k++) exact = mfma_f32(wk[u][k], xk[u][k], exact);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; r++) total[r] = again >> r & 1u ? exact[r] : total[r];
+    }
+    if (!live) return;
+    float* const d = Q.dst + ((n0 + dn) * Q.G + g) * Q.Og * P + ob * P + pp;
+    float old[16];
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+        const int o = r % 4 + 8 * (r / 4);
+        old[r] = Q.acc && ob + o < Q.Og ? d[o * P] : 0.f;
     }
 #pragma unroll
     for (int r = 0; r < 16; r++) {
         const int o = r % 4 + 8 * (r / 4);
-        if (ob + o < Q.Og && !(again >> r & 1u)) d[o * P] = Q.acc ? old[r] + total[r] : total[r];
-    }
-    // results that an infinity, a NaN or a value beyond the range of bf16 reached: once more, in fp32
-    while (again) {
-        const int r = __ffs(again) - 1, o = r % 4 + 8 * (r / 4);
-        again &= again - 1u;
-        const float* const w = wbase + (tr ? (int64_t)(ob + o) * TVT : (int64_t)(ob + o) * Q.K);
-        const float* const xs = src + dn * Q.G * Q.R * P;
-        float sum = 0.f;
-        for (int c = 0; c < Q.R; c++)
-            for (int k = 0; k < TVT; k++) {
-                const int y = hh + k / 3 - 1, x = pp - hh * Q.W + k % 3 - 1;
-                const bool in = !WIN || ((unsigned)y < (unsigned)Q.H && (unsigned)x < (unsigned)Q.W);
-                sum = fmaf(w[c * wch + (tr ? TVT - 1 - k : k)], in ? xs[c * P + (WIN ? y * Q.W + x : pp)] : 0.f, sum);
-            }
-        d[o * P] = Q.acc ? d[o * P] + sum : sum;
+        if (ob + o < Q.Og) d[o * P] = Q.acc ? old[r] + total[r] : total[r];
     }
 }
 
@@ -271,6 +297,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     constexpr int APART = AR * 32, XPART = 32 * kXRow;    // dwords of a part
     constexpr int BUF = 3 * (APART + XPART);
     extern __shared__ u32x4 lds_split[];  // [2][BUF] dwords
+    __shared__ int redo;
     uint32_t* const lds = reinterpret_cast<uint32_t*>(lds_split);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, half = lane >> 5;
@@ -410,6 +437,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     uint32_t *cur = lds, *next = lds + BUF;
     // (sign of dy in the step that begins at q)
     auto sign_of = [](int64_t q) { return (q >> 6) & 1 ? -1.f : 1.f; };
+    if (tid == 0) redo = 0;  // (read after the barriers of the steps)
     load();
     store(cur, sign_of(first));
     for (int64_t q = first; q < last; q += 64) {
@@ -469,50 +497,86 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         next = t;
     }
     // the sums of the wavefronts that shared the tile
-    __syncthreads();
     float* const share = reinterpret_cast<float*>(lds_split);  // [WS - 1][WM][3 * 16][64]
-    if (ws > 0) {
+    auto sum_up = [&](f16v (&part)[3]) {
+        __syncthreads();
+        if (ws > 0) {
 #pragma unroll
-        for (int t = 0; t < 3; t++)
+            for (int t = 0; t < 3; t++)
 #pragma unroll
-            for (int r = 0; r < 16; r++) share[(((ws - 1) * WM + wm) * 48 + t * 16 + r) * 64 + lane] = total[t][r];
-    }
-    __syncthreads();
-    if (ws > 0) return;
+                for (int r = 0; r < 16; r++) share[(((ws - 1) * WM + wm) * 48 + t * 16 + r) * 64 + lane] = part[t][r];
+        }
+        __syncthreads();
+        if (ws > 0) return;
 #pragma unroll
-    for (int k = 0; k < WS - 1; k++)
+        for (int k = 0; k < WS - 1; k++)
 #pragma unroll
-        for (int t = 0; t < 3; t++)
+            for (int t = 0; t < 3; t++)
 #pragma unroll
-            for (int r = 0; r < 16; r++) total[t][r] += share[((k * WM + wm) * 48 + t * 16 + r) * 64 + lane];
+                for (int r = 0; r < 16; r++) part[t][r] += share[((k * WM + wm) * 48 + t * 16 + r) * 64 + lane];
+    };
+    sum_up(total);
     // lane: channel `col`, outputs r % 4 + 8 * (r / 4) + 4 * half
-    if (col >= chans) return;
     const int ob = wm * 32 + 4 * half;
     float* const dw = Q.partial + (((int64_t)slice * Q.G + g) * Q.Og + o0) * Q.K + (int64_t)(r0 + col) * 9 + kh * 3;
     uint64_t again = 0;
+    if (ws == 0 && col < chans) {
 #pragma unroll
-    for (int r = 0; r < 16; r++) {
-        const int o = ob + r % 4 + 8 * (r / 4);
-        if (o >= rows) continue;
+        for (int r = 0; r < 16; r++) {
+            const int o = ob + r % 4 + 8 * (r / 4);
+            if (o >= rows) continue;
 #pragma unroll
-        for (int t = 0; t < 3; t++) {
-            dw[(int64_t)o * Q.K + t] = total[t][r];
-            if (!(fabsf(total[t][r]) <= 3.4e38f)) again |= (uint64_t)1 << (r * 3 + t);
+            for (int t = 0; t < 3; t++) {
+                dw[(int64_t)o * Q.K + t] = total[t][r];
+                if (!(fabsf(total[t][r]) <= 3.4e38f)) again |= (uint64_t)1 << (r * 3 + t);
+            }
         }
     }
-    while (again) {
-        const int k = __ffsll((unsigned long long)again) - 1, r = k / 3, t = k - r * 3, o = ob + r % 4 + 8 * (r / 4);
-        again &= again - 1;
-        float sum = 0.f;
-        for (int64_t q = first; q < last; q++) {
-            const int n = (int)(q / HPW), rem = (int)(q - (int64_t)n * HPW), h = rem / Q.Wp, w = rem - h * Q.Wp;
-            const int y = h + kh - 1, x = w + t - 1;
-            if (h >= Q.H || w >= Q.W) continue;
-            const bool in = (unsigned)y < (unsigned)Q.H && (unsigned)x < (unsigned)Q.W;  // (else in the margin: the zero is multiplied)
-            sum = fmaf(ds[(int64_t)n * dlen + (int64_t)o * Q.P + h * Q.W + w], in ? xs[(int64_t)n * xlen + (int64_t)col * Q.P + y * Q.W + x] : 0.f, sum);
+    if (__ballot(again != 0) != 0 && lane == 0) redo = 1;
+    __syncthreads();
+    // Once more in fp32, as in k_fwd_split; the wavefronts take eight positions in turn.
+    if (!redo) return;
+    f16v exact[3];
+#pragma unroll
+    for (int t = 0; t < 3; t++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) exact[t][r] = 0.f;
+    const float* const dr = ds + (int64_t)min(wm * 32 + col, rows - 1) * Q.P;
+    const float* const xr = xs + (int64_t)min(col, chans - 1) * Q.P;
+    constexpr int STEP = 8;
+    Pair pos = place(first + ws * STEP + half);
+    for (int64_t q = first + ws * STEP; q < last; q += WS * STEP) {
+        float a[STEP / 2], x[STEP / 2][3];
+#pragma unroll
+        for (int u = 0; u < STEP / 2; u++) {
+            while (pos.rem >= HPW) {
+                pos.rem -= HPW;
+                pos.n++;
+            }
+            const int h = quotient(pos.rem, Q.Wp, Q.mWp), w = pos.rem - h * Q.Wp, y = h + kh - 1;
+            const bool in = q + 2 * u + half < last && pos.n < Q.N && h < Q.H && w < Q.W;  // (else there is no such pixel of dy)
+            a[u] = dr[in ? (int64_t)pos.n * dlen + h * Q.W + w : 0];
+            if (!in) a[u] = 0.f;
+#pragma unroll
+            for (int t = 0; t < 3; t++) {
+                const bool xin = in && (unsigned)y < (unsigned)Q.H && (unsigned)(w + t - 1) < (unsigned)Q.W;
+                x[u][t] = xr[xin ? (int64_t)pos.n * xlen + y * Q.W + w + t - 1 : 0];
+                if (!xin) x[u][t] = 0.f;
+            }
+            pos.rem += 2;
         }
-        dw[(int64_t)o * Q.K + t] = sum;
+#pragma unroll
+        for (int u = 0; u < STEP / 2; u++)
+#pragma unroll
+            for (int t = 0; t < 3; t++) exact[t] = mfma_f32(a[u], x[u][t], exact[t]);
+        pos.rem += (WS - 1) * STEP;
     }
+    sum_up(exact);
+#pragma unroll
+    for (int r = 0; r < 16; r++)
+#pragma unroll
+        for (int t = 0; t < 3; t++)
+            if (again >> (r * 3 + t) & 1u) dw[(int64_t)(ob + r % 4 + 8 * (r / 4)) * Q.K + t] = exact[t][r];
 }
 
 // The weights of a contraction in the order in which k_fwd_split reads them: [group][32 outputs][step][part][lane], a lane's

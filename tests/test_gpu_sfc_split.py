@@ -194,3 +194,34 @@ def test_infinite_weights_and_gradients_at_the_border(shape, o, groups):
         inf, ok = np.isinf(want), np.isfinite(want)
         assert np.array_equal(got[inf], want[inf]) and inf.any(), name
         assert np.abs(got[ok] - want[ok]).max() <= 1e-5 * np.abs(want[ok]).max(), name
+
+
+def test_a_step_of_nan_is_no_slower_than_a_few_steps():
+    """Results computed again go through the fp32 matrix units as tiles: a step in which every result does takes about three times as
+    long as one of finite values (two passes, the second at the fp32 rate), and not a time that grows with each result's terms."""
+    import torch
+
+    r = harness.DagRunner(WIN.format(g=1, o=64), (16, 64, 28, 28), "f32")
+    times = []
+    for nan in [False, True]:
+        for t in [r.x, r.dy, *r.w]:
+            t.normal_()
+        if nan:
+            r.w[0].fill_(float("nan"))
+            r.dy.fill_(float("nan"))
+        best = float("inf")
+        for _ in range(5):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            for _ in range(3):
+                r.forward()
+                r.backward()
+            ev[1].record()
+            torch.cuda.synchronize()
+            best = min(best, ev[0].elapsed_time(ev[1]) / 3)
+        times.append(best)
+        if nan:
+            assert torch.isnan(r.y).all() and torch.isnan(r.dx).all() and torch.isnan(r.dw[0]).all()
+    r.close()
+    print(f"[nan step] finite {times[0] * 1e3:.1f} us, NaN {times[1] * 1e3:.1f} us")
+    assert times[1] <= 10 * times[0]
