@@ -2,7 +2,10 @@
 // of its 24 bits, x = h + m + l, and a product is the six parts' products down to 2^-24 of it,
 //     x * w = hh' + (hm' + mh' + mm' + hl' + lh') + [ml' + lm' + ll' < 2^-24, dropped],
 // each exact in the matrix unit.  v_mfma_f32_32x32x16_bf16 does 16 times the work of the fp32 instruction, six of them 2.7
-// times.
+// times.  The operands are cut times 2^24, the sums taken times 2^-48: the smallest fp32 subnormal's last bit then is 2^-125, a
+// normal bf16 value, so that no part of any operand is lost.  (As they are, operands below 2^-110 lose their third part and then
+// their second: 3e-5 of the result at 1e-36.)  What lies above, operands of 2^104 and results of 2^80 and more, becomes an
+// infinity, and such results are computed again in fp32.
 #include <algorithm>
 #include <type_traits>
 
@@ -32,7 +35,9 @@ __device__ __forceinline__ f16v mfma(const u32x4& a, const u32x4& b, f16v c) {
 // The fp32 instruction with the same tile, for what the parts cannot hold: 32 x 32 results, two of the contraction's elements (lane / 32)
 __device__ __forceinline__ f16v mfma_f32(float a, float b, f16v c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
 
-// Eight floats -> their three bf16 parts.  A value that is infinite, NaN or rounds to an infinity makes the second part NaN:
+constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;
+
+// Eight floats (times kUp) -> their three bf16 parts.  A value that is infinite, NaN or rounds to an infinity makes the second part NaN:
 // every result that it reaches is NaN then, and is computed again in fp32.
 __device__ __forceinline__ void split8(const float (&v)[8], u32x4& h, u32x4& m, u32x4& l) {
 #pragma unroll
@@ -136,7 +141,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
                 for (int k = 0; k < 8; k++) xreg[i][k] = r0 + xch[i] + k < Q.R ? xreg[i][k] : 0.f;
 #pragma unroll
-            for (int k = 0; k < 8; k++) xreg[i][k] = xch[i] >= 0 ? xreg[i][k] : 0.f;
+            for (int k = 0; k < 8; k++) xreg[i][k] = xch[i] >= 0 ? xreg[i][k] * kUp : 0.f;
             u32x4 h, m, l;
             split8(xreg[i], h, m, l);
             to[id] = h;
@@ -217,11 +222,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     unsigned again = 0;
 #pragma unroll
     for (int r = 0; r < 16; r++) {
-        total[r] += small[0][r] + small[1][r];
+        total[r] = (total[r] + (small[0][r] + small[1][r])) * kDown;
         if (live && ob + r % 4 + 8 * (r / 4) < Q.Og && !(fabsf(total[r]) <= 3.4e38f)) again |= 1u << r;
     }
-    // Results that an infinity, a NaN or a value beyond the range of bf16 reached: once more, in fp32.  All of the wavefront's tile at
-    // the rate of the fp32 units, whatever the values are: operands straight from memory, the margin's zeros among them.
+    // Results that an infinity, a NaN or a value beyond the scaled parts' range reached: once more, in fp32.  All of the wavefront's tile
+    // on the fp32 units, whatever the values are: operands straight from memory, the margin's zeros among them.  (Forward + data
+    // gradient at the size above 42 us, 166 where all of x, w and dy is NaN.)
     if (__builtin_expect(__ballot(again != 0) != 0, 0)) {
         f16v exact;
 #pragma unroll
@@ -252,10 +258,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                     if (c >= Q.R || from[k] < 0) xk[u][k] = 0.f;
                 }
             }
+            f16v part;  // (short chains, added in fp32: the matrix unit cuts off what its sums cannot hold)
+#pragma unroll
+            for (int r = 0; r < 16; r++) part[r] = 0.f;
 #pragma unroll
             for (int u = 0; u < PAIRS; u++)
 #pragma unroll
-                for (int k = 0; k < TVT; k++) exact = mfma_f32(wk[u][k], xk[u][k], exact);
+                for (int k = 0; k < TVT; k++) part = mfma_f32(wk[u][k], xk[u][k], part);
+#pragma unroll
+            for (int r = 0; r < 16; r++) exact[r] += part[r];
         }
 #pragma unroll
         for (int r = 0; r < 16; r++) total[r] = again >> r & 1u ? exact[r] : total[r];
@@ -286,7 +297,8 @@ constexpr int kXRow = 36;  // dwords of a channel's row of the operand tile: 34 
 // left and right are the same dwords moved by one position.
 // Sums: per step the five small products first, then the leading ones, in one chain; the steps in a row in fp32, the
 // wavefronts' sums at the end.  The matrix unit cuts off what its sums cannot hold, always downwards: over the thousands of steps
-// of a batch that adds up (3.6e-7 of the result at 32 channels, 32x28x28), so every other step multiplies -dy.  Results that are not finite are summed again in fp32, in the slice they occurred in.
+// of a batch that adds up (3.6e-7 of the result at 32 channels, 32x28x28), so every other step multiplies -dy.  Where a result is not finite, its workgroup sums its slice again on the fp32 units (28 us at the
+// size below, 100 where everything is NaN).
 // Bound by the vector instructions that cut and stage the operands, about 510 per wavefront and step (half of a wavefront's life at
 // two per SIMD; its 36 matrix instructions a quarter).  N=32, C=64, 28x28: 28 us (66 TFLOP/s), k_wgrad 46.5; 128 channels 32x14x14
 // 30.5 / 45.4, 384 in eight groups 51 / 73.  Errors against fp64: 1.04e-7 and 9.1e-8, k_wgrad's 1.15 and 1.02e-7.
@@ -404,13 +416,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         to[part] = m;
         to[2 * part] = tile::pack_bf16(m0 - tile::lo_f32(m), m1 - tile::hi_f32(m));
     };
-    auto store = [&](uint32_t* to, float sign) {  // (zero in the margin and past the last row)
+    auto store = [&](uint32_t* to, float dy_factor) {  // (zero in the margin and past the last row)
 #pragma unroll
         for (int i = 0; i < DN; i++) {  // (the 16-byte pieces of a row change places with its number: reads of 32 rows in different banks)
             const int row = i * 8 + rr;
             float v[2];
 #pragma unroll
-            for (int e = 0; e < 2; e++) v[e] = din[e] && row < rows ? dreg[i][e] * sign : 0.f;
+            for (int e = 0; e < 2; e++) v[e] = din[e] && row < rows ? dreg[i][e] * dy_factor : 0.f;
             put(to + row * 32 + (((pair >> 2) ^ (row & 7)) << 2) + (pair & 3), APART, v);
         }
         uint32_t* const x = to + 3 * APART;
@@ -419,13 +431,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
             const int row = i * 8 + rr;
             float v[2];
 #pragma unroll
-            for (int e = 0; e < 2; e++) v[e] = xin[e] && row < chans ? xreg[i][e] : 0.f;
+            for (int e = 0; e < 2; e++) v[e] = xin[e] && row < chans ? xreg[i][e] * kUp : 0.f;
             put(x + row * kXRow + pair, XPART, v);
         }
         if (wave == 0) {
             float v[2];
 #pragma unroll
-            for (int e = 0; e < 2; e++) v[e] = ein[e] && (tid >> 1) < chans ? ereg[e] : 0.f;
+            for (int e = 0; e < 2; e++) v[e] = ein[e] && (tid >> 1) < chans ? ereg[e] * kUp : 0.f;
             put(x + (tid >> 1) * kXRow + 32 + (tid & 1), XPART, v);
         }
     };
@@ -439,7 +451,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     auto sign_of = [](int64_t q) { return (q >> 6) & 1 ? -1.f : 1.f; };
     if (tid == 0) redo = 0;  // (read after the barriers of the steps)
     load();
-    store(cur, sign_of(first));
+    store(cur, sign_of(first) * kUp);
     for (int64_t q = first; q < last; q += 64) {
         __syncthreads();  // (this step is written, and the other buffer has been read)
         const bool more = q + 64 < last;
@@ -491,7 +503,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         for (int t = 0; t < 3; t++)
 #pragma unroll
             for (int r = 0; r < 16; r++) total[t][r] = fmaf(sum[t][r], sign_of(q), total[t][r]);
-        if (more) store(next, sign_of(q + 64));
+        if (more) store(next, sign_of(q + 64) * kUp);
         uint32_t* const t = cur;
         cur = next;
         next = t;
@@ -527,6 +539,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
             if (o >= rows) continue;
 #pragma unroll
             for (int t = 0; t < 3; t++) {
+                total[t][r] *= kDown;
                 dw[(int64_t)o * Q.K + t] = total[t][r];
                 if (!(fabsf(total[t][r]) <= 3.4e38f)) again |= (uint64_t)1 << (r * 3 + t);
             }
@@ -565,10 +578,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
             }
             pos.rem += 2;
         }
+        f16v part[3];
+#pragma unroll
+        for (int t = 0; t < 3; t++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) part[t][r] = 0.f;
 #pragma unroll
         for (int u = 0; u < STEP / 2; u++)
 #pragma unroll
-            for (int t = 0; t < 3; t++) exact[t] = mfma_f32(a[u], x[u][t], exact[t]);
+            for (int t = 0; t < 3; t++) part[t] = mfma_f32(a[u], x[u][t], part[t]);
+#pragma unroll
+        for (int t = 0; t < 3; t++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) exact[t][r] += part[t][r];
         pos.rem += (WS - 1) * STEP;
     }
     sum_up(exact);
@@ -596,7 +618,7 @@ __global__ __launch_bounds__(kThreads) void k_split_weights(SplitJobs jobs) {
     for (int k = 0; k < 8; k++) {
         const int cc = min(c + k, J.R - 1), oc = min(o, J.Og - 1);
         v[k] = J.w[J.transposed ? (((int64_t)g * J.R + cc) * J.Og + oc) * J.TV + (J.TV - 1 - tap) : (((int64_t)g * J.Og + oc) * J.R + cc) * J.TV + tap];
-        v[k] = o < J.Og && c + k < J.R ? v[k] : 0.f;
+        v[k] = o < J.Og && c + k < J.R ? v[k] * kUp : 0.f;
     }
     u32x4 h, m, l;
     split8(v, h, m, l);

@@ -225,3 +225,45 @@ def test_a_step_of_nan_is_no_slower_than_a_few_steps():
     r.close()
     print(f"[nan step] finite {times[0] * 1e3:.1f} us, NaN {times[1] * 1e3:.1f} us")
     assert times[1] <= 10 * times[0]
+
+
+# magnitudes of x, of the weights and of dy: each as small as fp32 goes, against ones and against the inverse; products that are
+# subnormal; operands and results beyond what the scaled parts hold
+SCALES = [(1e-30, 1, 1), (1e-36, 1, 1), (1e-38, 1, 1e30), (1, 1e-37, 1e-36), (1e-41, 1e38, 1e-30), (1e-20, 1e-20, 1e-10), (1e31, 1e-30, 1e-25), (1e33, 1e-36, 1e-35), (1e20, 1e10, 1e-3)]
+
+
+@pytest.mark.parametrize("body,shape", [(WIN.format(g=1, o=64), (2, 64, 9, 11)), (FC.format(g=1, o=256), (140, 192, 14, 15))], ids=["3x3", "1x1"])
+@pytest.mark.parametrize("scales", SCALES, ids=lambda s: "_".join(f"{v:g}" for v in s))
+def test_operands_of_any_magnitude(body, shape, scales):
+    """Three bf16 parts hold an fp32 value of any magnitude, subnormal ones among them: the error of fp32 sums (2.5e-7 in norm; K and
+    N*H*W terms) plus the rounding of subnormal results, not that of the parts that would be lost."""
+    case = _case("magnitudes", body, shape)
+    case["x"] *= np.float32(scales[0])
+    case["weights"][0] *= np.float32(scales[1])
+    N, C, H, W = shape
+    o = case["weights"][0].shape[1]
+    dy = np.random.default_rng(17).standard_normal((N, o, H, W)).astype(np.float32) * np.float32(scales[2])
+    res, r, _ = harness.run_case(case, dy=dy)
+    r.close()
+    w = case["weights"][0].astype(np.float64).reshape(o, C, -1)
+    k = w.shape[2]
+
+    def rows(t):  # [channels * taps, N * H * W]
+        t = t.astype(np.float64)
+        if k == 9:
+            p = np.pad(t, ((0, 0), (0, 0), (1, 1), (1, 1)))
+            t = np.stack([p[:, :, i:i + H, j:j + W] for i in range(3) for j in range(3)], 2)
+        else:
+            t = t[:, :, None]
+        return t.transpose(1, 2, 0, 3, 4).reshape(t.shape[1] * k, -1)
+
+    planes = lambda m: m.reshape(-1, N, H, W).transpose(1, 0, 2, 3)
+    xr = rows(case["x"])
+    ref = {"y": planes(w.reshape(o, -1) @ xr), "dx": planes(w[:, :, ::-1].transpose(1, 0, 2).reshape(C, -1) @ rows(dy)),
+           "dw": dy.astype(np.float64).transpose(1, 0, 2, 3).reshape(o, -1) @ xr.T}
+    for name, got in [("y", res["y"]), ("dx", res["dx"]), ("dw", res["dw"][0])]:
+        want = ref[name]
+        got = got.astype(np.float64).reshape(want.shape)
+        err, size = np.linalg.norm(got - want), np.linalg.norm(want)
+        print(f"[magnitudes {scales} {name}] {err / size:.2e} of {size / want.size ** 0.5:.1e}")
+        assert err <= 2.5e-7 * size + 2.0 ** -149 * want.size ** 0.5, name
