@@ -665,7 +665,10 @@ class Emitter {
     // result, a softmax over the taps, the first maximum) cannot be had this way and the leaf keeps its hand-over (Fail).
     // mlanes: lanes of instance i in that view; meval: its value; mgrad: its gradient, mlanes(i) lanes.  The factor 1/T of
     // an avg fold on the way is applied where the lanes are added (`avg`; everything in between is linear).
+    // A consumer outside the image does not exist: its gradient is loaded as 0 and adds nothing, but times p's own value, if that is
+    // infinite or NaN, it would; then (mproduct) the lanes are masked before they are added.
     int mwin = -1;  // the window's context
+    bool mproduct = false;
     int mtaps() const { return G->ctxs[mwin].kh * G->ctxs[mwin].kw; }
     int mlanes(int i) const {
         const Inst& I = G->insts[i];
@@ -808,6 +811,7 @@ class Emitter {
             b.f1 = un.hi;
             emit(b);
             release(r);
+            mproduct |= lanes > 1;
             break;
         }
         case kBinaryI: {
@@ -820,8 +824,10 @@ class Emitter {
             }
             if (un.kind == kMul && G->insts[other].kind == kExt) {
                 mblend(other, lanes, kMul, false);
+                mproduct |= lanes > 1 && mlanes(other) == 1;  // (else the consumer's own, which is loaded as 0 as well)
                 break;
             }
+            mproduct |= lanes > 1;
             const int rg = alloc();
             emit(simple(OP_MOVR, lanes, rg));
             if (un.kind == kMul) {
@@ -843,6 +849,8 @@ class Emitter {
         default: throw Fail{"mirror: a gradient of all taps"};
         }
         if (mine < lanes) {
+            if (mproduct) emit(positional(OP_MASK, mwin, lanes));
+            mproduct = false;
             emit(simple(OP_FOLD, lanes, 0, avg ? kAvg : kSum));
             avg = false;
         }
@@ -853,6 +861,7 @@ class Emitter {
         const Ctx& c = G->ctxs[mwin];
         if (!c.terms.empty() || mlanes(i) != 1) throw Fail{"mirror: a window behind a shift"};
         bool avg = false;
+        mproduct = false;
         mgrad(i, avg);
         if (avg) throw Fail{"mirror: lanes that were never added"};
     }

@@ -58,3 +58,36 @@ def test_softmax_over_channels(oracle, idx, shape):
     res, r, dy = harness.run_case(case)
     check_against_oracle(oracle, case, res, dy)
     r.close()
+
+
+PRODUCTS = ["%1 = unfold %0 kh=3 kw=3\n%2 = unary %1 op=abs\n%3 = binary %1 %2 op=mul\n%4 = fold %3 op=sum\noutput %4\n",
+            "%1 = unfold %0 kh=5 kw=5\n%2 = binary %1 %1 op=mul\n%3 = fold %2 op=avg\noutput %3\n",
+            "%1 = unfold %0 kh=3 kw=3\n%2 = binary %0 %1 op=mul\n%3 = binary %1 %2 op=mul\n%4 = fold %3 op=sum\noutput %4\n",
+            "%1 = unfold %0 kh=5 kw=5\n%2 = binary %0 %1 op=mul\n%3 = binary %1 %2 op=mul\n%4 = fold %3 op=avg\noutput %4\n"]
+
+
+@pytest.mark.parametrize("shape", [(2, 10, 9, 7), (3, 16, 8, 16), (1, 33, 3, 2)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("idx", range(len(PRODUCTS)))
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_infinities_at_the_border(oracle, idx, shape, dtype):
+    """Consumers outside the image do not exist: an infinite pixel at the border gets what those inside hand back, and no 0 * infinity
+    from the others.  All values positive: nothing cancels."""
+    import numpy as np
+
+    from paper_2304_07741_amd import harness, workloads as wl
+
+    case = _mk(PRODUCTS[idx], shape, dtype, 930 + idx, [], f"mirror_inf{idx}")
+    x = np.abs(case["x"]) + np.float32(0.5)
+    x[0, 0, 0, 0], x[-1, 1, -1, -1], x[0, 3, shape[2] // 2, 0] = np.inf, np.inf, np.inf
+    case["x"] = x
+    dy = np.abs(wl.make_dy(case, shape)) + np.float32(0.5)
+    res, r, _ = harness.run_case(case, dy=dy)
+    assert "chain_bwd" in [d["name"] for d in r.launches(1)]
+    r.close()
+    ref = oracle.run(case["blob"], x, [], dy)
+    assert not np.isnan(ref["dx"]).any() and np.isinf(ref["dx"]).any()
+    for k in ("y", "dx"):
+        got, want = res[k], ref[k].reshape(res[k].shape)
+        assert np.array_equal(np.isposinf(got), np.isposinf(want)) and np.array_equal(np.isnan(got), np.isnan(want)), k
+        ok = np.isfinite(want)
+        assert np.abs(got[ok] - want[ok]).max() <= (1e-5 if dtype == "f32" else 2e-2) * np.abs(want[ok]).max(), k
