@@ -366,9 +366,16 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
     constexpr int64_t kLongPairs = (int64_t)16 << 20;
     std::vector<int> tm(dag.n_weights, 0);
     uint64_t plain_bytes = 0, tm_bytes = 0;  // weight copies and partials without and with them
+    uint64_t packed_bytes = 0;               // of the latter, what emit_fc and the cutting take when their launches are written
     for (int i = 0; i < dag.n_weights; i++) {
         const int k = dag.weight_node[i];
-        if (!dag.nodes[k].live || !fc_mfma[k]) continue;
+        if (!dag.nodes[k].live) continue;
+        if (!fc_mfma[k]) {
+            const uint64_t widened = bf16 ? align_up((uint64_t)wnumel[i] * 4) : 0;
+            plain_bytes += widened;
+            tm_bytes += widened;
+            continue;
+        }
         const bool from_x = fc_src(k) == 0, from_dy = k == dag.out && y_direct;
         const gfc::Params Q = fc_params(k), Wg = wgrad_params(k);
         const uint64_t wt = align_up((uint64_t)wnumel[i] * 2), part = align_up((uint64_t)gfc::wgrad_partials(Wg) * wnumel[i] * 4);
@@ -381,24 +388,37 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         const bool as_they_are = Q.TV == 1 && Q.R % 16 == 0 && covers(Q.R, Q.Og) && gfctm::shape(Q.N, Q.G, Q.R, 1, 1, Q.Og, Q.H, Q.W).Omp == Q.Og;
         if (from_x && covers(Q.R, Q.Og) && (Q.TV > 1 || as_they_are)) {
             tm[i] |= kTmFwd;
-            tm_bytes += align_up((uint64_t)gfctm::packed_elems(gfctm::shape(Q.N, Q.G, Q.R, Q.KH, Q.KW, Q.Og, Q.H, Q.W)) * 2);
+            if (!as_they_are) packed_bytes += align_up((uint64_t)gfctm::packed_elems(gfctm::shape(Q.N, Q.G, Q.R, Q.KH, Q.KW, Q.Og, Q.H, Q.W)) * 2);
         }
         if (from_dy && covers(Q.Og, Q.R)) {
             tm[i] |= kTmData;
-            tm_bytes += align_up((uint64_t)gfctm::packed_elems(gfctm::shape(Q.N, Q.G, Q.Og, Q.KH, Q.KW, Q.R, Q.H, Q.W)) * 2);
+            packed_bytes += align_up((uint64_t)gfctm::packed_elems(gfctm::shape(Q.N, Q.G, Q.Og, Q.KH, Q.KW, Q.R, Q.H, Q.W)) * 2);
         }
         if (!from_x && Q.K >= kLongContraction && (Q.TV > 1 || dag.numel(fc_src(k)) <= kLongPairs) && covers(2 * Q.R, Q.Og)) {
             tm[i] |= kTmFwd | kTmFwdPairs;
-            tm_bytes += align_up((uint64_t)gfctm::packed_elems(gfctm::shape(Q.N, Q.G, 2 * Q.R, Q.KH, Q.KW, Q.Og, Q.H, Q.W)) * 2) + align_up((uint64_t)dag.numel(fc_src(k)) * 4);
+            packed_bytes += align_up((uint64_t)gfctm::packed_elems(gfctm::shape(Q.N, Q.G, 2 * Q.R, Q.KH, Q.KW, Q.Og, Q.H, Q.W)) * 2) + align_up((uint64_t)dag.numel(fc_src(k)) * 4);
         }
         tm_bytes += part;
         if (!(tm[i] & kTmData)) tm_bytes += wt;
     }
     // (a plan that fits the library's static workspace keeps fitting it)
-    if (off + plain_bytes <= CANVAS_STATIC_WORKSPACE_BYTES && off + tm_bytes > CANVAS_STATIC_WORKSPACE_BYTES) tm.assign(dag.n_weights, 0);
+    if (off + plain_bytes <= CANVAS_STATIC_WORKSPACE_BYTES && off + tm_bytes + packed_bytes > CANVAS_STATIC_WORKSPACE_BYTES) {
+        tm.assign(dag.n_weights, 0);
+        packed_bytes = 0;
+    }
     const TakeFn take_bytes = [&off](uint64_t bytes) {
         const uint64_t o = off;
         off += align_up(bytes);
+        return (int64_t)o;
+    };
+    // Packed weights and pairs get their place now: what follows shares out the rest of the static workspace.
+    uint64_t packed_at = off;
+    off += packed_bytes;
+    const uint64_t packed_end = off;
+    const TakeFn take_packed = [&packed_at, packed_end](uint64_t bytes) {
+        const uint64_t o = packed_at;
+        packed_at += align_up(bytes);
+        if (packed_at > packed_end) throw std::runtime_error("internal: packed weights without a place");
         return (int64_t)o;
     };
     lay.wt.assign(dag.n_weights, -1);
@@ -587,12 +607,12 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
                 const bool src_x = srcn == 0;  // the caller's bf16 input is read directly
                 const bool to_y = k == dag.out && y_direct;  // the output node: written as bf16 where the caller wants it
                 if (tm[nd.widx] & kTmFwd) {
-                    const int64_t pairs = tm[nd.widx] & kTmFwdPairs ? take_bytes((uint64_t)dag.numel(srcn) * 4) : -1;
+                    const int64_t pairs = tm[nd.widx] & kTmFwdPairs ? take_packed((uint64_t)dag.numel(srcn) * 4) : -1;
                     if (pairs >= 0) {
                         const int64_t ne = dag.numel(srcn), block = (int64_t)Q.R * Q.P;
                         low->fwd.push_back({"gfc_split", 8.0 * ne, 0, [=](const RunArgs& a) { ref::split_bf16(val(a, srcn), a.ws + pairs, ne, block, a.stream); }});
                     }
-                    emit_fc(*low, false, dag, take_bytes, Q.TV > 1 ? "gfc_fwd_unfold" : "gfc_fwd", Q.G, Q.R, Q.KH, Q.KW, Q.Og, false, nd.widx,
+                    emit_fc(*low, false, dag, take_packed, Q.TV > 1 ? "gfc_fwd_unfold" : "gfc_fwd", Q.G, Q.R, Q.KH, Q.KW, Q.Og, false, nd.widx,
                             FcOperand{[=](const RunArgs& a) { return pairs >= 0 ? (const void*)(a.ws + pairs) : a.x; }, false, pairs >= 0},
                             [=](const RunArgs& a) { return to_y ? (const void*)a.y : (const void*)valw(a, k); }, false,
                             (pairs >= 0 ? 4.0 : 2.0) * dag.numel(srcn) + (to_y ? 2.0 : 4.0) * dag.numel(k) + 2.0 * wnumel[nd.widx], L.flops, !to_y);
@@ -773,7 +793,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             const double dgrad_bytes = (from_dy ? 2.0 : 4.0) * dag.numel(k) + (to_dx ? 2.0 : 4.0 * (1 + acc_s)) * dag.numel(srcn) + 2.0 * nw;
             if (tm[widx] & kTmData) {  // (the output's gradient is the first of the backward pass: there is nothing to add to yet)
                 if (D.acc) throw std::runtime_error("internal: a gradient before the output's");
-                emit_fc(*low, true, dag, take_bytes, TV > 1 ? "gfc_dgrad_unfold" : "gfc_dgrad", G, Og, Q.KH, Q.KW, Rrows, true, widx,
+                emit_fc(*low, true, dag, take_packed, TV > 1 ? "gfc_dgrad_unfold" : "gfc_dgrad", G, Og, Q.KH, Q.KW, Rrows, true, widx,
                         FcOperand{[](const RunArgs& a) { return a.dy; }, false},
                         [=](const RunArgs& a) { return to_dx ? (const void*)a.dx : (const void*)grad(a, srcn); }, false, dgrad_bytes, flops, !to_dx);
                 const WeightJob job = low->wjobs.back();  // (packed in the backward pass, where they are needed)
@@ -950,7 +970,6 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         else low->bwd.push_back({"copy_dx", ne * 8.0, 0, [=](const RunArgs& a) { ref::copy_f32(grad(a, 0), (float*)a.dx, ne, a.stream); }});
     }
     (void)esz;
-    if (bf16) low->ws_bytes = std::max<uint64_t>(off, 256);
     return low;
 }
 

@@ -381,3 +381,18 @@ def test_single_dim_spatial_folds_shapes_and_legality(lib, oracle):
             oracle.infer(H_ + body, (2, 8, 5, 6))
         with pytest.raises(B.CanvasError):
             B.canvas_dag_compile(H_ + body, (2, 8, 5, 6), B.CANVAS_BF16)
+
+
+# an FC behind a window of an fp32 tensor, and a squeeze whose two FCs run on the fp32 kernels, times its output
+SQUEEZE = (wl.HEADER + "%1 = unary %0 op=gelu\n%2 = unfold %1 kh=3 kw=3\n%3 = fc %2 groups=1 out=64\n%4 = fold %3 op=avg axis=HW\n"
+           "%5 = fc %4 groups=1 out=2048\n%6 = unary %5 op=relu\n%7 = fc %6 groups=1 out=64\n%8 = binary %7 %3 op=mul\noutput %8\n")
+
+
+@pytest.mark.parametrize("N,H", [(20, 43), (34, 33), (43, 28), (47, 28), (48, 28), (67, 23), (89, 20)])
+def test_packed_weights_and_pairs_leave_a_plan_in_the_static_workspace(lib, N, H):
+    """Plans that fit the static workspace without the tap-major kernels' buffers (58 to 65 MB here) fit it: either with them, the
+    widened weights and the partials of the fp32 FCs together, or the plan goes without."""
+    h = B.canvas_dag_compile(SQUEEZE, (N, 64, H, H), B.CANVAS_BF16)
+    need = B.canvas_dag_query(h).workspace_bytes
+    B.canvas_dag_destroy(h)
+    assert 50 << 20 < need <= 64 << 20
