@@ -137,8 +137,8 @@ int canvas_dag_compile(const void* blob, size_t blob_len, const int64_t in_shape
         int rc = canvas::parse_dag((const char*)blob, blob_len, in_shape, d->dag, err);
         if (rc != 0) return set_err(rc, err);
         d->bf16 = dt == CANVAS_BF16;
-        d->low = canvas::lower(d->dag, d->bf16, (flags & CANVAS_OPT_NO_FUSION) != 0);
         d->inference = (flags & CANVAS_OPT_INFERENCE) != 0;
+        d->low = canvas::lower(d->dag, d->bf16, (flags & CANVAS_OPT_NO_FUSION) != 0, d->inference);
         if (d->inference) canvas::make_inference_plan(*d->low);
 
         canvas_dag_info& I = d->info;

@@ -8,7 +8,7 @@ namespace canvas {
 
 constexpr int64_t kMinWeightElemsForBf16Intermediates = 16;
 
-std::unique_ptr<Lowering> lower(const Dag& full, bool bf16, bool no_fusion) {
+std::unique_ptr<Lowering> lower(const Dag& full, bool bf16, bool no_fusion, bool inference) {
     const Dag dag = without_dead_views(full);
     std::unique_ptr<Lowering> l;
     if (!no_fusion) {
@@ -26,7 +26,7 @@ std::unique_ptr<Lowering> lower(const Dag& full, bool bf16, bool no_fusion) {
         if (!l && !tiny_weight) l = lower_ufc(dag, bf16);
         if (!l && !tiny_weight) l = lower_dyn(dag, bf16);
     }
-    if (!l) l = lower_per_node(dag, bf16, !no_fusion);
+    if (!l) l = lower_per_node(dag, bf16, !no_fusion, inference);
     batch_weight_jobs(*l);
     batch_reduce_jobs(*l);
     return l;

@@ -87,7 +87,7 @@ void run_program(const chain::Program& pg0, const std::vector<Binding>& bind, bo
 
 }  // namespace
 
-std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_chains) {
+std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_chains, bool inference) {
     auto low = std::make_unique<Lowering>();
     const int n = (int)dag.nodes.size();
     const int P = dag.P();
@@ -453,8 +453,9 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         sfc::prepare_forward(sdata[i], !bf16);
         uint64_t bytes[2] = {0, 0};
         const bool both = sfwd[i].split && sdata[i].split;
+        const int directions = inference ? 1 : 2;  // (the transposed weights: for the backward pass alone)
         if (both)
-            for (int d = 0; d < 2; d++) bytes[d] = align_up((uint64_t)48 * sfc::split_job(d ? sdata[i] : sfwd[i]).items);
+            for (int d = 0; d < directions; d++) bytes[d] = align_up((uint64_t)48 * sfc::split_job(d ? sdata[i] : sfwd[i]).items);
         if (!both || (off <= CANVAS_STATIC_WORKSPACE_BYTES && off + bytes[0] + bytes[1] > CANVAS_STATIC_WORKSPACE_BYTES)) {
             sfwd[i] = sfc_params(k);
             sdata[i] = sfc::data_gradient_of(sfwd[i]);
@@ -462,7 +463,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             sfc::prepare_forward(sdata[i]);
             continue;
         }
-        for (int d = 0; d < 2; d++) {
+        for (int d = 0; d < directions; d++) {
             wsplit[d].push_back({i, (int64_t)off});
             off += bytes[d];
         }

@@ -96,8 +96,9 @@ inline bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_byt
 inline uint64_t align_up(uint64_t v, uint64_t a = 256) { return (v + a - 1) / a * a; }
 
 // Lowering by units: fused chains of memory-bound primitives between the FC nodes (fuse_chains), one kernel per
-// node for whatever no chain takes; fp32 tensors between units.  Handles every legal DAG.
-std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_chains);
+// node for whatever no chain takes; fp32 tensors between units.  Handles every legal DAG.  inference: no split weights for a
+// backward pass (the caller drops the pass itself).
+std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_chains, bool inference);
 
 // Fused shift -> grouped FC -> unary chain -> (+ input); nullptr when the DAG is not of that form.
 std::unique_ptr<Lowering> lower_sgfc(const Dag& dag, bool bf16);
@@ -111,6 +112,6 @@ std::unique_ptr<Lowering> lower_ufc(const Dag& dag, bool bf16);
 std::unique_ptr<Lowering> lower_dyn(const Dag& dag, bool bf16);
 
 // Picks the lowering: fused kernel families where a pattern applies, else per node.
-std::unique_ptr<Lowering> lower(const Dag& dag, bool bf16, bool no_fusion);
+std::unique_ptr<Lowering> lower(const Dag& dag, bool bf16, bool no_fusion, bool inference);
 
 }  // namespace canvas

@@ -396,3 +396,15 @@ def test_packed_weights_and_pairs_leave_a_plan_in_the_static_workspace(lib, N, H
     need = B.canvas_dag_query(h).workspace_bytes
     B.canvas_dag_destroy(h)
     assert 50 << 20 < need <= 64 << 20
+
+
+@pytest.mark.parametrize("body,shape,cut", [("%1 = unfold %0 kh=3 kw=3\n%2 = fc %1 groups=1 out=64\noutput %2\n", (8, 64, 28, 28), 2 * 4 * 9), ("%1 = fc %0 groups=1 out=128\noutput %1\n", (32, 128, 28, 28), 4 * 8)])
+def test_an_inference_plan_keeps_no_transposed_weights(lib, body, shape, cut):
+    """fp32 FCs on the bf16 matrix units cut their weights into 3 KB per 32 outputs x 16 rows x tap, forward and transposed; a plan
+    without a backward pass has the former only."""
+    need = []
+    for flags in (0, B.CANVAS_OPT_INFERENCE):
+        h = B.canvas_dag_compile(wl.HEADER + body, shape, B.CANVAS_F32, flags)
+        need.append(B.canvas_dag_query(h).workspace_bytes)
+        B.canvas_dag_destroy(h)
+    assert need[1] == need[0] - cut * 3072
