@@ -162,7 +162,7 @@ def infer_latency(args):
         "warmup": args.warmup, "ms_per_step": eager_ms, "higher_is_better": False, "scaling": "weak", "vs_baseline": None,
         "dtype": case["dtype"], "data": "synthetic",
         "config": {"workload": f"{case['name']} N={N} C={case['shape'][1]} H=W={case['shape'][2]} {case['dtype']} (seed {case['seed']})",
-                   "fused": bool(r.info.fused), "launches_fwd": nf, "launches_prepare": r.info.n_launches_prepare},
+                   "fused": bool(r.info.family), "launches_fwd": nf, "launches_prepare": r.info.n_launches_prepare},
         "eager_ms": eager_ms, "graph_ms": graph_ms, "graph_equals_eager": same, "kernel_sum_ms": sum(acc),
         "images_per_s_graph": N / (graph_ms * 1e-3),
         "kernels": [{"name": d["name"], "ms": round(acc[k], 5)} for k, d in enumerate(r.launches(0))]}))
@@ -275,7 +275,7 @@ def measure(case, flags, steps, warmup, rotate=True, kernel_steps=50):
     for b in (0, 1):
         for k, d in enumerate(first.launches(b)):
             launches.append({"phase": "bwd" if b else "fwd", "name": d["name"], "ms": acc[b][k], "bytes": d["bytes"], "flops": d["flops"]})
-    info = {"fused": bool(first.info.fused), "chains": int(first.info.n_fused_chains), "chain_nodes": int(first.info.n_fused_nodes),
+    info = {"fused": bool(first.info.family), "chains": int(first.info.n_fused_chains), "chain_nodes": int(first.info.n_fused_nodes),
             "buffer_sets": n_sets, "launches_fwd": nf, "launches_bwd": nb, "workspace_bytes": int(first.info.workspace_bytes),
             "min_bytes": first.info.min_bytes_fwd + first.info.min_bytes_bwd}
     for r in runners:

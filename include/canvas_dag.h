@@ -112,12 +112,20 @@ typedef struct canvas_options {
     uint32_t reserved[7]; /* must be zero */
 } canvas_options;
 
+typedef enum canvas_family {
+    CANVAS_FAMILY_UNITS = 0,         /* lowering by units: FC nodes, fused chains, single nodes */
+    CANVAS_FAMILY_SHIFT_FC = 1,      /* shift / grouped FC / unary / residual, one kernel per direction */
+    CANVAS_FAMILY_FC_GATE_FC = 2,    /* [unfold /] FC / [unary /] shift / gate / FC */
+    CANVAS_FAMILY_PIXEL_WEIGHTS = 3  /* window weights per pixel (FC / [softmax /] product with the unfolded input / fold / FC) */
+} canvas_family;
+
 typedef struct canvas_dag_info {
     int32_t n_nodes;                          /* including node 0, the input */
     int32_t out_node;
     int32_t n_weights;                        /* number of fc nodes */
     int32_t n_launches_fwd, n_launches_bwd;   /* kernels enqueued per call */
-    int32_t fused;                            /* 1 when one of the whole-DAG kernel families was chosen, else 0 (lowering by units; also the shift / FC family on planes that are no multiple of 8 pixels or narrower) */
+    int32_t fused;                            /* 1 when one of the whole-DAG kernel families was chosen, else 0; also 0, though `family` names it,
+                                                 for CANVAS_FAMILY_SHIFT_FC on planes that are no multiple of 8 pixels or narrower than 8 */
     int32_t n_launches_prepare;               /* inference plans: kernels canvas_dag_prepare enqueues, else 0 */
     int32_t n_fused_chains;                   /* lowering by units: chains of memory-bound nodes fused into one kernel each */
     int64_t out_shape[5];                     /* N, C, T, H, W */
@@ -129,7 +137,7 @@ typedef struct canvas_dag_info {
     double min_bytes_fwd;                     /* x read + y written + weights read, once each */
     double min_bytes_bwd;                     /* x, dy read + dx written + weights read + dW written */
     int32_t n_fused_nodes;                    /* nodes inside those chains (none of them is materialised unless a later unit reads it) */
-    int32_t reserved1;
+    int32_t family;                           /* canvas_family: whose kernels the plan launches */
 } canvas_dag_info;
 
 typedef struct canvas_launch_desc {

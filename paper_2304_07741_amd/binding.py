@@ -13,6 +13,7 @@ LIB_PATH = os.path.join(_HERE, "libcanvas_dag.so")
 CANVAS_F32, CANVAS_BF16 = 0, 1
 CANVAS_OPT_NO_FUSION = 1
 CANVAS_OPT_INFERENCE = 2
+CANVAS_FAMILY_UNITS, CANVAS_FAMILY_SHIFT_FC, CANVAS_FAMILY_FC_GATE_FC, CANVAS_FAMILY_PIXEL_WEIGHTS = 0, 1, 2, 3
 CANVAS_MAX_NODES = 64
 STATUS = {0: "OK", -1: "INVALID_BLOB", -2: "UNKNOWN_OP", -3: "SHAPE_MISMATCH", -4: "BAD_ARG",
           -5: "WORKSPACE_TOO_SMALL", -6: "UNSUPPORTED", -7: "HIP_ERROR"}
@@ -44,7 +45,7 @@ class CanvasDagInfo(ctypes.Structure):
         ("weight_node", ctypes.c_int32 * CANVAS_MAX_NODES),
         ("workspace_bytes", ctypes.c_uint64),
         ("fc_flops_fwd", ctypes.c_double), ("min_bytes_fwd", ctypes.c_double), ("min_bytes_bwd", ctypes.c_double),
-        ("n_fused_nodes", ctypes.c_int32), ("reserved1", ctypes.c_int32),
+        ("n_fused_nodes", ctypes.c_int32), ("family", ctypes.c_int32),
     ]
 
 

@@ -91,6 +91,7 @@ std::unique_ptr<Lowering> lower_dyn(const Dag& dag, bool bf16) {
 
     auto low = std::make_unique<Lowering>();
     low->fused = true;
+    low->family = CANVAS_FAMILY_PIXEL_WEIGHTS;
     uint64_t off = 0;
     const TakeFn take = [&off](uint64_t bytes) {
         const uint64_t o = off;

@@ -91,7 +91,8 @@ std::unique_ptr<Lowering> lower_sgfc(const Dag& dag, bool bf16) {
     P.wgs_per_group = (tiles_per_group + 4 * tpw - 1) / (4 * tpw);
 
     auto low = std::make_unique<Lowering>();
-    low->fused = Pn % 8 == 0 && dag.W >= 8;  // (what the query has always reported: planes of whole 8-pixel units)
+    low->fused = Pn % 8 == 0 && dag.W >= 8;  // (what the query has always reported; `family` says it for every plane)
+    low->family = CANVAS_FAMILY_SHIFT_FC;
     low->strided_io = true;
     const int elems = OG * CG;
     low->ws_bytes = align_up((uint64_t)G * P.wgs_per_group * elems * 4);

@@ -105,6 +105,7 @@ std::unique_ptr<Lowering> lower_ufc(const Dag& dag, bool bf16) {
 
     auto low = std::make_unique<Lowering>();
     low->fused = true;
+    low->family = CANVAS_FAMILY_FC_GATE_FC;
     const int64_t nw1 = (int64_t)C * K1, nw2 = (int64_t)O2 * K2;
     const double act = 2.0 * dag.numel(0), outb = 2.0 * dag.numel(dag.out);
     uint64_t off = 0;

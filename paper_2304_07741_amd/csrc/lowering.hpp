@@ -8,6 +8,7 @@
 #include <string>
 #include <vector>
 
+#include "../../include/canvas_dag.h"
 #include "dag.hpp"
 #include "wprep_kernels.hpp"
 #include "wreduce_kernels.hpp"
@@ -62,7 +63,8 @@ struct ReduceJob {
 };
 
 struct Lowering {
-    bool fused = false;            // one of the whole-DAG kernel families
+    bool fused = false;            // canvas_dag_info::fused
+    int family = 0;                // canvas_family
     bool strided_io = false;       // honours RunArgs::x_stride / y_stride
     int max_instances = 0;         // up to so many instances of a block run in the launches of block_fwd / block_bwd
     std::function<void(const BlockArgs&)> block_fwd, block_bwd;

@@ -408,3 +408,22 @@ def test_an_inference_plan_keeps_no_transposed_weights(lib, body, shape, cut):
         need.append(B.canvas_dag_query(h).workspace_bytes)
         B.canvas_dag_destroy(h)
     assert need[1] == need[0] - cut * 3072
+
+
+@pytest.mark.parametrize("H,W", [(56, 56), (8, 8), (13, 13), (7, 7), (4, 4), (9, 3), (16, 1)])
+def test_the_query_names_the_family_whose_kernels_run(lib, H, W):
+    """`family` says what the plan launches, on planes of any size; `fused` keeps what it has always said of ragged and narrow ones."""
+    first = {B.CANVAS_FAMILY_SHIFT_FC: "sgfc_fwd", B.CANVAS_FAMILY_FC_GATE_FC: "weight_prep", B.CANVAS_FAMILY_PIXEL_WEIGHTS: "weight_prep"}
+    for blob, C, want in ((wl.blob_shift_residual(64), 64, B.CANVAS_FAMILY_SHIFT_FC if W > 1 else B.CANVAS_FAMILY_UNITS),
+                          (wl.blob_sampled(64), 64, B.CANVAS_FAMILY_FC_GATE_FC), (wl.blob_involution(128), 128, B.CANVAS_FAMILY_PIXEL_WEIGHTS)):
+        if W < 4 and want in (B.CANVAS_FAMILY_FC_GATE_FC, B.CANVAS_FAMILY_PIXEL_WEIGHTS):
+            continue
+        for flags in (0, B.CANVAS_OPT_NO_FUSION):
+            h = B.canvas_dag_compile(blob, (2, C, H, W), B.CANVAS_BF16, flags)
+            info, name = B.canvas_dag_query(h), B.canvas_dag_launch_desc(h, 0, 0)["name"]
+            B.canvas_dag_destroy(h)
+            assert info.family == (0 if flags else want)
+            if info.family:
+                assert name == first[want] and info.fused == (1 if want != B.CANVAS_FAMILY_SHIFT_FC or (H * W % 8 == 0 and W >= 8) else 0)
+            else:
+                assert info.fused == 0 and name != "sgfc_fwd"
