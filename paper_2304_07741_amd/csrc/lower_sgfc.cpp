@@ -124,9 +124,7 @@ std::unique_ptr<Lowering> lower_sgfc(const Dag& dag, bool bf16) {
                         }});
     const int wpg = P.wgs_per_group;
     low->bwd.push_back({"sgfc_dw_reduce", 4.0 * G * elems * (wpg + 1), 0, [=](const RunArgs& a) {
-                            sgfc::Instances I;
-                            I.dw[0] = (float*)a.dw[widx];
-                            sgfc::dw_reduce((const float*)a.ws, I, G, wpg, elems, a.stream);
+                            sgfc::dw_reduce((const float*)a.ws, (float*)a.dw[widx], G, wpg, elems, a.stream);
                         }});
     // Blocks: the instances of one tile in one wavefront.  Groups of 16 channels and an output as wide as the input; up to
     // eight instances, whose dW accumulators (4 KB of LDS each per workgroup) leave two workgroups a compute unit.  One
@@ -161,7 +159,7 @@ std::unique_ptr<Lowering> lower_sgfc(const Dag& dag, bool bf16) {
             sgfc::Instances I;
             fill(b, Q, I);
             sgfc::backward_multi(Q, I, b.expand, b.args.stream);
-            sgfc::dw_reduce(Q.partial, I, G, wpg, elems, b.args.stream);
+            sgfc::dw_reduce_multi(Q.partial, I, G, wpg, elems, b.args.stream);
         };
     }
     return low;

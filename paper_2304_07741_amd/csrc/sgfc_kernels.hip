@@ -881,12 +881,11 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(mul
 // partials at a time, 16 bytes each, up to four loads in flight; eight lanes of a wavefront are added by lane exchanges, the
 // sixteen wavefronts through LDS with one barrier.  4 x 200 partials of 256 elements take 4.2-4.5 us, two instances' 4.2; with
 // eight elements per workgroup and a tree of seven barriers it was 4.2-4.6 (the step 0.1 us longer).
-template <bool MULTI>
-__global__ __launch_bounds__(1024) void k_dw_reduce(const float* __restrict__ partial, float* __restrict__ dw, Instances I, int n_partials, int elems) {
+__device__ __forceinline__ void dw_reduce_body(const float* __restrict__ partial, float* __restrict__ dw, int n_partials, int elems) {
     __shared__ float4_t red[16][8];
     const int g = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = lane & 7, row = wave * 8 + (lane >> 3);
-    const float* src = partial + (MULTI ? blockIdx.z * I.part_stride : 0) + (long long)g * n_partials * elems + blockIdx.x * 32 + col * 4;
+    const float* src = partial + (long long)g * n_partials * elems + blockIdx.x * 32 + col * 4;
     float4_t sum = {0.f, 0.f, 0.f, 0.f};
     for (int k0 = row; k0 < n_partials; k0 += 512) {
         float4_t v[4];
@@ -910,9 +909,14 @@ __global__ __launch_bounds__(1024) void k_dw_reduce(const float* __restrict__ pa
         float total = 0.f;
 #pragma unroll
         for (int w = 0; w < 16; w++) total += reinterpret_cast<const float*>(red[w])[threadIdx.x];
-        float* out = MULTI ? I.dw[blockIdx.z] : dw;
-        out[(long long)g * elems + blockIdx.x * 32 + threadIdx.x] = total;
+        dw[(long long)g * elems + blockIdx.x * 32 + threadIdx.x] = total;
     }
+}
+__global__ __launch_bounds__(1024) void k_dw_reduce(const float* __restrict__ partial, float* __restrict__ dw, int n_partials, int elems) {
+    dw_reduce_body(partial, dw, n_partials, elems);
+}
+__global__ __launch_bounds__(1024) void k_dw_reduce_multi(const float* __restrict__ partial, Instances I, int n_partials, int elems) {
+    dw_reduce_body(partial + blockIdx.z * I.part_stride, I.dw[blockIdx.z], n_partials, elems);
 }
 
 }  // namespace
@@ -1006,10 +1010,11 @@ static void launch_bwd_multi(const Params& P, const Instances& I, bool expand, h
 void forward_multi(const Params& P, const Instances& I, bool expand, hipStream_t s) { SGFC_DISPATCH_MULTI(launch_fwd_multi) }
 void backward_multi(const Params& P, const Instances& I, bool expand, hipStream_t s) { SGFC_DISPATCH_MULTI(launch_bwd_multi) }
 
-void dw_reduce(const float* partial, const Instances& I, int G, int n_partials, int elems, hipStream_t s) {
-    const dim3 grid((unsigned)(elems / 32), (unsigned)G, (unsigned)I.m);
-    if (I.m > 1) CANVAS_LAUNCH(k_dw_reduce<true>, grid, dim3(1024), 0, s, partial, (float*)nullptr, I, n_partials, elems);
-    else CANVAS_LAUNCH(k_dw_reduce<false>, grid, dim3(1024), 0, s, partial, I.dw[0], Instances(), n_partials, elems);
+void dw_reduce(const float* partial, float* dw, int G, int n_partials, int elems, hipStream_t s) {
+    CANVAS_LAUNCH(k_dw_reduce, dim3((unsigned)(elems / 32), (unsigned)G), dim3(1024), 0, s, partial, dw, n_partials, elems);
+}
+void dw_reduce_multi(const float* partial, const Instances& I, int G, int n_partials, int elems, hipStream_t s) {
+    CANVAS_LAUNCH(k_dw_reduce_multi, dim3((unsigned)(elems / 32), (unsigned)G, (unsigned)I.m), dim3(1024), 0, s, partial, I, n_partials, elems);
 }
 
 }  // namespace sgfc

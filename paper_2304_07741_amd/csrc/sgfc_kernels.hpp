@@ -48,7 +48,8 @@ void backward(const Params& P, int KC, int MO, hipStream_t s);
 // tensor, `w` and the partials of the instances are in I.
 void forward_multi(const Params& P, const Instances& I, bool expand, hipStream_t s);
 void backward_multi(const Params& P, const Instances& I, bool expand, hipStream_t s);
-void dw_reduce(const float* partial, const Instances& I, int G, int n_partials, int elems, hipStream_t s);
+void dw_reduce(const float* partial, float* dw, int G, int n_partials, int elems, hipStream_t s);
+void dw_reduce_multi(const float* partial, const Instances& I, int G, int n_partials, int elems, hipStream_t s);
 
 }  // namespace sgfc
 }  // namespace canvas
