@@ -80,10 +80,14 @@ std::unique_ptr<Lowering> lower_sgfc(const Dag& dag, bool bf16) {
     P.chunks = (Pn + 127) / 128;
     P.magicChunks = (uint32_t)((((uint64_t)1 << 32) + P.chunks - 1) / P.chunks);
     P.total_tiles = (long long)dag.N * G * P.chunks;
-    // Tiles per wavefront of the backward kernels: two share a wavefront's weights and its partial, but one after the other, so only
-    // where the launch is more than one round of wavefronts (four per SIMD: 4096).  Backward with one / two tiles, us: 840 tiles
-    // (30x128 planes of 28x28) 8.2 / 11.3, 5200 (100x128 of 40x40) 25.0 / 27.3, block 256 => 64 30x28x28 10.7 / 16.7, 64 => 128 11x32x32 7.3 / 10.5,
-    // 128 => 64 60x40x40 (3120) 13.7 / 15.1; 6400 (64x64 planes of 56x56) 16.6 / 16.8, block 64 => 128 there 26.7 / 26.2.
+    // Tiles per wavefront of the backward kernels: two share a wavefront's weights and its partial, but come one after the other.
+    // Backward with one / two, us, by the tiles of the launch, 56x56: 64 channels 2000 6.7 / 8.0, 4100 10.7 / 12.9, 5100 13.8 / 14.6,
+    // 5600 15.3 / 14.6, 6400 16.7 / 16.8, 7200 17.7 / 17.6, 8200 19.3 / 20.6; 128 channels 2000 10.5 / 12.8, 5100 25.4 / 26.9, 6400 30.3 / 32.4,
+    // 8200 38.2 / 38.6; blocks 64 => 128 2000 9.0 / 12.5, 3100 14.7 / 15.0, 5100 20.9 / 23.2, 6400 26.1 / 26.1, 128 => 64 2000 9.8 / 12.6, 5100 19.9 / 19.7,
+    // 6400 24.3 / 26.5; 55x55 4900 18.8 / 20.2, 6144 20.0 / 22.7.  One is faster or level by less than 5 % up to the line; beyond it
+    // the kernel alone would take one as well, within 6 % (on ragged planes 20), but a partial per workgroup then is 1 KB for every four tiles of a
+    // group, which two tiles halve: at most 1.6 MB below the line (6.3 with groups of 32), and above it what the reduction reads and the workspace holds grow with the
+    // batch (4096x64 planes of 56x56: 52 MB with two, within the 64 MB of the static workspace).
     int tpw = P.total_tiles > 6144 ? 2 : 1;
     if (const char* e = std::getenv("CANVAS_SGFC_TPW")) tpw = std::max(1, std::atoi(e));
     P.tiles_per_wave = tpw;

@@ -747,7 +747,9 @@ Params data_gradient_of(const Params& f) {
 // 32x14x14 40.8 + 39.7 / 21.4 + 21.4; eight groups of 32 32x14x14 22.8 + 21.0 / 14.2 + 14.2, of 64 16x7x7 16.7 + 17.4 / 13.4 + 13.4
 // (6.0 for the weights); 32 channels 32x28x28 13.9 + 13.0 / 10.6 + 10.7; but 48 channels 32x14x14 (98 workgroups) 12.7 + 13.0 /
 // 11.1 + 11.2.  Without a window: 128 channels 32x28x28 24.8 + 23.5 / 18.4 + 18.2, 512 channels 32x14x14 69.6 + 68.3 / 41.1 + 41.0;
-// but 64 channels 32x28x28 9.2 + 8.9 / 8.1 + 8.2, 512 channels 16x7x7 (104 workgroups) 19.1 + 18.2 / 17.7 + 16.8.
+// but 64 channels 32x28x28 9.2 + 8.9 / 8.1 + 8.2, 512 channels 16x7x7 (104 workgroups) 19.1 + 18.2 / 17.7 + 16.8.  Not below 32
+// channels or outputs, where part of a tile is padding: 3 x 3, the weights included, 24 channels 32x28x28 21.8 / 24.7, 5x14x14 15.9 / 22.6, 16
+// channels 32x28x28 13.7 / 18.8, eight groups of 16 44.6 / 58.0, of 24 16x14x14 21.6 / 23.9; 24 -> 64 channels 32x28x28 39.7 / 32.6 would gain.
 static bool split_forward(Params& p) {
     const bool win = p.KH == 3 && p.KW == 3;
     if (!win && p.TV != 1) return false;
@@ -822,7 +824,8 @@ static void split(Params& p, int workgroups, int step, int64_t max_partial_bytes
 // Weight gradient on the bf16 matrix units, behind a 3 x 3 window where a tile of 32 x 32 is filled (fp32 units / here, us): 64
 // channels 32x28x28 46.5 / 28.0, 1x28x28 10.3 / 7.9, 32x7x7 11.2 / 9.0; 128 channels 32x14x14 45.4 / 30.5, 16x56x20 95 / 62;
 // eight groups of 32 32x14x14 43.6 / 21.5, of 64 16x7x7 22.0 / 15.2; 48 channels 6x23x17 11.4 / 8.7; 32 channels 32x28x28
-// 22.7 / 14.7, 4x28x28 7.7 / 7.5; 64 channels 1x8x8 9.8 / 9.7.
+// 22.7 / 14.7, 4x28x28 7.7 / 7.5; 64 channels 1x8x8 9.8 / 9.7.  Below 32 channels it is a tile of padding in part: 16 channels 32x28x28
+// 11.2 / 12.4, eight groups of 16 42.4 / 52.6, though 24 channels 18.6 / 13.1.
 static bool split_wgrad(Params& p, int64_t max_partial_bytes) {
     if (p.KH != 3 || p.KW != 3 || p.Og < 32 || p.R < 32) return false;
     Params q = p;

@@ -92,8 +92,8 @@ __device__ __forceinline__ float act_dz(const Params& P, float z, float dy) {
 
 // Planes that are no multiple of eight pixels (RAG): a plane's last unit is `left` < 8 pixels of its own, then the next plane's.
 // Those are cleared where a sum over pixels would take them in and never stored, rows begin at any element, and an unshifted
-// access too can cross the tensor's end.  (The lowering by units, which such planes used to take: a step of N=6, 64 channels, 20x41 71.7 us, here
-// 19.3; N=64, 27x29 231, here 19.6; 64 => 128 channels N=5, 21x11 289, here 19.0.)
+// access too can cross the tensor's end.  (The lowering by units, which such planes used to take: a step of N=6, 64 channels, 20x41 72.7 us, here
+// 19.6; N=64, 27x29 235, here 19.5; 64 => 128 channels N=5, 21x11 289, here 19.8.)
 template <bool RAG>
 __device__ __forceinline__ void store_unit(rsrc_t r, int off, const u32x4& v, int left) {
     if (!RAG) {
@@ -481,8 +481,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(kTw
 // once and not m times, and the sum is taken in fp32 in instance order in registers and rounded once; the instances as
 // launches of their own wrote m rounded parts and added them in one more launch.  The loads of instance j + 1 are issued
 // as soon as the registers of instance j's are free.  N=64, 56x56, a step, launches
-// of their own / here: 64 => 128 channels 84.6 / 48.6 us, 128 => 64 81 / 52, 64 => 256 153 / 73, 256 => 64 158 / 84; N=8, 256 => 64,
-// 14x28 64 / 25.
+// of their own / here: 64 => 128 channels 84.6 / 46.8 us, 128 => 64 85.4 / 50.5, 64 => 256 159 / 82.6, 256 => 64 165 / 82.1.
 
 // dW accumulators of the instances live in LDS between tiles (m of them in registers would have to be indexed by a
 // constant); rows of the transposers are not padded but swizzled (unit ^ row), which leaves room for two instances'
