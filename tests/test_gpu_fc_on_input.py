@@ -103,3 +103,25 @@ def test_fp32_operands_keep_sixteen_bits(oracle, idx):
     off = float(np.mean(res["y"] != want.reshape(res["y"].shape)))
     print(f"[squares {idx}] share of y that is not the rounded exact sum: {off:.4f}")
     assert off <= 0.02
+
+
+SQUEEZE = ("%1 = unary %0 op=gelu\n%2 = unfold %1 kh=3 kw=3\n%3 = fc %2 groups=1 out=64\n%4 = fold %3 op=avg axis=HW\n%5 = fc %4 groups=1 out=96\n"
+           "%6 = unary %5 op=gelu\n%7 = fc %6 groups=1 out=64\n%8 = binary %7 %3 op=mul\noutput %8\n")
+
+
+@pytest.mark.parametrize("shape", [(2, 64, 7, 9), (5, 64, 16, 16)])
+def test_fcs_of_both_kinds_share_a_workspace(oracle, shape):
+    """Pairs and packed weights beside widened weights and the partials of the fp32 kernels: none of them overwrites another, in the
+    caller's workspace or in the library's."""
+    import torch
+
+    from paper_2304_07741_amd import binding as B, harness
+
+    case = wl._case("squeeze", wl.HEADER + SQUEEZE, shape, "bf16", 77, [(1, 64, 576), (1, 96, 64), (1, 64, 96)], [1 / 24, 1 / 8, 1 / 10])
+    res, r, dy = harness.run_case(case)
+    check_against_oracle(oracle, case, res, dy)
+    y = torch.full_like(r.y, float("nan"))
+    B.canvas_dag_forward_static(r.handle, r.x, r.w, y)
+    torch.cuda.synchronize()
+    assert torch.equal(y, r.y)
+    r.close()
