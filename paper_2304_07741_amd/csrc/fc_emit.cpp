@@ -1,22 +1,27 @@
 #include "fc_emit.hpp"
 
 #include "gfc_kernels.hpp"
+#include "gfc_staged_kernels.hpp"
 #include "gfc_tm_kernels.hpp"
 
 namespace canvas {
 
 void emit_fc(Lowering& low, bool backward, const Dag& dag, const TakeFn& take, const std::string& name, int G, int R, int kh, int kw, int Og,
-             bool transposed, int widx, FcOperand src, PtrFn dst, bool addend_is_dst, double bytes, double flops, bool dst_f32, bool softmax) {
+             bool transposed, int widx, FcOperand src, PtrFn dst, bool addend_is_dst, double bytes, double flops, bool dst_f32, bool softmax, bool weights_as_they_are) {
     std::vector<Launch>& list = backward ? low.bwd : low.fwd;
     const int64_t nw = (int64_t)G * Og * R * kh * kw;
     const int rows = src.pairs ? 2 * R : R;
     if (!src.f32 && gfctm::supported(dag.N, G, rows, kh, kw, Og, dag.H, dag.W)) {
         const gfctm::Params T = gfctm::shape(dag.N, G, rows, kh, kw, Og, dag.H, dag.W);
-        const bool identity = !src.pairs && !transposed && T.TV == 1 && T.gm == 1 && T.Rp == R && T.Omp == Og;
-        const int64_t opk = identity ? -1 : take((uint64_t)gfctm::packed_elems(T) * 2);
+        gfcst::Params S;
+        const bool staged = !weights_as_they_are && gfcst::plan(S, T, dst_f32, addend_is_dst, softmax);
+        const bool identity = !src.pairs && !transposed && gfctm::reads_weights_as_they_are(T) && !staged;
+        const int64_t elems = staged ? gfcst::packed_elems(S) : gfctm::packed_elems(T);
+        const int64_t opk = identity ? -1 : take((uint64_t)elems * 2);
         if (!identity) {
             WeightJob j;
-            j.job.kind = 0;
+            j.job.kind = staged ? 2 : 0;
+            j.job.steps = S.steps;
             j.job.G = T.G;
             j.job.R = T.R;
             j.job.Rw = R;
@@ -24,14 +29,25 @@ void emit_fc(Lowering& low, bool backward, const Dag& dag, const TakeFn& take, c
             j.job.TV = T.TV;
             j.job.gm = T.gm;
             j.job.Gm = T.Gm;
-            j.job.Rp = T.Rp;
-            j.job.Omp = T.Omp;
+            j.job.Rp = staged ? S.Rp : T.Rp;
+            j.job.Omp = staged ? S.Omp : T.Omp;
             j.job.transposed = transposed ? 1 : 0;
-            j.job.total = gfctm::packed_elems(T);
+            j.job.total = elems;
             j.widx = widx;
             j.off = opk;
-            j.bytes = 2.0 * nw + 2.0 * gfctm::packed_elems(T);
+            j.bytes = 2.0 * nw + 2.0 * elems;
             low.wjobs.push_back(j);
+        }
+        if (staged) {
+            list.push_back({name, bytes, flops, [=](const RunArgs& a) {
+                                gfcst::Params Q = S;
+                                Q.src = (const uint16_t*)src.ptr(a);
+                                Q.wp = (const uint16_t*)(a.ws + opk);
+                                Q.dst = const_cast<void*>(dst(a));
+                                Q.addend = addend_is_dst ? (const uint16_t*)dst(a) : nullptr;  // each lane reads the elements it then overwrites
+                                gfcst::forward(Q, a.stream);
+                            }});
+            return;
         }
         list.push_back({name, bytes, flops, [=](const RunArgs& a) {
                             gfctm::Params Q = T;
@@ -71,6 +87,12 @@ void emit_fc(Lowering& low, bool backward, const Dag& dag, const TakeFn& take, c
                         Q.addend = addend_is_dst ? (const uint16_t*)dst(a) : nullptr;
                         gfc::forward(Q, a.stream);
                     }});
+}
+
+uint64_t fc_packed_bytes(const Dag& dag, int G, int rows, int kh, int kw, int Og) {
+    const gfctm::Params T = gfctm::shape(dag.N, G, rows, kh, kw, Og, dag.H, dag.W);
+    gfcst::Params S;
+    return 2 * (uint64_t)(gfcst::plan(S, T, false, false, false) ? gfcst::packed_elems(S) : gfctm::packed_elems(T));
 }
 
 bool fc_softmax_fusable(const Dag& dag, int G, int R, int kh, int kw, int Og, const FcOperand& src) {

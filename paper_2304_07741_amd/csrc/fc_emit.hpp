@@ -23,10 +23,14 @@ struct FcOperand {
 // then (R, Og) are the swapped dims and the FC's own weights [G][R][Og][taps] are read transposed with the
 // taps flipped.  `addend_is_dst`: dst (bf16) already holds a tensor that the result is added to.
 // dst is bf16 unless dst_f32.  softmax (see fc_softmax_fusable): dst receives the softmax over the outputs of each pixel.
+// weights_as_they_are: only a kernel that reads the FC's own weights (gfctm::reads_weights_as_they_are holds), so that packing them is no launch more.
 // The launch goes to low.fwd or (backward) low.bwd; derived weight copies are registered in low.wjobs.
 void emit_fc(Lowering& low, bool backward, const Dag& dag, const TakeFn& take, const std::string& name, int G, int R, int kh, int kw, int Og,
              bool transposed, int widx, FcOperand src, PtrFn dst, bool addend_is_dst, double bytes, double flops, bool dst_f32 = false,
-             bool softmax = false);
+             bool softmax = false, bool weights_as_they_are = false);
+// What emit_fc takes from `take` where it packs the weights of a contraction over a bf16 source that gfctm::supported covers, without a
+// tensor that is added or a softmax (rows: 2 R for pairs).
+uint64_t fc_packed_bytes(const Dag& dag, int G, int rows, int kh, int kw, int Og);
 // Whether emit_fc can be asked (softmax = true, dst_f32) for the softmax over the FC's outputs instead of the outputs.
 bool fc_softmax_fusable(const Dag& dag, int G, int R, int kh, int kw, int Og, const FcOperand& src);
 

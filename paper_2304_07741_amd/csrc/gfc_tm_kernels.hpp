@@ -40,6 +40,8 @@ bool supported(int N, int G, int R, int KH, int KW, int Og, int H, int W);
 Params shape(int N, int G, int R, int KH, int KW, int Og, int H, int W);
 // Geometry of the data gradient: rows and outputs swapped (pack the weights with transposed = true).
 Params data_gradient_of(const Params& fwd);
+// The FC's own weights are in the packed layout already (no window, nothing merged or padded).
+inline bool reads_weights_as_they_are(const Params& P) { return P.TV == 1 && P.gm == 1 && P.Rp == P.R && P.Omp == P.Og; }
 inline int64_t packed_elems(const Params& P) { return (int64_t)P.Gm * P.Omp * P.TV * P.Rp; }
 
 // y = FC(src) on the packed weights P.wp (packed by a job of wprep_kernels.hpp; `transposed` there gives the data

@@ -388,15 +388,15 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         const bool as_they_are = Q.TV == 1 && Q.R % 16 == 0 && covers(Q.R, Q.Og) && gfctm::shape(Q.N, Q.G, Q.R, 1, 1, Q.Og, Q.H, Q.W).Omp == Q.Og;
         if (from_x && covers(Q.R, Q.Og) && (Q.TV > 1 || as_they_are)) {
             tm[i] |= kTmFwd;
-            if (!as_they_are) packed_bytes += align_up((uint64_t)gfctm::packed_elems(gfctm::shape(Q.N, Q.G, Q.R, Q.KH, Q.KW, Q.Og, Q.H, Q.W)) * 2);
+            if (!as_they_are) packed_bytes += align_up(fc_packed_bytes(dag, Q.G, Q.R, Q.KH, Q.KW, Q.Og));
         }
         if (from_dy && covers(Q.Og, Q.R)) {
             tm[i] |= kTmData;
-            packed_bytes += align_up((uint64_t)gfctm::packed_elems(gfctm::shape(Q.N, Q.G, Q.Og, Q.KH, Q.KW, Q.R, Q.H, Q.W)) * 2);
+            packed_bytes += align_up(fc_packed_bytes(dag, Q.G, Q.Og, Q.KH, Q.KW, Q.R));
         }
         if (!from_x && Q.K >= kLongContraction && (Q.TV > 1 || dag.numel(fc_src(k)) <= kLongPairs) && covers(2 * Q.R, Q.Og)) {
             tm[i] |= kTmFwd | kTmFwdPairs;
-            packed_bytes += align_up((uint64_t)gfctm::packed_elems(gfctm::shape(Q.N, Q.G, 2 * Q.R, Q.KH, Q.KW, Q.Og, Q.H, Q.W)) * 2) + align_up((uint64_t)dag.numel(fc_src(k)) * 4);
+            packed_bytes += align_up(fc_packed_bytes(dag, Q.G, 2 * Q.R, Q.KH, Q.KW, Q.Og)) + align_up((uint64_t)dag.numel(fc_src(k)) * 4);
         }
         tm_bytes += part;
         if (!(tm[i] & kTmData)) tm_bytes += wt;
@@ -616,7 +616,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
                     emit_fc(*low, false, dag, take_packed, Q.TV > 1 ? "gfc_fwd_unfold" : "gfc_fwd", Q.G, Q.R, Q.KH, Q.KW, Q.Og, false, nd.widx,
                             FcOperand{[=](const RunArgs& a) { return pairs >= 0 ? (const void*)(a.ws + pairs) : a.x; }, false, pairs >= 0},
                             [=](const RunArgs& a) { return to_y ? (const void*)a.y : (const void*)valw(a, k); }, false,
-                            (pairs >= 0 ? 4.0 : 2.0) * dag.numel(srcn) + (to_y ? 2.0 : 4.0) * dag.numel(k) + 2.0 * wnumel[nd.widx], L.flops, !to_y);
+                            (pairs >= 0 ? 4.0 : 2.0) * dag.numel(srcn) + (to_y ? 2.0 : 4.0) * dag.numel(k) + 2.0 * wnumel[nd.widx], L.flops, !to_y, false, pairs < 0 && Q.TV == 1);
                     continue;
                 }
                 Q.src_f32 = src_x ? 0 : 1;

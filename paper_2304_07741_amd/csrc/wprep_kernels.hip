@@ -13,18 +13,34 @@ namespace {
 // instruction sequence several times as long).
 template <typename IDX>
 __device__ __forceinline__ void write_element(const Job& J, IDX i) {
-    if (J.kind == 0) {
+    if (J.kind != 1) {
         // wp[gmi][op][tap][rp]: block-diagonal over the gm merged groups, zero in the padding
-        const int rp = (int)(i % (IDX)J.Rp);
-        IDX t = i / (IDX)J.Rp;
-        const int tap = (int)(t % (IDX)J.TV);
-        t /= (IDX)J.TV;
-        const int op = (int)(t % (IDX)J.Omp), gmi = (int)(t / (IDX)J.Omp);
+        int rp, tap, op, gmi;
+        if (J.kind == 0) {
+            rp = (int)(i % (IDX)J.Rp);
+            IDX t = i / (IDX)J.Rp;
+            tap = (int)(t % (IDX)J.TV);
+            t /= (IDX)J.TV;
+            op = (int)(t % (IDX)J.Omp);
+            gmi = (int)(t / (IDX)J.Omp);
+        } else {
+            // [gmi][16 outputs][step][lane][8]: lane l of a step holds 8 contraction indices of output l % 16
+            const int e = (int)(i & 7), lane = (int)(i >> 3) & 63;
+            IDX t = i >> 9;
+            const int step = (int)(t % (IDX)J.steps);
+            t /= (IDX)J.steps;
+            const int ot = (int)(t % (IDX)(J.Omp / 16));
+            gmi = (int)(t / (IDX)(J.Omp / 16));
+            op = ot * 16 + (lane & 15);
+            const int k = step * 32 + (lane >> 4) * 8 + e;
+            tap = k / J.Rp;
+            rp = k - tap * J.Rp;
+        }
         const int sub = op / J.Og, o = op - sub * J.Og;
         const int subr = rp / J.R, r = rp - subr * J.R, row = r < J.Rw ? r : r - J.Rw;
         const int g = gmi * J.gm + sub;
         uint16_t v = 0;
-        if (sub < J.gm && subr == sub && g < J.G)
+        if (sub < J.gm && subr == sub && g < J.G && tap < J.TV)
             v = J.transposed ? J.w[(((long long)g * J.Rw + row) * J.Og + o) * J.TV + (J.TV - 1 - tap)]
                              : J.w[(((long long)g * J.Og + o) * J.Rw + row) * J.TV + tap];
         J.out[i] = v;

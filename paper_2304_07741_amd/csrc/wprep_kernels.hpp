@@ -12,11 +12,12 @@ namespace wprep {
 struct Job {
     const uint16_t* w = nullptr;  // the FC's weights [G][Og][R][TV] (transposed jobs: [G][R][Og][TV], read swapped)
     uint16_t* out = nullptr;
-    int kind = 0;                 // 0: tap-major pack [Gm][Omp][TV][Rp]; 1: plain transpose [G][R][Og][TV] -> [G][Og][R][TV flipped]
+    int kind = 0;                 // 0: tap-major pack [Gm][Omp][TV][Rp]; 2: the same in the order of the staged kernels' operands (gfc_staged_kernels.hpp); 1: plain transpose [G][R][Og][TV] -> [G][Og][R][TV flipped]
     int G = 0, R = 0, Og = 0, TV = 1;
-    int Rw = 0;                           // kind 0: rows of the weights; 2 Rw = R: the contraction reads every row twice, as a high and a low part
-    int gm = 1, Gm = 0, Rp = 0, Omp = 0;  // kind 0 only
-    int transposed = 0;           // kind 0 only
+    int Rw = 0;                           // kinds 0, 2: rows of the weights; 2 Rw = R: the contraction reads every row twice, as a high and a low part
+    int gm = 1, Gm = 0, Rp = 0, Omp = 0;  // kinds 0, 2
+    int transposed = 0;           // kinds 0, 2
+    int steps = 0;                // kind 2: steps of 32 contraction indices (tap, row)
     long long total = 0;          // elements written
 };
 
