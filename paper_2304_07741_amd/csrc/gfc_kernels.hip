@@ -484,124 +484,132 @@ __global__ __launch_bounds__(64 * kWaves) void k_wgrad(Params P) {
             }
 }
 
-// 64 x 64 tile of dW per wavefront for bf16 operands without a window, 64 pixels per step.  The operand rows are
-// loaded the way memory likes it -- one instruction covers 8 rows x 128 contiguous bytes -- and turned into the MFMA
-// layout (lane (r, s): row s, pixels 8r .. 8r+7 of a 32-pixel half) through a wavefront-private LDS tile of
-// 64 rows x (128 + 16) bytes, first dy, then x through the same rows.  (With the loads in the MFMA layout an
-// instruction touched 16 rows x 64 bytes, and the kernel was bound by the address pipeline: 27 -> 20 us for the
-// same bytes when only the shape of the loads was changed.)  The four wavefronts of a workgroup (consecutive
-// slices of the same tile) are summed through the same LDS in a fixed order: one partial per workgroup.
-__global__ __launch_bounds__(64 * kWaves) void k_wgrad64(Params P) {
-    constexpr int MO = 4, NK = 4, kRow = 144;
-    __shared__ __align__(16) unsigned char lds[kWaves * 64 * kRow];
-    static_assert(sizeof(lds) >= 2 * MO * NK * 4 * 64 * sizeof(float), "the cross-wavefront sum reuses the tiles");
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int slice = blockIdx.x * kWaves + wave;
-    const bool active = slice < P.slices;  // (no early exit: every wavefront takes part in the workgroup sum below)
-    const int g = blockIdx.z;
-    const int ot = blockIdx.y / P.ktiles, kt = blockIdx.y - ot * P.ktiles;
-    const int r = lane >> 4, s = lane & 15;
-    const int lrow = lane >> 3, lseg = lane & 7;  // shape of the loads: 8 rows x 8 pieces of 16 bytes
-    const int src_elems = P.N * P.G * P.R * P.P, dy_elems = P.N * P.G * P.Og * P.P;
-    const rsrc_t rs = make_rsrc(P.src, src_elems * 2);
-    const rsrc_t rdy = make_rsrc(P.dy, dy_elems * 2);
-    const int obase = ot * 64, kbase = kt * 64;
-    unsigned char* mine = lds + wave * 64 * kRow;
-
-    float4_t acc[MO][NK];
-#pragma unroll
-    for (int mo = 0; mo < MO; mo++)
-#pragma unroll
-        for (int nk = 0; nk < NK; nk++) acc[mo][nk] = float4_t{0.f, 0.f, 0.f, 0.f};
-
-    // steps of 64 pixels: P.chunks32 counts them here
-    const int c_begin = active ? slice * P.per_slice : 0, c_end = active ? min(P.N * P.chunks32, c_begin + P.per_slice) : 0;
-    int n = (int)div_magic((uint32_t)c_begin, P.magicC32);
-    int pc = c_begin - n * P.chunks32;
-    for (int c = c_begin; c < c_end; c++) {
-        const int px0 = pc * 64;
-        const int row0 = (n * P.G + g) * P.R, orow0 = (n * P.G + g) * P.Og;
-        const bool near_ends = (row0 + P.R - 1) * P.P + px0 + 72 > src_elems || (orow0 + P.Og - 1) * P.P + px0 + 72 > dy_elems;
-        const int pl = px0 + lseg * 8;
-        u32x4 ra[8], rb[8];
-#pragma unroll
-        for (int k = 0; k < 8; k++) {
-            const int o = obase + 8 * k + lrow;
-            ra[k] = load8<false>(rdy, (orow0 + o) * P.P + pl, pl < P.P && o < P.Og, near_ends, dy_elems * 2).hi;
-        }
-#pragma unroll
-        for (int k = 0; k < 8; k++) {
-            const int kr = kbase + 8 * k + lrow;
-            rb[k] = load8<false>(rs, (row0 + kr) * P.P + pl, pl < P.P && kr < P.K, near_ends, src_elems * 2).hi;
-        }
-        u32x4 a[2][MO], b[2][NK];
-#pragma unroll
-        for (int k = 0; k < 8; k++) *reinterpret_cast<u32x4*>(mine + (8 * k + lrow) * kRow + lseg * 16) = ra[k];
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            // (a 16-byte piece that begins inside the plane may run past its end into the next row: masked here, on dy)
-            const int nvalid = max(0, min(8, P.P - (px0 + h * 32 + 8 * r)));
-            const u32x4 mvalid = mask_of((1u << nvalid) - 1u);
-#pragma unroll
-            for (int mo = 0; mo < MO; mo++)
-                a[h][mo] = *reinterpret_cast<const u32x4*>(mine + (mo * 16 + s) * kRow + h * 64 + r * 16) & mvalid;
-        }
-#pragma unroll
-        for (int k = 0; k < 8; k++) *reinterpret_cast<u32x4*>(mine + (8 * k + lrow) * kRow + lseg * 16) = rb[k];
-#pragma unroll
-        for (int h = 0; h < 2; h++)
-#pragma unroll
-            for (int nk = 0; nk < NK; nk++) b[h][nk] = *reinterpret_cast<const u32x4*>(mine + (nk * 16 + s) * kRow + h * 64 + r * 16);
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            if (h == 1 && px0 + 32 >= P.P) continue;  // (wave-uniform: the plane ends in the first half)
-#pragma unroll
-            for (int mo = 0; mo < MO; mo++)
-#pragma unroll
-                for (int nk = 0; nk < NK; nk++) {
-                    float4_t t = acc[mo][nk];
-                    t = mfma32(a[h][mo], b[h][nk], t);
-                    acc[mo][nk] = t;
-                }
-        }
-        if (++pc == P.chunks32) { pc = 0; n++; }
+// (32 WO) x (32 WK) tile of dW per workgroup for bf16 operands without a window, 32 x 32 of it per wavefront, 8 units of 8 pixels per step
+// (units are counted through the images: at 14x14 pixels a step of 64 pixels of ONE image would be a quarter padding).  At 56x56
+// pixels the launch is bound by memory, below by the reads of what neighbouring tiles have in common (from the L2 of their XCD: the tiles of
+// one slice are neighbours there) and by the latency of a step, so kAhead steps are in flight in registers while one
+// is written to LDS (rows of 128 + 16 bytes, two buffers, one barrier per step) and contracted; a load covers 8 rows x 128 bytes.
+// (With a tile and a quarter of the slice per wavefront, nothing in flight across steps and a sum of the four through LDS: C=64, 128 planes
+// of 56x56 26.4 us, now 22.3 = 4.6 TB/s; C=256, 14x14 17.5 / 13.9; C=512, 7x7 19.3 / 16.6; C=80, 20 of 27x29 8.5 / 5.7; C=128, 32 of 28x28 10.5 / 8.0.
+// Six steps in flight, or 128 x 128 tiles with sixteen wavefronts: slower.)
+constexpr int kAhead = 4, kRow64 = 144;
+// The last `left` (1 .. 7) of eight bf16, moved to the front; zeros behind them.
+__device__ __forceinline__ u32x4 last_elems(const u32x4& v, int left) {
+    uint64_t lo = v[0] | (uint64_t)v[1] << 32, hi = v[2] | (uint64_t)v[3] << 32;
+    const int gone = 8 - left;
+    if (gone & 4) {
+        lo = hi;
+        hi = 0;
     }
-    // sum of the four wavefronts in a fixed order, (w0 + w2) + (w1 + w3)
-    __syncthreads();  // every wavefront has left its tile
-    float (*red)[MO * NK * 4][64] = reinterpret_cast<float (*)[MO * NK * 4][64]>(lds);
-    auto put = [&](int slot) {
+    const int bits = (gone & 3) * 16;
+    lo = lo >> bits | hi << 1 << (63 - bits);
+    hi >>= bits;
+    return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
+
+template <int WO, int WK>
+__global__ __launch_bounds__(64 * WO * WK, WO * WK > 4 ? WO * WK / 4 : 2) void k_wgrad64(Params P) {
+    constexpr int kRows = 32 * (WO + WK), kSweep = 8 * WO * WK;  // rows of a step; of one load per thread
+    constexpr int NL = kRows / kSweep, ND = 32 * WO / kSweep;    // loads per thread, of dy
+    __shared__ __align__(16) unsigned char lds[2][kRows * kRow64];
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wo = wave % WO, wk = wave / WO;
+    const int r = lane >> 4, s = lane & 15;
+    const int tiles = P.otiles * P.ktiles * P.G;
+    const int seq = (int)xcd_sequence();
+    const int slice = seq / tiles, t2 = seq - slice * tiles;
+    const int g = t2 / (P.otiles * P.ktiles), t3 = t2 - g * (P.otiles * P.ktiles);
+    const int ot = t3 / P.ktiles, kt = t3 - ot * P.ktiles;
+    const int obase = ot * 32 * WO, kbase = kt * 32 * WK;
+    const rsrc_t rs = make_rsrc(P.src, P.N * P.G * P.R * P.P * 2), rdy = make_rsrc(P.dy, P.N * P.G * P.Og * P.P * 2);
+    const int begin = slice * P.per_slice, end = min(P.chunks32, begin + P.per_slice);  // (P.chunks32: steps of the batch)
+
+    // this thread's pieces of a step: row lrow of each sweep, unit lseg
+    const int lrow = tid >> 3, lseg = tid & 7;
+    int n = (begin * 8 + lseg) / P.upi, u = begin * 8 + lseg - n * P.upi;
+    const int dimg = P.G * P.Og * P.P, simg = P.G * P.R * P.P;
+    int row[NL];  // first element of the row in image 0, or where every image's is outside
+    bool ok[NL];
 #pragma unroll
-        for (int mo = 0; mo < MO; mo++)
+    for (int i = 0; i < NL; i++) {
+        const int x = i < ND ? obase + lrow + kSweep * i : kbase + lrow + kSweep * (i - ND);
+        ok[i] = x < (i < ND ? P.Og : P.K);
+        row[i] = (g * (i < ND ? P.Og : P.R) + x) * P.P;
+    }
+    u32x4 v[kAhead][NL];
+    int left[kAhead];
+    auto issue = [&](int step, int f) {
+        const bool in = (step < end) & (n < P.N);
+        const int p = min(u * 8, P.P - 8);  // (the last piece of a row ends with it, and is moved down when it is used)
+        left[f] = P.P - u * 8;
+        int at[NL];
 #pragma unroll
-            for (int nk = 0; nk < NK; nk++)
+        for (int i = 0; i < NL; i++) {
+            at[i] = in & ok[i] ? (n * (i < ND ? dimg : simg) + row[i] + p) * 2 : kOob;
+            asm volatile("" : "+v"(at[i]));  // (a select, not two loads under a branch)
+        }
 #pragma unroll
-                for (int jj = 0; jj < 4; jj++) red[slot][(mo * NK + nk) * 4 + jj][lane] = acc[mo][nk][jj];
+        for (int i = 0; i < NL; i++) v[f][i] = bload16(i < ND ? rdy : rs, at[i]);
+        u += 8;
+        if (P.upi >= 8) {
+            const bool over = u >= P.upi;
+            u = over ? u - P.upi : u;
+            n = over ? n + 1 : n;
+        } else {  // (exact: a quotient below 2^29 by less than 8)
+            const int more = (int)div_magic((uint32_t)u, P.magicUpi);
+            n += more;
+            u -= more * P.upi;
+        }
     };
-    auto add = [&](int slot) {
 #pragma unroll
-        for (int mo = 0; mo < MO; mo++)
+    for (int f = 0; f < kAhead; f++) issue(begin + f, f);
+
+    float4_t acc[2][2];
 #pragma unroll
-            for (int nk = 0; nk < NK; nk++)
+    for (int mo = 0; mo < 2; mo++)
 #pragma unroll
-                for (int jj = 0; jj < 4; jj++) acc[mo][nk][jj] += red[slot][(mo * NK + nk) * 4 + jj][lane];
-    };
-    if (wave >= 2) put(wave - 2);
-    __syncthreads();
-    if (wave < 2) add(wave);
-    __syncthreads();
-    if (wave == 1) put(0);
-    __syncthreads();
-    if (wave != 0) return;
-    add(0);
-    float* part = P.partial + (long long)blockIdx.x * P.G * P.Og * P.K;
+        for (int nk = 0; nk < 2; nk++) acc[mo][nk] = float4_t{0.f, 0.f, 0.f, 0.f};
+    const int to = lrow * kRow64 + lseg * 16;
+    const int aoff = (wo * 32 + s) * kRow64 + r * 16, boff = ((WO + wk) * 32 + s) * kRow64 + r * 16;
+    int buf = 0;
+    // (steps past the last one contract zeros: with a way out between the steps the compiler waits for all loads at the loop's head)
+    for (int c = begin; c < end; c += kAhead) {
 #pragma unroll
-    for (int mo = 0; mo < MO; mo++)
+        for (int f = 0; f < kAhead; f++) {
+            unsigned char* tile = lds[buf];
+            buf ^= 1;
+            if (left[f] < 8) {
 #pragma unroll
-        for (int nk = 0; nk < NK; nk++)
+                for (int i = 0; i < NL; i++) v[f][i] = last_elems(v[f][i], left[f]);
+            }
+#pragma unroll
+            for (int i = 0; i < NL; i++) *reinterpret_cast<u32x4*>(tile + to + i * kSweep * kRow64) = v[f][i];
+            issue(c + f + kAhead, f);
+            lds_barrier();  // (the buffer written next is the one that all wavefronts have read before this)
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                u32x4 a[2], b[2];
+#pragma unroll
+                for (int k = 0; k < 2; k++) {
+                    a[k] = *reinterpret_cast<const u32x4*>(tile + aoff + k * 16 * kRow64 + h * 64);
+                    b[k] = *reinterpret_cast<const u32x4*>(tile + boff + k * 16 * kRow64 + h * 64);
+                }
+#pragma unroll
+                for (int mo = 0; mo < 2; mo++)
+#pragma unroll
+                    for (int nk = 0; nk < 2; nk++) acc[mo][nk] = mfma32(a[mo], b[nk], acc[mo][nk]);
+            }
+        }
+    }
+    float* part = P.partial + (long long)slice * P.G * P.Og * P.K;
+#pragma unroll
+    for (int mo = 0; mo < 2; mo++)
+#pragma unroll
+        for (int nk = 0; nk < 2; nk++)
 #pragma unroll
             for (int jj = 0; jj < 4; jj++) {
-                const int o = obase + mo * 16 + 4 * r + jj, k = kbase + nk * 16 + s;
+                const int o = obase + wo * 32 + mo * 16 + 4 * r + jj, k = kbase + wk * 32 + nk * 16 + s;
                 if (o < P.Og && k < P.K) part[((long long)g * P.Og + o) * P.K + k] = acc[mo][nk][jj];
             }
 }
@@ -668,14 +676,32 @@ void prepare_forward(Params& P) {
 void prepare_wgrad(Params& P) {
     // bf16 operands without a window and at least 64 x 64 weights per group: 64 x 64 tiles (each loaded
     // register feeds four MFMAs instead of two); set src_f32 / dy_f32 before this call
-    P.wtile = (!P.src_f32 && !P.dy_f32 && P.TV == 1 && P.Og >= 64 && P.K >= 64) ? 4 : 2;
+    P.wtile = (!P.src_f32 && !P.dy_f32 && P.TV == 1 && P.Og >= 64 && P.K >= 64 && P.P >= 8) ? 4 : 2;
     P.otiles = (P.Og + 16 * P.wtile - 1) / (16 * P.wtile);
     P.ktiles = (P.K + 16 * P.wtile - 1) / (16 * P.wtile);
-    const int chunk_px = P.wtile == 4 ? 64 : 32;  // pixels per step of a wavefront
-    P.chunks32 = (P.P + chunk_px - 1) / chunk_px;
-    P.magicC32 = magic_u32(P.chunks32);
     const int64_t wnumel = (int64_t)P.G * P.Og * P.K;
+    if (P.wtile == 4) {
+        // 64 x 64 tiles, or 128 x 64 with eight wavefronts where they are many: each operand is read once per tile of the other's
+        // rows, and from 256 channels on these reads (L2) are what bounds the launch (C=256, 128 planes of 14x14: 15.9 / 13.9 us with
+        // 64 x 64 / 128 x 64; C=512, 7x7: 17.9 / 16.6; C=128, 32 planes of 28x28: 8.0 / 8.6; C=80, 20 of 27x29: 5.7 / 6.9)
+        const bool many = (int64_t)P.G * ((P.Og + 63) / 64) * ((P.K + 63) / 64) >= 8 && P.Og > 64;
+        P.wo = many ? 4 : 2;
+        P.otiles = (P.Og + 32 * P.wo - 1) / (32 * P.wo);
+        P.ktiles = (P.K + 63) / 64;
+        const int64_t tiles = (int64_t)P.G * P.otiles * P.ktiles;
+        const int64_t steps = ((int64_t)P.N * P.upi + 7) / 8;
+        // one workgroup per compute unit (two: 23.6 / 22.3 us at C=64, 128 planes of 56x56, 9.2 / 8.0 at C=128, 32 of 28x28: more
+        // partials), at most 8 MB of partials (16 MB measured slower: they are written once and read once more by the sum)
+        int64_t slices = std::max<int64_t>(1, std::min<int64_t>(steps, (256 + tiles - 1) / tiles));
+        slices = std::max<int64_t>(1, std::min<int64_t>(slices, ((int64_t)8 << 20) / std::max<int64_t>(1, wnumel * 4)));
+        P.chunks32 = (int)steps;
+        P.per_slice = (int)((steps + slices - 1) / slices);
+        P.slices = (int)((steps + P.per_slice - 1) / P.per_slice);
+        return;
+    }
     const int64_t tiles = (int64_t)P.G * P.otiles * P.ktiles;
+    P.chunks32 = (P.P + 31) / 32;
+    P.magicC32 = magic_u32(P.chunks32);
     const int64_t steps = (int64_t)P.N * P.chunks32;
     // at most 2048 slices per tile and about 4 k wavefronts in all;
     // one partial per workgroup of kWaves slices, at most 8 MB of partials (16 MB measured slower: the
@@ -713,7 +739,9 @@ void wgrad_partial(const Params& P, hipStream_t s) {
 #define GFC_WG(SF, DF) \
     do { if (taps) CANVAS_LAUNCH((k_wgrad<2, 2, SF, DF, true>), grid, block, 0, s, P); else CANVAS_LAUNCH((k_wgrad<2, 2, SF, DF, false>), grid, block, 0, s, P); } while (0)
     if (P.wtile == 4) {
-        CANVAS_LAUNCH(k_wgrad64, grid, block, 0, s, P);
+        const dim3 grid64((unsigned)(P.slices * P.otiles * P.ktiles * P.G));
+        if (P.wo == 2) CANVAS_LAUNCH((k_wgrad64<2, 2>), grid64, dim3(256), 0, s, P);
+        else CANVAS_LAUNCH((k_wgrad64<4, 2>), grid64, dim3(512), 0, s, P);
         return;
     }
     if (P.src_f32) { if (P.dy_f32) GFC_WG(true, true); else GFC_WG(true, false); }
@@ -721,8 +749,7 @@ void wgrad_partial(const Params& P, hipStream_t s) {
 #undef GFC_WG
 }
 
-int wgrad_partials(const Params& P) { return (P.slices + kWaves - 1) / kWaves; }
-
+int wgrad_partials(const Params& P) { return P.wtile == 4 ? P.slices : (P.slices + kWaves - 1) / kWaves; }
 
 void transpose_weights(const uint16_t* w, uint16_t* wt, int G, int Og, int R, int TV, hipStream_t s) {
     const long long total = (long long)G * R * Og * TV;

@@ -24,7 +24,8 @@ struct Params {
     int upi = 0;                  // forward: 8-pixel units per image, ceil(P / 8)
     int otiles = 0, ktiles = 0;   // tiles of 16*MO output channels / 16*NK contraction rows
     int slices = 0, chunks32 = 0, per_slice = 0;  // weight gradient: pixel chunks of 32 split over slices
-    int wtile = 2;                // weight gradient: the wavefront's dW tile is (16*wtile) x (16*wtile)
+    int wtile = 2;                // weight gradient: the dW tile is (16*wtile) x (16*wtile) per wavefront, or (4) larger and shared by a workgroup
+    int wo = 2;                   // wtile 4: the workgroup's tile is (32*wo) x 64
     uint32_t magicW = 0, magicTV = 0, magicKW = 0, magicC32 = 0, magicUpi = 0;
 };
 
@@ -32,9 +33,9 @@ inline uint32_t magic_u32(uint32_t d) { return d <= 1 ? 0u : (uint32_t)((((uint6
 
 // y[n, g*Og+o, p] (+)= sum_k w[g][o][k] * src_row(n, g, k)[p + off(k)]
 void forward(const Params& P, hipStream_t s);
-// partial[wg][g][o][k] = sum over the (n, p) of the workgroup's four slices of dy[n, g*Og+o, p] * src_row(n, g, k)[p + off(k)]
+// partial[wg][g][o][k] = sum over the (n, p) of the workgroup's slices of dy[n, g*Og+o, p] * src_row(n, g, k)[p + off(k)]
 void wgrad_partial(const Params& P, hipStream_t s);
-// number of partials wgrad_partial writes (one per workgroup of four slices); dw[e] = sum_i partial[i][e] is a
+// number of partials wgrad_partial writes (one per workgroup of a tile); dw[e] = sum_i partial[i][e] is a
 // job of wreduce_kernels.hpp
 int wgrad_partials(const Params& P);
 // wt[g][row][o*TV + tv] = w[g][o][row*TV + (TV-1-tv)]: the weights of the data-gradient contraction
@@ -45,7 +46,8 @@ int choose_mo(int Og);
 // `rows` rows per group seen through a KH x KW window; the three `prepare_*` calls complete it for one launch kind.
 Params shape(int N, int G, int rows, int KH, int KW, int Og, int H, int W);
 void prepare_forward(Params& P);
-// Splits the N * ceil(P/32) pixel chunks over at most 2048 slices per tile (one partial per four slices, at most 8 MB).
+// Splits the pixels over slices of wavefronts (one partial per four slices) or, for 64 x 64 tiles and more, of workgroups (one partial per
+// slice); at most 8 MB of partials.
 void prepare_wgrad(Params& P);
 // Forward geometry -> geometry of the data gradient (rows and outputs swapped); use with transposed weights.
 Params data_gradient_of(const Params& fwd);

@@ -140,6 +140,14 @@ __device__ __forceinline__ float4_t mfma32(const u32x4& a, const u32x4& b, float
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, c, 0, 0, 0);
 }
 
+// A barrier behind which every thread sees what the others wrote to LDS before it.  Loads from memory stay in flight (__syncthreads
+// waits for them too).
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // kMaskLut.m[b] = the four dword masks that keep the bf16 elements whose bit is set in the 8-bit pattern b.
 struct alignas(16) MaskLut {
     uint32_t m[256][4];
