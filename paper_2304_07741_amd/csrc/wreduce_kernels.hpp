@@ -15,9 +15,11 @@ struct Job {
     int slices = 0;
     int kind = 0;                    // 0: partials in the order of dw; 1: tap-major packed [Gm][Omp][TV][Rp] (gfc_tm_kernels.hpp)
     unsigned count = 0;              // elements per partial
-    int segs = 8;                    // 2 or 8 segments of partials per element, combined through LDS in order
-    unsigned blocks = 0;             // workgroups of 256 threads = 256 / segs elements each
+    int segs = 1;                    // segments of partials per element (1 ... 16), combined through LDS in order
+    int vec = 1;                     // consecutive elements per thread (4 where the partials' elements are 16-byte aligned: count % 4 == 0)
+    unsigned blocks = 0;             // workgroups of 256 threads = vec * 256 / segs elements each
     int G = 0, R = 0, Og = 0, TV = 1, gm = 1, Omp = 0, Rp = 0;  // kind 1 only
+    uint32_t magicRp = 0, magicTV = 0, magicOmp = 0, magicOg = 0, magicR = 0;    // exact division by them, or 0: divided by
 };
 
 constexpr int kMaxJobs = 8;
@@ -26,7 +28,7 @@ struct Jobs {
     int n = 0;
 };
 
-// Fills segs and blocks from slices and count.
+// Fills segs, vec, blocks and the multipliers from the rest.
 void plan(Job& job);
 
 void run(const Jobs& jobs, hipStream_t s);
