@@ -3,6 +3,7 @@
 #include "gfc_kernels.hpp"
 #include "gfc_staged_kernels.hpp"
 #include "gfc_tm_kernels.hpp"
+#include "gfc_wgrad_kernels.hpp"
 
 namespace canvas {
 
@@ -106,16 +107,21 @@ void emit_wgrad(Lowering& low, const Dag& dag, const TakeFn& take, const std::st
     const int64_t nw = (int64_t)G * Og * R * kh * kw;
     if (kh * kw > 1 && !src.f32 && !dy.f32 && gfctm::supported(dag.N, G, R, kh, kw, Og, dag.H, dag.W)) {
         gfctm::Params T = gfctm::shape(dag.N, G, R, kh, kw, Og, dag.H, dag.W);
-        gfctm::prepare_wgrad(T);
-        const int ts = gfctm::wgrad_slices(T);
+        gfcwg::Params S;
+        const bool by_taps = gfcwg::plan(S, T);
+        if (!by_taps) gfctm::prepare_wgrad(T);
+        const int ts = by_taps ? S.slices : gfctm::wgrad_slices(T);
         const int64_t pk = gfctm::packed_elems(T);
         const int64_t opt = take((uint64_t)ts * pk * 4);
+        auto bind = [=](auto Q, const RunArgs& a) {
+            Q.src = (const uint16_t*)src.ptr(a);
+            Q.dy = (const uint16_t*)dy.ptr(a);
+            Q.partial = (float*)(a.ws + opt);
+            return Q;
+        };
         list.push_back({name, operand_bytes + 4.0 * ts * pk, flops, [=](const RunArgs& a) {
-                            gfctm::Params Q = T;
-                            Q.src = (const uint16_t*)src.ptr(a);
-                            Q.dy = (const uint16_t*)dy.ptr(a);
-                            Q.partial = (float*)(a.ws + opt);
-                            gfctm::wgrad_partial(Q, a.stream);
+                            if (by_taps) gfcwg::wgrad_partial(bind(S, a), a.stream);
+                            else gfctm::wgrad_partial(bind(T, a), a.stream);
                         }});
         ReduceJob rj;
         rj.job.slices = ts;

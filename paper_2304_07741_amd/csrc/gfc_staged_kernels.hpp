@@ -33,6 +33,7 @@ struct Params {
 bool plan(Params& P, const gfctm::Params& T, bool dst_f32, bool adds, bool softmax);
 inline int64_t packed_elems(const Params& P) { return (int64_t)P.Gm * P.Omp * P.steps * 32; }
 void forward(const Params& P, hipStream_t s);
+uint32_t magic(int d);  // multiplier of an exact division by d
 bool plan_as(Params& P, int KW, int mo, int wo, int np);  // the tile `mo, wo, np`, or false where it does not fit
 
 }  // namespace gfcst
