@@ -7,6 +7,31 @@
 
 namespace canvas {
 
+// Room for the weights of the contraction T (R rows per group of the FC's own) in the layout of the staged kernels (S) or of the tap-major ones, and
+// the job that fills it; returns the offset.
+static int64_t pack_weights(Lowering& low, const TakeFn& take, const gfctm::Params& T, const gfcst::Params* S, int R, bool transposed, int widx) {
+    const int64_t elems = S ? gfcst::packed_elems(*S) : gfctm::packed_elems(T);
+    WeightJob j;
+    j.job.kind = S ? 2 : 0;
+    j.job.steps = S ? S->steps : 0;
+    j.job.G = T.G;
+    j.job.R = T.R;
+    j.job.Rw = R;
+    j.job.Og = T.Og;
+    j.job.TV = T.TV;
+    j.job.gm = T.gm;
+    j.job.Gm = T.Gm;
+    j.job.Rp = S ? S->Rp : T.Rp;
+    j.job.Omp = S ? S->Omp : T.Omp;
+    j.job.transposed = transposed ? 1 : 0;
+    j.job.total = elems;
+    j.widx = widx;
+    j.off = take((uint64_t)elems * 2);
+    j.bytes = 2.0 * T.G * T.Og * R * T.TV + 2.0 * elems;
+    low.wjobs.push_back(j);
+    return j.off;
+}
+
 void emit_fc(Lowering& low, bool backward, const Dag& dag, const TakeFn& take, const std::string& name, int G, int R, int kh, int kw, int Og,
              bool transposed, int widx, FcOperand src, PtrFn dst, bool addend_is_dst, double bytes, double flops, bool dst_f32, bool softmax, bool weights_as_they_are) {
     std::vector<Launch>& list = backward ? low.bwd : low.fwd;
@@ -17,28 +42,7 @@ void emit_fc(Lowering& low, bool backward, const Dag& dag, const TakeFn& take, c
         gfcst::Params S;
         const bool staged = !weights_as_they_are && gfcst::plan(S, T, dst_f32, addend_is_dst, softmax);
         const bool identity = !src.pairs && !transposed && gfctm::reads_weights_as_they_are(T) && !staged;
-        const int64_t elems = staged ? gfcst::packed_elems(S) : gfctm::packed_elems(T);
-        const int64_t opk = identity ? -1 : take((uint64_t)elems * 2);
-        if (!identity) {
-            WeightJob j;
-            j.job.kind = staged ? 2 : 0;
-            j.job.steps = S.steps;
-            j.job.G = T.G;
-            j.job.R = T.R;
-            j.job.Rw = R;
-            j.job.Og = T.Og;
-            j.job.TV = T.TV;
-            j.job.gm = T.gm;
-            j.job.Gm = T.Gm;
-            j.job.Rp = staged ? S.Rp : T.Rp;
-            j.job.Omp = staged ? S.Omp : T.Omp;
-            j.job.transposed = transposed ? 1 : 0;
-            j.job.total = elems;
-            j.widx = widx;
-            j.off = opk;
-            j.bytes = 2.0 * nw + 2.0 * elems;
-            low.wjobs.push_back(j);
-        }
+        const int64_t opk = identity ? -1 : pack_weights(low, take, T, staged ? &S : nullptr, R, transposed, widx);
         if (staged) {
             list.push_back({name, bytes, flops, [=](const RunArgs& a) {
                                 gfcst::Params Q = S;
@@ -88,6 +92,28 @@ void emit_fc(Lowering& low, bool backward, const Dag& dag, const TakeFn& take, c
                         Q.addend = addend_is_dst ? (const uint16_t*)dst(a) : nullptr;
                         gfc::forward(Q, a.stream);
                     }});
+}
+
+bool emit_fc_with_middle(Lowering& low, bool adjoint, const Dag& dag, const TakeFn& take, const std::string& name, int G, int R, int kh, int kw, int Og,
+                         int widx, PtrFn src, PtrFn dst, double bytes, double flops, int act,
+                         const std::function<ufc::MidParams(const RunArgs&)>& middle) {
+    if (!gfctm::supported(dag.N, G, R, kh, kw, Og, dag.H, dag.W)) return false;
+    const gfctm::Params T = gfctm::shape(dag.N, G, R, kh, kw, Og, dag.H, dag.W);
+    gfcst::Params S;
+    if (!gfcst::plan(S, T, false, false, false) || !gfcst::takes_middle(S, adjoint, act)) return false;
+    const int64_t opk = pack_weights(low, take, T, &S, R, adjoint, widx);
+    (adjoint ? low.bwd : low.fwd).push_back({name, bytes, flops, [=](const RunArgs& a) {
+                                                 gfcst::Params Q = S;
+                                                 Q.src = (const uint16_t*)src(a);
+                                                 Q.wp = (const uint16_t*)(a.ws + opk);
+                                                 if (adjoint) {
+                                                     gfcst::dgrad_with_middle(Q, middle(a), a.stream);
+                                                     return;
+                                                 }
+                                                 Q.dst = const_cast<void*>(dst(a));
+                                                 gfcst::forward_with_middle(Q, middle(a), a.stream);
+                                             }});
+    return true;
 }
 
 uint64_t fc_packed_bytes(const Dag& dag, int G, int rows, int kh, int kw, int Og) {

@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "lowering.hpp"
+#include "ufc_kernels.hpp"
 
 namespace canvas {
 
@@ -28,6 +29,12 @@ struct FcOperand {
 void emit_fc(Lowering& low, bool backward, const Dag& dag, const TakeFn& take, const std::string& name, int G, int R, int kh, int kw, int Og,
              bool transposed, int widx, FcOperand src, PtrFn dst, bool addend_is_dst, double bytes, double flops, bool dst_f32 = false,
              bool softmax = false, bool weights_as_they_are = false);
+// The same, all in bf16, with the element-wise middle v = x (*|+) shift(act(z)) in the same launch: forward (dst = z, then v), or, with `adjoint`, the
+// transposed contraction whose result dv stays in the registers (then dx1 and dz; dst is not called).  False, and nothing emitted, where no
+// kernel does it.
+bool emit_fc_with_middle(Lowering& low, bool adjoint, const Dag& dag, const TakeFn& take, const std::string& name, int G, int R, int kh, int kw, int Og,
+                         int widx, PtrFn src, PtrFn dst, double bytes, double flops, int act,
+                         const std::function<ufc::MidParams(const RunArgs&)>& middle);
 // What emit_fc takes from `take` where it packs the weights of a contraction over a bf16 source that gfctm::supported covers, without a
 // tensor that is added or a softmax (rows: 2 R for pairs).
 uint64_t fc_packed_bytes(const Dag& dag, int G, int rows, int kh, int kw, int Og);

@@ -1,4 +1,4 @@
-// Grouped FC through LDS (gfc_staged_kernels.hip): bf16 source, 3x3 window or none, for the shapes where it is faster than the
+// Grouped FC through LDS (gfc_staged_kernel.hpp): bf16 source, 3x3 window or none, for the shapes where it is faster than the
 // tap-major kernels (gfc_tm_kernels.hpp), whose geometry (merged groups, padded rows) it shares.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -6,6 +6,7 @@
 #include <cstdint>
 
 #include "gfc_tm_kernels.hpp"
+#include "ufc_kernels.hpp"
 
 namespace canvas {
 namespace gfcst {
@@ -33,6 +34,12 @@ struct Params {
 bool plan(Params& P, const gfctm::Params& T, bool dst_f32, bool adds, bool softmax);
 inline int64_t packed_elems(const Params& P) { return (int64_t)P.Gm * P.Omp * P.steps * 32; }
 void forward(const Params& P, hipStream_t s);
+// Whether a planned launch has a form that goes on with the middle v = x (*|+) shift(act(z)) of a sampled kernel: with its forward (the result
+// is z, stored as ever, and v follows), or with its adjoint (the result is dv, which is not stored; dx1 and dz follow); act as in
+// MidParams.
+bool takes_middle(const Params& P, bool adjoint, int act);
+void forward_with_middle(const Params& P, const ufc::MidParams& M, hipStream_t s);  // M: x, v
+void dgrad_with_middle(const Params& P, const ufc::MidParams& M, hipStream_t s);    // M: x, z, dz, dx1
 uint32_t magic(int d);  // multiplier of an exact division by d
 bool plan_as(Params& P, int KW, int mo, int wo, int np);  // the tile `mo, wo, np`, or false where it does not fit
 

@@ -114,7 +114,7 @@ std::unique_ptr<Lowering> lower_ufc(const Dag& dag, bool bf16) {
         off += align_up(bytes);
         return (int64_t)o;
     };
-    const int64_t oz = take((uint64_t)act), ov = take((uint64_t)act), odv = take((uint64_t)act), odz = take((uint64_t)act);
+    const int64_t oz = take((uint64_t)act), ov = take((uint64_t)act), odz = take((uint64_t)act);
     const int w1 = fc1.widx, w2 = fc2.widx;
     const double fl1 = 2.0 * dag.N * Pn * (double)C * K1, fl2 = 2.0 * dag.N * Pn * (double)O2 * K2;
 
@@ -123,30 +123,51 @@ std::unique_ptr<Lowering> lower_ufc(const Dag& dag, bool bf16) {
     const FcOperand in_x{[](const RunArgs& a) { return a.x; }, false};
     const FcOperand in_dy{[](const RunArgs& a) { return a.dy; }, false};
     auto ws_at = [](int64_t o) { return [=](const RunArgs& a) { return (const void*)(a.ws + o); }; };
-    emit_fc(*low, false, dag, takef, TV > 1 ? "ufc_fc1_unfold" : "ufc_fc1", G1, C / G1, KH, KW, C / G1, false, w1, in_x, ws_at(oz), false,
-            2.0 * act + 2.0 * nw1, fl1);
-    low->fwd.push_back({"ufc_mid_fwd", 3.0 * act, 0, [=](const RunArgs& a) {
-                            ufc::MidParams R = M;
-                            R.x = (const uint16_t*)a.x;
-                            R.z = (const uint16_t*)(a.ws + oz);
-                            R.v = (uint16_t*)(a.ws + ov);
-                            ufc::mid_forward(R, a.stream);
-                        }});
+    auto middle = [=](const RunArgs& a) {
+        ufc::MidParams R = M;
+        R.x = (const uint16_t*)a.x;
+        R.z = (const uint16_t*)(a.ws + oz);
+        R.v = (uint16_t*)(a.ws + ov);
+        return R;
+    };
+    // The middle in the launch of the FC before it (forward), and its adjoint in that of the FC whose data gradient it takes (backward): a
+    // launch of 4-5 us less, but its vector instructions then stand behind the contraction of each of few wavefronts, where the launches of
+    // their own fill the chip.  A pass without / with both, us: inference 1x256x14x14 13.9 / 11.2, 8x512x7x7 15.2 / 13.7; training 8x128x28x28
+    // 46.6 / 40.5, 20x80x27x29 54.9 / 51.7, 12x384x10x10 58.0 / 54.2.  Forward alone: 16x96x32x32 (1.6 M elements) 49.2 / 47.4, 32x256x14x14 62.7 / 63.4,
+    // 100x320x7x7 87.1 / 90.1, 40x160x20x20 (2.6 M) 71.0 / 74.4, 128x256x14x14 110.8 / 114.8.  Backward alone: 64x512x7x7 (1.6 M) 78.6 / 76.1,
+    // 100x320x7x7 87.1 / 87.3, 40x160x20x20 71.0 / 74.2, 32x128x28x28 (3.2 M) 61.1 / 64.2, 64x256x28x28 173.4 / 181.7.
+    const int64_t elems = (int64_t)dag.N * C * Pn;
+    const bool fuse_f = elems <= 1300000, fuse_b = elems <= 1700000;
+    if (!(fuse_f && emit_fc_with_middle(*low, false, dag, takef, TV > 1 ? "ufc_fc1_unfold_mid" : "ufc_fc1_mid", G1, C / G1, KH, KW, C / G1, w1, in_x.ptr, ws_at(oz),
+                                       3.0 * act + 2.0 * nw1, fl1, M.act, middle))) {
+        emit_fc(*low, false, dag, takef, TV > 1 ? "ufc_fc1_unfold" : "ufc_fc1", G1, C / G1, KH, KW, C / G1, false, w1, in_x, ws_at(oz), false,
+                2.0 * act + 2.0 * nw1, fl1);
+        low->fwd.push_back({"ufc_mid_fwd", 3.0 * act, 0, [=](const RunArgs& a) { ufc::mid_forward(middle(a), a.stream); }});
+    }
     emit_fc(*low, false, dag, takef, "ufc_fc2", G2, C / G2, 1, 1, O2 / G2, false, w2, FcOperand{ws_at(ov), false},
             [](const RunArgs& a) { return (const void*)a.y; }, false, act + outb + 2.0 * nw2, fl2);
 
     // backward (forward must have run with the same workspace: z and v are read back, and left intact)
     emit_wgrad(*low, dag, takef, "ufc_fc2_wgrad", G2, C / G2, 1, 1, O2 / G2, w2, FcOperand{ws_at(ov), false}, in_dy, act + outb, fl2);
-    emit_fc(*low, true, dag, takef, "ufc_fc2_dgrad", G2, O2 / G2, 1, 1, C / G2, true, w2, in_dy, ws_at(odv), false, act + outb + 2.0 * nw2, fl2);
-    low->bwd.push_back({"ufc_mid_bwd", (M.bin ? 5.0 : 4.0) * act, 0, [=](const RunArgs& a) {
-                            ufc::MidParams R = M;
-                            R.x = (const uint16_t*)a.x;
-                            R.z = (const uint16_t*)(a.ws + oz);
-                            R.dv = (const uint16_t*)(a.ws + odv);
-                            R.dz = (uint16_t*)(a.ws + odz);
-                            R.dx1 = (uint16_t*)a.dx;  // completed by the data gradient of FC1 below
-                            ufc::mid_backward(R, a.stream);
-                        }});
+    auto adjoint = [=](const RunArgs& a) {
+        ufc::MidParams R = M;
+        R.x = (const uint16_t*)a.x;
+        R.z = (const uint16_t*)(a.ws + oz);
+        R.dz = (uint16_t*)(a.ws + odz);
+        R.dx1 = (uint16_t*)a.dx;  // completed by the data gradient of FC1 below
+        return R;
+    };
+    const double adjoint_bytes = (M.bin ? 4.0 : 3.0) * act;
+    if (!(fuse_b && emit_fc_with_middle(*low, true, dag, takef, "ufc_mid_bwd", G2, O2 / G2, 1, 1, C / G2, w2, in_dy.ptr, nullptr,
+                                        adjoint_bytes + outb + 2.0 * nw2, fl2, M.act, adjoint))) {
+        const int64_t odv = take((uint64_t)act);
+        emit_fc(*low, true, dag, takef, "ufc_fc2_dgrad", G2, O2 / G2, 1, 1, C / G2, true, w2, in_dy, ws_at(odv), false, act + outb + 2.0 * nw2, fl2);
+        low->bwd.push_back({"ufc_mid_bwd", adjoint_bytes + act, 0, [=](const RunArgs& a) {
+                                ufc::MidParams R = adjoint(a);
+                                R.dv = (const uint16_t*)(a.ws + odv);
+                                ufc::mid_backward(R, a.stream);
+                            }});
+    }
     emit_wgrad(*low, dag, takef, TV > 1 ? "ufc_fc1_wgrad_unfold" : "ufc_fc1_wgrad", G1, C / G1, KH, KW, C / G1, w1, in_x,
                FcOperand{ws_at(odz), false}, 2.0 * act, fl1);
     // mid_backward left dx_direct in dx; the data gradient of FC1 (through the Unfold adjoint) adds to it

@@ -6,59 +6,13 @@
 
 #include <type_traits>
 
-#include "device_util.hpp"
 #include "launch.hpp"
-#include "tile_util.hpp"
+#include "ufc_device.hpp"
 
 namespace canvas {
 namespace ufc {
 
 namespace {
-
-using namespace canvas::tile;
-
-__device__ __forceinline__ uint32_t div_magic(uint32_t x, uint32_t magic) { return magic ? __umulhi(x, magic) : x; }
-
-// bit q: pixel p+q exists and its source (h+dh, w+dw) is inside the image
-__device__ __forceinline__ uint32_t shift_bits(const MidParams& P, int p, int dh, int dw) {
-    int h = (int)div_magic((uint32_t)p, P.magicW), c = p - h * P.W;
-    uint32_t bits = 0;
-#pragma unroll
-    for (int q = 0; q < 8; q++) {
-        const bool v = p + q < P.P && (unsigned)(h + dh) < (unsigned)P.H && (unsigned)(c + dw) < (unsigned)P.W;
-        bits |= (v ? 1u : 0u) << q;
-        if (++c == P.W) { c = 0; h++; }
-    }
-    return bits;
-}
-
-__device__ __forceinline__ void unpack8(const u32x4& v, float (&f)[8]) {
-#pragma unroll
-    for (int k = 0; k < 4; k++) {
-        f[2 * k] = lo_f32(v[k]);
-        f[2 * k + 1] = hi_f32(v[k]);
-    }
-}
-
-__device__ __forceinline__ u32x4 load8(rsrc_t r, int e, int bytes) {
-    u32x4 v = bload16(r, e * 2);
-    reload_if_partial(v, r, e * 2, bytes);
-    return v;
-}
-
-__device__ __forceinline__ void store8(rsrc_t r, uint16_t* base, int e, const float (&f)[8], int nvalid, bool nt = true) {
-    if (nvalid == 8) {
-        u32x4 out;
-#pragma unroll
-        for (int k = 0; k < 4; k++) out[k] = pack_bf16(f[2 * k], f[2 * k + 1]);
-        if (nt) bstore16_nt(r, e * 2, out);
-        else bstore16(r, e * 2, out);
-    } else {
-#pragma unroll
-        for (int q = 0; q < 8; q++)
-            if (q < nvalid) base[e + q] = (uint16_t)(pack_bf16(f[q], 0.f) & 0xffffu);
-    }
-}
 
 struct Unit {
     int plane, p, dh, dw, nvalid;
@@ -84,33 +38,6 @@ __device__ __forceinline__ Unit decode(const MidParams& P) {
     return u;
 }
 
-// Normal CDF and density at z.  erfc by the rational-times-Gaussian approximation of Abramowitz and Stegun,
-// formula 7.1.26 (absolute error of erf below 1.5e-7, far below the bf16 rounding of every tensor these
-// kernels write); the Gaussian is shared with the density, so gelu and its derivative at one point cost one
-// exponential and one reciprocal.  (The fp32 per-node kernels use erff.)
-__device__ __forceinline__ void normal_parts(float z, float& cdf, float& pdf) {
-    const float t = __builtin_amdgcn_rcpf(1.f + 0.3275911f * 0.70710678f * fabsf(z));
-    const float e = __expf(-0.5f * z * z);
-    const float poly = t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
-    const float tail = 0.5f * poly * e;  // 0.5 * erfc(|z| / sqrt 2)
-    cdf = z >= 0.f ? 1.f - tail : tail;
-    pdf = 0.39894228f * e;
-}
-
-// ACT: -1 none, else UnaryKind (relu 0, abs 1, gelu 2, sin 4)
-template <int ACT>
-__device__ __forceinline__ float act_apply(float z) {
-    if constexpr (ACT == 2) {
-        float cdf, pdf;
-        normal_parts(z, cdf, pdf);
-        return z * cdf;
-    } else if constexpr (ACT < 0) {
-        return z;
-    } else {
-        return unary_apply(ACT, z, 0.f, 0.f);
-    }
-}
-
 template <int ACT, int BIN>
 __global__ __launch_bounds__(256) void k_mid_fwd(MidParams P) {
     const Unit u = decode(P);
@@ -129,21 +56,6 @@ __global__ __launch_bounds__(256) void k_mid_fwd(MidParams P) {
         v[q] = BIN ? x[q] * t : x[q] + t;
     }
     store8(rv, P.v, u.plane + u.p, v, u.nvalid);
-}
-
-// act(z) and act'(z)
-template <int ACT>
-__device__ __forceinline__ void act_both(float z, float& t, float& d) {
-    if constexpr (ACT == 2) {
-        float cdf, pdf;
-        normal_parts(z, cdf, pdf);
-        t = z * cdf;
-        d = cdf + z * pdf;
-    } else {
-        t = act_apply<ACT>(z);
-        if constexpr (ACT < 0) d = 1.f;
-        else d = unary_grad(ACT, z, 0.f, 0.f);
-    }
 }
 
 // The adjoint, written from the side of p:
