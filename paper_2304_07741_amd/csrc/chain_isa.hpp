@@ -42,7 +42,7 @@ enum Opcode : uint8_t {
     OP_UNBX,       // A = R[r] * unary_kind'(A)                         (A: the unary's input, R[r]: gradient)
     OP_BING,       // A = d blend_kind(L, A) / d side, L = R[r]         (A: RHS value, R[r]: LHS value; T lanes)
     OP_SMTBX,      // A = A * (R[r] - sum_s R[r][s] * A[s])             (A: softmax output, R[r]: gradient)
-    OP_FOLDBX,     // A[t] = gradient of the fold's input: R[r][0] spread (sum), / T (avg), to the first maximum of A (max)
+    OP_FOLDBX,     // A[t] = gradient of the fold's input: R[r][0] spread (sum), / T or / f0 where that is set (avg), to the first maximum of A (max)
     OP_PSET,       // P[a + t] = f0
     OP_PADD,       // P[a + t % b] += A[t]
     OP_PLD,        // A[t] = P[a + t]
@@ -52,6 +52,8 @@ enum Opcode : uint8_t {
     OP_SMCBX,      // A[t] = A[t] * (R[r][t] - P[a + t])                (A: softmax output, R[r]: gradient)
     OP_XADD,       // P[a (+ t)] += A[t] of the thread whose load at offset(b) [+ window tap t] read THIS pixel
     OP_BINLD,      // A = blend_kind(loaded, A) or (A, loaded): OP_LD and OP_BIN in one, the loaded operand never visits a register
+    OP_LDFOLD,     // A = fold over the taps of a window of ext[a], each tap blended with A's own lane or with the tap of a second window: OP_LD ...
+                   // OP_FOLD in one, no lane of the window is ever kept (TM = 1)
     OP_COUNT
 };
 
@@ -70,6 +72,11 @@ constexpr uint8_t kExtTaps = 0x02;         // the external tensor has taps of it
 constexpr int kBinLdKindShift = 2;          // the blend kind, three bits
 constexpr uint8_t kBinLdLoadedIsLhs = 0x20; // the loaded operand is the LHS (else A is)
 constexpr uint8_t kBinLdLoadedScalar = 0x40;  // the loaded operand has one lane, replicated over A's T lanes
+// OP_LDFOLD (a window of three or five columns at the pixel's own position): r as OP_LD; kind: the fold kind, two bits, then
+constexpr int kLfBlendShift = 2;            // the blend, three bits: 0 sum, 1 product, 2 tap - other, 3 other - tap
+constexpr uint8_t kLfBlend = 0x20;          // there is a blend
+constexpr uint8_t kLfSecond = 0x80;         // blended with the tap of a second window of the same size, over ext[b]
+// f0: the unary applied to the tap before the blend, -1 for none
 // OP_ST flags
 constexpr uint8_t kStAdd = 0x01;
 // extra unary kind for the planner (after the five of the DAG): negation

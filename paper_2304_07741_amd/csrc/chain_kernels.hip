@@ -15,12 +15,14 @@ void run(const Program& pg, hipStream_t stream) {
         run_ragged(pg, stream);
         return;
     }
-    if (pg.tm <= 1) {
-        if (v == 16) launch<1, 16>(pg, stream);
-        else if (v == 8) launch<1, 8>(pg, stream);
-        else if (v == 4) launch<1, 4>(pg, stream);
-        else if (v == 2) launch<1, 2>(pg, stream);
-        else launch<1, 1>(pg, stream);
+    if (pg.tm <= 1 && streams_windows(pg)) {
+        run_streamed(pg, stream);
+    } else if (pg.tm <= 1) {
+        if (v == 16) launch<1, 16, false>(pg, stream);
+        else if (v == 8) launch<1, 8, false>(pg, stream);
+        else if (v == 4) launch<1, 4, false>(pg, stream);
+        else if (v == 2) launch<1, 2, false>(pg, stream);
+        else launch<1, 1, false>(pg, stream);
     } else if (pg.tm <= 9) {
         if (v == 4) launch<9, 4>(pg, stream);
         else if (v == 2 && f32_windows(pg)) launch<9, 2>(pg, stream);

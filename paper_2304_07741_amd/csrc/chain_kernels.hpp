@@ -13,6 +13,15 @@ constexpr int regs_for(int tm) { return tm <= 1 ? 10 : (tm <= 9 ? 6 : 4); }
 // Pixels per thread the instances with TM lanes exist for: 16 ... 1 without taps, 4, 2 or 1 up to 9 taps, 1 beyond.
 constexpr int max_vec_for(int tm) { return tm <= 1 ? 16 : (tm <= 9 ? 4 : 1); }
 
+// Programs with OP_LDFOLD have instances of their own, of 4 or 8 pixels per thread: three taps of two windows at a time are 48 registers with 8,
+// and the sixteen channels of a one-pixel thread would be as many copies of the code.
+constexpr int kMaxStreamVec = 8, kMinStreamVec = 4;
+inline bool streams_windows(const Program& pg) {
+    for (int i = 0; i < pg.n_instr; i++)
+        if (pg.ins[i].op == OP_LDFOLD) return true;
+    return false;
+}
+
 // Largest workgroup of that instance (the tap vectors of a thread live in registers: wider lanes, fewer threads).
 constexpr int max_threads_for(int) { return 512; }
 // Wavefronts per SIMD that the register allocation of an instance leaves room for (1: no requirement).  The instance with
@@ -39,6 +48,7 @@ constexpr size_t kMaxLdsBytes = 144 * 1024;  // of the 160 KB of a compute unit 
 
 // Enqueues the program; every pointer of pg.ext must be set.  pg.tm must be 1, 9 or 25, pg.vec one of max_vec_for's.
 void run(const Program& pg, hipStream_t stream);
+void run_streamed(const Program& pg, hipStream_t stream);  // programs with OP_LDFOLD
 void run_ragged(const Program& pg, hipStream_t stream);  // where pg.vec does not divide the plane
 
 }  // namespace chain

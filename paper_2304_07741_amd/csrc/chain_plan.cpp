@@ -72,6 +72,7 @@ double instr_weight(const Instr& I) {
     case OP_BINLD:
     case OP_ST: w = 4; break;
     case OP_XADD: w = 6; break;
+    case OP_LDFOLD: w = 4; break;
     case OP_UN:
     case OP_UNBX: w = (I.kind == 0 || I.kind == 1 || I.kind == kUnNeg) ? 1 : 6; break;
     case OP_SMT:
@@ -996,6 +997,7 @@ double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
     for (int p = 0; p < pg.n_pass; p++)
         for (int i = pg.pass[p].body_begin; i < pg.pass[p].body_end; i++)
             if (pg.ins[i].op == OP_PSET || pg.ins[i].op == OP_PADD || pg.ins[i].op == OP_PLD || pg.ins[i].op == OP_XADD) one_copy = false;
+    const bool streams = streams_windows(pg);  // (threads of one image row each)
     Program best_shape = pg;
     double best_cost = -1;
     auto look = [&](bool one_copy, int widest, int narrowest, int64_t most_workgroups) {
@@ -1004,7 +1006,7 @@ double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
             // pixel per thread, 18 + 37 with sixteen.  Not where four divide them: 64x64 planes of 14x14 8.9 + 19.3 with four, 9.6 + 18.8
             // with eight.  Nor where a workgroup holds all channels: there the estimate errs, one program over 9x96 planes of 23x17
             // took 126 us with two pixels, 38 with one)
-            if (dag.W < V || (HW % V != 0 && (all_channels || HW % 4 == 0))) continue;
+            if (dag.W < V || (streams && dag.W % V != 0) || (HW % V != 0 && (all_channels || HW % 4 == 0))) continue;
             pg.vec = V;
             pg.unroll = unroll_for(pg.tm, V);
             pg.persist_copies = one_copy ? 1 : pg.unroll;
@@ -1032,7 +1034,7 @@ double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
             }
         }
     };
-    look(one_trip && one_copy, max_vec_for(pg.tm), 1, INT64_MAX);
+    look(one_trip && one_copy, streams ? kMaxStreamVec : max_vec_for(pg.tm), streams ? kMinStreamVec : 1, INT64_MAX);
     if (!one_trip && one_copy && best_cost >= 0) look(true, best_shape.vec, best_shape.vec, 256);
     if (best_cost < 0) throw Fail{"tile, halo and persistent state do not fit one workgroup"};
     pg = best_shape;
@@ -1040,6 +1042,219 @@ double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
 }
 
 }  // namespace
+
+// Windows whose taps are folded right away (an elementwise function of a window's tap, of the pixel's own values and of a second window's tap,
+// under sum, avg or max): OP_LD ... OP_FOLD becomes one OP_LDFOLD.  Done only where no instruction over taps is left: the program then
+// runs on the instances without taps, with up to 16 pixels per thread instead of one or two.
+// The lanes of A and of the registers are followed symbolically; what computes lanes is not emitted, what computes one lane is.
+class Streamer {
+   public:
+    explicit Streamer(const Program& p) : in_(p), out_(p) {}
+    bool run(std::vector<ExtRef>& refs) {
+        bool any = false;
+        std::vector<int> where(in_.n_instr, -1);
+        out_.n_instr = 0;
+        for (int p = 0; p < in_.n_pass; p++) {
+            const Pass& P = in_.pass[p];
+            Pass& Q = out_.pass[p];
+            Q.pro_begin = (uint16_t)out_.n_instr;
+            for (int i = P.pro_begin; i < P.pro_end; i++) {
+                if (in_.ins[i].T > 1) return false;
+                where[i] = push(in_.ins[i]);
+            }
+            Q.pro_end = Q.body_begin = (uint16_t)out_.n_instr;
+            a_ = Value();
+            for (int i = P.body_begin; i < P.body_end; i++) {
+                if (!step(in_.ins[i], any)) return false;
+                where[i] = out_.n_instr - 1;
+            }
+            Q.body_end = (uint16_t)out_.n_instr;
+        }
+        if (!any) return false;
+        out_.tm = 1;
+        out_.n_regs = 0;
+        for (int i = 0; i < out_.n_instr; i++) {
+            const Opcode op = (Opcode)out_.ins[i].op;
+            if (op == OP_MOVR || op == OP_MOVA || op == OP_BIN || op == OP_UNBX || op == OP_BING || op == OP_FOLDBX || op == OP_SMCDOT || op == OP_SMCBX || op == OP_SMTBX)
+                out_.n_regs = std::max(out_.n_regs, out_.ins[i].r + 1);
+        }
+        for (ExtRef& r : refs)
+            if (r.store_instr >= 0) r.store_instr = where[r.store_instr];
+        return true;
+    }
+    const Program& result() const { return out_; }
+
+   private:
+    struct Value {
+        enum Kind { kOne, kWin, kSpread, kBlend } kind = kOne;  // one lane (or nothing), a window, a register's lane in every tap, a blend
+        Instr win, win2;           // the window loads
+        int before = -1;           // unary of the window's taps
+        int blend = -1;
+        bool tap_is_lhs = true, second = false;
+        // the other operand, or what is spread: a register's lane (`version` of it), or a lane loaded from a tensor
+        int reg = -1, version = 0, divisor = 0;
+        bool from_ext = false;
+        Instr load;
+        int T = 1;
+    };
+    int push(const Instr& I) {
+        out_.ins[out_.n_instr] = I;
+        return out_.n_instr++;
+    }
+    static int as_unary(const Instr& I) { return I.kind == 0 || I.kind == 1 || I.kind == 2 || I.kind == kUnNeg ? I.kind : -1; }
+    bool blend_with(Value& a, int kind, bool tap_is_lhs) {
+        if (a.kind != Value::kWin || a.blend >= 0 || (kind != kAdd && kind != kMul && kind != kSub)) return false;
+        a.kind = Value::kBlend;
+        a.blend = kind;
+        a.tap_is_lhs = tap_is_lhs;
+        return true;
+    }
+    bool step(const Instr& I, bool& any) {
+        switch (I.op) {
+        case OP_LD:
+            if (I.T == 1) break;
+            if (!(I.kind & kWin) || (I.kind & kExtTaps) || in_.ext[I.a].T != 1 || (I.b & 255) || ((I.r & 15) != 3 && (I.r & 15) != 5)) return false;
+            a_ = Value();
+            a_.kind = Value::kWin;
+            a_.win = I;
+            a_.T = I.T;
+            return true;
+        case OP_UN: {
+            if (a_.kind == Value::kOne) break;
+            const int u = as_unary(I);
+            if (u < 0 || I.T != a_.T) return false;
+            if (a_.kind == Value::kWin && a_.before < 0) a_.before = u;
+            else return false;
+            return true;
+        }
+        case OP_MOVR:
+            if (a_.kind == Value::kOne) {
+                version_[I.r]++;
+                r_[I.r] = Value();
+                if (I.T != 1) return false;
+                break;
+            }
+            if (I.T != a_.T) return false;
+            r_[I.r] = a_;  // (nothing is written: a lane that the register held stays there)
+            return true;
+        case OP_MOVA:
+            a_ = r_[I.r];
+            if (a_.kind != Value::kOne) return I.T == a_.T;
+            if (I.T != 1) return false;
+            break;
+        case OP_BIN: {
+            const bool reg_lhs = I.kind & kBinRegIsLhs, reg_one = I.kind & kBinRegScalar, acc_one = I.kind & kBinAccScalar;
+            const Value& r = r_[I.r];
+            if (I.T == 1) {
+                if (a_.kind != Value::kOne || r.kind != Value::kOne) return false;
+                break;
+            }
+            if (acc_one) return false;
+            if (reg_one || r.kind == Value::kSpread) {  // lanes with one lane of a register
+                if (a_.T != I.T || !blend_with(a_, I.kind & 7, !reg_lhs)) return false;
+                if (reg_one) {
+                    if (r.kind != Value::kOne) return false;
+                    a_.reg = I.r;
+                    a_.version = version_[I.r];
+                } else {
+                    if (r.from_ext || r.T != I.T) return false;
+                    a_.reg = r.reg;
+                    a_.version = r.version;
+                    a_.divisor = r.divisor;
+                }
+                return true;
+            }
+            if (r.kind == Value::kWin && r.before < 0 && r.win.r == a_.win.r && r.T == I.T && a_.T == I.T) {  // two windows
+                if (!blend_with(a_, I.kind & 7, !reg_lhs)) return false;
+                a_.second = true;
+                a_.win2 = r.win;
+                return true;
+            }
+            return false;
+        }
+        case OP_BINLD: {
+            if (I.T == 1) {
+                if (a_.kind != Value::kOne) return false;
+                break;
+            }
+            const bool loaded_lhs = I.kind & kBinLdLoadedIsLhs;
+            if (a_.T != I.T || !blend_with(a_, I.kind >> kBinLdKindShift & 7, !loaded_lhs)) return false;
+            Instr L;
+            L.op = OP_LD;
+            L.kind = I.kind & (kWin | kExtTaps);
+            L.a = I.a;
+            L.b = I.b;
+            L.r = I.r;
+            L.T = 1;
+            if (I.kind & kBinLdLoadedScalar) {
+                if (L.kind) return false;
+                a_.from_ext = true;
+                a_.load = L;
+                return true;
+            }
+            if (L.kind != kWin || in_.ext[I.a].T != 1 || I.r != a_.win.r || (I.b & 255)) return false;
+            L.T = I.T;
+            a_.second = true;
+            a_.win2 = L;
+            return true;
+        }
+        case OP_FOLDBX: {  // a register's lane spread over the taps
+            const Value& r = r_[I.r];
+            if (r.kind != Value::kOne || I.kind == 2 || I.T == 1) return false;
+            a_ = Value();
+            a_.kind = Value::kSpread;
+            a_.reg = I.r;
+            a_.version = version_[I.r];
+            a_.divisor = I.kind == 1 ? I.T : 0;
+            a_.T = I.T;
+            return true;
+        }
+        case OP_FOLD: {
+            if (I.T == 1 || I.T != a_.T || (a_.kind != Value::kWin && a_.kind != Value::kBlend)) return false;
+            if (a_.from_ext) push(a_.load);
+            else if (a_.reg >= 0) {
+                if (version_[a_.reg] != a_.version) return false;  // (overwritten in between)
+                Instr m;
+                m.op = a_.divisor ? OP_FOLDBX : OP_MOVA;
+                m.T = 1;
+                m.r = (uint8_t)a_.reg;
+                m.kind = a_.divisor ? 1 : 0;
+                m.f0 = (float)a_.divisor;
+                push(m);
+            }
+            Instr f;
+            f.op = OP_LDFOLD;
+            f.T = I.T;
+            f.a = a_.win.a;
+            f.r = a_.win.r;
+            f.kind = (uint8_t)(I.kind & 3);
+            if (a_.blend >= 0) f.kind |= (uint8_t)(kLfBlend | ((a_.blend == kSub && !a_.tap_is_lhs ? 3 : a_.blend) << kLfBlendShift));
+            if (a_.second) {
+                f.kind |= kLfSecond;
+                f.b = a_.win2.a;
+            }
+            f.f0 = (float)a_.before;
+            push(f);
+            any = true;
+            a_ = Value();
+            return true;
+        }
+        default:
+            if (I.T != 1 || a_.kind != Value::kOne || I.op == OP_XADD) return false;
+            if ((I.op == OP_UNBX || I.op == OP_BING || I.op == OP_SMCDOT || I.op == OP_SMCBX) && r_[I.r].kind != Value::kOne) return false;
+            break;
+        }
+        if (out_.n_instr >= kMaxInstr) return false;
+        push(I);
+        if (I.op == OP_LD) a_ = Value();
+        return true;
+    }
+    const Program& in_;
+    Program out_;
+    Value a_;
+    std::map<int, Value> r_;
+    std::map<int, int> version_;
+};
 
 bool chain_candidate(const Dag& dag, int k) {
     const Node& nd = dag.nodes[k];
@@ -1338,6 +1553,28 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
         };
         out.cost = best_of(emit_fwd, false, out.fwd, out.fwd_ext);
         out.cost += best_of(emit_bwd, true, out.bwd, out.bwd_ext);
+        // (Pays off from a plane of 32 threads and 3.6 M taps on, with four pixels per thread from 7.2 M on: the channels of a trip go one after
+        // the other here.  3x3 box, forward + backward, us with all lanes / streamed: 128x64 planes of 56x56 327 / 163, 16x96 of 32x32 33 / 17, 8x64 of
+        // 56x56 32 / 17, 128x64 of 28x28 90 / 74, 16x64 of 28x28 20.8 / 20.3, 8x32 of 28x28 14.8 / 19.9, 128x128 of 8x8 26 / 40, 16x64 of 16x16 15.2 / 15.7; 5x5 under a product
+        // and an avg fold, 16x96 of 32x32, forward 69 / 13, backward 159 / 20.)
+        auto stream = [&](Program& pg, std::vector<ExtRef>& refs) {
+            std::vector<ExtRef> r = refs;
+            Streamer S(pg);
+            if (!S.run(r)) return;
+            try {
+                Program q = S.result();
+                set_geometry(q, dag, C, 0, !smc.empty(), false);
+                const int64_t taps = (int64_t)dag.N * C * dag.H * dag.W * tm;
+                if (dag.H * dag.W < 32 * q.vec || taps < (q.vec < kMaxStreamVec ? 7200000 : 3600000)) return;
+                pg = q;
+                refs = r;
+            } catch (const Fail&) {
+            }
+        };
+        if (variants && tm > 1) {
+            stream(out.fwd, out.fwd_ext);
+            stream(out.bwd, out.bwd_ext);
+        }
         return true;
     } catch (const Fail& f) {
         why = f.why;
@@ -1358,7 +1595,7 @@ double program_cost(const Program& pg) {
 
 std::string dump(const Program& pg) {
     static const char* names[] = {"LD", "MASK", "UN", "MOVR", "MOVA", "BIN", "FOLD", "SMT", "ST", "UNBX", "BING", "SMTBX", "FOLDBX",
-                                  "PSET", "PADD", "PLD", "SMCSTAT", "SMCAPPLY", "SMCDOT", "SMCBX", "XADD", "BINLD"};
+                                  "PSET", "PADD", "PLD", "SMCSTAT", "SMCAPPLY", "SMCDOT", "SMCBX", "XADD", "BINLD", "LDFOLD"};
     std::ostringstream os;
     os << "program: C=" << pg.C << " HxW=" << pg.H << "x" << pg.W << " vec=" << pg.vec << " own=" << pg.own_threads << " halo=" << pg.halo_threads
        << " unroll=" << pg.unroll << " tiles=" << pg.tiles << " chunk=" << pg.chunk << " slices=" << pg.slices << " threads=" << pg.threads << " persist=" << pg.n_persist

@@ -70,6 +70,17 @@ CHAIN_HD int vm_u(int v) { return __builtin_amdgcn_readfirstlane(v); }
 #else
 CHAIN_HD int vm_u(int v) { return v; }
 #endif
+// A uniform value that the compiler knows nothing about: a branch on it stays where it is (a loop is not copied for each of its outcomes).
+#if defined(__HIP_DEVICE_COMPILE__)
+__device__ __forceinline__ int vm_opaque(int v) {
+    v = vm_u(v);
+    asm volatile("" : "+s"(v));
+    return v;
+}
+#endif
+#if !defined(__HIP_DEVICE_COMPILE__)
+inline int vm_opaque(int v) { return v; }
+#endif
 // A 16-byte instruction, made uniform.
 CHAIN_HD Instr vm_fetch(const Instr& src) {
     uint32_t w[4];
@@ -359,6 +370,17 @@ CHAIN_HD float vm_gelu_grad_fast(float x) {
     float cdf, pdf;
     vm_normal_parts(x, cdf, pdf);
     return cdf + x * pdf;
+}
+
+// x / n as a product with the reciprocal and one correction step from the remainder: the quotient to within one unit in the last
+// place, a fifth of the instructions of a division per pixel (infinities and NaN come out as a division gives them).
+CHAIN_HD float vm_over(float x, float n) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const float r = 1.f / n, q = x * r;
+    return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-n, q, x), r, q), n, x);
+#else
+    return x / n;
+#endif
 }
 
 // Sum of the offsets of a position for channel c: terms [b >> 8, (b >> 8) + (b & 255)) that cover c.
@@ -719,7 +741,7 @@ struct Env {
     int h = 0;        // channels of the trip that exist (0 .. U)
     bool pro = false; // the prologue of a pass (once per workgroup item, not per channel)
     bool fast = false; // Program::fast_math
-    bool f32_windows = true;  // window loads of fp32 tensors by vm_ld_window_f32, not by the general loads
+    bool f32_windows = true;  // window loads of fp32 tensors by vm_ld_window_f32, not by the general loads; without taps: OP_LDFOLD
     int np = 0;       // persistent floats per pixel and channel
     int pstride = 0;  // floats between consecutive persistent floats of a thread (the workgroup's size)
     int rstride = 0;  // floats between consecutive register pieces of a thread
@@ -789,6 +811,172 @@ CHAIN_HD void vm_blend_lanes(int kind, bool x_lhs, const float* X, float* A, int
     case 3: CHAIN_CASE; CHAIN_EACH(T, e, l, A[e] = X[e] <= A[e] ? X[e] : A[e];); break;
     default: CHAIN_CASE; CHAIN_EACH(T, e, l, A[e] = X[e] >= A[e] ? X[e] : A[e];); break;
     }
+}
+
+// A row of a window as a thread of V pixels (4 or 8, of one image row) sees it: its pixels and two more on either side, 0 outside the
+// image.  The main access is aligned and lies inside the tensor or is sent outside as a whole; so does each pair beside it.
+// BF16: the tensor's type, as a constant: with a branch on it between the loads and their use the compiler waits for each load where it stands.
+template <int V, bool BF16>
+struct RowRaw {
+    uint32_t d[BF16 ? V / 2 + 2 : V + 4];  // bf16: pairs; fp32: pixels
+};
+#if defined(__HIP_DEVICE_COMPILE__)
+template <int V, bool BF16>
+__device__ __forceinline__ void vm_row_issue(const Tensor& e, const Geo& g, const Thread& th, int chan, int row, RowRaw<V, BF16>& raw) {
+    constexpr int es = BF16 ? 2 : 4;
+    const bool ok = (int)th.active & (int)((unsigned)row < (unsigned)g.H);
+    const int o = (chan * g.HW + row * g.W + th.col0) * es;
+    int left = (int)ok & (int)(th.col0 > 0) ? o - 2 * es : tile::kOob, main = ok ? o : tile::kOob, right = (int)ok & (int)(th.col0 + V < g.W) ? o + V * es : tile::kOob;
+    asm volatile("" : "+v"(left), "+v"(main), "+v"(right));
+    if constexpr (BF16) {
+        raw.d[0] = __builtin_amdgcn_raw_buffer_load_b32(e.rs, left, 0, 0);
+        if constexpr (V == 8) {
+            const tile::u32x4 m = tile::bload16(e.rs, main);
+#pragma unroll
+            for (int k = 0; k < 4; k++) raw.d[1 + k] = m[k];
+        } else {
+            const vm_u32x2 m = __builtin_amdgcn_raw_buffer_load_b64(e.rs, main, 0, 0);
+            raw.d[1] = m[0];
+            raw.d[2] = m[1];
+        }
+        raw.d[1 + V / 2] = __builtin_amdgcn_raw_buffer_load_b32(e.rs, right, 0, 0);
+    } else {
+        const vm_u32x2 l = __builtin_amdgcn_raw_buffer_load_b64(e.rs, left, 0, 0);
+        raw.d[0] = l[0];
+        raw.d[1] = l[1];
+#pragma unroll
+        for (int q = 0; q < V / 4; q++) {
+            int p = main == tile::kOob ? tile::kOob : main + 16 * q;
+            asm volatile("" : "+v"(p));
+            const tile::u32x4 m = tile::bload16(e.rs, p);
+#pragma unroll
+            for (int k = 0; k < 4; k++) raw.d[2 + 4 * q + k] = m[k];
+        }
+        const vm_u32x2 r = __builtin_amdgcn_raw_buffer_load_b64(e.rs, right, 0, 0);
+        raw.d[V + 2] = r[0];
+        raw.d[V + 3] = r[1];
+    }
+}
+#else
+template <int V, bool BF16>
+inline void vm_row_issue(const Tensor& e, const Geo& g, const Thread& th, int chan, int row, RowRaw<V, BF16>& raw) {
+    for (int k = 0; k < V + 4; k++) {
+        const int col = th.col0 + k - 2;
+        const bool ok = th.active && (unsigned)row < (unsigned)g.H && (unsigned)col < (unsigned)g.W;
+        const int64_t i = (int64_t)chan * g.HW + row * g.W + col;
+        if (BF16) {
+            const uint32_t h = ok ? ((const uint16_t*)e.ptr)[i] : 0;
+            raw.d[k / 2] = k & 1 ? raw.d[k / 2] | h << 16 : h;
+        } else {
+            raw.d[k] = ok ? ((const uint32_t*)e.ptr)[i] : 0;
+        }
+    }
+}
+#endif
+template <int V, bool BF16>
+CHAIN_HD void vm_row_floats(const RowRaw<V, BF16>& raw, float* x) {
+#pragma unroll
+    for (int k = 0; k < V + 4; k++) {
+        if (BF16) x[k] = vm_bits_to_f32(k & 1 ? raw.d[k / 2] & 0xffff0000u : raw.d[k / 2] << 16);
+        else x[k] = vm_bits_to_f32(raw.d[BF16 ? 0 : k]);
+    }
+}
+
+// One of the planner's streamable unaries (no clipped exp) on L lanes.
+template <int L>
+CHAIN_HD void vm_unary_lanes(int kind, bool fast, float* x) {
+    switch (kind) {
+    case 0:
+        CHAIN_CASE;
+#pragma unroll
+        for (int e = 0; e < L; e++) x[e] = fmaxf(x[e], 0.f);
+        break;
+    case 1:
+        CHAIN_CASE;
+#pragma unroll
+        for (int e = 0; e < L; e++) x[e] = fabsf(x[e]);
+        break;
+    case 2:
+        CHAIN_CASE;
+        if (fast) {
+#pragma unroll
+            for (int e = 0; e < L; e++) x[e] = vm_gelu_fast(x[e]);
+        } else {
+            for (int e = 0; e < L; e++) x[e] = vm_gelu(x[e]);
+        }
+        break;
+    default:
+        CHAIN_CASE;
+#pragma unroll
+        for (int e = 0; e < L; e++) x[e] = -x[e];
+        break;
+    }
+}
+
+// A row of an OP_LDFOLD: its KW taps, blended, join the fold.  x, y: the row of the tap's tensor and of the other operand (a second window's row, or
+// the pixel's own value in y[2 ..]).  Sums begin at -0, which changes no first term.
+template <int V, int KW, bool SECOND>
+CHAIN_HD void vm_fold_row(const Instr& I, bool first, const float* x, const float* y, float* acc) {
+    const int blend = I.kind & kLfBlend ? I.kind >> kLfBlendShift & 7 : 7;
+#define CHAIN_TAPS(JOIN)                                                                       \
+    _Pragma("unroll") for (int j = 0; j < KW; j++) {                                           \
+        _Pragma("unroll") for (int v = 0; v < V; v++) {                                        \
+            const float a = x[v + 2 + j - KW / 2], b = y[SECOND ? v + 2 + j - KW / 2 : v + 2]; \
+            (void)b;                                                                           \
+            JOIN;                                                                              \
+        }                                                                                      \
+    }
+    if (vm_opaque((I.kind & 3) == 2)) {
+        const int kind = vm_opaque(blend);
+        CHAIN_TAPS({
+            const float t = kind == 0 ? a + b : (kind == 1 ? a * b : (kind == 2 ? a - b : (kind == 3 ? b - a : a)));
+            acc[v] = (first && j == 0) || t > acc[v] ? t : acc[v];
+        })
+        return;
+    }
+    switch (vm_opaque(blend)) {
+    case 0: CHAIN_CASE; CHAIN_TAPS(acc[v] += a + b) break;
+    case 1: CHAIN_CASE; CHAIN_TAPS(acc[v] += a * b) break;
+    case 2: CHAIN_CASE; CHAIN_TAPS(acc[v] += a - b) break;
+    case 3: CHAIN_CASE; CHAIN_TAPS(acc[v] += b - a) break;
+    default: CHAIN_CASE; CHAIN_TAPS(acc[v] += a) break;
+    }
+#undef CHAIN_TAPS
+}
+
+// OP_LDFOLD for one channel: A (its V lanes) becomes the fold.  Row by row, the next row's loads in flight; a row is loaded and
+// taken apart once for all its taps.  Taps are added in their order, as OP_FOLD adds them.
+template <int V, bool BF16, bool SECOND, bool BF16_2>
+CHAIN_HD void vm_ldfold(const Geo& g, const Instr& I, const Env& ev, const Thread& th, const Tensor& e, const Tensor& e2, int c, float* A) {
+    const int KH = I.r >> 4, KW = I.r & 15;
+    const int before = (int)I.f0;
+    const int chan = th.n * g.C + c, row0 = th.row0 - KH / 2;
+    float acc[V], x[V + 4], y[V + 4];
+#pragma unroll
+    for (int v = 0; v < V; v++) {
+        acc[v] = -0.f;
+        y[v + 2] = A[v];
+    }
+    RowRaw<V, BF16> n1;
+    RowRaw<V, BF16_2> n2;
+    vm_row_issue<V, BF16>(e, g, th, chan, row0, n1);
+    if (SECOND) vm_row_issue<V, BF16_2>(e2, g, th, chan, row0, n2);
+#pragma unroll 1
+    for (int i = 0; i < KH; i++) {
+        const RowRaw<V, BF16> r1 = n1;
+        const RowRaw<V, BF16_2> r2 = n2;
+        // (past the last row: row H, outside the image)
+        vm_row_issue<V, BF16>(e, g, th, chan, i + 1 < KH ? row0 + i + 1 : g.H, n1);
+        if (SECOND) vm_row_issue<V, BF16_2>(e2, g, th, chan, i + 1 < KH ? row0 + i + 1 : g.H, n2);
+        vm_row_floats<V, BF16>(r1, x);
+        if (vm_opaque(before) >= 0) vm_unary_lanes<V + 4>(before, ev.fast, x);
+        if (SECOND) vm_row_floats<V, BF16_2>(r2, y);
+        if (vm_opaque(KW) == 3) vm_fold_row<V, 3, SECOND>(I, i == 0, x, y, acc);
+        else vm_fold_row<V, 5, SECOND>(I, i == 0, x, y, acc);
+    }
+    const bool avg = (I.kind & 3) == 1;
+#pragma unroll
+    for (int v = 0; v < V; v++) A[v] = avg ? vm_over(acc[v], (float)I.T) : acc[v];
 }
 
 // Every instruction except OP_XADD.  Pm: this thread's persistent floats.  A float that lives across the channel loop
@@ -902,20 +1090,8 @@ CHAIN_HD void vm_exec_lanes(const Program& pg, const Geo& g, const Instr& I, con
                         for (int v = 0; v < V; v++) Au[v] += Au[t * V + v];
                     }
                 if (I.kind == 1) {
-                    // sum / T as a product with the reciprocal and one correction step from the remainder: the quotient
-                    // to within one unit in the last place, a fifth of the instructions of a division per pixel
-                    // (infinities and NaN come out as a division gives them)
-                    const float n = (float)T;
-#if defined(__HIP_DEVICE_COMPILE__)
-                    const float r = 1.f / n;
 #pragma unroll
-                    for (int v = 0; v < V; v++) {
-                        const float q = Au[v] * r;
-                        Au[v] = __builtin_amdgcn_div_fixupf(fmaf(fmaf(-n, q, Au[v]), r, q), n, Au[v]);
-                    }
-#else
-                    for (int v = 0; v < V; v++) Au[v] /= n;
-#endif
+                    for (int v = 0; v < V; v++) Au[v] = vm_over(Au[v], (float)T);
                 }
             }
         }
@@ -1073,7 +1249,7 @@ CHAIN_HD void vm_exec_lanes(const Program& pg, const Geo& g, const Instr& I, con
 #pragma unroll
                 for (int u = 0; u < U; u++)
 #pragma unroll
-                    for (int v = 0; v < V; v++) X[u * TV + v] = X[u * TV + v] / (float)T;
+                    for (int v = 0; v < V; v++) X[u * TV + v] = X[u * TV + v] / (I.f0 > 0.f ? I.f0 : (float)T);
             }
             CHAIN_EACH(T, e, l, A[e] = X[e - l + l % V];);
         }
@@ -1180,6 +1356,38 @@ CHAIN_HD void vm_exec_lanes(const Program& pg, const Geo& g, const Instr& I, con
         CHAIN_CASE;
         vm_reg_read<TM, V, U>(Rm, rstride, I.r, T, X);
         CHAIN_EACH(T, e, l, A[e] = A[e] * (X[e] - Pm[(I.a * V + l) * pstride]););
+        break;
+    case OP_LDFOLD:
+        if constexpr (TM == 1 && (V == 4 || V == 8)) {
+            if (!ev.f32_windows) break;
+            CHAIN_CASE;
+            const Tensor e = vm_tensor(pg, g, I.a);
+            const Tensor e2 = vm_tensor(pg, g, (I.kind & kLfSecond) ? I.b : I.a);
+            // (one copy of the code for all channels of the trip: as many copies as channels spilled scalar registers)
+#pragma unroll 1
+            for (int u = 0; u < ev.h; u++) {
+                float a[V];
+#pragma unroll
+                for (int v = 0; v < V; v++) {
+                    a[v] = A[v];
+#pragma unroll
+                    for (int w = 1; w < U; w++) a[v] = u == w ? A[w * V + v] : a[v];
+                }
+                const int c = ev.c + u;
+                switch (vm_opaque((e.bf16 ? 1 : 0) | ((I.kind & kLfSecond) ? (e2.bf16 ? 6 : 2) : 0))) {
+                case 0: vm_ldfold<V, false, false, false>(g, I, ev, th, e, e2, c, a); break;
+                case 1: vm_ldfold<V, true, false, false>(g, I, ev, th, e, e2, c, a); break;
+                case 2: vm_ldfold<V, false, true, false>(g, I, ev, th, e, e2, c, a); break;
+                case 3: vm_ldfold<V, true, true, false>(g, I, ev, th, e, e2, c, a); break;
+                case 6: vm_ldfold<V, false, true, true>(g, I, ev, th, e, e2, c, a); break;
+                default: vm_ldfold<V, true, true, true>(g, I, ev, th, e, e2, c, a); break;
+                }
+#pragma unroll
+                for (int w = 0; w < U; w++)
+#pragma unroll
+                    for (int v = 0; v < V; v++) A[w * V + v] = u == w ? a[v] : A[w * V + v];
+            }
+        }
         break;
     default: break;
     }
