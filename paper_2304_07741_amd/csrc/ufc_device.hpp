@@ -16,9 +16,22 @@ using namespace canvas::tile;
 
 __device__ __forceinline__ uint32_t div_magic(uint32_t x, uint32_t magic) { return magic ? __umulhi(x, magic) : x; }
 
+// bits [lo, hi), 0 <= lo, hi <= 8
+__device__ __forceinline__ uint32_t run_of_bits(int lo, int hi) { return hi > lo ? ((1u << hi) - 1u) & ~((1u << lo) - 1u) : 0u; }
 // bit q: pixel p+q exists and its source (h+dh, w+dw) is inside the image
 __device__ __forceinline__ uint32_t shift_bits(const MidParams& P, int p, int dh, int dw) {
     int h = (int)div_magic((uint32_t)p, P.magicW), c = p - h * P.W;
+    if (c < 0) {  // (the multiplier is exact below 2^32 / W and one too high at most beyond)
+        c += P.W;
+        h--;
+    }
+    if (P.W >= 8) {  // a run of pixels in each of at most two image rows
+        const int n1 = min(8, P.W - c);  // pixels [0, n1) lie in row h
+        uint32_t bits = 0;
+        if ((unsigned)(h + dh) < (unsigned)P.H) bits = run_of_bits(max(0, -(c + dw)), min(n1, P.W - c - dw));
+        if ((unsigned)(h + 1 + dh) < (unsigned)P.H) bits |= run_of_bits(max(n1, n1 - dw), min(8, n1 + P.W - dw));
+        return P.P - p < 8 ? bits & ((1u << (P.P - p)) - 1u) : bits;
+    }
     uint32_t bits = 0;
 #pragma unroll
     for (int q = 0; q < 8; q++) {

@@ -29,6 +29,7 @@ struct MidParams {
 
 void mid_forward(const MidParams& P, hipStream_t s);
 void mid_backward(const MidParams& P, hipStream_t s);
+void self_backward(const MidParams& P, hipStream_t s);  // of y = x (*|+) shift(act(x)): x, dv = dy -> dx1 = dx
 
 }  // namespace ufc
 }  // namespace canvas
