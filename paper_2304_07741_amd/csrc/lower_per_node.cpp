@@ -16,6 +16,7 @@
 #include "gfc_tm_kernels.hpp"
 #include "ref_kernels.hpp"
 #include "sfc_kernels.hpp"
+#include "smc_kernels.hpp"
 #include "ufc_kernels.hpp"
 
 #include <algorithm>
@@ -84,6 +85,24 @@ void run_program(const chain::Program& pg0, const std::vector<Binding>& bind, bo
         }
     }
     chain::run(pg, a.stream);
+}
+
+// A tensor of a unit as its kernel finds it.
+const void* bound(const Binding& b, const RunArgs& a) {
+    switch (b.where) {
+    case 0: return a.ws + b.off;
+    case 1: return a.x;
+    case 2: return a.y;
+    case 3: return a.dy;
+    default: return a.dx;
+    }
+}
+
+// Whether the unit is a softmax over channels and nothing else, which has kernels of its own.
+bool softmax_of_channels(const Dag& dag, const Unit& U, smc::Params& P) {
+    if (U.nodes.size() != 1) return false;
+    const Node& nd = dag.nodes[U.nodes[0]];
+    return nd.op == Op::Softmax && nd.kind == kAxisC && nd.T == 1 && dag.nodes[nd.a].T == 1 && smc::plan(P, dag.N, nd.C, dag.H * dag.W);
 }
 
 // Whether the unit is y = x (*|+) shift(act(x)) of one tensor and nothing else: an activation and shifts of disjoint channel slices in any order
@@ -629,6 +648,11 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         for (const Binding& e : b) t += (e.where == 0 ? 4.0 : esz) * dag.numel(e.node);
         return t;
     };
+    auto bind_of = [](const std::vector<Binding>& b, chain::ExtRole role) {
+        for (const Binding& e : b)
+            if (e.role == role) return e;
+        throw std::runtime_error("chain: a tensor of the unit is missing");
+    };
     auto self_direct = [&](const Unit& U, ufc::MidParams& M) {
         return bf16 && y_direct && dx_direct && U.plan.inputs == std::vector<int>{0} && U.plan.outputs == std::vector<int>{dag.out} && self_blend(dag, U, M);
     };
@@ -637,6 +661,20 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         if (U.chain) {
             const chain::Program pg = U.plan.fwd;
             const std::vector<Binding> b = bind(U.plan.fwd_ext);
+            smc::Params S;
+            if (softmax_of_channels(dag, U, S)) {
+                const Binding bx = bind_of(b, chain::kValueIn), by = bind_of(b, chain::kValueOut);
+                low->fwd.push_back({"chain_fwd", ext_bytes(b), 0, [=](const RunArgs& a) {
+                                        smc::Params Q = S;
+                                        Q.x = bound(bx, a);
+                                        Q.out = const_cast<void*>(bound(by, a));
+                                        Q.x_f32 = !bf16 || bx.where == 0;
+                                        Q.out_f32 = !bf16 || by.where == 0;
+                                        Q.fast = bf16;
+                                        smc::forward(Q, a.stream);
+                                    }});
+                continue;
+            }
             ufc::MidParams M;
             if (self_direct(U, M)) {
                 low->fwd.push_back({"chain_fwd", ext_bytes(b), 0, [=](const RunArgs& a) {
@@ -808,12 +846,31 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         if (U.chain) {
             chain::Program pg = U.plan.bwd;
             const std::vector<Binding> b = bind(U.plan.bwd_ext);
+            bool adds = false;
             for (size_t i = 0; i < b.size(); i++)
                 if (b[i].role == chain::kGradOut) {
+                    adds = written[b[i].node];
                     // the first writer of a gradient overwrites, later ones add (fp32 buffers only)
                     if (written[b[i].node]) pg.ins[U.plan.bwd_ext[i].store_instr].kind |= chain::kStAdd;
                     written[b[i].node] = true;
                 }
+            smc::Params S;
+            if (softmax_of_channels(dag, U, S)) {
+                const Binding bx = bind_of(b, chain::kValueIn), bg = bind_of(b, chain::kGradIn), bd = bind_of(b, chain::kGradOut);
+                low->bwd.push_back({"chain_bwd", ext_bytes(b), 0, [=](const RunArgs& a) {
+                                        smc::Params Q = S;
+                                        Q.x = bound(bx, a);
+                                        Q.dy = bound(bg, a);
+                                        Q.out = const_cast<void*>(bound(bd, a));
+                                        Q.x_f32 = !bf16 || bx.where == 0;
+                                        Q.dy_f32 = !bf16 || bg.where == 0;
+                                        Q.out_f32 = !bf16 || bd.where == 0;
+                                        Q.acc = adds;
+                                        Q.fast = bf16;
+                                        smc::backward(Q, a.stream);
+                                    }});
+                continue;
+            }
             ufc::MidParams M;
             if (self_direct(U, M)) {
                 low->bwd.push_back({"chain_bwd", ext_bytes(b), 0, [=](const RunArgs& a) {
