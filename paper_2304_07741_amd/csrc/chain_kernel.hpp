@@ -39,11 +39,12 @@ __global__ __launch_bounds__(max_threads_for(TM), min_waves_for(TM, V)) void k_c
     const int chunks = vm_u(pg.chunks), tiles = vm_u(pg.tiles), chunk = vm_u(pg.chunk);
     const int own_threads = vm_u(pg.own_threads), halo_threads = vm_u(pg.halo_threads), n_pass = vm_u(pg.n_pass);
     const int xfloats = vm_u(pg.xadd_lanes) * g.npx;             // hand-over buffer of a slice (OP_XADD)
-    // LDS: registers (16-byte pieces, see vm_reg_read) | hand-over buffers | persistent floats (float k of pixel v of thread i at [(k * V + v) * threads + i])
+    // LDS: registers (16-byte pieces, see vm_reg_read; the hand-over buffers over them: xadd_alias) | hand-over buffers | persistent floats (float k of pixel v of thread i at [(k * V + v) * threads + i])
     const int rstride = threads * 4;
     float* const Rm = lds + threadIdx.x * 4;
-    float* const xbase = lds + vm_u(pg.n_regs) * reg_pieces(U * TM * V) * rstride;
-    float* const Pbase = xbase + S * xfloats;
+    const bool alias = vm_u(pg.xadd_alias) != 0;
+    float* const xbase = alias ? lds : lds + vm_u(pg.n_regs) * reg_pieces(U * TM * V) * rstride;
+    float* const Pbase = alias ? lds + vm_u(pg.n_regs) * reg_pieces(U * TM * V) * rstride : xbase + S * xfloats;
     float* const Pm = Pbase + threadIdx.x;
     const int slice = __builtin_amdgcn_readfirstlane(threadIdx.x / PT);  // (PT is a multiple of 64: uniform in a wavefront)
     float* const xbuf = xbase + slice * xfloats;
@@ -103,6 +104,7 @@ __global__ __launch_bounds__(max_threads_for(TM), min_waves_for(TM, V)) void k_c
                         for (int u = 0; u < U; u++) {
                             __syncthreads();
                             __syncthreads();
+                            if (alias) __syncthreads();
                         }
                     }
                     continue;
@@ -122,6 +124,7 @@ __global__ __launch_bounds__(max_threads_for(TM), min_waves_for(TM, V)) void k_c
                         vm_xadd_write<TM, V>(g, I, th, st.A + u * TM * V, xbuf);
                         __syncthreads();
                         if (u < ev.h) vm_xadd_gather<TM, V>(g, I, dh, dw, th, xbuf, Pm + u * ev.np * V * threads, threads);
+                        if (alias) __syncthreads();  // (the registers under the buffer may be written again)
                     }
                 }
             }

@@ -41,7 +41,7 @@ constexpr int reg_pieces_of(int tm, int vec) { return ((tm <= 1 ? 1 : (tm <= 9 ?
 
 // Bytes of LDS a thread of `pg` takes: its registers, its share of the hand-over buffer of OP_XADD, its persistent floats.
 inline size_t lds_bytes_per_thread(const Program& pg) {
-    return ((size_t)pg.n_regs * reg_pieces_of(pg.tm, pg.vec) * 4 + (size_t)(pg.xadd_lanes + pg.n_persist * pg.persist_copies) * pg.vec) * sizeof(float);
+    return ((size_t)pg.n_regs * reg_pieces_of(pg.tm, pg.vec) * 4 + (size_t)((pg.xadd_alias ? 0 : pg.xadd_lanes) + pg.n_persist * pg.persist_copies) * pg.vec) * sizeof(float);
 }
 inline size_t lds_bytes(const Program& pg) { return lds_bytes_per_thread(pg) * pg.threads; }
 constexpr size_t kMaxLdsBytes = 144 * 1024;  // of the 160 KB of a compute unit (the kernel keeps its copy of the program in LDS as well)

@@ -987,6 +987,7 @@ double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
     pg.xadd_lanes = 0;
     for (int i = 0; i < pg.n_instr; i++)
         if (pg.ins[i].op == OP_XADD) pg.xadd_lanes = std::max<int>(pg.xadd_lanes, pg.ins[i].T);
+    if (pg.xadd_lanes == 0 || (int64_t)pg.n_regs * reg_pieces_of(pg.tm, 1) * 4 < pg.xadd_lanes) pg.xadd_alias = 0;
     const int HW = dag.H * dag.W;
     // (a program that makes one trip keeps its registers' LDS: floats that no channel has for itself exist once.  The other
     // programs' workgroups were weighed with a copy per channel of the trip, and the estimate errs without them: softmax over
@@ -1042,6 +1043,69 @@ double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
 }
 
 }  // namespace
+
+// Fewer registers for a finished program: stores that nothing reads go, the others get the lowest register that is free where they stand (a
+// register is as many bytes of LDS per thread as the instance has lanes, and LDS decides how many wavefronts a compute unit holds);
+// where no register holds anything during a hand-over, its buffer takes their place.  Backward of unfold 3x3 -> softmax -> product ->
+// gelu -> sum, 16x96 planes of 32x32: 280 -> 196 bytes per thread, 239 -> 192 us.
+// Not for programs that keep registers from pass to pass.
+void compact_registers(Emitter& E) {
+    Program& pg = E.pg;
+    auto reads = [](const Instr& I) {
+        return I.op == OP_MOVA || I.op == OP_BIN || I.op == OP_UNBX || I.op == OP_BING || I.op == OP_SMTBX || I.op == OP_FOLDBX || I.op == OP_SMCDOT || I.op == OP_SMCBX;
+    };
+    std::vector<int> last_use(pg.n_instr, -1);  // of a store's value
+    for (int p = 0; p < pg.n_pass; p++) {
+        std::map<int, int> def;
+        for (int i = pg.pass[p].body_begin; i < pg.pass[p].body_end; i++) {
+            const Instr& I = pg.ins[i];
+            if (reads(I)) {
+                if (!def.count(I.r)) return;  // (a value from elsewhere)
+                last_use[def[I.r]] = i;
+            }
+            if (I.op == OP_MOVR) def[I.r] = i;
+        }
+    }
+    std::vector<int> where(pg.n_instr, -1);
+    std::map<int, int64_t> reach;
+    int n = 0, n_regs = 0;
+    bool alias = true;
+    for (int p = 0; p < pg.n_pass; p++) {
+        Pass& P = pg.pass[p];
+        const int pro = P.pro_begin, body = P.body_begin, end = P.body_end;
+        P.pro_begin = (uint16_t)n;
+        std::map<int, int> color, until;  // of the value that a register holds; by color: its last use
+        for (int i = pro; i < end; i++) {
+            if (i == body) P.pro_end = P.body_begin = (uint16_t)n;
+            Instr I = pg.ins[i];
+            if (I.op == OP_MOVR) {
+                if (last_use[i] < 0) continue;
+                int c = 0;
+                while (until.count(c) && until[c] > i) c++;
+                color[I.r] = c;
+                until[c] = last_use[i];
+                n_regs = std::max(n_regs, c + 1);
+                I.r = (uint8_t)c;
+            } else if (reads(I)) {
+                I.r = (uint8_t)color[I.r];
+            } else if (I.op == OP_XADD) {
+                for (const auto& u : until)
+                    if (u.second > i) alias = false;
+                reach[n] = E.reach_of[i];
+            }
+            where[i] = n;
+            pg.ins[n++] = I;
+        }
+        if (body == end) P.pro_end = P.body_begin = (uint16_t)n;
+        P.body_end = (uint16_t)n;
+    }
+    pg.n_instr = n;
+    pg.n_regs = n_regs;
+    pg.xadd_alias = alias ? 1 : 0;
+    E.reach_of = reach;
+    for (ExtRef& r : E.ext)
+        if (r.store_instr >= 0) r.store_instr = where[r.store_instr];
+}
 
 // Windows whose taps are folded right away (an elementwise function of a window's tap, of the pixel's own values and of a second window's tap,
 // under sum, avg or max): OP_LD ... OP_FOLD becomes one OP_LDFOLD.  Done only where no instruction over taps is left: the program then
@@ -1531,6 +1595,7 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
                     try {
                         auto E = shortest(emit_program, one_trip, most_kept);
                         most_kept = std::min(most_kept, (int)E->keep.size());
+                        if (!one_trip && variants) compact_registers(*E);
                         int64_t halo = 0;
                         for (int i = 0; i < E->pg.n_instr; i++)  // (the reach of the hand-overs of the program that was chosen)
                             if (E->pg.ins[i].op == OP_XADD) halo = std::max(halo, E->reach_of[i]);
