@@ -134,7 +134,7 @@ struct Program {
     int32_t n_red = 0;
     int32_t n_persist = 0;     // floats of P per pixel
     int32_t persist_copies = 1;  // `unroll` where a float of P belongs to one channel of the trip (accumulators), 1 where all live across the channel loop
-    int32_t xadd_alias = 0;    // 1: the hand-over buffer lies over the registers, none of which holds anything while an OP_XADD runs
+    int32_t xadd_alias = 0;    // 1: the hand-over buffer lies over the registers, none of which holds anything while an OP_XADD runs (tm > 1)
     int32_t pad[2] = {0, 0};
     int32_t xadd_lanes = 0;    // most lanes any OP_XADD hands over (0: the program has none)
     int32_t n_pass = 0, n_ext = 0, n_instr = 0, n_terms = 0;

@@ -25,8 +25,9 @@ __device__ __forceinline__ const Program& stage_program(unsigned char* sprog) {
     return *(const Program*)sprog;
 }
 
-// RAG: planes that are no multiple of V pixels.
-template <int TM, int V, int U, bool F32W, bool RAG>
+// RAG: planes that are no multiple of V pixels.  ALIAS: Program::xadd_alias (as a value read from the program it cost the programs without hand-overs
+// 4-5 %: relu, 128x64 planes of 56x56, 55.8 / 58.4 us).
+template <int TM, int V, int U, bool F32W, bool RAG, bool ALIAS>
 __global__ __launch_bounds__(max_threads_for(TM), min_waves_for(TM, V)) void k_chain(const Program) {
     __shared__ __align__(16) unsigned char sprog[sizeof(Program)];
     const Program& pg = stage_program(sprog);
@@ -42,9 +43,8 @@ __global__ __launch_bounds__(max_threads_for(TM), min_waves_for(TM, V)) void k_c
     // LDS: registers (16-byte pieces, see vm_reg_read; the hand-over buffers over them: xadd_alias) | hand-over buffers | persistent floats (float k of pixel v of thread i at [(k * V + v) * threads + i])
     const int rstride = threads * 4;
     float* const Rm = lds + threadIdx.x * 4;
-    const bool alias = vm_u(pg.xadd_alias) != 0;
-    float* const xbase = alias ? lds : lds + vm_u(pg.n_regs) * reg_pieces(U * TM * V) * rstride;
-    float* const Pbase = alias ? lds + vm_u(pg.n_regs) * reg_pieces(U * TM * V) * rstride : xbase + S * xfloats;
+    float* const xbase = ALIAS ? lds : lds + vm_u(pg.n_regs) * reg_pieces(U * TM * V) * rstride;
+    float* const Pbase = ALIAS ? lds + vm_u(pg.n_regs) * reg_pieces(U * TM * V) * rstride : xbase + S * xfloats;
     float* const Pm = Pbase + threadIdx.x;
     const int slice = __builtin_amdgcn_readfirstlane(threadIdx.x / PT);  // (PT is a multiple of 64: uniform in a wavefront)
     float* const xbuf = xbase + slice * xfloats;
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(max_threads_for(TM), min_waves_for(TM, V)) void k_c
                         for (int u = 0; u < U; u++) {
                             __syncthreads();
                             __syncthreads();
-                            if (alias) __syncthreads();
+                            if (ALIAS) __syncthreads();
                         }
                     }
                     continue;
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(max_threads_for(TM), min_waves_for(TM, V)) void k_c
                         vm_xadd_write<TM, V>(g, I, th, st.A + u * TM * V, xbuf);
                         __syncthreads();
                         if (u < ev.h) vm_xadd_gather<TM, V>(g, I, dh, dw, th, xbuf, Pm + u * ev.np * V * threads, threads);
-                        if (alias) __syncthreads();  // (the registers under the buffer may be written again)
+                        if (ALIAS) __syncthreads();  // (the registers under the buffer may be written again)
                     }
                 }
             }
@@ -174,14 +174,24 @@ inline bool f32_windows(const Program& pg) {
     return false;
 }
 
-template <int TM, int V, bool F32W = true, bool RAG = false>
-void launch(const Program& pg, hipStream_t stream) {
+template <int TM, int V, bool F32W, bool RAG, bool ALIAS>
+void launch_as(const Program& pg, hipStream_t stream) {
     constexpr int U = unroll_for(TM, V);
     // (more than 64 KB of dynamic LDS must be asked for, once per kernel)
-    static const hipError_t lds_ok = hipFuncSetAttribute((const void*)k_chain<TM, V, U, F32W, RAG>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLdsBytes);
+    static const hipError_t lds_ok = hipFuncSetAttribute((const void*)k_chain<TM, V, U, F32W, RAG, ALIAS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLdsBytes);
     (void)lds_ok;
     const dim3 grid(grid_for(pg));
-    CANVAS_LAUNCH((k_chain<TM, V, U, F32W, RAG>), grid, dim3((unsigned)pg.threads), lds_bytes(pg), stream, pg);
+    CANVAS_LAUNCH((k_chain<TM, V, U, F32W, RAG, ALIAS>), grid, dim3((unsigned)pg.threads), lds_bytes(pg), stream, pg);
+}
+template <int TM, int V, bool F32W = true, bool RAG = false>
+void launch(const Program& pg, hipStream_t stream) {
+    if constexpr (TM > 1) {
+        if (pg.xadd_alias) {
+            launch_as<TM, V, F32W, RAG, true>(pg, stream);
+            return;
+        }
+    }
+    launch_as<TM, V, F32W, RAG, false>(pg, stream);
 }
 
 }  // namespace

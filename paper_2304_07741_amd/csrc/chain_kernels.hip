@@ -23,13 +23,8 @@ void run(const Program& pg, hipStream_t stream) {
         else if (v == 4) launch<1, 4, false>(pg, stream);
         else if (v == 2) launch<1, 2, false>(pg, stream);
         else launch<1, 1, false>(pg, stream);
-    } else if (pg.tm <= 9) {
-        if (v == 4) launch<9, 4>(pg, stream);
-        else if (v == 2 && f32_windows(pg)) launch<9, 2>(pg, stream);
-        else if (v == 2) launch<9, 2, false>(pg, stream);
-        else launch<9, 1>(pg, stream);
     } else {
-        launch<25, 1>(pg, stream);
+        run_taps(pg, stream);
     }
 }
 

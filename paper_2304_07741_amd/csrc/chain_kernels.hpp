@@ -48,6 +48,7 @@ constexpr size_t kMaxLdsBytes = 144 * 1024;  // of the 160 KB of a compute unit 
 
 // Enqueues the program; every pointer of pg.ext must be set.  pg.tm must be 1, 9 or 25, pg.vec one of max_vec_for's.
 void run(const Program& pg, hipStream_t stream);
+void run_taps(const Program& pg, hipStream_t stream);      // programs with taps
 void run_streamed(const Program& pg, hipStream_t stream);  // programs with OP_LDFOLD
 void run_ragged(const Program& pg, hipStream_t stream);  // where pg.vec does not divide the plane
 

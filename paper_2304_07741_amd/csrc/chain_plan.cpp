@@ -987,7 +987,7 @@ double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
     pg.xadd_lanes = 0;
     for (int i = 0; i < pg.n_instr; i++)
         if (pg.ins[i].op == OP_XADD) pg.xadd_lanes = std::max<int>(pg.xadd_lanes, pg.ins[i].T);
-    if (pg.xadd_lanes == 0 || (int64_t)pg.n_regs * reg_pieces_of(pg.tm, 1) * 4 < pg.xadd_lanes) pg.xadd_alias = 0;
+    if (pg.tm == 1 || pg.xadd_lanes == 0 || (int64_t)pg.n_regs * reg_pieces_of(pg.tm, 1) * 4 < pg.xadd_lanes) pg.xadd_alias = 0;
     const int HW = dag.H * dag.W;
     // (a program that makes one trip keeps its registers' LDS: floats that no channel has for itself exist once.  The other
     // programs' workgroups were weighed with a copy per channel of the trip, and the estimate errs without them: softmax over
