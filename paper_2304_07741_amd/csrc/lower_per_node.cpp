@@ -98,11 +98,18 @@ const void* bound(const Binding& b, const RunArgs& a) {
     }
 }
 
-// Whether the unit is a softmax over channels and nothing else, which has kernels of its own.
+// Whether the unit is a softmax over channels, behind up to two unaries of its input, and nothing else, which has kernels of its own.
 bool softmax_of_channels(const Dag& dag, const Unit& U, smc::Params& P) {
-    if (U.nodes.size() != 1) return false;
-    const Node& nd = dag.nodes[U.nodes[0]];
-    return nd.op == Op::Softmax && nd.kind == kAxisC && nd.T == 1 && dag.nodes[nd.a].T == 1 && smc::plan(P, dag.N, nd.C, dag.H * dag.W);
+    const int n = (int)U.nodes.size();
+    if (n > 3 || U.plan.inputs.size() != 1 || U.plan.outputs != std::vector<int>{U.nodes.back()}) return false;
+    for (int i = 0; i < n; i++) {  // (a path: each node reads the one before it)
+        const Node& nd = dag.nodes[U.nodes[i]];
+        if (nd.a != (i ? U.nodes[i - 1] : U.plan.inputs[0]) || nd.T != 1) return false;
+        if (i == n - 1) return nd.op == Op::Softmax && nd.kind == kAxisC && dag.nodes[nd.a].T == 1 && smc::plan(P, dag.N, nd.C, dag.H * dag.W);
+        if (nd.op != Op::Unary || (nd.kind != kRelu && nd.kind != kAbs && nd.kind != kGelu)) return false;
+        P.before[P.n_before++] = nd.kind;
+    }
+    return false;
 }
 
 // Whether the unit is y = x (*|+) shift(act(x)) of one tensor and nothing else: an activation and shifts of disjoint channel slices in any order

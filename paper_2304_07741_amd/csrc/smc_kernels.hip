@@ -10,6 +10,7 @@
 
 #include "launch.hpp"
 #include "tile_util.hpp"
+#include "ufc_device.hpp"
 
 namespace canvas {
 namespace smc {
@@ -74,6 +75,23 @@ __device__ __forceinline__ void store(void* p, int64_t e, float (&v)[V], bool ac
     }
 }
 
+// act(x) and, where wanted, act'(x), for a uniform kind
+template <bool GRAD>
+__device__ __forceinline__ float unary(int kind, bool fast, float x, float& d) {
+    if (kind == 2) {
+        if (fast) {
+            float cdf, pdf;
+            ufc::normal_parts(x, cdf, pdf);
+            if (GRAD) d = cdf + x * pdf;
+            return x * cdf;
+        }
+        if (GRAD) d = unary_grad(2, x, 0.f, 0.f);
+        return unary_apply(2, x, 0.f, 0.f);
+    }
+    if (GRAD) d = x > 0.f ? 1.f : (x < 0.f && kind == 1 ? -1.f : 0.f);
+    return kind == 0 ? __builtin_fmaxf(x, 0.f) : fabsf(x);
+}
+
 template <int V, int CPT, bool XF, bool GF, bool OF, bool BWD>
 __global__ __launch_bounds__(1024) void k_softmax_c(Params P) {
     extern __shared__ __align__(16) float lds[];  // [slices][2][64 * V], backward: [slices][64 * V] more
@@ -90,6 +108,15 @@ __global__ __launch_bounds__(1024) void k_softmax_c(Params P) {
     if constexpr (BWD) {
 #pragma unroll
         for (int k = 0; k < CPT; k++) load<V, GF>(P.dy, base + (int64_t)min(k, nc - 1) * P.P, g[k]);
+    }
+#pragma unroll 1
+    for (int i = 0; i < P.n_before; i++) {
+        const int kind = P.before[i];
+        float unused;
+#pragma unroll
+        for (int k = 0; k < CPT; k++)
+#pragma unroll
+            for (int v = 0; v < V; v++) x[k][v] = unary<false>(kind, P.fast, x[k][v], unused);
     }
     // maximum and sum of this thread's channels, then of all
     float m[V], z[V];
@@ -166,6 +193,22 @@ __global__ __launch_bounds__(1024) void k_softmax_c(Params P) {
 #pragma unroll
                 for (int v = 0; v < V; v++) x[k][v] = x[k][v] * (g[k][v] - dot[v]);
             }
+        if (P.n_before > 0) {  // (x once more: from the caches)
+#pragma unroll
+            for (int k = 0; k < CPT; k++) load<V, XF>(P.x, base + (int64_t)min(k, nc - 1) * P.P, g[k]);
+#pragma unroll 1
+            for (int i = 0; i < P.n_before; i++) {
+                const int kind = P.before[i];
+#pragma unroll
+                for (int k = 0; k < CPT; k++)
+#pragma unroll
+                    for (int v = 0; v < V; v++) {
+                        float d;
+                        g[k][v] = unary<true>(kind, P.fast, g[k][v], d);
+                        x[k][v] *= d;
+                    }
+            }
+        }
     }
     if (!in) return;
 #pragma unroll

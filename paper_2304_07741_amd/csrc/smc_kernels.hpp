@@ -1,4 +1,4 @@
-// Softmax over the channels of a tensor without taps (Canvas paper, Section 5: Softmax), forward and backward, each tensor in bf16 or fp32.
+// Softmax over the channels of a tensor without taps, behind up to two unaries (Canvas paper, Section 5), forward and backward, each tensor in bf16 or fp32.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -13,6 +13,7 @@ struct Params {
     void* out = nullptr;       // the result, or dx
     int x_f32 = 0, dy_f32 = 0, out_f32 = 0;
     int acc = 0;               // backward, fp32 dx: added to what is there
+    int n_before = 0, before[2] = {0, 0};  // unaries of x before the softmax, in their order: relu 0, abs 1 or gelu 2
     int fast = 0;              // exponential and reciprocal by the hardware's instructions (micro-DAGs in bf16)
     int N = 0, C = 0, P = 0;
     int vec = 1, cpt = 8, slices = 1, tiles = 1;  // pixels and channels per thread, wavefronts that share the channels, pixel tiles of a plane

@@ -44,6 +44,19 @@ def test_between_units(oracle, body, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("ops", [["relu"], ["gelu"], ["abs", "gelu"], ["gelu", "relu"], ["sin"], ["abs", "abs", "gelu"]], ids="_".join)
+def test_behind_unaries(oracle, ops, dtype):
+    from paper_2304_07741_amd import harness
+
+    body = "".join(f"%{k + 1} = unary %{k} op={op}\n" for k, op in enumerate(ops)) + f"%{len(ops) + 1} = softmax %{len(ops)} axis=C\noutput %{len(ops) + 1}\n"
+    for shape in [(2, 37, 12, 10), (130, 12, 16, 33), (1, 140, 5, 6)]:
+        case = _mk(body, shape, dtype, 1120, [], "softmax_unary")
+        res, r, dy = harness.run_case(case)
+        check_against_oracle(oracle, case, res, dy)
+        r.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_infinities(dtype):
     import torch
 
