@@ -14,8 +14,8 @@ __device__ __forceinline__ unsigned quot(unsigned x, int d, uint32_t magic) { re
 // Sum of `segs` ranges of partials for VEC consecutive elements per thread.  A launch of this kernel is bound by the round trips of a
 // thread and by the number of workgroups that have to be started (13 000 of them took 20-35 us for 19 MB), not by the bytes: a
 // thread loads sixteen partials at once, four elements wide where there are enough of them, and a sum has no more segments than
-// that takes (plan).  With one element per thread and 8 segments, 2 below 32 partials: 32 partials of 65 K and of 74 K elements 7.2 us, now 5.9; 8 of
-// 262 K and of 295 K 8.4 / 5.9; 256 of 4 K and 228 of 9 K 7.0 / 6.1.
+// that takes (plan).  With one element per thread and 8 segments, 2 below 32 partials: 32 partials of 65 K and of 74 K elements 7.2 us, now 5.5; 8 of
+// 262 K and of 295 K 8.4 / 5.6; 256 of 4 K and 228 of 9 K 7.0 / 6.1.
 // The padding of the packed layout (whose element order differs from dw: the tap is innermost there) is skipped and the
 // small result is written scattered.
 // Order of the sum of one element: the partials of a segment in ascending blocks of sixteen and four, then the segments in
@@ -92,8 +92,9 @@ __global__ __launch_bounds__(256) void k_reduce(Jobs jobs) {
 }  // namespace
 
 void plan(Job& job) {
-    // four elements per thread from 32 K elements on (16-byte loads, a quarter of the workgroups; fewer elements do not fill the chip so)
-    job.vec = job.count >= 32768 && job.count % 4 == 0 ? 4 : 1;
+    // four elements per thread from 128 K elements on: 16-byte loads and a quarter of the workgroups (one / four per thread, 8 partials of 262 K and 295 K elements 6.9 / 5.6 us; 32 of
+    // 65 K and 74 K 5.5 / 6.6, 9 of 83 K 4.1 / 4.8: fewer elements do not fill the chip so)
+    job.vec = job.count >= 131072 && job.count % 4 == 0 ? 4 : 1;
     job.segs = 1;
     while (job.segs < 16 && job.slices > 16 * job.segs) job.segs *= 2;
     const unsigned per_wg = 256u / (unsigned)job.segs * (unsigned)job.vec;
