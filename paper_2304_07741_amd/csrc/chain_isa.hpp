@@ -41,7 +41,7 @@ enum Opcode : uint8_t {
     OP_ST,         // ext[a](channel, t, pixel) = A[t] (flag: +=) for pixels the workgroup owns
     OP_UNBX,       // A = R[r] * unary_kind'(A)                         (A: the unary's input, R[r]: gradient)
     OP_BING,       // A = d blend_kind(L, A) / d side, L = R[r]         (A: RHS value, R[r]: LHS value; T lanes)
-    OP_SMTBX,      // A = A * (R[r] - sum_s R[r][s] * A[s])             (A: softmax output, R[r]: gradient)
+    OP_SMTBX,      // A = A * (R[r] - sum_s R[r][s] * A[s])             (A: softmax output, R[r]: gradient; kind 1: the other way round, A = R[r] * (A - ...))
     OP_FOLDBX,     // A[t] = gradient of the fold's input: R[r][0] spread (sum), / T or / f0 where that is set (avg), to the first maximum of A (max)
     OP_PSET,       // P[a + t] = f0
     OP_PADD,       // P[a + t % b] += A[t]
@@ -54,6 +54,7 @@ enum Opcode : uint8_t {
     OP_BINLD,      // A = blend_kind(loaded, A) or (A, loaded): OP_LD and OP_BIN in one, the loaded operand never visits a register
     OP_LDFOLD,     // A = fold over the taps of a window of ext[a], each tap blended with A's own lane or with the tap of a second window: OP_LD ...
                    // OP_FOLD in one, no lane of the window is ever kept (TM = 1)
+    OP_MADD,       // A += R[r] * R[a]  (T lanes, TM > 1; a finished program's OP_MOVR x, OP_MOVA r, OP_BIN product with a, OP_BIN sum with x)
     OP_COUNT
 };
 

@@ -632,7 +632,20 @@ class Emitter {
             break;
         }
         case kSmT: {
-            const int r = to_reg(u, 1, mine);
+            int r = kept(u, 1);
+            if (r < 0) {
+                grad(u);
+                if (kept(u, 0) >= 0) {  // (evaluated on the way: the gradient stays in A)
+                    emit(simple(OP_SMTBX, U.lanes, kept(u, 0), 1));
+                    break;
+                }
+                r = kept(u, 1);
+                if (r < 0) {
+                    mine = true;
+                    r = alloc();
+                    emit(simple(OP_MOVR, U.lanes, r));
+                }
+            }
             eval(u);
             emit(simple(OP_SMTBX, U.lanes, r));
             if (mine) release(r);
@@ -1016,16 +1029,18 @@ double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
             const int per_thread = std::max<int>(1, (int)lds_bytes_per_thread(pg));
             const int cap = (int)(std::min<int64_t>(max_threads_for(pg.tm), (int64_t)kMaxLdsBytes / per_thread) / 64 * 64);
             for (int pt = 64; pt <= cap; pt += 64) {
-                if (2 * HT >= pt) continue;
-                int own = pt - 2 * (int)HT;
-                if (own >= PP) {  // the whole plane in one tile
-                    if (ceil_div(PP + 2 * (int)HT, 64) * 64 != pt) break;  // (counted once, at its own size)
+                int own = pt - 2 * (int)HT, ht = (int)HT;
+                if (pt >= PP) {  // the whole plane in one tile: nothing comes from beside it
+                    if (ceil_div(PP, 64) * 64 != pt) break;  // (counted once, at its own size)
                     own = PP;
+                    ht = 0;
+                } else if (own <= 0) {
+                    continue;
                 } else {
                     own = ceil_div(PP, ceil_div(PP, own));  // tiles evened out over the plane
                 }
                 for (int trips = 1; trips <= (all_channels ? 1 : 8); trips *= 2) {
-                    const double cost = geometry_for(pg, dag, C, all_channels, one_trip, PP, (int)HT, cap, own, pt, trips);
+                    const double cost = geometry_for(pg, dag, C, all_channels, one_trip, PP, ht, cap, own, pt, trips);
                     if (cost >= 0 && (int64_t)dag.N * pg.tiles * pg.chunks <= most_workgroups && (best_cost < 0 || cost < best_cost * 0.999)) {  // (ties: the wider vector, the smaller workgroup, fewer trips)
                         best_cost = cost;
                         best_shape = pg;
@@ -1044,15 +1059,43 @@ double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
 
 }  // namespace
 
+// A sum with a product of two registers, of all taps: one instruction, and a register less while it runs (OP_COUNT: gone).  With the softmax's
+// gradient left in the accumulator (kSmT above) the program below takes three registers instead of four, which lets a workgroup hold
+// a plane of 32x32 whole, two pixels per thread and no halo: 192 -> 109 us.
+void add_products(Program& pg) {
+    for (int p = 0; p < pg.n_pass; p++)
+        for (int i = pg.pass[p].body_begin; i + 3 < pg.pass[p].body_end; i++) {
+            const Instr &keep = pg.ins[i], &get = pg.ins[i + 1], &mul = pg.ins[i + 2], &add = pg.ins[i + 3];
+            if (keep.op != OP_MOVR || get.op != OP_MOVA || mul.op != OP_BIN || add.op != OP_BIN) continue;
+            if (keep.T < 2 || get.T != keep.T || mul.T != keep.T || add.T != keep.T || add.r != keep.r || get.r == keep.r || mul.r == keep.r) continue;
+            if ((mul.kind & ~kBinRegIsLhs) != kMul || (add.kind & ~kBinRegIsLhs) != kAdd) continue;
+            bool read_on = false;  // (what was kept must not be needed again)
+            for (int j = i + 4; j < pg.pass[p].body_end; j++) {
+                const Instr& I = pg.ins[j];
+                if (I.r == keep.r && I.op == OP_MOVR) break;
+                if (I.r == keep.r && I.op != OP_LD && I.op != OP_ST) read_on = true;
+                if (I.op == OP_MADD && I.a == keep.r) read_on = true;
+            }
+            if (read_on) continue;
+            Instr m = get;
+            m.op = OP_MADD;
+            m.kind = 0;
+            m.a = mul.r;
+            pg.ins[i].op = pg.ins[i + 1].op = pg.ins[i + 2].op = OP_COUNT;
+            pg.ins[i + 3] = m;
+        }
+}
+
 // Fewer registers for a finished program: stores that nothing reads go, the others get the lowest register that is free where they stand (a
 // register is as many bytes of LDS per thread as the instance has lanes, and LDS decides how many wavefronts a compute unit holds);
 // where no register holds anything during a hand-over, its buffer takes their place.  Backward of unfold 3x3 -> softmax -> product ->
-// gelu -> sum, 16x96 planes of 32x32: 280 -> 196 bytes per thread, 239 -> 192 us.
+// gelu -> sum, 16x96 planes of 32x32: 280 -> 196 bytes per thread, 239 -> 192 us (with add_products 109).
 // Not for programs that keep registers from pass to pass.
 void compact_registers(Emitter& E) {
     Program& pg = E.pg;
+    if (pg.tm > 1) add_products(pg);
     auto reads = [](const Instr& I) {
-        return I.op == OP_MOVA || I.op == OP_BIN || I.op == OP_UNBX || I.op == OP_BING || I.op == OP_SMTBX || I.op == OP_FOLDBX || I.op == OP_SMCDOT || I.op == OP_SMCBX;
+        return I.op == OP_MADD || I.op == OP_MOVA || I.op == OP_BIN || I.op == OP_UNBX || I.op == OP_BING || I.op == OP_SMTBX || I.op == OP_FOLDBX || I.op == OP_SMCDOT || I.op == OP_SMCBX;
     };
     std::vector<int> last_use(pg.n_instr, -1);  // of a store's value
     for (int p = 0; p < pg.n_pass; p++) {
@@ -1062,6 +1105,10 @@ void compact_registers(Emitter& E) {
             if (reads(I)) {
                 if (!def.count(I.r)) return;  // (a value from elsewhere)
                 last_use[def[I.r]] = i;
+            }
+            if (I.op == OP_MADD) {
+                if (!def.count(I.a)) return;
+                last_use[def[I.a]] = i;
             }
             if (I.op == OP_MOVR) def[I.r] = i;
         }
@@ -1078,6 +1125,7 @@ void compact_registers(Emitter& E) {
         for (int i = pro; i < end; i++) {
             if (i == body) P.pro_end = P.body_begin = (uint16_t)n;
             Instr I = pg.ins[i];
+            if (I.op == OP_COUNT) continue;
             if (I.op == OP_MOVR) {
                 if (last_use[i] < 0) continue;
                 int c = 0;
@@ -1088,6 +1136,7 @@ void compact_registers(Emitter& E) {
                 I.r = (uint8_t)c;
             } else if (reads(I)) {
                 I.r = (uint8_t)color[I.r];
+                if (I.op == OP_MADD) I.a = (uint16_t)color[I.a];
             } else if (I.op == OP_XADD) {
                 for (const auto& u : until)
                     if (u.second > i) alias = false;
@@ -1660,7 +1709,7 @@ double program_cost(const Program& pg) {
 
 std::string dump(const Program& pg) {
     static const char* names[] = {"LD", "MASK", "UN", "MOVR", "MOVA", "BIN", "FOLD", "SMT", "ST", "UNBX", "BING", "SMTBX", "FOLDBX",
-                                  "PSET", "PADD", "PLD", "SMCSTAT", "SMCAPPLY", "SMCDOT", "SMCBX", "XADD", "BINLD", "LDFOLD"};
+                                  "PSET", "PADD", "PLD", "SMCSTAT", "SMCAPPLY", "SMCDOT", "SMCBX", "XADD", "BINLD", "LDFOLD", "MADD"};
     std::ostringstream os;
     os << "program: C=" << pg.C << " HxW=" << pg.H << "x" << pg.W << " vec=" << pg.vec << " own=" << pg.own_threads << " halo=" << pg.halo_threads
        << " unroll=" << pg.unroll << " tiles=" << pg.tiles << " chunk=" << pg.chunk << " slices=" << pg.slices << " threads=" << pg.threads << " persist=" << pg.n_persist

@@ -452,6 +452,21 @@ CHAIN_HD void vm_reg_read(const float* Rm, int rstride, int r, int T, float* X) 
         }
     }
 }
+// A += X * R[r], a piece at a time (a second array of lanes would cost the instances with taps wavefronts or scratch)
+template <int TM, int V, int U>
+CHAIN_HD void vm_reg_madd(const float* Rm, int rstride, int r, int T, const float* X, float* A) {
+    constexpr int L = U * TM * V, Q = reg_pieces(L);
+    const float* src = Rm + r * Q * rstride;
+#pragma unroll
+    for (int q = 0; q < Q; q++) {
+        float w[4];
+        memcpy(w, src + q * rstride, 16);
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            if (q * 4 + k < L && (q * 4 + k) % (TM * V) < T * V) A[q * 4 + k] += X[q * 4 + k] * w[k];
+        asm volatile("" ::: "memory");
+    }
+}
 template <int TM, int V, int U>
 CHAIN_HD void vm_reg_write(float* Rm, int rstride, int r, int T, const float* X) {
     constexpr int L = U * TM * V, Q = reg_pieces(L);
@@ -1202,6 +1217,13 @@ CHAIN_HD void vm_exec_lanes(const Program& pg, const Geo& g, const Instr& I, con
         }
         break;
     }
+    case OP_MADD:
+        if constexpr (TM > 1) {
+            CHAIN_CASE;
+            vm_reg_read<TM, V, U>(Rm, rstride, I.r, T, X);
+            vm_reg_madd<TM, V, U>(Rm, rstride, I.a, T, X, A);
+        }
+        break;
     case OP_SMTBX:
         CHAIN_CASE;
         vm_reg_read<TM, V, U>(Rm, rstride, I.r, T, X);
@@ -1217,7 +1239,7 @@ CHAIN_HD void vm_exec_lanes(const Program& pg, const Geo& g, const Instr& I, con
                     if (t < T) dot += Xu[t * V + v] * Au[t * V + v];
 #pragma unroll
                 for (int t = 0; t < TM; t++)
-                    if (t < T) Au[t * V + v] = Au[t * V + v] * (Xu[t * V + v] - dot);
+                    if (t < T) Au[t * V + v] = I.kind ? Xu[t * V + v] * (Au[t * V + v] - dot) : Au[t * V + v] * (Xu[t * V + v] - dot);
             }
         }
         break;
