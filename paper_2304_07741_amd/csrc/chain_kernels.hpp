@@ -25,7 +25,7 @@ inline bool streams_windows(const Program& pg) {
 // Largest workgroup of that instance (the tap vectors of a thread live in registers: wider lanes, fewer threads).
 constexpr int max_threads_for(int) { return 512; }
 // Wavefronts per SIMD that the register allocation of an instance leaves room for (1: no requirement).  The instance with
-// 9 lanes x 2 pixels came out one register above the 128 of four wavefronts; held to them it spills one, stored and read
+// 9 lanes x 2 pixels came out one register above the 128 of four wavefronts; held to them it spills one or two, stored and read
 // back once per work item, outside the channel loop.
 constexpr int min_waves_for(int tm, int vec) { return tm > 1 && tm <= 9 && vec == 2 ? 4 : 1; }
 

@@ -1061,7 +1061,7 @@ double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
 
 // A sum with a product of two registers, of all taps: one instruction, and a register less while it runs (OP_COUNT: gone).  With the softmax's
 // gradient left in the accumulator (kSmT above) the program below takes three registers instead of four, which lets a workgroup hold
-// a plane of 32x32 whole, two pixels per thread and no halo: 192 -> 109 us.
+// a plane of 32x32 whole, two pixels per thread and no halo: 192 -> 109 us (97 with the gather of two pixels in registers).
 void add_products(Program& pg) {
     for (int p = 0; p < pg.n_pass; p++)
         for (int i = pg.pass[p].body_begin; i + 3 < pg.pass[p].body_end; i++) {
@@ -1089,7 +1089,7 @@ void add_products(Program& pg) {
 // Fewer registers for a finished program: stores that nothing reads go, the others get the lowest register that is free where they stand (a
 // register is as many bytes of LDS per thread as the instance has lanes, and LDS decides how many wavefronts a compute unit holds);
 // where no register holds anything during a hand-over, its buffer takes their place.  Backward of unfold 3x3 -> softmax -> product ->
-// gelu -> sum, 16x96 planes of 32x32: 280 -> 196 bytes per thread, 239 -> 192 us (with add_products 109).
+// gelu -> sum, 16x96 planes of 32x32: 280 -> 196 bytes per thread, 239 -> 192 us (97 with add_products).
 // Not for programs that keep registers from pass to pass.
 void compact_registers(Emitter& E) {
     Program& pg = E.pg;

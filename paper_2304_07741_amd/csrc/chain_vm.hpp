@@ -1468,6 +1468,29 @@ CHAIN_HD float vm_xadd_window(const Geo& g, int KH, int KW, int T, int dh, int d
     return sum;
 }
 
+// The same for a 3x3 window and V pixels per thread: summed in registers (the general gather below adds every tap to P, in LDS, each behind the last: backward
+// of unfold 3x3 -> softmax -> product -> gelu -> sum, 16x96 planes of 32x32, 109 us, now 97).
+template <int TM, int V>
+CHAIN_HD void vm_xadd_window3(const Geo& g, int dh, int dw, const Thread& th, const float* buf, float (&sum)[V]) {
+#pragma unroll
+    for (int v = 0; v < V; v++) sum[v] = 0.f;
+#pragma unroll
+    for (int t = 0; t < 9; t++) {
+        int oh, ow;
+        vm_tap(t, 3, 3, oh, ow);
+        oh += dh;
+        ow += dw;
+        const uint32_t m = th.own ? vm_valid<V>(g, th, -oh, -ow) : 0u;
+        const int at = th.ptid * V - (oh * g.W + ow);
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            const bool ok = (m >> v) & 1u;
+            const float x = buf[t * g.npx + (ok ? at + v : th.ptid * V)];
+            sum[v] += ok ? x : 0.f;
+        }
+    }
+}
+
 // OP_XADD of channel u, second half (after a barrier): P[a (+ t)] of every pixel of the thread collects lane t of the
 // pixel whose load at offset (dh, dw) [+ window tap t] read it, if that pixel is inside the image and inside the pixels
 // the slice computes (the planner sizes the halo so that an owned pixel never misses one).  Fixed order: deterministic.
@@ -1482,6 +1505,16 @@ CHAIN_HD void vm_xadd_gather(const Geo& g, const Instr& I, int dh, int dw, const
         else sum = vm_xadd_window<TM, 0, 0>(g, KH, KW, T, dh, dw, th, buf);
         if (th.own) Pu[I.a * pstride] += sum;
         return;
+    }
+    if constexpr (V == 2 && TM >= 9) {
+        if ((I.kind & kWin) && !(I.kind & kExtTaps) && I.r == 0x33 && I.T == 9) {
+            float sum[V];
+            vm_xadd_window3<TM, V>(g, dh, dw, th, buf, sum);
+#pragma unroll
+            for (int v = 0; v < V; v++)
+                if (th.own) Pu[(I.a * V + v) * pstride] += sum[v];
+            return;
+        }
     }
 #pragma unroll
     for (int t = 0; t < TM; t++)
