@@ -29,8 +29,6 @@ constexpr int kGuard = 8;   // LDS slots on either side of the tile that pieces 
 constexpr int kMaxBatch = 4;  // source pieces (4 rows x 8 pixels) per thread
 constexpr int kAhead = 4;   // contraction steps whose weights are in flight
 
-__device__ __forceinline__ int div_magic(int x, uint32_t magic) { return magic ? (int)__umulhi((uint32_t)x, magic) : x; }
-
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 extern __shared__ __align__(16) unsigned char lds_src[];
@@ -49,8 +47,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_fc(Params P, std::conditional_t
     const int wo = wave % WO, wp = wave / WO;
     const int r = lane >> 4, s = lane & 15;
     const int seq = (int)xcd_sequence();
-    const int t2 = div_magic(seq, P.magicOgroups), og = seq - t2 * P.ogroups;
-    const int gmi = div_magic(t2, P.magicTiles), tile = t2 - gmi * P.tiles;
+    const Place at_tile = place_of(P, seq);
+    const int gmi = at_tile.gmi, tile = at_tile.tile, og = at_tile.og;
     const int gcount = min(P.gm, P.G - gmi * P.gm);
     const int Rm = gcount * P.R, Om = gcount * P.Og;
     const int rows_img = P.G * P.R, outs_img = P.G * P.Og;
@@ -61,7 +59,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fc(Params P, std::conditional_t
     const int WS = P.W + HW;  // slots of an image row
     const int total_units = P.N * P.upi;
     // the tile of a window: rows [h0, h0 + TH) of images [n0, n0 + J); the pixels of an image begin at `first` in LDS
-    const int tg = KW > 1 ? div_magic(tile, P.magicRowTiles) : 0;
+    const int tg = KW > 1 ? (int)div_magic((uint32_t)tile, P.magicRowTiles) : 0;
     const int h0 = KW > 1 ? (tile - tg * P.row_tiles) * P.TH : 0, n0 = tg * P.J;
     const int first = KW > 1 && P.J == 1 ? (h0 - HW) * P.W : 0;
     const int skip = KW > 1 && P.J > 1 ? HW * P.W : 0;  // (several images: the rows around them are not loaded, but cleared)
@@ -80,7 +78,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fc(Params P, std::conditional_t
         bool in;
         if constexpr (KW == 1) {
             const int U = tile * P.units_in + u;
-            n = div_magic(U, P.magicUpi);
+            n = (int)div_magic((uint32_t)U, P.magicUpi);
             q = (U - n * P.upi) * 8;
             if (quad < P.quads) at[b] = u * 8 * pitch + quad * 8;
             in = U < total_units;
@@ -90,7 +88,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fc(Params P, std::conditional_t
             q = ((first >> 3) + uu) * 8;
             in = n < P.N && q >= 0 && q < P.P;
             const int rel = q - first + skip;  // -7 at least
-            const int h = rel < 0 ? -1 : div_magic(rel, P.magicW);
+            const int h = rel < 0 ? -1 : (int)div_magic((uint32_t)rel, P.magicW);
             col[b] = rel - h * P.W;
             if (quad < P.quads && uu < P.units_img && j < P.J && rel < (P.TH + 2 * HW) * P.W)
                 at[b] = (kGuard + HW + j * P.SI + h * WS + col[b]) * pitch + quad * 8;
@@ -182,7 +180,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fc(Params P, std::conditional_t
 #pragma unroll
     for (int k = 0; k < NP; k++) {
         const int x = (wp * NP + k) * 4 + (s >> 2);
-        int j = KW > 1 && P.J > 1 ? div_magic(x, P.magicUnits) : 0;
+        int j = KW > 1 && P.J > 1 ? (int)div_magic((uint32_t)x, P.magicUnits) : 0;
         const int pu = KW > 1 ? (x - j * P.units_out) * 8 : 0;
         if (KW > 1 && j >= P.J) j = 0;
 #pragma unroll
@@ -193,7 +191,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fc(Params P, std::conditional_t
             } else {
                 int px = pu + e;
                 if (px >= P.TH * P.W) px = 0;
-                const int h = div_magic(px, P.magicW);
+                const int h = (int)div_magic((uint32_t)px, P.magicW);
                 ab[2 * k + t] = (kGuard + HW + j * P.SI + (h + HW) * WS + px - h * P.W) * pitch + (TP == 2 ? r & 1 : r) * 16;
             }
         }
@@ -214,11 +212,11 @@ __global__ __launch_bounds__(kThreads, 2) void k_fc(Params P, std::conditional_t
         int n, p;
         if constexpr (KW == 1) {
             const int U = tile * P.units_in + x;
-            n = div_magic(U, P.magicUpi);
+            n = (int)div_magic((uint32_t)U, P.magicUpi);
             p = (U - n * P.upi) * 8;
             left[k] = U < total_units ? P.P - p : 0;
         } else {
-            const int j = P.J > 1 ? div_magic(x, P.magicUnits) : 0, pu = (x - j * P.units_out) * 8;
+            const int j = P.J > 1 ? (int)div_magic((uint32_t)x, P.magicUnits) : 0, pu = (x - j * P.units_out) * 8;
             n = n0 + j;
             p = h0 * P.W + pu;
             left[k] = j < P.J && n < P.N ? min(P.TH, P.H - h0) * P.W - pu : 0;

@@ -6,8 +6,6 @@
 namespace canvas {
 namespace gfcst {
 
-uint32_t magic(int d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + (uint64_t)d - 1) / (uint64_t)d); }
-
 static int log2_up(int x) {
     int l = 0;
     while ((1 << l) < x) l++;
@@ -71,12 +69,12 @@ bool plan_as(Params& P, int KW, int mo, int wo, int np) {
     const int items = (P.quads + (1 << P.qshift) - 1) >> P.qshift << (P.qshift + P.ushift + 2);
     P.batches = (items + kThreads - 1) / kThreads;
     if (P.batches > kMaxBatch) return false;
-    P.magicOgroups = magic(P.ogroups);
-    P.magicTiles = magic(P.tiles);
-    P.magicUpi = magic(P.upi);
-    P.magicW = magic(P.W);
-    P.magicRowTiles = magic(P.row_tiles);
-    P.magicUnits = magic(P.units_out);
+    P.magicOgroups = magic_u32((uint32_t)P.ogroups);
+    P.magicTiles = magic_u32((uint32_t)P.tiles);
+    P.magicUpi = magic_u32((uint32_t)P.upi);
+    P.magicW = magic_u32((uint32_t)P.W);
+    P.magicRowTiles = magic_u32((uint32_t)P.row_tiles);
+    P.magicUnits = magic_u32((uint32_t)P.units_out);
     return true;
 }
 

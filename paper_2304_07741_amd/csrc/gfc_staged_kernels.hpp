@@ -6,6 +6,7 @@
 #include <cstdint>
 
 #include "gfc_tm_kernels.hpp"
+#include "magic.hpp"
 #include "ufc_kernels.hpp"
 
 namespace canvas {
@@ -30,6 +31,18 @@ struct Params {
     uint32_t magicOgroups = 0, magicTiles = 0, magicUpi = 0, magicW = 0, magicRowTiles = 0, magicUnits = 0;
 };
 
+// What workgroup number `seq` works on: outputs fastest, then pixel tiles, then merged groups.  (Pixel tiles and workgroups are not limited by
+// gfctm::supported as units, image rows and pixels of a plane are: from 2^16 tiles on their products pass 2^32.)
+struct Place {
+    int gmi, tile, og;
+};
+__host__ __device__ inline Place place_of(const Params& P, int seq) {
+    Place at;
+    const int t2 = div_magic(seq, P.ogroups, P.magicOgroups, at.og);
+    at.gmi = div_magic(t2, P.tiles, P.magicTiles, at.tile);
+    return at;
+}
+
 // Whether the contraction of T (a source in bf16) runs here, and with which tile; sets everything but the pointers.
 bool plan(Params& P, const gfctm::Params& T, bool dst_f32, bool adds, bool softmax);
 inline int64_t packed_elems(const Params& P) { return (int64_t)P.Gm * P.Omp * P.steps * 32; }
@@ -40,7 +53,6 @@ void forward(const Params& P, hipStream_t s);
 bool takes_middle(const Params& P, bool adjoint, int act);
 void forward_with_middle(const Params& P, const ufc::MidParams& M, hipStream_t s);  // M: x, v
 void dgrad_with_middle(const Params& P, const ufc::MidParams& M, hipStream_t s);    // M: x, z, dz, dx1
-uint32_t magic(int d);  // multiplier of an exact division by d
 bool plan_as(Params& P, int KW, int mo, int wo, int np);  // the tile `mo, wo, np`, or false where it does not fit
 
 }  // namespace gfcst

@@ -13,8 +13,8 @@
 
 #include <algorithm>
 
-#include "gfc_staged_kernels.hpp"
 #include "launch.hpp"
+#include "magic.hpp"
 #include "tile_util.hpp"
 
 namespace canvas {
@@ -27,7 +27,6 @@ using namespace canvas::tile;
 constexpr int kWaves = 8, kThreads = 64 * kWaves;
 constexpr int MT = 2;                   // a workgroup's tile: 16 MT outputs x 16 MT rows x 9 taps
 constexpr int KS = kWaves / (2 * MT);   // wavefronts that share a tile and split its contraction steps
-__device__ __forceinline__ int div_magic(int x, uint32_t magic) { return magic ? (int)__umulhi((uint32_t)x, magic) : x; }
 
 constexpr int items_for(int U) { return 2 / U; }  // image rows of either tensor per thread and step
 
@@ -42,9 +41,9 @@ __global__ __launch_bounds__(kThreads, 2) void k_wgrad_taps(Params P) {
     const int nk = wave % MT, th = wave / MT & 1, kq = wave / (2 * MT);  // row tile; taps 0-4 or 5-8; share of the contraction steps
     const int ot = P.Omp / (16 * MT), kt = P.Rp / (16 * MT), tiles = P.Gm * ot * kt;
     const int seq = (int)xcd_sequence();
-    const int slice = div_magic(seq, P.magicTiles), t2 = seq - slice * tiles;
-    const int gmi = div_magic(t2, P.magicGroup), t3 = t2 - gmi * (ot * kt);
-    const int oi = div_magic(t3, P.magicKt), o0 = oi * 16 * MT, k0 = (t3 - oi * kt) * 16 * MT;
+    const int slice = (int)div_magic((uint32_t)seq, P.magicTiles), t2 = seq - slice * tiles;
+    const int gmi = (int)div_magic((uint32_t)t2, P.magicGroup), t3 = t2 - gmi * (ot * kt);
+    const int oi = (int)div_magic((uint32_t)t3, P.magicKt), o0 = oi * 16 * MT, k0 = (t3 - oi * kt) * 16 * MT;
     const int gcount = min(P.gm, P.G - gmi * P.gm);
     const int Rm = gcount * P.R, Om = gcount * P.Og;
     const int src_img = P.G * P.R * P.P, dy_img = P.G * P.Og * P.P;
@@ -57,15 +56,15 @@ __global__ __launch_bounds__(kThreads, 2) void k_wgrad_taps(Params P) {
 #pragma unroll
     for (int i = 0; i < NI; i++) {
         const int it = tid + i * kThreads;
-        int c = div_magic(it, P.magicRx), y = it - c * P.rx;
-        xj[i] = P.J > 1 ? div_magic(y, P.magicH) : 0;
+        int c = (int)div_magic((uint32_t)it, P.magicRx), y = it - c * P.rx;
+        xj[i] = P.J > 1 ? (int)div_magic((uint32_t)y, P.magicH) : 0;
         xh[i] = P.J > 1 ? y - xj[i] * P.H : y - 1;
         xat[i] = c < 16 * MT ? (c * P.xu + (P.J > 1 ? xj[i] * (P.H + 1) + 1 + xh[i] : y) * U) * 16 : -1;
         if (c >= 16 * MT || k0 + c >= Rm) xj[i] = P.N;
         xe[i] = (gmi * P.gm * P.R + k0 + c) * P.P + xj[i] * src_img + xh[i] * P.W;
-        c = div_magic(it, P.magicRd);
+        c = (int)div_magic((uint32_t)it, P.magicRd);
         y = it - c * P.rd;
-        dj[i] = P.J > 1 ? div_magic(y, P.magicH) : 0;
+        dj[i] = P.J > 1 ? (int)div_magic((uint32_t)y, P.magicH) : 0;
         dh[i] = P.J > 1 ? y - dj[i] * P.H : y;
         dat[i] = c < 16 * MT ? 3 * copy + (c * P.du + (P.J > 1 ? dj[i] * (P.H + 1) + dh[i] : y) * U) * 16 : -1;
         if (c >= 16 * MT || o0 + c >= Om) dj[i] = P.N;
@@ -80,7 +79,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_wgrad_taps(Params P) {
         int xm[NI], dm[NI];  // by how many pixels the last unit moves
     };
     auto issue = [&](int step, Rows& v) {
-        const int g = P.J > 1 ? step : div_magic(step, P.magicRowTiles);
+        const int g = P.J > 1 ? step : (int)div_magic((uint32_t)step, P.magicRowTiles);
         const int n0 = g * P.J, h0 = P.J > 1 ? 0 : (step - g * P.row_tiles) * P.TH;
         const bool live = step < end;
 #pragma unroll
@@ -297,13 +296,13 @@ bool plan(Params& P, const gfctm::Params& T) {
     // 128x512x7x7; the sum of the partials took 1 us less)
     int64_t slices = std::max<int64_t>(1, std::min<int64_t>(steps, (256 + tiles - 1) / tiles));
     slices = std::max<int64_t>(1, std::min<int64_t>(slices, ((int64_t)10 << 20) / (packed * 4)));
-    P.magicTiles = gfcst::magic((int)tiles);  // (all quotients are exact: indices times divisors stay below 2^32)
-    P.magicGroup = gfcst::magic((P.Omp / ch) * (P.Rp / ch));
-    P.magicKt = gfcst::magic(P.Rp / ch);
-    P.magicRx = gfcst::magic(P.rx);
-    P.magicRd = gfcst::magic(P.rd);
-    P.magicH = gfcst::magic(P.H);
-    P.magicRowTiles = gfcst::magic(P.row_tiles);
+    P.magicTiles = magic_u32((uint32_t)tiles);  // (all quotients are exact: indices times divisors stay below 2^32)
+    P.magicGroup = magic_u32((uint32_t)((P.Omp / ch) * (P.Rp / ch)));
+    P.magicKt = magic_u32((uint32_t)(P.Rp / ch));
+    P.magicRx = magic_u32((uint32_t)P.rx);
+    P.magicRd = magic_u32((uint32_t)P.rd);
+    P.magicH = magic_u32((uint32_t)P.H);
+    P.magicRowTiles = magic_u32((uint32_t)P.row_tiles);
     P.steps = (int)steps;
     P.per_slice = (int)((steps + slices - 1) / slices);
     P.slices = (int)((steps + P.per_slice - 1) / P.per_slice);
