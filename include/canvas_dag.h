@@ -187,7 +187,8 @@ int canvas_dag_forward(canvas_dag* dag, const void* x, const void* const* weight
  * All calls on one GPU, of any plan, share the one array: calls that overlap on a GPU (different streams
  * or host threads) race; calls enqueued on one stream are ordered and safe.
  * Errors: WORKSPACE_TOO_SMALL when the plan's workspace_bytes, without the room a single fp32 fc keeps for overlapping
- * tensors unless they do overlap, exceeds CANVAS_STATIC_WORKSPACE_BYTES (nothing is launched), BAD_ARG, HIP_ERROR. */
+ * tensors unless they do overlap, and without the partial sums of weight gradients of CANVAS_FAMILY_FC_GATE_FC and
+ * CANVAS_FAMILY_PIXEL_WEIGHTS, exceeds CANVAS_STATIC_WORKSPACE_BYTES (nothing is launched), BAD_ARG, HIP_ERROR. */
 #define CANVAS_STATIC_WORKSPACE_BYTES (64u << 20)
 int canvas_dag_forward_static(canvas_dag* dag, const void* x, const void* const* weights, void* y, void* stream);
 

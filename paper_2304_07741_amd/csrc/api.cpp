@@ -213,7 +213,7 @@ int canvas_dag_forward_static(canvas_dag* dag, const void* x, const void* const*
                                                        std::to_string((uint64_t)CANVAS_STATIC_WORKSPACE_BYTES) +
                                                        ": use canvas_dag_forward with a workspace of the caller");
     };
-    const uint64_t need = dag->low->ws_bytes - dag->low->stage_bytes;
+    const uint64_t need = dag->low->ws_bytes - dag->low->stage_bytes - dag->low->partial_bytes;
     if (need > (uint64_t)CANVAS_STATIC_WORKSPACE_BYTES) return too_small(need);
     void* ws = nullptr;
     int rc = static_scratch_of_current_device(&ws);
@@ -227,7 +227,7 @@ int canvas_dag_forward_static(canvas_dag* dag, const void* x, const void* const*
     a.y = y;
     a.ws = (char*)ws;
     a.stream = (hipStream_t)stream;
-    if (dag->low->ws_bytes > (uint64_t)CANVAS_STATIC_WORKSPACE_BYTES && dag->low->fwd_staged(a)) return too_small(dag->low->ws_bytes);
+    if (dag->low->stage_bytes > 0 && dag->low->ws_bytes > (uint64_t)CANVAS_STATIC_WORKSPACE_BYTES && dag->low->fwd_staged(a)) return too_small(dag->low->ws_bytes);
     (void)hipGetLastError();
     // an inference plan keeps its weight-only launches apart: here they run with every call, as the static
     // workspace is shared by all plans and calls on this GPU and keeps nothing between them

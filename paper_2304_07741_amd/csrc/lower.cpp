@@ -8,6 +8,13 @@ namespace canvas {
 
 constexpr int64_t kMinWeightElemsForBf16Intermediates = 16;
 
+// With the partial sums of the weight gradients at the end of the workspace: a forward call on the library's static one has no use for them.
+template <typename F>
+static std::unique_ptr<Lowering> partials_last(F lower_with) {
+    const std::unique_ptr<Lowering> l = lower_with((uint64_t)0);
+    return l ? lower_with(l->ws_bytes - l->partial_bytes) : nullptr;
+}
+
 std::unique_ptr<Lowering> lower(const Dag& full, bool bf16, bool no_fusion, bool inference) {
     const Dag dag = without_dead_views(full);
     std::unique_ptr<Lowering> l;
@@ -23,8 +30,8 @@ std::unique_ptr<Lowering> lower(const Dag& full, bool bf16, bool no_fusion, bool
             const Node& A = dag.nodes[f.a];
             if (f.live && (int64_t)f.out * (A.C / f.groups) * A.T < kMinWeightElemsForBf16Intermediates) tiny_weight = true;
         }
-        if (!l && !tiny_weight) l = lower_ufc(dag, bf16);
-        if (!l && !tiny_weight) l = lower_dyn(dag, bf16);
+        if (!l && !tiny_weight) l = partials_last([&](uint64_t at) { return lower_ufc(dag, bf16, at); });
+        if (!l && !tiny_weight) l = partials_last([&](uint64_t at) { return lower_dyn(dag, bf16, at); });
     }
     if (!l) l = lower_per_node(dag, bf16, !no_fusion, inference);
     batch_weight_jobs(*l);

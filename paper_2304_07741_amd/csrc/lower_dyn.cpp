@@ -17,7 +17,7 @@
 
 namespace canvas {
 
-std::unique_ptr<Lowering> lower_dyn(const Dag& dag, bool bf16) {
+std::unique_ptr<Lowering> lower_dyn(const Dag& dag, bool bf16, uint64_t partials_at) {
     if (!bf16) return nullptr;
     const int n = (int)dag.nodes.size();
     for (int k = 0; k < n; k++)
@@ -98,6 +98,12 @@ std::unique_ptr<Lowering> lower_dyn(const Dag& dag, bool bf16) {
         off += align_up(bytes);
         return (int64_t)o;
     };
+    uint64_t at = partials_at;
+    const TakeFn take_partials = [&at](uint64_t bytes) {
+        const uint64_t o = at;
+        at += align_up(bytes);
+        return (int64_t)o;
+    };
     const double act = 2.0 * dag.numel(0), outb = 2.0 * dag.numel(dag.out), ab = 4.0 * dag.N * TVa * Pn;
     const int64_t ol = take((uint64_t)ab), oa = isoft >= 0 ? take((uint64_t)ab) : ol;  // logits, softmax output (fp32)
     const int64_t ou = take((uint64_t)act), odu = take((uint64_t)act);
@@ -134,7 +140,7 @@ std::unique_ptr<Lowering> lower_dyn(const Dag& dag, bool bf16) {
             [](const RunArgs& a) { return (const void*)a.y; }, false, act + outb + 2.0 * nw2, fl2);
 
     // backward (forward must have run with the same workspace: a and u are read back)
-    emit_wgrad(*low, dag, take, "dyn_fc2_wgrad", G2, C / G2, 1, 1, O2 / G2, w2, FcOperand{ws_at(ou), false}, in_dy, act + outb, fl2);
+    emit_wgrad(*low, dag, take_partials, "dyn_fc2_wgrad", G2, C / G2, 1, 1, O2 / G2, w2, FcOperand{ws_at(ou), false}, in_dy, act + outb, fl2);
     emit_fc(*low, true, dag, take, "dyn_fc2_dgrad", G2, O2 / G2, 1, 1, C / G2, true, w2, in_dy, ws_at(odu), false, act + outb + 2.0 * nw2, fl2);
     low->bwd.push_back({"dyn_apply_dx_da", 3.0 * act + 2.0 * ab, 2.0 * fld, [=](const RunArgs& a) {
                             dyn::Params Q = D;
@@ -150,12 +156,13 @@ std::unique_ptr<Lowering> lower_dyn(const Dag& dag, bool bf16) {
                                 ref::softmax_bwd((const float*)(a.ws + oa), (const float*)(a.ws + oda), (float*)(a.ws + odl), N, TVa, 1, Pn, 1, 0,
                                                  a.stream, (uint16_t*)(a.ws + odl16));
                             }});
-    emit_wgrad(*low, dag, take, "dyn_fc1_wgrad", G1, C / G1, 1, 1, TVa / G1, w1, in_x, FcOperand{ws_at(odl), true}, act + ab, fl1);
+    emit_wgrad(*low, dag, take_partials, "dyn_fc1_wgrad", G1, C / G1, 1, 1, TVa / G1, w1, in_x, FcOperand{ws_at(odl), true}, act + ab, fl1);
     // the data gradient of FC1 adds to the dx that dyn_apply_dx_da has written
     emit_fc(*low, true, dag, take, "dyn_fc1_dgrad", G1, TVa / G1, 1, 1, C / G1, true, w1,
             soft ? FcOperand{ws_at(odl16), false} : FcOperand{ws_at(odl), true},
             [](const RunArgs& a) { return (const void*)a.dx; }, true, 2.0 * act + ab + 2.0 * nw1, fl1);
-    low->ws_bytes = off;
+    low->partial_bytes = at - partials_at;
+    low->ws_bytes = off + low->partial_bytes;
     return low;
 }
 

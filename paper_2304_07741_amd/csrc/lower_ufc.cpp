@@ -17,7 +17,7 @@
 
 namespace canvas {
 
-std::unique_ptr<Lowering> lower_ufc(const Dag& dag, bool bf16) {
+std::unique_ptr<Lowering> lower_ufc(const Dag& dag, bool bf16, uint64_t partials_at) {
     if (!bf16) return nullptr;
     const int n = (int)dag.nodes.size();
     for (int k = 0; k < n; k++)
@@ -114,6 +114,12 @@ std::unique_ptr<Lowering> lower_ufc(const Dag& dag, bool bf16) {
         off += align_up(bytes);
         return (int64_t)o;
     };
+    uint64_t at = partials_at;
+    const TakeFn take_partials = [&at](uint64_t bytes) {
+        const uint64_t o = at;
+        at += align_up(bytes);
+        return (int64_t)o;
+    };
     const int64_t oz = take((uint64_t)act), ov = take((uint64_t)act), odz = take((uint64_t)act);
     const int w1 = fc1.widx, w2 = fc2.widx;
     const double fl1 = 2.0 * dag.N * Pn * (double)C * K1, fl2 = 2.0 * dag.N * Pn * (double)O2 * K2;
@@ -148,7 +154,7 @@ std::unique_ptr<Lowering> lower_ufc(const Dag& dag, bool bf16) {
             [](const RunArgs& a) { return (const void*)a.y; }, false, act + outb + 2.0 * nw2, fl2);
 
     // backward (forward must have run with the same workspace: z and v are read back, and left intact)
-    emit_wgrad(*low, dag, takef, "ufc_fc2_wgrad", G2, C / G2, 1, 1, O2 / G2, w2, FcOperand{ws_at(ov), false}, in_dy, act + outb, fl2);
+    emit_wgrad(*low, dag, take_partials, "ufc_fc2_wgrad", G2, C / G2, 1, 1, O2 / G2, w2, FcOperand{ws_at(ov), false}, in_dy, act + outb, fl2);
     auto adjoint = [=](const RunArgs& a) {
         ufc::MidParams R = M;
         R.x = (const uint16_t*)a.x;
@@ -168,12 +174,13 @@ std::unique_ptr<Lowering> lower_ufc(const Dag& dag, bool bf16) {
                                 ufc::mid_backward(R, a.stream);
                             }});
     }
-    emit_wgrad(*low, dag, takef, TV > 1 ? "ufc_fc1_wgrad_unfold" : "ufc_fc1_wgrad", G1, C / G1, KH, KW, C / G1, w1, in_x,
+    emit_wgrad(*low, dag, take_partials, TV > 1 ? "ufc_fc1_wgrad_unfold" : "ufc_fc1_wgrad", G1, C / G1, KH, KW, C / G1, w1, in_x,
                FcOperand{ws_at(odz), false}, 2.0 * act, fl1);
     // mid_backward left dx_direct in dx; the data gradient of FC1 (through the Unfold adjoint) adds to it
     emit_fc(*low, true, dag, takef, TV > 1 ? "ufc_fc1_dgrad_unfold" : "ufc_fc1_dgrad", G1, C / G1, KH, KW, C / G1, true, w1,
             FcOperand{ws_at(odz), false}, [](const RunArgs& a) { return (const void*)a.dx; }, true, 3.0 * act + 2.0 * nw1, fl1);
-    low->ws_bytes = off;
+    low->partial_bytes = at - partials_at;
+    low->ws_bytes = off + low->partial_bytes;
     return low;
 }
 

@@ -72,6 +72,7 @@ struct Lowering {
     int chain_nodes = 0;           // nodes inside them
     uint64_t ws_bytes = 0;
     uint64_t stage_bytes = 0;      // the end of the workspace, used only by calls whose tensors overlap
+    uint64_t partial_bytes = 0;    // the end of the workspace, used only by the backward pass (partial sums of weight gradients)
     std::function<bool(const RunArgs&)> fwd_staged;  // with stage_bytes: whether a forward call is one
     std::vector<Launch> fwd, bwd;
     std::vector<WeightJob> wjobs;  // collected while lowering; batch_weight_jobs turns them into launches
@@ -106,12 +107,14 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
 std::unique_ptr<Lowering> lower_sgfc(const Dag& dag, bool bf16);
 
 // [Unfold] -> grouped FC -> [unary] -> Shift* -> add|mul with the input -> grouped FC, bf16 intermediates;
-// nullptr when the DAG is not of that form.
-std::unique_ptr<Lowering> lower_ufc(const Dag& dag, bool bf16);
+// nullptr when the DAG is not of that form.  partials_at: where the partial sums of the weight gradients begin, behind everything
+// else (the rest is as large whatever it is).
+std::unique_ptr<Lowering> lower_ufc(const Dag& dag, bool bf16, uint64_t partials_at);
 
 // FC -> [softmax] -> broadcast-mul onto Unfold(x) -> Fold(sum|avg over taps) -> FC (per-pixel window weights);
-// nullptr when the DAG is not of that form.
-std::unique_ptr<Lowering> lower_dyn(const Dag& dag, bool bf16);
+// nullptr when the DAG is not of that form.  partials_at: where the partial sums of the weight gradients begin, behind everything
+// else (the rest is as large whatever it is).
+std::unique_ptr<Lowering> lower_dyn(const Dag& dag, bool bf16, uint64_t partials_at);
 
 // Picks the lowering: fused kernel families where a pattern applies, else per node.
 std::unique_ptr<Lowering> lower(const Dag& dag, bool bf16, bool no_fusion, bool inference);
