@@ -684,15 +684,21 @@ void prepare_wgrad(Params& P) {
         // 64 x 64 tiles, or 128 x 64 with eight wavefronts where they are many: each operand is read once per tile of the other's
         // rows, and from 256 channels on these reads (L2) are what bounds the launch (C=256, 128 planes of 14x14: 15.9 / 13.9 us with
         // 64 x 64 / 128 x 64; C=512, 7x7: 17.9 / 16.6; C=128, 32 planes of 28x28: 8.0 / 8.6; C=80, 20 of 27x29: 5.7 / 6.9)
-        const bool many = (int64_t)P.G * ((P.Og + 63) / 64) * ((P.K + 63) / 64) >= 8 && P.Og > 64;
-        P.wo = many ? 4 : 2;
+        // Three tiles of 64 outputs and two of 128 read as much: there the larger ones pay from about 420 steps on (C=160, launch and sum, 16 planes of
+        // 40x40, 400 steps, 10.2 / 10.7 us; C=176, 10 of 56x56, 490 steps, 12.4 / 11.0; C=160, 24 of 56x56, 1176 steps, 20.0 / 17.8).
+        const int64_t steps = ((int64_t)P.N * P.upi + 7) / 8;
+        const int orows = (P.Og + 63) / 64;
+        const bool many = (int64_t)P.G * orows * ((P.K + 63) / 64) >= 8 && orows > 1;
+        P.wo = many && (orows != 3 || steps >= 420) ? 4 : 2;
         P.otiles = (P.Og + 32 * P.wo - 1) / (32 * P.wo);
         P.ktiles = (P.K + 63) / 64;
         const int64_t tiles = (int64_t)P.G * P.otiles * P.ktiles;
-        const int64_t steps = ((int64_t)P.N * P.upi + 7) / 8;
         // one workgroup per compute unit (two: 23.6 / 22.3 us at C=64, 128 planes of 56x56, 9.2 / 8.0 at C=128, 32 of 28x28: more
-        // partials), at most 8 MB of partials (16 MB measured slower: they are written once and read once more by the sum)
-        int64_t slices = std::max<int64_t>(1, std::min<int64_t>(steps, (256 + tiles - 1) / tiles));
+        // partials), and not one too many (258 or 261 / 252: C=144, 13 of 56x56 16.4 / 12.3, C=288, 6 of 56x56 20.8 / 14.2) unless its slice then has
+        // the steps in flight and no more (C=136 for 128, 28 of 28x28 8.7 / 7.5); at most 8 MB of partials (16 MB measured slower: they
+        // are written once and read once more by the sum)
+        int64_t slices = std::max<int64_t>(1, std::min<int64_t>(steps, 256 / tiles));
+        if (256 % tiles != 0 && steps > kAhead * slices && steps <= kAhead * (slices + 1)) slices++;
         slices = std::max<int64_t>(1, std::min<int64_t>(slices, ((int64_t)8 << 20) / std::max<int64_t>(1, wnumel * 4)));
         P.chunks32 = (int)steps;
         P.per_slice = (int)((steps + slices - 1) / slices);

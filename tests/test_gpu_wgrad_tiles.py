@@ -21,6 +21,8 @@ CASES = [
     (4, 256, 512, 3, (10, 11)),    # 128 x 64 tiles in groups
     (1, 64, 64, 50, (28, 29)),     # many steps per slice, the last one short
     (1, 64, 64, 1, (1, 8)),        # a single unit
+    (1, 160, 144, 9, (9, 7)),      # three tiles of outputs: 64 x 64, a slice more than fits for its four steps
+    (1, 132, 136, 500, (7, 7)),    # the same in 128 x 64 tiles from 420 steps on
 ]
 
 
