@@ -951,6 +951,15 @@ class Emitter {
 
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
+double workgroups_per_cu(const Program& pg) {
+    // (the instances with 9 lanes x 4 pixels and with 25 lanes hold more than 128 vector registers: two wavefronts per
+    // SIMD, not four)
+    const double resident_threads = (pg.tm > 9 || (pg.tm > 1 && pg.vec >= 4)) ? 512.0 : 1024.0;
+    return std::max(1.0, std::min(resident_threads / pg.threads, std::floor(160.0 * 1024.0 / (double)(lds_bytes(pg) + 4352))));
+}
+// How many times over the launch fills the chip.
+double rounds_of(const Program& pg) { return (double)pg.N * pg.tiles * pg.chunks / (256.0 * workgroups_per_cu(pg)); }
+
 // Workgroup shape for the pixels per thread already set and `pt` threads per slice (at most `cap`): tile and halo (`own`
 // threads of the tile store, HT more on either side), channel range and slices.
 // Returns the estimated cost of the launch (arbitrary units, see set_geometry) or a negative number when it does not fit.
@@ -979,20 +988,15 @@ double geometry_for(Program& pg, const Dag& dag, int C, bool all_channels, bool 
     // about eight pixels of arithmetic, plus per channel the pixels and about four pixels' worth for its narrow memory
     // accesses) x how many times over the launch fills the chip (256 compute units, about 1024 resident threads each)
     const double trips_per_thread = (double)ceil_div(pg.chunk, pg.slices * pg.unroll);
-    const double threads_total = (double)dag.N * pg.tiles * pg.chunks * pg.threads;
-    // (the instances with 9 lanes x 4 pixels and with 25 lanes hold more than 128 vector registers: two wavefronts per
-    // SIMD, not four)
-    const double resident_threads = (pg.tm > 9 || (pg.tm > 1 && pg.vec >= 4)) ? 512.0 : 1024.0;
-    const double wgs_per_cu = std::max(1.0, std::min(resident_threads / pg.threads, std::floor(160.0 * 1024.0 / (double)(lds_bytes(pg) + 4352))));
     // (whole rounds: a round that a few left-over workgroups make takes as long as a full one)
-    const double rounds = std::max(1.0, std::ceil(threads_total / (256.0 * wgs_per_cu * pg.threads) - 0.05));
+    const double rounds = std::max(1.0, std::ceil(rounds_of(pg) - 0.05));
     // (a work item also costs its set-up: the thread's position, the pass headers; worth about 6 of these units)
     return (6.0 + trips_per_thread * (8.0 + (pg.vec + 4.0) * pg.unroll)) * rounds;
 }
 
 // Pixels per thread, threads per slice and trips per thread: whatever the estimate likes best.
-// Returns the estimate.
-double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool all_channels, bool one_trip) {
+// whole_planes: a tile that holds a plane whole has no halo.  Returns the estimate.
+double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool all_channels, bool one_trip, bool whole_planes = true) {
     pg.N = dag.N;
     pg.C = C;
     pg.H = dag.H;
@@ -1030,10 +1034,11 @@ double set_geometry(Program& pg, const Dag& dag, int C, int64_t reach_px, bool a
             const int cap = (int)(std::min<int64_t>(max_threads_for(pg.tm), (int64_t)kMaxLdsBytes / per_thread) / 64 * 64);
             for (int pt = 64; pt <= cap; pt += 64) {
                 int own = pt - 2 * (int)HT, ht = (int)HT;
-                if (pt >= PP) {  // the whole plane in one tile: nothing comes from beside it
-                    if (ceil_div(PP, 64) * 64 != pt) break;  // (counted once, at its own size)
+                const int one_tile = PP + (whole_planes ? 0 : 2 * (int)HT);
+                if (pt >= one_tile) {  // the whole plane in one tile: nothing comes from beside it
+                    if (ceil_div(one_tile, 64) * 64 != pt) break;  // (counted once, at its own size)
                     own = PP;
-                    ht = 0;
+                    if (whole_planes) ht = 0;
                 } else if (own <= 0) {
                     continue;
                 } else {
@@ -1632,9 +1637,9 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
         // (bit 0), where the workgroup that suits the plain program has a thread for every channel anyway: 16x96 planes of
         // 32x32 forward + backward 19.9 + 38.7 -> 16.9 + 26.5 us; a workgroup chosen for it lost more than the passes gained
         // (128x64 planes of 56x56 backward 177 -> 252 us, 128x40 of 28x28 48.5 -> 75.4).  Where a chain is cut goes by the plain
-        // programs.  Returns the plain program's cost.
+        // programs.  Adds the plain program's cost to out.cost and, with a halo around whole planes too, to out.halo_cost.
         auto best_of = [&](const std::function<void(Emitter&)>& emit_program, bool backward, Program& pg, std::vector<ExtRef>& refs) {
-            double plain = -1, best = -1, best_geometry = 0;
+            double best = -1, best_geometry = 0;
             for (int v = 0; v < 4; v++) {
                 const bool one_trip = v & 1, mirrors = v & 2;
                 if ((one_trip && (!variants || smc.empty())) || (mirrors && (!backward || mirrored.empty()))) continue;
@@ -1648,9 +1653,23 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
                         int64_t halo = 0;
                         for (int i = 0; i < E->pg.n_instr; i++)  // (the reach of the hand-overs of the program that was chosen)
                             if (E->pg.ins[i].op == OP_XADD) halo = std::max(halo, E->reach_of[i]);
+                        Program haloed;
+                        if (v == 0 && !variants && halo > 0) haloed = E->pg;
                         const double geometry = set_geometry(E->pg, dag, C, halo, !smc.empty(), one_trip);
                         const double cost = program_cost(E->pg);
-                        if (v == 0) plain = cost;
+                        if (v == 0) {
+                            out.cost += cost;
+                            double halo_cost = cost;
+                            if (!variants && halo > 0) {
+                                try {
+                                    set_geometry(haloed, dag, C, halo, !smc.empty(), false, false);
+                                    halo_cost = program_cost(haloed);
+                                } catch (const Fail&) {
+                                    halo_cost = -1;
+                                }
+                            }
+                            out.halo_cost = halo_cost < 0 || out.halo_cost < 0 ? -1 : out.halo_cost + halo_cost;
+                        }
                         if (v == 0 || (cost < best && (!one_trip || (geometry <= best_geometry * 1.001 && E->pg.vec == pg.vec)))) {
                             best = cost;
                             best_geometry = geometry;
@@ -1663,10 +1682,9 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
                     }
                 }
             }
-            return plain;
         };
-        out.cost = best_of(emit_fwd, false, out.fwd, out.fwd_ext);
-        out.cost += best_of(emit_bwd, true, out.bwd, out.bwd_ext);
+        best_of(emit_fwd, false, out.fwd, out.fwd_ext);
+        best_of(emit_bwd, true, out.bwd, out.bwd_ext);
         // (Pays off from a plane of 32 threads and 3.6 M taps on, with four pixels per thread from 7.2 M on: the channels of a trip go one after
         // the other here.  3x3 box, forward + backward, us with all lanes / streamed: 128x64 planes of 56x56 327 / 163, 16x96 of 32x32 33 / 17, 8x64 of
         // 56x56 32 / 17, 128x64 of 28x28 90 / 74, 16x64 of 28x28 20.8 / 20.3, 8x32 of 28x28 14.8 / 19.9, 128x128 of 8x8 26 / 40, 16x64 of 16x16 15.2 / 15.7; 5x5 under a product
@@ -1694,6 +1712,19 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
         why = f.why;
         return false;
     }
+}
+
+double launch_us(const Program& pg) {
+    double weight = 0, instructions = 0;
+    for (int p = 0; p < pg.n_pass; p++)
+        for (int i = pg.pass[p].body_begin; i < pg.pass[p].body_end; i++) {
+            weight += instr_weight(pg.ins[i]);
+            instructions++;
+        }
+    const double trips = (double)ceil_div(pg.chunk, pg.slices * pg.unroll), rounds = rounds_of(pg);
+    // threads that share a compute unit's vector units, of about 1024
+    const double resident = pg.threads / 1024.0 * (rounds >= 1 ? workgroups_per_cu(pg) : std::min(1024.0 / pg.threads, (double)pg.N * pg.tiles * pg.chunks / 256.0));
+    return std::max(1.0, std::ceil(rounds - 0.05)) * trips * (0.75 * instructions + 0.025 * weight * pg.unroll * (pg.vec * resident + 0.5));
 }
 
 double program_cost(const Program& pg) {

@@ -31,6 +31,7 @@ struct UnitPlan {
     Program fwd, bwd;
     std::vector<ExtRef> fwd_ext, bwd_ext;  // one per ext slot of the program
     double cost = 0;            // estimated work of both programs per pixel and channel (see program_cost)
+    double halo_cost = 0;       // the same (variants false) with a halo around planes that a workgroup holds whole too; negative where that does not fit
 };
 
 // True when node k can be part of a fused chain at all (op, shapes, attributes).
@@ -50,6 +51,11 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
 // the channels beyond 16 trips.  The lowering lets a node join a chain only
 // while the grown chain is not much dearer than the two chains apart.
 double program_cost(const Program& pg);
+
+// Estimated time of a program's launch in us beyond that of an empty one: per trip of a thread an instruction takes 0.75 us (its dispatch, and the loads
+// and barriers that it waits for) and 0.025 us for each lane of work, the more wavefronts share a SIMD.  Fitted to 5000 launches of 5 us
+// to 2 ms of random micro-DAGs; a factor of 1.5 either way.
+double launch_us(const Program& pg);
 
 // Text form of a program (for CANVAS_LOG and debugging).
 std::string dump(const Program& pg);

@@ -166,7 +166,12 @@ bool self_blend(const Dag& dag, const Unit& U, ufc::MidParams& M) {
 
 }  // namespace
 
-std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_chains, bool inference) {
+// Costs of chains by their plain programs, with whole planes and with halos; negative where there is none (the searches ask for some chains
+// several times).
+typedef std::map<std::vector<int>, std::pair<double, double>> ChainCosts;
+
+// The lowering whose search over the chains goes by the costs with halos or by the others; nullptr where it comes to the chains of `unlike`.
+static std::unique_ptr<Lowering> lower_by(const Dag& dag, bool bf16, bool fuse_chains, bool inference, bool halos, ChainCosts& costs, const Lowering* unlike) {
     auto low = std::make_unique<Lowering>();
     const int n = (int)dag.nodes.size();
     const int P = dag.P();
@@ -236,15 +241,15 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         return outp;
     };
     const bool log = std::getenv("CANVAS_LOG") != nullptr;
-    // What a chain of these nodes costs by its plain programs, negative where there is none (the search asks for some chains
-    // several times).
-    std::map<std::vector<int>, double> known_cost;
     std::string why;
     auto chain_cost = [&](const std::vector<int>& nodes) {
-        auto it = known_cost.find(nodes);
-        if (it != known_cost.end()) return it->second;
-        chain::UnitPlan plan;
-        return known_cost[nodes] = chain::compile_unit(dag, nodes, outputs_of(nodes), false, plan, why) ? plan.cost : -1.0;
+        auto it = costs.find(nodes);
+        if (it == costs.end()) {
+            chain::UnitPlan plan;
+            const bool compiles = chain::compile_unit(dag, nodes, outputs_of(nodes), false, plan, why);
+            it = costs.insert({nodes, compiles ? std::make_pair(plan.cost, plan.halo_cost) : std::make_pair(-1.0, -1.0)}).first;
+        }
+        return halos ? it->second.second : it->second.first;
     };
     for (int k = 1; k < n; k++) {
         const Node& nd = dag.nodes[k];
@@ -330,6 +335,9 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             for (int k : units[v].nodes) unit_of[k] = (int)v;
         u--;  // (the first half again, then the second)
     }
+    for (const Unit& U : units)
+        if (U.chain) low->chains.push_back(U.nodes);
+    if (unlike && unlike->chains == low->chains) return nullptr;
     // a unit was last compiled when it last grew, against the consumers known then; later nodes may have joined
     // other units, which never removes an output, but a later joiner of THIS unit may have: compile the final sets
     for (Unit& U : units)
@@ -670,6 +678,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             const std::vector<Binding> b = bind(U.plan.fwd_ext);
             smc::Params S;
             if (softmax_of_channels(dag, U, S)) {
+                low->est_us += ext_bytes(b) / 3e6;
                 const Binding bx = bind_of(b, chain::kValueIn), by = bind_of(b, chain::kValueOut);
                 low->fwd.push_back({"chain_fwd", ext_bytes(b), 0, [=](const RunArgs& a) {
                                         smc::Params Q = S;
@@ -684,6 +693,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             }
             ufc::MidParams M;
             if (self_direct(U, M)) {
+                low->est_us += ext_bytes(b) / 3e6;
                 low->fwd.push_back({"chain_fwd", ext_bytes(b), 0, [=](const RunArgs& a) {
                                         ufc::MidParams Q = M;
                                         Q.x = Q.z = (const uint16_t*)a.x;
@@ -692,6 +702,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
                                     }});
                 continue;
             }
+            low->est_us += chain::launch_us(pg);
             low->fwd.push_back({"chain_fwd", ext_bytes(b), 0, [=](const RunArgs& a) { run_program(pg, b, bf16, a); }});
             continue;
         }
@@ -863,6 +874,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
                 }
             smc::Params S;
             if (softmax_of_channels(dag, U, S)) {
+                if (!inference) low->est_us += ext_bytes(b) / 3e6;
                 const Binding bx = bind_of(b, chain::kValueIn), bg = bind_of(b, chain::kGradIn), bd = bind_of(b, chain::kGradOut);
                 low->bwd.push_back({"chain_bwd", ext_bytes(b), 0, [=](const RunArgs& a) {
                                         smc::Params Q = S;
@@ -880,6 +892,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
             }
             ufc::MidParams M;
             if (self_direct(U, M)) {
+                if (!inference) low->est_us += ext_bytes(b) / 3e6;
                 low->bwd.push_back({"chain_bwd", ext_bytes(b), 0, [=](const RunArgs& a) {
                                         ufc::MidParams Q = M;
                                         Q.x = (const uint16_t*)a.x;
@@ -889,6 +902,7 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
                                     }});
                 continue;
             }
+            if (!inference) low->est_us += chain::launch_us(pg);
             low->bwd.push_back({"chain_bwd", ext_bytes(b), 0, [=](const RunArgs& a) { run_program(pg, b, bf16, a); }});
             continue;
         }
@@ -1112,7 +1126,25 @@ std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_ch
         else low->bwd.push_back({"copy_dx", ne * 8.0, 0, [=](const RunArgs& a) { ref::copy_f32(grad(a, 0), (float*)a.dx, ne, a.stream); }});
     }
     (void)esz;
+    low->est_us += 5.0 * (double)(low->fwd.size() + (inference ? 0 : low->bwd.size()));  // (about what an empty launch and the gap behind it take)
     return low;
+}
+
+// Planes that a workgroup holds whole need no halo, which makes every part of a chain cheaper, but not alike: the search then cuts some chains that it
+// keeps whole by the costs with halos, and keeps some that it cuts.  Neither is always the better one, so both are written where they
+// differ, and the estimated times of their launches decide: the one with whole planes where it is 5 % shorter.  (760 plans of 46 random
+// micro-DAGs that differ, time over that of the better one, geometric mean: by halos 1.044, by whole planes 1.305, by this
+// rule 1.003.  16x96 planes of 27x15, |x|, product with a 5x5 window, avg: 213 / 239 us; 7x96 of 19x25, softmax, relu, max over 5x5, product: 212 / 143.)
+// Except that a plan which fits the library's static workspace either way fits it.
+std::unique_ptr<Lowering> lower_per_node(const Dag& dag, bool bf16, bool fuse_chains, bool inference) {
+    ChainCosts costs;
+    std::unique_ptr<Lowering> a = lower_by(dag, bf16, fuse_chains, inference, true, costs, nullptr);
+    if (!fuse_chains) return a;
+    std::unique_ptr<Lowering> b = lower_by(dag, bf16, fuse_chains, inference, false, costs, a.get());
+    if (!b) return a;
+    auto fits = [](const Lowering& l) { return l.ws_bytes - l.stage_bytes <= CANVAS_STATIC_WORKSPACE_BYTES; };
+    if (fits(*a) != fits(*b)) return fits(*a) ? std::move(a) : std::move(b);
+    return b->est_us * 1.05 < a->est_us ? std::move(b) : std::move(a);
 }
 
 }  // namespace canvas

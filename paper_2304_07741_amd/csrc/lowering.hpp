@@ -70,6 +70,8 @@ struct Lowering {
     std::function<void(const BlockArgs&)> block_fwd, block_bwd;
     int chain_units = 0;           // fused chains in the forward list (each is one kernel forward, one backward)
     int chain_nodes = 0;           // nodes inside them
+    std::vector<std::vector<int>> chains;  // their nodes
+    double est_us = 0;             // estimated time of the chains' launches (of the forward pass alone in an inference plan)
     uint64_t ws_bytes = 0;
     uint64_t stage_bytes = 0;      // the end of the workspace, used only by calls whose tensors overlap
     uint64_t partial_bytes = 0;    // the end of the workspace, used only by the backward pass (partial sums of weight gradients)
