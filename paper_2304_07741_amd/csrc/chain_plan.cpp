@@ -1639,7 +1639,13 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
         // (128x64 planes of 56x56 backward 177 -> 252 us, 128x40 of 28x28 48.5 -> 75.4).  Where a chain is cut goes by the plain
         // programs.  Adds the plain program's cost to out.cost and, with a halo around whole planes too, to out.halo_cost.
         auto best_of = [&](const std::function<void(Emitter&)>& emit_program, bool backward, Program& pg, std::vector<ExtRef>& refs) {
-            double best = -1, best_geometry = 0;
+            struct Shape {
+                double estimate = 0;
+                int vec = 0;
+                bool suits(const Shape& plain) const { return estimate <= plain.estimate * 1.001 && vec == plain.vec; }
+            };
+            double best = -1;
+            Shape packed, emitted;  // the workgroup of the best program; the one before its registers were packed
             for (int v = 0; v < 4; v++) {
                 const bool one_trip = v & 1, mirrors = v & 2;
                 if ((one_trip && (!variants || smc.empty())) || (mirrors && (!backward || mirrored.empty()))) continue;
@@ -1649,30 +1655,42 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
                     try {
                         auto E = shortest(emit_program, one_trip, most_kept);
                         most_kept = std::min(most_kept, (int)E->keep.size());
-                        if (!one_trip && variants) compact_registers(*E);
                         int64_t halo = 0;
                         for (int i = 0; i < E->pg.n_instr; i++)  // (the reach of the hand-overs of the program that was chosen)
                             if (E->pg.ins[i].op == OP_XADD) halo = std::max(halo, E->reach_of[i]);
-                        Program haloed;
-                        if (v == 0 && !variants && halo > 0) haloed = E->pg;
-                        const double geometry = set_geometry(E->pg, dag, C, halo, !smc.empty(), one_trip);
+                        Program unpacked = E->pg;
+                        if (!one_trip && variants) compact_registers(*E);
+                        Shape shape, before;
+                        shape.estimate = set_geometry(E->pg, dag, C, halo, !smc.empty(), one_trip);
+                        shape.vec = E->pg.vec;
+                        if (!one_trip && variants && !smc.empty()) {
+                            try {
+                                before.estimate = set_geometry(unpacked, dag, C, halo, true, false);
+                                before.vec = unpacked.vec;
+                            } catch (const Fail&) {
+                            }
+                        }
                         const double cost = program_cost(E->pg);
                         if (v == 0) {
                             out.cost += cost;
                             double halo_cost = cost;
                             if (!variants && halo > 0) {
                                 try {
-                                    set_geometry(haloed, dag, C, halo, !smc.empty(), false, false);
-                                    halo_cost = program_cost(haloed);
+                                    set_geometry(unpacked, dag, C, halo, !smc.empty(), false, false);
+                                    halo_cost = program_cost(unpacked);
                                 } catch (const Fail&) {
                                     halo_cost = -1;
                                 }
                             }
                             out.halo_cost = halo_cost < 0 || out.halo_cost < 0 ? -1 : out.halo_cost + halo_cost;
                         }
-                        if (v == 0 || (cost < best && (!one_trip || (geometry <= best_geometry * 1.001 && E->pg.vec == pg.vec)))) {
+                        // (packed registers can leave room for a workgroup that suits the plain program better; where kept values suit the one before,
+                        // the estimates of the launches decide: two softmaxes over 96 channels, 16 planes of 16x16, forward + backward 159 us with packed
+                        // registers, 109 with kept values)
+                        if (v == 0 || (cost < best && (!one_trip || shape.suits(packed) || (shape.suits(emitted) && launch_us(E->pg) < launch_us(pg))))) {
                             best = cost;
-                            best_geometry = geometry;
+                            packed = shape;
+                            emitted = before;
                             pg = E->pg;
                             refs = E->ext;
                         }
