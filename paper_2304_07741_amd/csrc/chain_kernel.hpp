@@ -177,9 +177,10 @@ inline bool f32_windows(const Program& pg) {
 template <int TM, int V, bool F32W, bool RAG, bool ALIAS>
 void launch_as(const Program& pg, hipStream_t stream) {
     constexpr int U = unroll_for(TM, V);
-    // (more than 64 KB of dynamic LDS must be asked for, once per kernel)
-    static const hipError_t lds_ok = hipFuncSetAttribute((const void*)k_chain<TM, V, U, F32W, RAG, ALIAS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLdsBytes);
-    (void)lds_ok;
+    if (lds_bytes(pg) > 64 * 1024) {
+        static std::atomic<uint64_t> asked;
+        allow_lds(asked, (const void*)k_chain<TM, V, U, F32W, RAG, ALIAS>, (int)kMaxLdsBytes);
+    }
     const dim3 grid(grid_for(pg));
     CANVAS_LAUNCH((k_chain<TM, V, U, F32W, RAG, ALIAS>), grid, dim3((unsigned)pg.threads), lds_bytes(pg), stream, pg);
 }

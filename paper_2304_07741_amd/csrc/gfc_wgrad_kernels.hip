@@ -236,9 +236,8 @@ constexpr int kMaxLds = 78 * 1024;  // of a step: two of them in flight, of the 
 
 template <int U>
 void launch(const Params& P, hipStream_t s) {
-    // (more than 64 KB of dynamic LDS must be asked for, once per kernel)
-    static const hipError_t lds_ok = hipFuncSetAttribute((const void*)k_wgrad_taps<U>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kMaxLds);
-    (void)lds_ok;
+    static std::atomic<uint64_t> asked;
+    allow_lds(asked, (const void*)k_wgrad_taps<U>, 2 * kMaxLds);
     const dim3 grid((unsigned)(P.slices * P.Gm * (P.Omp / (16 * MT)) * (P.Rp / (16 * MT))));
     CANVAS_LAUNCH((k_wgrad_taps<U>), grid, dim3(kThreads), (size_t)P.lds_bytes * 2, s, P);
 }

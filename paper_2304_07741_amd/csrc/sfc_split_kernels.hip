@@ -630,8 +630,8 @@ __global__ __launch_bounds__(kThreads) void k_split_weights(SplitJobs jobs) {
 
 template <int WM, int TVT, int NPI>
 void launch_one(const Params& p, dim3 grid, hipStream_t s) {
-    static const hipError_t lds_ok = hipFuncSetAttribute((const void*)k_fwd_split<WM, TVT, NPI>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxSplitLds);
-    (void)lds_ok;
+    static std::atomic<uint64_t> asked;
+    allow_lds(asked, (const void*)k_fwd_split<WM, TVT, NPI>, kMaxSplitLds);
     CANVAS_LAUNCH((k_fwd_split<WM, TVT, NPI>), grid, dim3(kThreads), split_lds(p), s, p);
 }
 
@@ -680,10 +680,9 @@ static size_t wgrad_split_lds(const Params& p) { return (size_t)4 * 2 * 3 * (32 
 void wgrad_split(const Params& p, dim3 grid, hipStream_t s) {
     const dim3 block(kThreads);
     const size_t lds = wgrad_split_lds(p);
-    auto allow = [](const void* f) { return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxSplitLds); };
     if (p.wm == 2) {
-        static const hipError_t ok = allow((const void*)k_wgrad_split<2>);
-        (void)ok;
+        static std::atomic<uint64_t> asked;
+        allow_lds(asked, (const void*)k_wgrad_split<2>, kMaxSplitLds);
         CANVAS_LAUNCH((k_wgrad_split<2>), grid, block, lds, s, p);
     } else {
         CANVAS_LAUNCH((k_wgrad_split<1>), grid, block, lds, s, p);

@@ -978,11 +978,11 @@ static void launch_bwd_of(const Params& P, const Instances& I, bool expand, hipS
     const dim3 grid((unsigned)P.wgs_per_group, (unsigned)P.G);
     if (!P.total_tiles) return;
     const size_t lds = (size_t)lds_pieces_multi(1, I.m, tiles_multi(ACT, RAG)) * 16;
-    if constexpr (kTwoParts<ACT, RAG>) {  // (80 KB for eight instances; more than 64 must be asked for, once per kernel)
+    if constexpr (kTwoParts<ACT, RAG>) {  // (80 KB for eight instances)
         constexpr int most = lds_pieces_multi(1, kMaxInstances, tiles_multi(ACT, RAG)) * 16;
-        auto allow = [](const void* f) { return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, most); };
-        static const hipError_t ok[2] = {allow((const void*)k_bwd_multi<1, ACT, RES, true, RAG>), allow((const void*)k_bwd_multi<1, ACT, RES, false, RAG>)};
-        (void)ok;
+        static std::atomic<uint64_t> asked[2];
+        if (expand) allow_lds(asked[0], (const void*)k_bwd_multi<1, ACT, RES, true, RAG>, most);
+        else allow_lds(asked[1], (const void*)k_bwd_multi<1, ACT, RES, false, RAG>, most);
     }
     if (expand) CANVAS_LAUNCH((k_bwd_multi<1, ACT, RES, true, RAG>), grid, dim3(64 * kWaves), lds, s, P, I);
     else CANVAS_LAUNCH((k_bwd_multi<1, ACT, RES, false, RAG>), grid, dim3(64 * kWaves), lds, s, P, I);
