@@ -1095,26 +1095,30 @@ void add_products(Program& pg) {
 // register is as many bytes of LDS per thread as the instance has lanes, and LDS decides how many wavefronts a compute unit holds);
 // where no register holds anything during a hand-over, its buffer takes their place.  Backward of unfold 3x3 -> softmax -> product ->
 // gelu -> sum, 16x96 planes of 32x32: 280 -> 196 bytes per thread, 239 -> 192 us (97 with add_products).
-// Not for programs that keep registers from pass to pass.
+// Not for programs that keep registers from pass to pass: those are left as they are.
 void compact_registers(Emitter& E) {
     Program& pg = E.pg;
-    if (pg.tm > 1) add_products(pg);
     auto reads = [](const Instr& I) {
         return I.op == OP_MADD || I.op == OP_MOVA || I.op == OP_BIN || I.op == OP_UNBX || I.op == OP_BING || I.op == OP_SMTBX || I.op == OP_FOLDBX || I.op == OP_SMCDOT || I.op == OP_SMCBX;
     };
+    for (int p = 0; p < pg.n_pass; p++) {
+        std::set<int> defined;
+        for (int i = pg.pass[p].pro_begin; i < pg.pass[p].body_end; i++) {
+            const Instr& I = pg.ins[i];
+            if (reads(I) && !defined.count(I.r)) return;  // (a value from elsewhere)
+            if (I.op != OP_MOVR) continue;
+            if (i < pg.pass[p].body_begin) return;        // (a prologue's value holds for every channel of the body)
+            defined.insert(I.r);
+        }
+    }
+    if (pg.tm > 1) add_products(pg);
     std::vector<int> last_use(pg.n_instr, -1);  // of a store's value
     for (int p = 0; p < pg.n_pass; p++) {
         std::map<int, int> def;
         for (int i = pg.pass[p].body_begin; i < pg.pass[p].body_end; i++) {
             const Instr& I = pg.ins[i];
-            if (reads(I)) {
-                if (!def.count(I.r)) return;  // (a value from elsewhere)
-                last_use[def[I.r]] = i;
-            }
-            if (I.op == OP_MADD) {
-                if (!def.count(I.a)) return;
-                last_use[def[I.a]] = i;
-            }
+            if (reads(I)) last_use[def.at(I.r)] = i;
+            if (I.op == OP_MADD) last_use[def.at(I.a)] = i;
             if (I.op == OP_MOVR) def[I.r] = i;
         }
     }
