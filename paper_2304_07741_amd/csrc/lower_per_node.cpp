@@ -678,6 +678,7 @@ static std::unique_ptr<Lowering> lower_by(const Dag& dag, bool bf16, bool fuse_c
             const std::vector<Binding> b = bind(U.plan.fwd_ext);
             smc::Params S;
             if (softmax_of_channels(dag, U, S)) {
+                if (log) std::fprintf(stderr, "canvas: chain of node %d: the kernels of a softmax over channels\n", U.nodes[0]);
                 low->est_us += ext_bytes(b) / 3e6;
                 const Binding bx = bind_of(b, chain::kValueIn), by = bind_of(b, chain::kValueOut);
                 low->fwd.push_back({"chain_fwd", ext_bytes(b), 0, [=](const RunArgs& a) {
@@ -693,6 +694,7 @@ static std::unique_ptr<Lowering> lower_by(const Dag& dag, bool bf16, bool fuse_c
             }
             ufc::MidParams M;
             if (self_direct(U, M)) {
+                if (log) std::fprintf(stderr, "canvas: chain of node %d: the kernels of a tensor blended with itself\n", U.nodes[0]);
                 low->est_us += ext_bytes(b) / 3e6;
                 low->fwd.push_back({"chain_fwd", ext_bytes(b), 0, [=](const RunArgs& a) {
                                         ufc::MidParams Q = M;

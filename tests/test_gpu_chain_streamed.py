@@ -14,6 +14,7 @@ BODIES = [
     "%1 = unfold %0 kh=5 kw=5\n%2 = binary %0 %1 op=mul\n%3 = fold %2 op=avg\noutput %3\n",
     "%1 = unfold %0 kh=3 kw=3\n%2 = binary %0 %1 op=sub\n%3 = fold %2 op=sum\noutput %3\n",
     "%1 = unary %0 op=relu\n%2 = unfold %0 kh=1 kw=3\n%3 = binary %1 %2 op=add\n%4 = fold %3 op=max\noutput %4\n",
+    # (an unfolded tensor that a unit of its own writes: lanes)
     "%1 = unary %0 op=sin\n%2 = unfold %0 kh=3 kw=3\n%3 = unfold %1 kh=3 kw=3\n%4 = binary %2 %3 op=mul\n%5 = fold %4 op=sum\noutput %5\n",
     # a window over another chain's result (fp32), in turn folded
     "%1 = unfold %0 kh=3 kw=3\n%2 = fold %1 op=sum\n%3 = unfold %2 kh=5 kw=5\n%4 = binary %2 %3 op=mul\n%5 = fold %4 op=avg\noutput %5\n",
@@ -23,7 +24,7 @@ BODIES = [
     "%1 = shift %0 dh=1 dw=-1 c0=0 c1=5\n%2 = unfold %1 kh=3 kw=3\n%3 = fold %2 op=sum\noutput %3\n",
     "%1 = unfold %0 kh=3 kw=3\n%2 = softmax %1 axis=T\n%3 = binary %0 %2 op=mul\n%4 = fold %3 op=sum\noutput %4\n",
 ]
-SHAPES = [(2, 100, 40, 56), (9, 52, 28, 60), (4, 97, 32, 32)]   # 8, 4 and 8 pixels per thread
+SHAPES = [(2, 100, 40, 56), (10, 53, 28, 60), (4, 101, 32, 32)]   # 8, 4 and 8 pixels per thread (test_chain_paths_host.py looks at the programs)
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
