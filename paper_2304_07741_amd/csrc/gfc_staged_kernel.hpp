@@ -398,12 +398,17 @@ __global__ __launch_bounds__(kThreads, 2) void k_fc(Params P, std::conditional_t
     }
 }
 
+// (The instances are those that plan comes to, as tests/host/staged_plans.cpp checks.)
 template <int KW, int MO, int NP, int WO, int TP, int NW, int MID, bool SM = false, class M>
 void launch_nb(const Params& P, const M& m, hipStream_t s) {
     const dim3 grid((unsigned)(P.tiles * P.ogroups * P.Gm)), block(kThreads);
-    if (P.batches == 1) CANVAS_LAUNCH((k_fc<KW, MO, NP, WO, TP, NW, 1, SM, MID>), grid, block, (size_t)P.lds_bytes, s, P, m);
-    else if (P.batches == 2) CANVAS_LAUNCH((k_fc<KW, MO, NP, WO, TP, NW, 2, SM, MID>), grid, block, (size_t)P.lds_bytes, s, P, m);
-    else CANVAS_LAUNCH((k_fc<KW, MO, NP, WO, TP, NW, kMaxBatch, SM, MID>), grid, block, (size_t)P.lds_bytes, s, P, m);
+    if (P.batches == 1) {
+        CANVAS_LAUNCH((k_fc<KW, MO, NP, WO, TP, NW, 1, SM, MID>), grid, block, (size_t)P.lds_bytes, s, P, m);
+    } else if (P.batches == 2) {
+        CANVAS_LAUNCH((k_fc<KW, MO, NP, WO, TP, NW, 2, SM, MID>), grid, block, (size_t)P.lds_bytes, s, P, m);
+    } else if constexpr (KW > 1 || WO > 1) {
+        CANVAS_LAUNCH((k_fc<KW, MO, NP, WO, TP, NW, kMaxBatch, SM, MID>), grid, block, (size_t)P.lds_bytes, s, P, m);
+    }
 }
 
 template <int KW, int MO, int NP, int WO, int MID, class M>
@@ -426,7 +431,7 @@ void launch(const Params& P, const M& m, hipStream_t s) {
 template <int KW, int MO, int WO, int MID, class M>
 void launch_np(const Params& P, const M& m, hipStream_t s) {
     if (P.np == 4) {
-        if constexpr (MO * 4 <= 8) launch<KW, MO, 4, WO, MID>(P, m, s);
+        if constexpr (KW == 3 && MO == 2 && WO == 1) launch<KW, MO, 4, WO, MID>(P, m, s);
     } else if (P.np == 2) {
         launch<KW, MO, 2, WO, MID>(P, m, s);
     } else {

@@ -156,8 +156,7 @@ void forward(const Params& P, hipStream_t s) {
             else if (P.mo == 2) launch_np<1, 2, 4, 0>(P, m, s);
             else launch_np<1, 4, 4, 0>(P, m, s);
         } else {
-            if (P.mo == 1) launch_np<1, 1, 1, 0>(P, m, s);
-            else launch_np<1, 2, 1, 0>(P, m, s);
+            launch_np<1, 1, 1, 0>(P, m, s);
         }
     } else {
         if (P.wo == 2) launch_np<3, 2, 2, 0>(P, m, s);

@@ -1,5 +1,5 @@
 // Decodes every workgroup number of plans of the staged FC kernels, and the units, rows and slices behind it, with the arithmetic of the kernels, and
-// compares with plain division.  Prints the number of plans looked at and, per wrong quotient, the shape.
+// compares with plain division; and whether each plan has its kernel instance.  Prints the number of plans looked at and, per wrong quotient, the shape.
 #include <algorithm>
 #include <cstdio>
 #include <random>
@@ -17,6 +17,14 @@ static bool quotients(int last, int d, uint32_t magic) {  // of 0 .. last: wrong
     return (int)div_magic((uint32_t)last, magic) == last / d;
 }
 
+// Whether there is a kernel instance of this tile (gfc_staged_kernel.hpp: launch_np, launch_nb).
+static bool has_instance(const gfcst::Params& P) {
+    if (P.batches < 1 || P.batches > 4 || (P.np != 1 && P.np != 2 && P.np != 4)) return false;
+    if (P.np == 4 && !(P.KW == 3 && P.mo == 2 && P.wo == 1)) return false;
+    if (P.KW == 1) return P.wo == 4 ? (P.mo == 1 || P.mo == 2 || P.mo == 4) : P.wo == 1 && P.mo == 1 && P.batches <= 2;
+    return P.KW == 3 && ((P.wo == 2 && P.mo == 2) || (P.wo == 1 && (P.mo == 1 || P.mo == 2)));
+}
+
 static void look(int N, int G, int R, int K, int Og, int H, int W, bool f32) {
     if (!gfctm::supported(N, G, R, K, K, Og, H, W)) return;
     const gfctm::Params T = gfctm::shape(N, G, R, K, K, Og, H, W);
@@ -25,6 +33,7 @@ static void look(int N, int G, int R, int K, int Og, int H, int W, bool f32) {
     if (gfcst::plan(P, T, f32, false, false)) {
         plans++;
         largest = std::max(largest, P.tiles);
+        ok = has_instance(P);
         const int total = P.tiles * P.ogroups * P.Gm;
         for (int seq = 0; seq < total && ok; seq++) {
             const gfcst::Place at = gfcst::place_of(P, seq);
@@ -63,6 +72,10 @@ int main() {
         const int64_t most = ((int64_t)1 << 29) / ((int64_t)G * std::max(R, Og) * H * W);
         if (most < 1) continue;
         look(i % 4 ? (int)std::min<int64_t>(most, 1 << 20) : pick(1, (double)most), G, R, K, Og, H, W, i % 8 == 7);
+    }
+    for (int i = 0; i < 20000; i++) {  // ordinary sizes
+        const int K = rng() % 2 ? 1 : 3, G = 1 << rng() % 5, R = pick(1, 700), Og = pick(1, 700), H = pick(1, 60), W = pick(4, 60);
+        look(pick(1, 130), G, R, K, Og, H, W, i % 8 == 7);
     }
     std::printf("plans %d, weight gradients %d, most pixel tiles %d, wrong %d\n", plans, slices, largest, wrong);
     return wrong != 0;
