@@ -493,20 +493,6 @@ __global__ __launch_bounds__(64 * kWaves) void k_wgrad(Params P) {
 // of 56x56 26.4 us, now 22.3 = 4.6 TB/s; C=256, 14x14 17.5 / 13.9; C=512, 7x7 19.3 / 16.6; C=80, 20 of 27x29 8.5 / 5.7; C=128, 32 of 28x28 10.5 / 8.0.
 // Six steps in flight, or 128 x 128 tiles with sixteen wavefronts: slower.)
 constexpr int kAhead = 4, kRow64 = 144;
-// The last `left` (1 .. 7) of eight bf16, moved to the front; zeros behind them.
-__device__ __forceinline__ u32x4 last_elems(const u32x4& v, int left) {
-    uint64_t lo = v[0] | (uint64_t)v[1] << 32, hi = v[2] | (uint64_t)v[3] << 32;
-    const int gone = 8 - left;
-    if (gone & 4) {
-        lo = hi;
-        hi = 0;
-    }
-    const int bits = (gone & 3) * 16;
-    lo = lo >> bits | hi << 1 << (63 - bits);
-    hi >>= bits;
-    return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
-}
-
 template <int WO, int WK>
 __global__ __launch_bounds__(64 * WO * WK, WO * WK > 4 ? WO * WK / 4 : 2) void k_wgrad64(Params P) {
     constexpr int kRows = 32 * (WO + WK), kSweep = 8 * WO * WK;  // rows of a step; of one load per thread
@@ -581,7 +567,7 @@ __global__ __launch_bounds__(64 * WO * WK, WO * WK > 4 ? WO * WK / 4 : 2) void k
             buf ^= 1;
             if (left[f] < 8) {
 #pragma unroll
-                for (int i = 0; i < NL; i++) v[f][i] = last_elems(v[f][i], left[f]);
+                for (int i = 0; i < NL; i++) v[f][i] = drop_first(v[f][i], 8 - left[f]);
             }
 #pragma unroll
             for (int i = 0; i < NL; i++) *reinterpret_cast<u32x4*>(tile + to + i * kSweep * kRow64) = v[f][i];

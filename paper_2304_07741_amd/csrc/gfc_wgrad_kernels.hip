@@ -107,23 +107,12 @@ __global__ __launch_bounds__(kThreads, 2) void k_wgrad_taps(Params P) {
     u32x4 keep;  // the pixels of a row's last unit that exist
 #pragma unroll
     for (int k = 0; k < 4; k++) keep[k] = (2 * k < 8 - over ? 0xffffu : 0u) | (2 * k + 1 < 8 - over ? 0xffff0000u : 0u);
-    auto last = [&](u32x4 v, int move) {
-        uint64_t lo = v[0] | (uint64_t)v[1] << 32, hi = v[2] | (uint64_t)v[3] << 32;
-        if (move & 4) {
-            lo = hi;
-            hi = 0;
-        }
-        const int bits = (move & 3) * 16;
-        lo = lo >> bits | hi << 1 << (63 - bits);
-        hi >>= bits;
-        return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)} & keep;
-    };
     auto write = [&](Rows& v, int buf) {
 #pragma unroll
         for (int i = 0; i < NI; i++) {
             if (over) {
-                v.x[i][U - 1] = last(v.x[i][U - 1], v.xm[i]);
-                v.d[i][U - 1] = last(v.d[i][U - 1], v.dm[i]);
+                v.x[i][U - 1] = drop_first(v.x[i][U - 1], v.xm[i]) & keep;
+                v.d[i][U - 1] = drop_first(v.d[i][U - 1], v.dm[i]) & keep;
             }
             if (xat[i] >= 0) {
                 uint32_t d[D + 2];  // [zeros | the row | zeros]

@@ -140,6 +140,19 @@ __device__ __forceinline__ float4_t mfma32(const u32x4& a, const u32x4& b, float
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, c, 0, 0, 0);
 }
 
+// Eight bf16 without the first `gone` (0 .. 7), the others moved to the front; zeros behind them.
+__device__ __forceinline__ u32x4 drop_first(const u32x4& v, int gone) {
+    uint64_t lo = v[0] | (uint64_t)v[1] << 32, hi = v[2] | (uint64_t)v[3] << 32;
+    if (gone & 4) {
+        lo = hi;
+        hi = 0;
+    }
+    const int bits = (gone & 3) * 16;
+    lo = lo >> bits | hi << 1 << (63 - bits);
+    hi >>= bits;
+    return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
+
 // A barrier behind which every thread sees what the others wrote to LDS before it.  Loads from memory stay in flight (__syncthreads
 // waits for them too).
 __device__ __forceinline__ void lds_barrier() {
