@@ -1237,9 +1237,15 @@ CHAIN_HD void vm_exec_lanes(const Program& pg, const Geo& g, const Instr& I, con
 #pragma unroll
                 for (int t = 0; t < TM; t++)
                     if (t < T) dot += Xu[t * V + v] * Au[t * V + v];
+                if (I.kind) {
 #pragma unroll
-                for (int t = 0; t < TM; t++)
-                    if (t < T) Au[t * V + v] = I.kind ? Xu[t * V + v] * (Au[t * V + v] - dot) : Au[t * V + v] * (Xu[t * V + v] - dot);
+                    for (int t = 0; t < TM; t++)
+                        if (t < T) Au[t * V + v] = Xu[t * V + v] * (Au[t * V + v] - dot);
+                } else {
+#pragma unroll
+                    for (int t = 0; t < TM; t++)
+                        if (t < T) Au[t * V + v] = Au[t * V + v] * (Xu[t * V + v] - dot);
+                }
             }
         }
         break;
@@ -1271,7 +1277,7 @@ CHAIN_HD void vm_exec_lanes(const Program& pg, const Geo& g, const Instr& I, con
 #pragma unroll
                 for (int u = 0; u < U; u++)
 #pragma unroll
-                    for (int v = 0; v < V; v++) X[u * TV + v] = X[u * TV + v] / (I.f0 > 0.f ? I.f0 : (float)T);
+                    for (int v = 0; v < V; v++) X[u * TV + v] = X[u * TV + v] / (TM == 1 && I.f0 > 0.f ? I.f0 : (float)T);
             }
             CHAIN_EACH(T, e, l, A[e] = X[e - l + l % V];);
         }
