@@ -53,7 +53,7 @@ bool compile_unit(const Dag& dag, const std::vector<int>& nodes, const std::vect
 double program_cost(const Program& pg);
 
 // Estimated time of a program's launch in us beyond that of an empty one: per trip of a thread an instruction takes 0.75 us (its dispatch, and the loads
-// and barriers that it waits for) and 0.025 us for each lane of work, the more wavefronts share a SIMD.  Fitted to 5000 launches of 5 us
+// and barriers that it waits for) and 0.025 us for each lane of work, the more wavefronts share a SIMD.  Fitted to 6600 launches of 5 us
 // to 2 ms of random micro-DAGs; a factor of 1.5 either way.
 double launch_us(const Program& pg);
 

@@ -205,7 +205,7 @@ __global__ __launch_bounds__(1024) void k_softmax_c(Params P) {
                     for (int v = 0; v < V; v++) {
                         float d;
                         g[k][v] = unary<true>(kind, P.fast, g[k][v], d);
-                        x[k][v] *= d;
+                        x[k][v] = kind == 0 && d == 0.f ? 0.f : x[k][v] * d;  // (relu selects, whatever the gradient)
                     }
             }
         }

@@ -120,6 +120,13 @@ __global__ __launch_bounds__(256) void k_mid_bwd(MidParams P) {
 // (for a sum dv(p) + act'(x(p)) dv(p - d)).  Reads of x and dv at three pixels, two of them unaligned and served by the caches; bound by
 // the vector unit (two evaluations of the activation).  As programs of the fused-chain kernels, gelu, half of the channels shifted,
 // product, 128x64 planes of 56x56: backward 121.6 us, now 36.7 (4.2 TB/s of what it must move).
+// The activation's adjoint as the chain programs have it: relu selects (an infinite or overflowing gradient does not pass where the input is not positive).
+template <int ACT>
+__device__ __forceinline__ float through_act(float x, float d, float g) {
+    if constexpr (ACT == 0) return x > 0.f ? g : 0.f;
+    else return d * g;
+}
+
 template <int ACT, int BIN>
 __global__ __launch_bounds__(256) void k_self_bwd(MidParams P) {
     const Unit u = decode(P);
@@ -136,7 +143,8 @@ __global__ __launch_bounds__(256) void k_self_bwd(MidParams P) {
         for (int q = 0; q < 8; q++) {
             float t, d;
             act_both<ACT>(x[q], t, d);
-            dx[q] = BIN ? dv[q] * t + d * (dv[q] * x[q]) : dv[q] + d * dv[q];
+            const float through = through_act<ACT>(x[q], d, BIN ? dv[q] * x[q] : dv[q]);
+            dx[q] = BIN ? dv[q] * t + through : dv[q] + through;
         }
     } else {
         float xf[8], xs[8], dvs[8];  // x at p + d, x and dv at p - d
@@ -150,7 +158,7 @@ __global__ __launch_bounds__(256) void k_self_bwd(MidParams P) {
             if (BIN) t = act_apply<ACT>(xf[q]);
             act_both<ACT>(x[q], unused, d);
             const float a = BIN ? dv[q] * ((to >> q) & 1u ? t : 0.f) : dv[q];
-            const float b = (from >> q) & 1u ? d * (BIN ? dvs[q] * xs[q] : dvs[q]) : 0.f;
+            const float b = (from >> q) & 1u ? through_act<ACT>(x[q], d, BIN ? dvs[q] * xs[q] : dvs[q]) : 0.f;
             dx[q] = a + b;
         }
     }

@@ -34,3 +34,37 @@ def test_blend_with_itself(oracle, idx, shape):
     assert [d["name"] for d in r.launches(0)] == ["chain_fwd"] and [d["name"] for d in r.launches(1)] == ["chain_bwd"]
     check_against_oracle(oracle, case, res, dy)
     r.close()
+
+
+@pytest.mark.parametrize("blend,shift", [("mul", ""), ("add", ""), ("mul", "%2 = shift %1 dh=0 dw=1 c0=0 c1=14\n"), ("add", "%2 = shift %1 dh=1 dw=0 c0=0 c1=14\n")])
+def test_relu_stops_infinite_gradients(blend, shift):
+    """Where the input is not positive, relu's adjoint is zero whatever arrives: an infinite gradient, and one that overflows in the product."""
+    import math
+
+    import torch
+
+    from paper_2304_07741_amd import harness
+    from paper_2304_07741_amd import workloads as wl
+
+    k = 2 if shift else 1
+    r = harness.DagRunner(wl.HEADER + f"%1 = unary %0 op=relu\n{shift}%{k + 1} = binary %0 %{k} op={blend}\noutput %{k + 1}\n", (2, 14, 16, 24), "bf16")
+    x = torch.full(r.x.shape, -1.0, device="cuda")
+    x[0, :, 3, 5], x[1, :, 7, 20] = -3e38, 2.0
+    dy = torch.full((2, 14, 16, 24), 2.0, device="cuda")
+    dy[:, :, 9, 9] = math.inf
+    r.x.copy_(x)
+    r.dy.copy_(dy.view(r.dy.shape))
+    r.forward()
+    r.backward()
+    xr = r.x.float().requires_grad_(True)
+    t = torch.relu(xr)
+    if "dw=1" in shift:
+        t = torch.nn.functional.pad(t, (0, 1))[..., 1:]
+    elif shift:
+        t = torch.nn.functional.pad(t, (0, 0, 0, 1))[:, :, 1:]
+    (xr * t if blend == "mul" else xr + t).backward(dy)
+    got, want = r.dx.float().view(xr.shape), xr.grad
+    assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.isinf(), want.isinf())
+    ok = want.isfinite()
+    assert (got[ok] - want[ok]).abs().max().item() <= 2.0 ** -8 * want[ok].abs().max().item()   # (one rounding to bf16)
+    r.close()

@@ -82,3 +82,25 @@ def test_infinities(dtype):
         assert torch.equal(got.isnan(), want.isnan())
         assert (got - want).nan_to_num().abs().max().item() <= tol * max(1.0, want.nan_to_num().abs().max().item())
     r.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_relu_in_front_stops_infinite_gradients(dtype):
+    """An infinite gradient leaves no number behind the softmax of its pixel, and zero behind relu where the input is negative."""
+    import torch
+
+    from paper_2304_07741_amd import harness
+
+    r = harness.DagRunner(wl.HEADER + "%1 = unary %0 op=relu\n%2 = softmax %1 axis=C\noutput %2\n", (2, 40, 6, 8), dtype)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    r.x.copy_(torch.randn(r.x.shape, generator=g, device="cuda"))
+    r.dy.copy_(torch.randn(r.dy.shape, generator=g, device="cuda"))
+    r.dy.view(2, 40, 6, 8)[1, 17, 2, 3] = math.inf
+    r.forward()
+    r.backward()
+    xr = r.x.double().requires_grad_(True)
+    torch.softmax(torch.relu(xr), dim=1).backward(r.dy.double().view(xr.shape))
+    got, want = r.dx.double().view(xr.shape), xr.grad
+    assert torch.equal(got.isfinite(), want.isfinite())
+    assert (got - want)[want.isfinite()].abs().max().item() <= (1e-6 if dtype == "f32" else 1e-2) * want[want.isfinite()].abs().max().item()
+    r.close()
