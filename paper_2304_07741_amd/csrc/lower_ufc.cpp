@@ -142,6 +142,8 @@ std::unique_ptr<Lowering> lower_ufc(const Dag& dag, bool bf16, uint64_t partials
     // 46.6 / 40.5, 20x80x27x29 54.9 / 51.7, 12x384x10x10 58.0 / 54.2.  Forward alone: 16x96x32x32 (1.6 M elements) 49.2 / 47.4, 32x256x14x14 62.7 / 63.4,
     // 100x320x7x7 87.1 / 90.1, 40x160x20x20 (2.6 M) 71.0 / 74.4, 128x256x14x14 110.8 / 114.8.  Backward alone: 64x512x7x7 (1.6 M) 78.6 / 76.1,
     // 100x320x7x7 87.1 / 87.3, 40x160x20x20 71.0 / 74.2, 32x128x28x28 (3.2 M) 61.1 / 64.2, 64x256x28x28 173.4 / 181.7.
+    // (Elements stand for wavefronts per launch.  Forward, of three sizes of 1.6 M one gains and two lose: the line lies below them.  Backward, of
+    // two sizes of 1.6 M one gains and one is level, at 2.6 M it loses.)
     const int64_t elems = (int64_t)dag.N * C * Pn;
     const bool fuse_f = elems <= 1300000, fuse_b = elems <= 1700000;
     if (!(fuse_f && emit_fc_with_middle(*low, false, dag, takef, TV > 1 ? "ufc_fc1_unfold_mid" : "ufc_fc1_mid", G1, C / G1, KH, KW, C / G1, w1, in_x.ptr, ws_at(oz),

@@ -115,11 +115,6 @@ __global__ __launch_bounds__(256) void k_mid_bwd(MidParams P) {
     }
 }
 
-// The adjoint of y = x (*|+) shift(act(x)), where x is both operands (MidParams: x, dv = dy, dx1 = dx):
-//     dx(p) = dv(p) t(p) + act'(x(p)) dv(p - d) x(p - d),  t(p) = act(x(p + d)), either term zero where its other pixel leaves the image
-// (for a sum dv(p) + act'(x(p)) dv(p - d)).  Reads of x and dv at three pixels, two of them unaligned and served by the caches; bound by
-// the vector unit (two evaluations of the activation).  As programs of the fused-chain kernels, gelu, half of the channels shifted,
-// product, 128x64 planes of 56x56: backward 121.6 us, now 36.7 (4.2 TB/s of what it must move).
 // The activation's adjoint as the chain programs have it: relu selects (an infinite or overflowing gradient does not pass where the input is not positive).
 template <int ACT>
 __device__ __forceinline__ float through_act(float x, float d, float g) {
@@ -127,6 +122,11 @@ __device__ __forceinline__ float through_act(float x, float d, float g) {
     else return d * g;
 }
 
+// The adjoint of y = x (*|+) shift(act(x)), where x is both operands (MidParams: x, dv = dy, dx1 = dx):
+//     dx(p) = dv(p) t(p) + act'(x(p)) dv(p - d) x(p - d),  t(p) = act(x(p + d)), either term zero where its other pixel leaves the image
+// (for a sum dv(p) + act'(x(p)) dv(p - d)).  Reads of x and dv at three pixels, two of them unaligned and served by the caches; bound by
+// the vector unit (two evaluations of the activation).  As programs of the fused-chain kernels, gelu, half of the channels shifted,
+// product, 128x64 planes of 56x56: backward 121.6 us, now 36.7 (4.2 TB/s of what it must move).
 template <int ACT, int BIN>
 __global__ __launch_bounds__(256) void k_self_bwd(MidParams P) {
     const Unit u = decode(P);
